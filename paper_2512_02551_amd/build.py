@@ -15,7 +15,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 OBJ = os.path.join(CSRC, "_build")
 LIB = os.path.join(_HERE, "libhgemm.so")
-HEADERS = [os.path.join(CSRC, n) for n in ("hgemm_mfma.hpp", "hgemm_aux.hpp", "hgemm_registry.hpp", "hgemm_configs.inc",
+HEADERS = [os.path.join(CSRC, n) for n in ("hgemm_mfma.hpp", "hgemm_phased.hpp", "hgemm_aux.hpp", "hgemm_registry.hpp", "hgemm_configs.inc",
                                            "hgemm_skinny.hpp", "dispatch_table.inc", "dispatch_table_tn.inc", "plan_model.inc")] + [os.path.join(os.path.dirname(_HERE), "include", "hgemm.h")]
 API_SRC = os.path.join(CSRC, "hgemm_api.hip")
 KERNEL_SRC = os.path.join(CSRC, "hgemm_kernels.hip")

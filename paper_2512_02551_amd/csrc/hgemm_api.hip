@@ -54,6 +54,7 @@ struct Spec {
     int ps = 0;     // 1 = persistent: one workgroup per compute unit walks the tiles without draining its copy pipeline
     int ac = 32;    // accumulator width: 32 = fp32 over all of K; 16 = rounded to fp16 after every 16 products
     int mi = 32;    // matrix-core output block: 32 = v_mfma_f32_32x32x16_f16, 16 = v_mfma_f32_16x16x32_f16
+    int ph = 0;     // 1 = the phased schedule of this tile (hgemm_phased.hpp)
     int wv = 4;     // skinny family: waves per workgroup (4, 8 or 16), each taking 16 k-rows of a step
     int nr = 16;    // skinny family, column-major B: rows of B (columns of C) per workgroup (16, 32 or 64)
 };
@@ -80,6 +81,7 @@ static std::string spec_to_string(const Spec& s)
     if (s.ps) strncat(buf, ",ps=1", sizeof buf - strlen(buf) - 1);
     if (s.ac == 16) strncat(buf, ",ac=16", sizeof buf - strlen(buf) - 1);
     if (s.mi == 16) strncat(buf, ",mi=16", sizeof buf - strlen(buf) - 1);
+    if (s.ph) strncat(buf, ",ph=1", sizeof buf - strlen(buf) - 1);
     return buf;
 }
 
@@ -124,6 +126,7 @@ static bool parse_spec(const char* text, Spec* out)
         else if (key == "ps") sp.ps = (int)v;
         else if (key == "ac") sp.ac = (int)v;
         else if (key == "mi") sp.mi = (int)v;
+        else if (key == "ph") sp.ph = (int)v;
         else if (key == "wv") sp.wv = (int)v;
         else if (key == "nr") sp.nr = (int)v;
         else if (key == "pad") { /* reported by hgemm_plan_describe; padding follows from the shape, not from the spec */ }
@@ -134,6 +137,7 @@ static bool parse_spec(const char* text, Spec* out)
     // the 16-bit accumulator is a running sum over all of K in k order: one tile per workgroup, no splitting of K
     if ((sp.ac != 32 && sp.ac != 16) || (sp.ac == 16 && (sp.fam != FAM_MFMA || sp.sk > 1 || sp.sm || sp.ps || sp.fr))) return false;
     if (sp.mi != 32 && sp.mi != 16) return false;
+    if (sp.ph > 1 || (sp.ph && (sp.fam != FAM_MFMA || sp.sm || sp.fr || sp.ps || sp.tb || sp.ac == 16))) return false;
     if ((sp.wv != 4 && sp.wv != 8 && sp.wv != 16) || (sp.wv != 4 && sp.fam != FAM_SKINNY)) return false;
     if ((sp.nr != 16 && sp.nr != 32 && sp.nr != 64) || (sp.nr != 16 && sp.fam != FAM_SKINNY)) return false;
     *out = sp;
@@ -648,6 +652,7 @@ hgemm_status_t finish_plan(hgemm_plan_s* p)
     // deep-staged configurations exist for one full-K tile per workgroup only; the 16-bit accumulator for 32-wide blocks only
     if (e->deep && (s.sk > 1 || s.sm || s.ps || s.fr || s.ac == 16)) return HGEMM_ERR_UNSUPPORTED;
     if (s.ac == 16 && !e->acc16) return HGEMM_ERR_UNSUPPORTED;
+    if (s.ph && !e->phased) return HGEMM_ERR_UNSUPPORTED;
     // dynamic LDS beyond 64 KiB has to be requested per kernel function
     {
         void (*const kernels[])(GemmArgs) = {e->plain, e->splitk, e->plain_tn, e->splitk_tn, e->streamk, e->streamk_tn, e->splitk_fused,
@@ -655,6 +660,8 @@ hgemm_status_t finish_plan(hgemm_plan_s* p)
         bool ok = true;
         for (auto k : kernels)
             if (k && hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, e->lds_bytes) != hipSuccess) ok = false;
+        for (auto k : {e->phased, e->phased_tn, e->phased_splitk, e->phased_splitk_tn})
+            if (k && hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, e->phased_lds) != hipSuccess) ok = false;
         if (!ok) {
             (void)hipGetLastError();
             return HGEMM_ERR_LAUNCH;
@@ -1158,14 +1165,20 @@ static hgemm_status_t run_plan(const hgemm_plan_s* plan, const void* A, const vo
         hipLaunchKernelGGL(plan->tn_kernel ? e->splitk_fused_tn : e->splitk_fused, dim3(wgs, (unsigned)a.splits), dim3(e->threads),
                            e->lds_bytes, stream, a);
     } else if (a.splits > 1) {
-        hipLaunchKernelGGL(plan->tn_kernel ? e->splitk_tn : e->splitk, dim3(wgs, (unsigned)a.splits), dim3(e->threads), e->lds_bytes,
-                           stream, a);
+        if (plan->spec.ph)
+            hipLaunchKernelGGL(plan->tn_kernel ? e->phased_splitk_tn : e->phased_splitk, dim3(wgs, (unsigned)a.splits), dim3(e->threads), e->phased_lds,
+                               stream, a);
+        else
+            hipLaunchKernelGGL(plan->tn_kernel ? e->splitk_tn : e->splitk, dim3(wgs, (unsigned)a.splits), dim3(e->threads), e->lds_bytes,
+                               stream, a);
         if (hipGetLastError() != hipSuccess) return HGEMM_ERR_LAUNCH;
         const int64_t quads = M * (N / 4);
         const int blocks = (int)std::min<int64_t>((quads + 255) / 256, 2048);
         hipLaunchKernelGGL(splitk_reduce_kernel, dim3(blocks), dim3(256), 0, stream,
                            (const float*)((const char*)plan->workspace + plan->partial_offset), (_Float16*)C, (int)M, (int)N,
                            (int)plan->lay.ldc, a.splits);
+    } else if (plan->spec.ph) {
+        hipLaunchKernelGGL(plan->tn_kernel ? e->phased_tn : e->phased, dim3(wgs), dim3(e->threads), e->phased_lds, stream, a);
     } else if (plan->spec.ac == 16) {
         hipLaunchKernelGGL(plan->tn_kernel ? e->acc16_tn : e->acc16, dim3(wgs), dim3(e->threads), e->lds_bytes, stream, a);
     } else {
@@ -1272,7 +1285,7 @@ hgemm_status_t hgemm_plan_launch_info(hgemm_plan_t plan, int64_t* workgroups, in
         wg = plan->spec.sm ? (int64_t)plan->args.dp_tiles + plan->args.sk_workers
                            : (int64_t)plan->args.tiles_m * plan->args.tiles_n * plan->args.splits;
         if (plan->spec.ps) wg = std::min<int64_t>(wg, cu_count());
-        lds = plan->entry->lds_bytes;
+        lds = plan->spec.ph ? plan->entry->phased_lds : plan->entry->lds_bytes;
         th = plan->entry->threads;
     } else {
         wg = ((plan->N + 63) / 64) * ((plan->M + 3) / 4);
@@ -1301,7 +1314,7 @@ const char* hgemm_spec_help(void)
             "    Column-major B (K contiguous): a workgroup takes nr = 16 (default), 32 or 64 rows of B (columns of C), its waves split its K\n"
             "    range into contiguous parts of whole 32-k steps, 16-byte loads are the operands of 16x16x32 instructions\n"
             "    as they come; sk splits K further across workgroups\n"
-            "mfma,bm=BM,bn=BN,bk=BK,wm=WM,wn=WN,st=STAGES[,pf=PREFETCH][,sk=SPLITS][,gm=GROUP][,tb=1][,sm=1][,fr=1][,ps=1][,ac=16][,mi=16]\n"
+            "mfma,bm=BM,bn=BN,bk=BK,wm=WM,wn=WN,st=STAGES[,pf=PREFETCH][,sk=SPLITS][,gm=GROUP][,tb=1][,sm=1][,fr=1][,ps=1][,ac=16][,mi=16][,ph=1]\n"
             "    pipelined 32x32x16 MFMA kernel; BMxBN tile per workgroup, WMxWN wavefronts, STAGES LDS buffers,\n"
             "    pf = register prefetch distance in k-steps (1 = ping-pong, 3 = four fragment sets),\n"
             "    sk = split-K factor (fp32 partials + ordered reduction), gm = tile-order group height (0 = row-major),\n"
@@ -1342,6 +1355,17 @@ const char* hgemm_spec_help(void)
             if (e.mi != 16) continue;
             char b[64];
             snprintf(b, sizeof b, " (%d,%d,%d,%d,%d,%d,%d)", e.bm, e.bn, e.bk, e.wm, e.wn, e.st, e.pf);
+            t += b;
+        }
+        t += "\n"
+             "    ph = 1: the phased schedule of the same tile and waves: a K-tile of 64 is multiplied in four phases, one quadrant of C\n"
+             "    each, every phase reads one half tile and refills another (two stages, 16x16x32 instructions); sk allowed, no sm,\n"
+             "    ps, fr, ac, tb\n"
+             "    phased (bm,bn,bk,wm,wn,st,pf,mi):";
+        for (const MfmaEntry& e : registry()) {
+            if (!e.phased) continue;
+            char b[64];
+            snprintf(b, sizeof b, " (%d,%d,%d,%d,%d,%d,%d,%d)", e.bm, e.bn, e.bk, e.wm, e.wn, e.st, e.pf, e.mi);
             t += b;
         }
         t += "\n";
@@ -1433,6 +1457,12 @@ hgemm_status_t hgemm_candidates(int64_t M, int64_t N, int64_t K, const hgemm_lay
                         out += spec_to_string(s);
                         out += "\n";
                         s.ps = 0;
+                    }
+                    if (e.phased) {                              // the same tiles on the phased schedule
+                        s.ph = 1;
+                        out += spec_to_string(s);
+                        out += "\n";
+                        s.ph = 0;
                     }
                     if (sk > 1 && gm == 8 && fused_delta_us(M, N, sk) < 1.0) {   // the same split with the reduction fused into the kernel
                         s.fr = 1;

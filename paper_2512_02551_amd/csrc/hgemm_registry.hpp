@@ -3,6 +3,7 @@
 #include <vector>
 
 #include "hgemm_mfma.hpp"
+#include "hgemm_phased.hpp"
 
 namespace hgemm {
 
@@ -24,7 +25,22 @@ struct MfmaEntry {
     void (*acc16_tn)(GemmArgs);
     void (*fixup)(GemmArgs);
     int mi = 32;                        // side of the matrix-core output block
+    // the phased schedule of the same tile and waves (null where there is none): plain and two-launch split-K
+    void (*phased)(GemmArgs) = nullptr;
+    void (*phased_tn)(GemmArgs) = nullptr;
+    void (*phased_splitk)(GemmArgs) = nullptr;
+    void (*phased_splitk_tn)(GemmArgs) = nullptr;
+    int phased_lds = 0;
 };
+
+template <class C> constexpr bool has_phased()
+{
+    return false
+#define HGEMM_PHASED(bm, bn, wm, wn, st, mi) \
+    || (C::BM == bm && C::BN == bn && C::BK == 64 && C::WAVES_M == wm && C::WAVES_N == wn && C::STAGES == st && C::PF == 1 && C::MI == mi)
+#include "hgemm_configs.inc"
+        ;
+}
 
 template <class C, bool TN> inline void (*persist_kernel())(GemmArgs)
 {
@@ -57,6 +73,15 @@ template <class C> inline MfmaEntry make_entry()
                          acc16_kernel<C, false>(), acc16_kernel<C, true>(),
                          streamk_fixup_kernel<C::BM, C::BN, C::BK>};
         e.mi = C::MI;
+        if constexpr (has_phased<C>()) {
+            typedef PhasedCfg<C::BM, C::BN, C::WAVES_M, C::WAVES_N> P;
+            static_assert(P::THREADS == C::THREADS, "the phased schedule keeps the waves");
+            e.phased = phased_gemm_kernel<P, false, false>;
+            e.phased_tn = phased_gemm_kernel<P, false, true>;
+            e.phased_splitk = phased_gemm_kernel<P, true, false>;
+            e.phased_splitk_tn = phased_gemm_kernel<P, true, true>;
+            e.phased_lds = P::LDS_BYTES;
+        }
         return e;
     }
 }

@@ -810,3 +810,41 @@ def test_runs_can_be_captured_in_a_graph_and_replayed():
     finally:
         for p in plans:
             p.destroy()
+
+
+def phased_specs(sk=1, gm=8):
+    line = next(s for s in hg.spec_help().splitlines() if s.strip().startswith("phased (bm"))
+    out = []
+    for tup in line.split(":")[1].split():
+        bm, bn, bk, wm, wn, st, pf, mi = (int(x) for x in tup.strip("()").split(","))
+        out.append(f"mfma,bm={bm},bn={bn},bk={bk},wm={wm},wn={wn},st={st},pf={pf},sk={sk},gm={gm}" + (",mi=16" if mi == 16 else "") + ",ph=1")
+    assert out
+    return out
+
+
+@pytest.mark.parametrize("shape", [(1, 8, 8), (256, 256, 64), (257, 264, 72), (300, 520, 328), (127, 136, 1000), (1030, 1544, 128)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_phased_kernels_bit_exact_both_layouts_and_split(shape):
+    """Phased kernels: one K-tile (both tiles in the prologue, the second all zeros), an odd and an even number of them,
+    a last K-tile of 8, tiles that M and N do not fill, several tiles per workgroup id run; split-K with a last split
+    that is shorter.  Small integers: exact in fp32 whatever the order of summation.  Real inputs repeat bit for bit."""
+    name, a, b = wl.exact_family_for(shape, seed=91)
+    ref = orc.hgemm(a, b)
+    bt = np.ascontiguousarray(b.T)
+    for spec in phased_specs() + phased_specs(gm=0) + phased_specs(sk=2) + phased_specs(sk=5):
+        c, before, after, desc = run_hgemm(a, b, spec=spec, guard=2)
+        assert_bit_exact(c, ref, f"{shape} {name} {desc}")
+        assert np.isnan(before).all() and np.isnan(after).all(), desc
+        c, before, after, desc = run_hgemm(a, bt, spec=spec, b_col_major=True, guard=2)
+        assert_bit_exact(c, ref, f"TN {shape} {name} {desc}")
+        assert np.isnan(before).all() and np.isnan(after).all(), desc
+    rng = np.random.default_rng(shape)
+    ar, br = wl.uniform_pm1(rng, shape[0], shape[2]), wl.uniform_pm1(rng, shape[2], shape[1])
+    for spec in phased_specs():
+        c1, _, _, desc = run_hgemm(ar, br, spec=spec)
+        c2, _, _, _ = run_hgemm(ar, br, spec=spec)
+        assert_close(c1, orc.hgemm(ar, br), desc)
+        assert np.array_equal(c1.view(np.uint16), c2.view(np.uint16)), desc
+        for bad in (spec + ",sm=1", spec + ",ps=1", spec + ",ac=16", spec.replace("sk=1", "sk=2") + ",fr=1", spec + ",tb=1"):
+            with pytest.raises(hg.HgemmError):
+                hg.Plan(*shape, None, bad)
