@@ -66,7 +66,7 @@ typedef struct {
  *   M,N,K    >= 0.  M, N or K equal to 0 is valid (K = 0 gives C = 0).
  *   layouts  host pointer; NULL means NN, packed
  * Allocates the plan's device workspace (split-K partial sums, stream-K
- * partial tiles, padded copies of unaligned operands) on the CURRENT device,
+ * partial tiles, padded copies of unaligned A and B) on the CURRENT device,
  * if the choice needs one.
  * Size: the matrix-core kernels address an operand with 32-bit byte offsets,
  * i.e. up to 2 GiB of it.  A problem with a larger A, B or C (dimensions and
@@ -104,17 +104,18 @@ hgemm_status_t hgemm_plan_override(hgemm_plan_t* out, int64_t M, int64_t N, int6
  * hgemm_run -- enqueue C = A*B on `hip_stream` (Section 2.1; the call shape
  * kernel(a, b, out) of Section 2.4.1's timing listing).
  *   A, B, C     DEVICE pointers to fp16, owned by the caller, non-overlapping.
- *               The matrix-core kernels need 16-byte aligned bases and K, N
- *               (and the leading dimensions) multiples of 8.  When K, N or a
- *               leading dimension is not, hgemm_plan() arranges zero-padded
- *               packed copies of A, B and C in the plan's workspace (Section
- *               5.2's zero padding; two copy kernels before and one after the
- *               GEMM, on the same stream), except for problems below 2^20
- *               multiply-adds, which take a generic one-thread-per-element
- *               kernel, as do calls whose base pointers are not 16-byte
- *               aligned.  C is write-only: every element is overwritten
- *               (beta = 0), earlier contents never leak, and nothing outside
- *               the M x N elements of C is written.
+ *               The matrix-core kernels read A and B in aligned 16-byte chunks
+ *               and store C at any address and width.  When K, N or a leading
+ *               dimension is not a multiple of 8, hgemm_plan() reserves room
+ *               in the plan's workspace for zero-padded packed copies of A and
+ *               B (Section 5.2's zero padding) and the run makes, in one launch
+ *               before the GEMM on the same stream, those that are needed: of
+ *               an operand whose rows are not whole aligned chunks.  Problems
+ *               below 2^20 multiply-adds with such sizes take a generic
+ *               one-thread-per-element kernel, as do calls on aligned sizes
+ *               whose A or B is not 16-byte aligned.  C is write-only: every
+ *               element is overwritten (beta = 0), earlier contents never
+ *               leak, and nothing outside the M x N elements of C is written.
  *   hip_stream  a hipStream_t passed as void*; NULL = the default stream.
  * Asynchronous; allocates nothing; all kernels (main, split-K reduction,
  * stream-K fix-up, the optional transposing copy of B) go to hip_stream in
@@ -159,7 +160,8 @@ hgemm_status_t hgemm_run_many(hgemm_plan_t plan, int64_t count, int64_t sets, in
  * HGEMM_STATIC_SCRATCH_BYTES inside the library (one copy per GPU, held until
  * the process ends) instead of a hipMalloc'ed buffer, and the plan itself
  * lives on the call's stack.  A problem whose chosen specialisation needs more
- * scratch than that returns HGEMM_ERR_WORKSPACE and launches nothing; problems
+ * scratch than that (an unaligned problem counts with padded copies of A, B
+ * and C) returns HGEMM_ERR_WORKSPACE and launches nothing; problems
  * that need no workspace are never refused.  The kernels overwrite every
  * scratch element they later read, so nothing has to be cleared between calls.
  * All calls on one GPU share that GPU's array: calls whose kernels may overlap

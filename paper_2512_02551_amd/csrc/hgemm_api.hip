@@ -167,13 +167,19 @@ struct hgemm_plan_s {
     size_t partial_offset;      // byte offset of the partial sums inside the workspace
     bool tn_kernel;             // the MFMA kernel reads B with K contiguous
     int device;
-    // Zero padding (Section 5.2) for problems whose N, K or leading dimensions are not multiples of 8:
-    // M, N, K, lay above then describe packed, zero-filled copies in the workspace whose N and K are
-    // rounded up to 8, and the fields below keep the caller's problem.
+    // Problems whose N, K or leading dimensions are not multiples of 8.  The kernels store C at any width and address,
+    // but read A and B in aligned 16-byte chunks: an operand whose rows do not consist of those is first copied into
+    // the workspace, packed and zero-filled to multiples of 8 (the zero padding of Section 5.2).  K above is then
+    // rounded up to 8 (zero columns of the copy of A make the extra products vanish), lay describes the operands as the
+    // kernels see them, and the fields below keep the caller's problem.  An operand that can be read where it lies is;
+    // its place in the workspace is kept all the same, for calls whose base pointer is not 16-byte aligned.
+    // Measured against copying A, B and C always, two bytes per lane (us): 1000 x 1001 x 1003 26.3 -> 10.9 (A and B
+    // copied, in one launch), 16 x 50257 x 4096 with column-major B 383 -> 89 (nothing copied), with row-major B 402 -> 240.
     bool padded;
-    int64_t uM, uN, uK;
+    bool copy_a, copy_b;
+    int64_t uN, uK;
     hgemm_layouts_t ulay;
-    size_t a_off, b_off, c_off; // byte offsets of the padded copies of A, B and C inside the workspace
+    size_t a_off, b_off;        // byte offsets of the padded copies of A and B inside the workspace
     size_t bt_off;              // byte offset of the transposed copy of B (spec.tb)
     bool static_ws;             // the workspace is this device's static scratch array, not an allocation
     // Operands beyond the reach of the kernels' 32-bit buffer offsets (2 GiB per operand): the problem runs
@@ -558,13 +564,44 @@ bool neighbour_choice(int64_t M, int64_t N, int64_t K, bool b_col_major, const S
     return true;
 }
 
+int64_t up8(int64_t v) { return (v + 7) / 8 * 8; }
+size_t up256(size_t b) { return (b + 255) / 256 * 256; }
+
+// Can the matrix-core and streaming kernels run the plan's problem (a padded one with its copies made)?
+bool kernels_can_run(const hgemm_plan_s* p)
+{
+    if (!p->padded) return fast_path_ok(p->M, p->N, p->K, p->lay);
+    hgemm_layouts_t l = p->lay;
+    l.ldc = up8(p->N);                      // C is addressed in 64 bits, whatever its leading dimension
+    return fast_path_ok(p->M, up8(p->N), p->K, l);
+}
+
+// Lays the padded copies of A and B out in the workspace behind the counters and returns their bytes.
+size_t place_copies(hgemm_plan_s* p)
+{
+    p->a_off = p->b_off = 0;
+    if (!p->padded) return 0;
+    const size_t N = (size_t)up8(p->N), K = (size_t)p->K;
+    p->b_off = up256((size_t)p->M * K * 2);
+    return p->b_off + up256(K * N * 2);
+}
+
+// hgemm_run_static accepts a problem by the scratch it would take with padded copies of all three operands: callers
+// size their problems by that rule.
+bool over_static_scratch(const hgemm_plan_s* p)
+{
+    if (!p->static_ws) return false;
+    const size_t c_copy = p->padded ? up256((size_t)p->M * (size_t)up8(p->N) * 2) : 0;
+    return p->workspace_bytes && p->workspace_bytes + c_copy > kScratchBytes;
+}
+
 // Gives the plan its workspace of p->workspace_bytes (static scratch or an allocation), points the
 // partial-sum and counter arguments into it and clears the counters of an allocated one.
 hgemm_status_t acquire_workspace(hgemm_plan_s* p, size_t partial_bytes, size_t ctr_bytes)
 {
     GemmArgs& a = p->args;
     if (p->workspace_bytes && p->static_ws) {
-        if (p->workspace_bytes > kScratchBytes) { p->workspace_bytes = 0; return HGEMM_ERR_WORKSPACE; }
+        if (over_static_scratch(p)) { p->workspace_bytes = 0; return HGEMM_ERR_WORKSPACE; }
         p->workspace = scratch_ptr_for(p->device);
         if (!p->workspace) { p->workspace_bytes = 0; return HGEMM_ERR_LAUNCH; }
         if (partial_bytes) a.partial = (float*)((char*)p->workspace + p->partial_offset);
@@ -605,7 +642,7 @@ hgemm_status_t finish_plan(hgemm_plan_s* p)
     if (s.fam == FAM_GENERIC) return HGEMM_OK;
     if (s.fam == FAM_SKINNY) {
         // strips of columns x K slabs of whole steps; partial planes as for split-K
-        if (!fast_path_ok(M, N, K, p->lay) || M <= 0 || N <= 0 || K <= 0 || M > kSkinnyMaxM) return HGEMM_ERR_UNSUPPORTED;
+        if (!kernels_can_run(p) || M <= 0 || N <= 0 || K <= 0 || M > kSkinnyMaxM) return HGEMM_ERR_UNSUPPORTED;
         const bool tn = p->lay.b == HGEMM_COL_MAJOR;
         p->tn_kernel = tn;
         const int mb = M <= 16 ? 1 : M <= 32 ? 2 : 4;
@@ -626,18 +663,13 @@ hgemm_status_t finish_plan(hgemm_plan_s* p)
         a.tiles_m = 1; a.tiles_n = (int)strips;
         a.splits = (int)sk;
         a.k_per_split = (int)(((ksteps + sk - 1) / sk) * step);
-        // workspace: [counters] [padded copies of A, B, C (plans on zero-padded operands)] [planes]
-        auto up256s = [](size_t b) { return ((b + 255) / 256) * 256; };
-        size_t pad_bytes = 0;
-        p->a_off = p->b_off = p->c_off = 0;
-        if (p->padded) {
-            p->b_off = up256s((size_t)M * (size_t)K * 2);
-            p->c_off = p->b_off + up256s((size_t)K * (size_t)N * 2);
-            pad_bytes = p->c_off + up256s((size_t)M * (size_t)N * 2);
-        }
-        const size_t partial_bytes = sk > 1 ? up256s((size_t)sk * (size_t)M * (size_t)N * sizeof(float)) : 0;
+        a.b_rows = (int)(p->padded && !p->copy_b ? p->uK : K);
+        a.part_ld = (int)up8(N);
+        // workspace: [counters] [padded copies of A and B (problems off the 16-byte grid)] [planes]
+        const size_t pad_bytes = place_copies(p);
+        const size_t partial_bytes = sk > 1 ? up256((size_t)sk * (size_t)M * (size_t)a.part_ld * sizeof(float)) : 0;
         const size_t ctr_bytes = (s.fr || (p->static_ws && pad_bytes + partial_bytes > 0)) ? kCounterBytes : 0;
-        p->a_off += ctr_bytes; p->b_off += ctr_bytes; p->c_off += ctr_bytes;
+        p->a_off += ctr_bytes; p->b_off += ctr_bytes;
         p->bt_off = ctr_bytes + pad_bytes;
         p->partial_offset = ctr_bytes + pad_bytes;
         p->workspace_bytes = ctr_bytes + pad_bytes + partial_bytes;
@@ -645,7 +677,7 @@ hgemm_status_t finish_plan(hgemm_plan_s* p)
     }
     const MfmaEntry* e = find_entry(s);
     if (!e) return HGEMM_ERR_UNSUPPORTED;
-    if (!fast_path_ok(M, N, K, p->lay)) return HGEMM_ERR_UNSUPPORTED;
+    if (!kernels_can_run(p)) return HGEMM_ERR_UNSUPPORTED;
     if (s.tb && p->lay.b != HGEMM_ROW_MAJOR) return HGEMM_ERR_UNSUPPORTED;
     p->tn_kernel = s.tb || p->lay.b == HGEMM_COL_MAJOR;
     p->entry = e;
@@ -710,17 +742,11 @@ hgemm_status_t finish_plan(hgemm_plan_s* p)
             a.sk_workers = (int)((total + ipw - 1) / ipw);
         }
     }
-    auto up256 = [](size_t b) { return ((b + 255) / 256) * 256; };
-    size_t pad_bytes = 0;
-    p->a_off = p->b_off = p->c_off = 0;
-    if (p->padded) {
-        p->a_off = 0;
-        p->b_off = up256((size_t)M * (size_t)K * 2);
-        p->c_off = p->b_off + up256((size_t)K * (size_t)N * 2);
-        pad_bytes = p->c_off + up256((size_t)M * (size_t)N * 2);
-    }
+    a.b_rows = (int)(p->padded && !p->copy_b ? p->uK : K);
+    a.part_ld = (int)up8(N);
+    const size_t pad_bytes = place_copies(p);
     size_t bt_bytes = s.tb ? up256((size_t)N * (size_t)K * 2) : 0;
-    size_t partial_bytes = sk > 1 ? (size_t)sk * (size_t)M * (size_t)N * sizeof(float) : 0;
+    size_t partial_bytes = sk > 1 ? (size_t)sk * (size_t)M * (size_t)a.part_ld * sizeof(float) : 0;
     if (s.sm) partial_bytes = (size_t)2 * a.sk_workers * e->bm * e->bn * sizeof(float);
     partial_bytes = up256(partial_bytes);
     // fused split-K: one arrival counter per tile in front of everything else.  Counters are zero
@@ -729,7 +755,7 @@ hgemm_status_t finish_plan(hgemm_plan_s* p)
     // (In the static scratch every plan keeps clear of that region, so it stays zero for the fused ones.)
     const size_t ctr_bytes = (s.fr || (p->static_ws && pad_bytes + bt_bytes + partial_bytes > 0)) ? kCounterBytes : 0;
     if (s.fr && (size_t)a.tiles_m * a.tiles_n * sizeof(int) > kCounterBytes) return HGEMM_ERR_UNSUPPORTED;
-    p->a_off += ctr_bytes; p->b_off += ctr_bytes; p->c_off += ctr_bytes;
+    p->a_off += ctr_bytes; p->b_off += ctr_bytes;
     p->bt_off = ctr_bytes + pad_bytes;
     p->partial_offset = ctr_bytes + pad_bytes + bt_bytes;
     p->workspace_bytes = ctr_bytes + pad_bytes + bt_bytes + partial_bytes;
@@ -806,8 +832,9 @@ hgemm_status_t init_plan(hgemm_plan_s* p, int64_t M, int64_t N, int64_t K, const
     p->M = M; p->N = N; p->K = K; p->lay = l; p->device = dev;
     p->padded = false;
     p->static_ws = static_ws;
-    p->uM = M; p->uN = N; p->uK = K; p->ulay = l;
-    p->a_off = p->b_off = p->c_off = p->bt_off = 0;
+    p->copy_a = p->copy_b = false;
+    p->uN = N; p->uK = K; p->ulay = l;
+    p->a_off = p->b_off = p->bt_off = 0;
 
     hgemm_status_t st;
     if (spec_text) {
@@ -817,19 +844,27 @@ hgemm_status_t init_plan(hgemm_plan_s* p, int64_t M, int64_t N, int64_t K, const
         bool fast = fast_path_ok(M, N, K, l) && M > 0 && N > 0 && K > 0;
         if (!fast && M > 0 && N > 0 && K > 0 && (double)M * (double)N * (double)K >= kPadMinMacs) {
             // N, K or a leading dimension is not a multiple of 8.  Above a size where the one-thread-per-
-            // element kernel would take longer than four extra launches, run the matrix-core kernel on
-            // packed copies whose N and K are rounded up to 8 and zero-filled (the paper's zero padding,
-            // Section 5.2, applied to the dimensions the 16-byte copies need aligned).
+            // element kernel would take longer than an extra launch, run the matrix-core kernel, with packed
+            // zero-filled copies of those operands that cannot be read in 16-byte chunks where they lie.
             const int64_t Kp = (K + 7) / 8 * 8, Np = (N + 7) / 8 * 8;
             hgemm_layouts_t lp = l;
             lp.lda = Kp;
             lp.ldb = (l.b == HGEMM_ROW_MAJOR) ? Np : Kp;
             lp.ldc = Np;
-            if (fast_path_ok(M, Np, Kp, lp)) {
+            if (fast_path_ok(M, Np, Kp, lp) && l.ldc < ((int64_t)1 << 31)) {
+                const bool row_b = l.b == HGEMM_ROW_MAJOR;
+                // readable where it lies: rows of whole aligned chunks, and the kernels' offsets reach all of it
+                hgemm_layouts_t la = lp, lb = lp;
+                la.lda = l.lda;
+                lb.ldb = l.ldb;
+                p->copy_a = K % 8 != 0 || !fast_path_ok(M, Np, Kp, la);
+                p->copy_b = (row_b ? N : K) % 8 != 0 || !fast_path_ok(M, Np, Kp, lb);
                 p->padded = true;
-                p->N = N = Np;
                 p->K = K = Kp;
-                p->lay = l = lp;
+                p->lay.lda = p->copy_a ? Kp : l.lda;
+                p->lay.ldb = p->copy_b ? lp.ldb : l.ldb;
+                N = Np;                               // the planner's view of the problem
+                l = lp;
                 fast = true;
             }
         }
@@ -858,8 +893,8 @@ hgemm_status_t init_plan(hgemm_plan_s* p, int64_t M, int64_t N, int64_t K, const
                 }
             }
             if (st != HGEMM_OK && st != HGEMM_ERR_WORKSPACE && p->padded) {   // e.g. no memory for the padded copies: the generic kernel needs none
-                p->padded = false;
-                p->M = p->uM; p->N = p->uN; p->K = p->uK; p->lay = p->ulay;
+                p->padded = p->copy_a = p->copy_b = false;
+                p->N = p->uN; p->K = p->uK; p->lay = p->ulay;
                 p->spec = Spec();
                 st = finish_plan(p);
             }
@@ -1017,7 +1052,7 @@ hgemm_status_t hgemm_plan_choice(int64_t M, int64_t N, int64_t K, const hgemm_la
         lp.lda = Kp;
         lp.ldb = (l.b == HGEMM_ROW_MAJOR) ? Np : Kp;
         lp.ldc = Np;
-        if (fast_path_ok(M, Np, Kp, lp)) { padded = fast = true; N = Np; K = Kp; l = lp; }
+        if (fast_path_ok(M, Np, Kp, lp) && l.ldc < ((int64_t)1 << 31)) { padded = fast = true; N = Np; K = Kp; l = lp; }
     }
     int64_t rows = 0, cols = 0;
     bool bt = false;
@@ -1075,40 +1110,33 @@ static hgemm_status_t run_plan(const hgemm_plan_s* plan, const void* A, const vo
         return HGEMM_OK;
     }
 
-    void* const user_C = C;
-    if (plan->padded) {
-        // zero-filled packed copies of A and B; the kernels below then see an aligned problem
-        char* ws = (char*)plan->workspace;
-        const hgemm_layouts_t& ul = plan->ulay;
-        auto copy = [&](const void* src, int64_t src_ld, int64_t src_rows, int64_t src_cols, void* dst, int64_t dst_ld, int64_t dst_rows,
-                        int64_t dst_cols) {
-            const dim3 grid((unsigned)((dst_cols + kCopyColsPerBlock - 1) / kCopyColsPerBlock),
-                            (unsigned)std::min<int64_t>((dst_rows + kCopyRowsPerBlock - 1) / kCopyRowsPerBlock, 32768));
-            hipLaunchKernelGGL(copy2d_kernel<true>, grid, dim3(256), 0, stream, (const _Float16*)src, src_ld, src_rows, src_cols,
-                               (_Float16*)dst, dst_ld, dst_rows, dst_cols);
-        };
-        copy(A, ul.lda, plan->uM, plan->uK, ws + plan->a_off, K, M, K);
-        if (ul.b == HGEMM_ROW_MAJOR) copy(B, ul.ldb, plan->uK, plan->uN, ws + plan->b_off, N, K, N);
-        else copy(B, ul.ldb, plan->uN, plan->uK, ws + plan->b_off, K, N, K);
-        if (hipGetLastError() != hipSuccess) return HGEMM_ERR_LAUNCH;
-        A = ws + plan->a_off;
-        B = ws + plan->b_off;
-        C = ws + plan->c_off;
-    }
-    // the padded output goes back to the caller's C (its N columns, its leading dimension)
-    auto finish = [&]() -> hgemm_status_t {
-        if (hipGetLastError() != hipSuccess) return HGEMM_ERR_LAUNCH;
-        if (plan->padded) {
-            const dim3 grid((unsigned)((plan->uN + kCopyColsPerBlock - 1) / kCopyColsPerBlock),
-                            (unsigned)std::min<int64_t>((plan->uM + kCopyRowsPerBlock - 1) / kCopyRowsPerBlock, 32768));
-            hipLaunchKernelGGL(copy2d_kernel<false>, grid, dim3(256), 0, stream, (const _Float16*)C, N, M, N, (_Float16*)user_C,
-                               plan->ulay.ldc, plan->uM, plan->uN);
+    // operands as the kernels see them: the caller's, or the padded copies made here
+    int64_t lda = plan->lay.lda, ldb = plan->lay.ldb, b_rows = plan->args.b_rows;
+    const bool row_b = plan->lay.b == HGEMM_ROW_MAJOR;
+    if (plan->padded && plan->spec.fam != FAM_GENERIC) {
+        const bool copy_a = plan->copy_a || ((uintptr_t)A & 15), copy_b = plan->copy_b || ((uintptr_t)B & 15);
+        if (copy_a || copy_b) {
+            char* ws = (char*)plan->workspace;
+            const int64_t Np = up8(N);
+            auto job = [](const void* src, int64_t src_ld, int64_t rows, int64_t cols, void* dst, int64_t dst_rows, int64_t dst_cols) {
+                return PadCopy{(const _Float16*)src, (_Float16*)dst, src_ld, (unsigned)rows, (unsigned)cols, (unsigned)(dst_cols / 8),
+                               (unsigned)(dst_rows * (dst_cols / 8))};
+            };
+            PadCopy ca{}, cb{};
+            if (copy_a) ca = job(A, plan->ulay.lda, M, plan->uK, ws + plan->a_off, M, K);
+            if (copy_b) cb = row_b ? job(B, plan->ulay.ldb, plan->uK, N, ws + plan->b_off, K, Np) : job(B, plan->ulay.ldb, N, plan->uK, ws + plan->b_off, N, K);
+            constexpr unsigned per = 256 * kPadChunks;
+            const unsigned blocks_a = (ca.total + per - 1) / per, blocks_b = (cb.total + per - 1) / per;
+            hipLaunchKernelGGL(pad_copy_kernel, dim3(blocks_a + blocks_b), dim3(256), 0, stream, ca, cb, blocks_a);
             if (hipGetLastError() != hipSuccess) return HGEMM_ERR_LAUNCH;
+            if (copy_a) { A = ws + plan->a_off; lda = K; }
+            if (copy_b) { B = ws + plan->b_off; ldb = row_b ? Np : K; b_rows = K; }
         }
-        return HGEMM_OK;
-    };
+    }
+    auto finish = [&]() -> hgemm_status_t { return hipGetLastError() == hipSuccess ? HGEMM_OK : HGEMM_ERR_LAUNCH; };
 
-    const bool aligned = ((((uintptr_t)A) | ((uintptr_t)B) | ((uintptr_t)C)) & 15) == 0;
+    // A and B are read in 16-byte chunks; C may start anywhere
+    const bool aligned = ((((uintptr_t)A) | ((uintptr_t)B)) & 15) == 0;
     if (plan->spec.fam == FAM_GENERIC || !aligned) {
         if (N > (int64_t)64 * 0x7fffffff || (M + 3) / 4 > 65535) {
             // grid.y limit: fold rows into several launches
@@ -1131,15 +1159,19 @@ static hgemm_status_t run_plan(const hgemm_plan_s* plan, const void* A, const vo
     a.A = (const _Float16*)A;
     a.B = (const _Float16*)B;
     a.C = (_Float16*)C;
+    a.lda = (int)lda;
+    if (!plan->spec.tb) a.ldb = (int)ldb;
+    a.b_rows = (int)b_rows;
+    a.c_wide = N % 8 == 0 && plan->lay.ldc % 8 == 0 && ((uintptr_t)C & 15) == 0;
     if (plan->skinny) {
         hipLaunchKernelGGL(plan->skinny, dim3((unsigned)a.tiles_n, (unsigned)a.splits), dim3(64u * (unsigned)plan->spec.wv), 0, stream, a);
         if (a.splits > 1 && !plan->spec.fr) {
             if (hipGetLastError() != hipSuccess) return HGEMM_ERR_LAUNCH;
-            const int64_t quads = M * (N / 4);
+            const int64_t quads = M * ((N + 3) / 4);
             const int blocks = (int)std::min<int64_t>((quads + 255) / 256, 2048);
             hipLaunchKernelGGL(splitk_reduce_kernel, dim3(blocks), dim3(256), 0, stream,
                                (const float*)((const char*)plan->workspace + plan->partial_offset), (_Float16*)C, (int)M, (int)N,
-                               (int)plan->lay.ldc, a.splits);
+                               a.part_ld, (int)plan->lay.ldc, a.c_wide, a.splits);
         }
         return finish();
     }
@@ -1172,11 +1204,11 @@ static hgemm_status_t run_plan(const hgemm_plan_s* plan, const void* A, const vo
             hipLaunchKernelGGL(plan->tn_kernel ? e->splitk_tn : e->splitk, dim3(wgs, (unsigned)a.splits), dim3(e->threads), e->lds_bytes,
                                stream, a);
         if (hipGetLastError() != hipSuccess) return HGEMM_ERR_LAUNCH;
-        const int64_t quads = M * (N / 4);
+        const int64_t quads = M * ((N + 3) / 4);
         const int blocks = (int)std::min<int64_t>((quads + 255) / 256, 2048);
         hipLaunchKernelGGL(splitk_reduce_kernel, dim3(blocks), dim3(256), 0, stream,
                            (const float*)((const char*)plan->workspace + plan->partial_offset), (_Float16*)C, (int)M, (int)N,
-                           (int)plan->lay.ldc, a.splits);
+                           a.part_ld, (int)plan->lay.ldc, a.c_wide, a.splits);
     } else if (plan->spec.ph) {
         hipLaunchKernelGGL(plan->tn_kernel ? e->phased_tn : e->phased, dim3(wgs), dim3(e->threads), e->phased_lds, stream, a);
     } else if (plan->spec.ac == 16) {
@@ -1329,7 +1361,8 @@ const char* hgemm_spec_help(void)
             "            (16 products); explicit specs only, with sk = 1 and without sm, ps, fr; never chosen by hgemm_plan,\n"
             "            which always accumulates in fp32 over all of K\n"
             "    pad = 1 in a description: N, K or a leading dimension is not a multiple of 8 and the kernel runs on\n"
-            "            zero-padded packed copies held in the plan's workspace (decided by hgemm_plan from the shape)\n"
+            "            zero-padded packed copies, held in the plan's workspace, of those of A and B whose rows are not whole\n"
+            "            aligned 16-byte chunks (decided by hgemm_plan from the shape)\n"
             "    compiled (bm,bn,bk,wm,wn,st,pf):";
         for (const MfmaEntry& e : registry()) {
             if (e.deep || e.mi != 32) continue;

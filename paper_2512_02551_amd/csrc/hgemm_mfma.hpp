@@ -78,6 +78,9 @@ struct GemmArgs {
     int* counters;       // fused split-K: one arrival counter per output tile, zero between launches
     int M, N, K;
     int lda, ldb, ldc;   // elements
+    int b_rows;          // rows a row-major B has: K, or fewer where K was rounded up to whole 16-byte chunks (A zero-filled)
+    int part_ld;         // floats per row of a split-K plane: N rounded up to 8
+    int c_wide;          // every row of C starts on 16 bytes and holds whole 16-byte chunks (else store_cols goes narrower)
     int tiles_m, tiles_n;
     int swizzle;         // group height in tiles for the tile order; 0 = row-major
     // divisors of the tile order, fixed per launch (set_tile_map): tiles_n; one band = group * tiles_n
@@ -105,6 +108,24 @@ struct GemmArgs {
 // fp32 accumulator registers and buys no register space).
 enum { MODE_PLAIN = 0, MODE_SPLITK = 1, MODE_STREAMK = 2, MODE_SPLITK_FUSED = 3, MODE_PERSIST = 4, MODE_ACC16 = 5 };
 
+// Stores the first `left` of V's 4 or 8 consecutive columns of C.  `wide` (GemmArgs::c_wide, the same for the whole
+// launch): one aligned store.  Otherwise the row may start at any element: a whole group is still one store (global
+// memory takes 8- and 16-byte accesses at any element's address), and the last group of a row, where N is not a
+// multiple of 8, goes element by element.
+template <class V> __device__ __forceinline__ void store_cols(_Float16* p, V v, int left, int wide)
+{
+    constexpr int W = sizeof(V) / 2;
+    if (wide) {
+        *(V*)p = v;
+    } else if (left >= W) {
+        __builtin_memcpy(p, &v, sizeof(V));
+    } else {
+#pragma unroll
+        for (int e = 0; e < W - 1; ++e)
+            if (e < left) p[e] = v[e];
+    }
+}
+
 // Agent-scope relaxed atomic accesses: the compiler emits loads and stores that are coherent across
 // the whole device (the eight XCDs have private, mutually non-coherent L2 caches; plain accesses
 // would need a write-back / invalidate of a whole L2 to be seen on another XCD).
@@ -127,7 +148,7 @@ template <int THREADS, int QPR>
 __device__ __forceinline__ void sum_split_planes(const GemmArgs& g, int m0, int n0, int rows, int t)
 {
     constexpr int QU = 4, SU = 4;
-    const size_t plane2 = (size_t)g.M * g.N / 2;              // plane size in 8-byte words
+    const size_t plane2 = (size_t)g.M * g.part_ld / 2;              // plane size in 8-byte words
     const int items = rows * QPR;
     for (int qb = 0; qb < items; qb += QU * THREADS) {
         const unsigned long long* src[QU];
@@ -139,7 +160,7 @@ __device__ __forceinline__ void sum_split_planes(const GemmArgs& g, int m0, int 
             const int q = qb + j * THREADS + t;
             const int m = m0 + q / QPR, n = n0 + (q % QPR) * 4;
             ok[j] = q < items && n < g.N;
-            src[j] = (const unsigned long long*)(g.partial + (ok[j] ? (size_t)m * g.N + n : (size_t)m0 * g.N + n0));
+            src[j] = (const unsigned long long*)(g.partial + (ok[j] ? (size_t)m * g.part_ld + n : (size_t)m0 * g.part_ld + n0));
             dst[j] = g.C + (size_t)m * g.ldc + n;
             sum[j] = float4v{0.f, 0.f, 0.f, 0.f};
         }
@@ -168,7 +189,7 @@ __device__ __forceinline__ void sum_split_planes(const GemmArgs& g, int m0, int 
             half4 o;
 #pragma unroll
             for (int e = 0; e < 4; ++e) o[e] = (_Float16)sum[j][e];
-            *(half4*)dst[j] = o;
+            store_cols(dst[j], o, g.N - n0 - ((qb + j * THREADS + t) % QPR) * 4, g.c_wide);
         }
     }
 }
@@ -397,7 +418,7 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(GemmArgs g)
     // left to itself the compiler fetches some of them later, inside branches, and every such fetch is
     // another round trip to memory in front of the first copy (short kernels are latency chains).
     asm volatile("" :: "s"(g.A), "s"(g.B), "s"(g.C), "s"(g.M), "s"(g.N), "s"(g.K), "s"(g.lda), "s"(g.ldb), "s"(g.ldc),
-                 "s"(g.tiles_m), "s"(g.tiles_n), "s"(g.swizzle), "s"(g.k_per_split), "s"(g.splits));
+                 "s"(g.tiles_m), "s"(g.tiles_n), "s"(g.swizzle), "s"(g.k_per_split), "s"(g.splits), "s"(g.b_rows), "s"(g.c_wide), "s"(g.part_ld));
     asm volatile("" :: "s"(g.by_tiles_n.m), "s"(g.by_tiles_n.l), "s"(g.by_band.m), "s"(g.by_band.l), "s"(g.by_rows.m),
                  "s"(g.by_rows.l), "s"(g.by_last_rows.m), "s"(g.by_last_rows.l));
 
@@ -462,7 +483,7 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(GemmArgs g)
 
     const unsigned OOB = 0x80000000u;        // beyond every num_records the host admits
     const int4v rsrcA = make_rsrc(g.A, (unsigned)min((long long)g.M * g.lda * 2, 0x7fffffffLL));
-    const int4v rsrcB = make_rsrc(g.B, (unsigned)min((long long)(TN ? g.N : k_end) * g.ldb * 2, 0x7fffffffLL));
+    const int4v rsrcB = make_rsrc(g.B, (unsigned)min((long long)(TN ? g.N : min(k_end, g.b_rows)) * g.ldb * 2, 0x7fffffffLL));
 
     // ---- global -> LDS addressing (per lane, fixed for the whole K loop) ----
     // A: wave-load q = j*NWAVES + wave covers rows [q*A_RPI, (q+1)*A_RPI); lane i writes LDS slot i,
@@ -824,8 +845,7 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(GemmArgs g)
                     *(half4*)(stage + (lane & (MI - 1)) * ROWB + (tn * MI + vg * 8 + 4 * (lane >> LG)) * 2) = o;
                 }
             }
-#pragma unroll
-            for (int j = 0; j < (MI * CPR) / 64; ++j) {
+            auto store_chunk = [&](int j, bool wide) {
                 const int idx = j * 64 + lane;
                 const int r = idx / CPR, ch = idx % CPR;
                 const half4 lo = *(const half4*)(stage + r * ROWB + ch * 16);
@@ -836,8 +856,16 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(GemmArgs g)
                     half8 v;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) { v[e] = lo[e]; v[4 + e] = hi[e]; }
-                    *(half8*)(g.C + (size_t)m * g.ldc + n) = v;
+                    store_cols(g.C + (size_t)m * g.ldc + n, v, g.N - n, wide);
                 }
+            };
+            // two loops, the one for narrow rows kept small and out of the way: short kernels pay for the code they fetch
+            if (__builtin_expect(g.c_wide != 0, 1)) {
+#pragma unroll
+                for (int j = 0; j < (MI * CPR) / 64; ++j) store_chunk(j, true);
+            } else {
+#pragma unroll 1
+                for (int j = 0; j < (MI * CPR) / 64; ++j) store_chunk(j, false);
             }
         }
     } else {
@@ -859,7 +887,7 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(GemmArgs g)
                     if (STREAMK) {
                         *(float4v*)(sk_slot + (row_t + tm * MI) * C::BN + col_t + tn * MI + vg * 8) = o;
                     } else if (m < g.M && n < g.N) {
-                        float* dst = g.partial + ((size_t)split * g.M + m) * g.N + n;
+                        float* dst = g.partial + ((size_t)split * g.M + m) * g.part_ld + n;
                         if (FUSED) {
                             // device-coherent stores: the summing workgroup may sit on another XCD
                             union { float4v f; unsigned long long u[2]; } w;
@@ -953,7 +981,7 @@ __global__ __launch_bounds__(256) void streamk_fixup_kernel(GemmArgs g)
         half4 o;
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] = (_Float16)sum[e];
-        *(half4*)(g.C + (size_t)(m0 + r) * g.ldc + n0 + c) = o;
+        store_cols(g.C + (size_t)(m0 + r) * g.ldc + n0 + c, o, g.N - n0 - c, g.c_wide);
     }
 }
 

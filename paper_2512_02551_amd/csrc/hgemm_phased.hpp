@@ -61,7 +61,7 @@ __global__ __launch_bounds__(C::THREADS) void phased_gemm_kernel(GemmArgs g)
 {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     asm volatile("" :: "s"(g.A), "s"(g.B), "s"(g.C), "s"(g.M), "s"(g.N), "s"(g.K), "s"(g.lda), "s"(g.ldb), "s"(g.ldc),
-                 "s"(g.tiles_m), "s"(g.tiles_n), "s"(g.swizzle), "s"(g.k_per_split));
+                 "s"(g.tiles_m), "s"(g.tiles_n), "s"(g.swizzle), "s"(g.k_per_split), "s"(g.b_rows), "s"(g.c_wide), "s"(g.part_ld));
     asm volatile("" :: "s"(g.by_tiles_n.m), "s"(g.by_tiles_n.l), "s"(g.by_band.m), "s"(g.by_band.l), "s"(g.by_rows.m),
                  "s"(g.by_rows.l), "s"(g.by_last_rows.m), "s"(g.by_last_rows.l));
     const int lane = threadIdx.x & 63;
@@ -78,7 +78,7 @@ __global__ __launch_bounds__(C::THREADS) void phased_gemm_kernel(GemmArgs g)
 
     const unsigned OOB = 0x80000000u;
     const int4v rsrcA = make_rsrc(g.A, (unsigned)min((long long)g.M * g.lda * 2, 0x7fffffffLL));
-    const int4v rsrcB = make_rsrc(g.B, (unsigned)min((long long)(TN ? g.N : k_end) * g.ldb * 2, 0x7fffffffLL));
+    const int4v rsrcB = make_rsrc(g.B, (unsigned)min((long long)(TN ? g.N : min(k_end, g.b_rows)) * g.ldb * 2, 0x7fffffffLL));
 
     // ---- copies.  Wave-load j of an A unit (TN: of a B unit) covers 8 rows of 128 bytes; lane i fills physical chunk
     // i % 8 of row i / 8 with logical chunk p ^ (row / 2) % 8.  Lanes whose chunk lies past K, and all lanes past the last
@@ -241,7 +241,7 @@ __global__ __launch_bounds__(C::THREADS) void phased_gemm_kernel(GemmArgs g)
 #pragma unroll
                 for (int tn = 0; tn < C::TN; ++tn) {
                     const int m = m0 + h * C::HM + wm * C::QM + tm * 16 + l16, n = n0 + q * C::HN + wn * C::QN + tn * 16 + 4 * lg;
-                    if (m < g.M && n < g.N) *(float4v*)(g.partial + ((size_t)split * g.M + m) * g.N + n) = acc[h][q][tm][tn];
+                    if (m < g.M && n < g.N) *(float4v*)(g.partial + ((size_t)split * g.M + m) * g.part_ld + n) = acc[h][q][tm][tn];
                 }
         }); });
         return;
@@ -259,13 +259,19 @@ __global__ __launch_bounds__(C::THREADS) void phased_gemm_kernel(GemmArgs g)
     }); });
     __syncthreads();
     constexpr int CPR = C::BN / 8;                              // 16-byte chunks per row
-#pragma unroll 4
-    for (int j = 0; j < C::BM * CPR / C::THREADS; ++j) {
+    auto store_chunk = [&](int j, bool wide) {
         const int idx = j * C::THREADS + (int)threadIdx.x;
         const int r = idx / CPR, ch = idx % CPR;
         const half8 v = *(const half8*)(lds + r * C::OUT_PITCH + ch * 16);
         const int m = m0 + r, n = n0 + ch * 8;
-        if (m < g.M && n < g.N) *(half8*)(g.C + (size_t)m * g.ldc + n) = v;
+        if (m < g.M && n < g.N) store_cols(g.C + (size_t)m * g.ldc + n, v, g.N - n, wide);
+    };
+    if (__builtin_expect(g.c_wide != 0, 1)) {
+#pragma unroll 4
+        for (int j = 0; j < C::BM * CPR / C::THREADS; ++j) store_chunk(j, true);
+    } else {
+#pragma unroll 1
+        for (int j = 0; j < C::BM * CPR / C::THREADS; ++j) store_chunk(j, false);
     }
 }
 

@@ -56,7 +56,7 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_gemm_kernel(GemmArgs g)
     const __amdgpu_buffer_rsrc_t rsrcA =
         __builtin_amdgcn_make_buffer_rsrc((void*)g.A, 0, (int)min((long long)g.M * g.lda * 2, 0x7fffffffLL), 0x00020000);
     const __amdgpu_buffer_rsrc_t rsrcB =
-        __builtin_amdgcn_make_buffer_rsrc((void*)g.B, 0, (int)min((long long)g.K * g.ldb * 2, 0x7fffffffLL), 0x00020000);
+        __builtin_amdgcn_make_buffer_rsrc((void*)g.B, 0, (int)min((long long)g.b_rows * g.ldb * 2, 0x7fffffffLL), 0x00020000);
 
     // lane (grp, c16): rows krow0 + STEP * step + s (s = 0..3) of B, columns n0 + 8 c16 .. + 7;
     // A[16 mb + c16][krow0 + STEP * step .. + 3]
@@ -170,9 +170,9 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_gemm_kernel(GemmArgs g)
                 o[e] = (_Float16)s0[e];
                 o[4 + e] = (_Float16)s1[e];
             }
-            *(half8*)(g.C + (size_t)m * g.ldc + n) = o;
+            store_cols(g.C + (size_t)m * g.ldc + n, o, g.N - n, g.c_wide);
         } else {
-            float* dst = g.partial + ((size_t)split * g.M + m) * g.N + n;
+            float* dst = g.partial + ((size_t)split * g.M + m) * g.part_ld + n;
             if (FUSED) {
                 union { float4v f; unsigned long long u[2]; } v0, v1;
                 v0.f = s0;
@@ -319,9 +319,9 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_tn_gemm_kernel(GemmArgs g)
                 half4 o;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) o[e] = (_Float16)s[e];
-                *(half4*)(g.C + (size_t)m * g.ldc + n) = o;
+                store_cols(g.C + (size_t)m * g.ldc + n, o, g.N - n, g.c_wide);
             } else {
-                float* dst = g.partial + ((size_t)split * g.M + m) * g.N + n;
+                float* dst = g.partial + ((size_t)split * g.M + m) * g.part_ld + n;
                 if (FUSED) {
                     union { float4v f; unsigned long long u[2]; } v;
                     v.f = s;

@@ -848,3 +848,65 @@ def test_phased_kernels_bit_exact_both_layouts_and_split(shape):
         for bad in (spec + ",sm=1", spec + ",ps=1", spec + ",ac=16", spec.replace("sk=1", "sk=2") + ",fr=1", spec + ",tb=1"):
             with pytest.raises(hg.HgemmError):
                 hg.Plan(*shape, None, bad)
+
+
+@pytest.mark.parametrize("shape", [(65, 130, 257), (130, 201, 264), (200, 264, 129), (1030, 1031, 5), (17, 4099, 520), (100, 1000, 1003), (512, 1001, 4096)],
+                         ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("tn", [False, True])
+def test_ragged_operands_are_copied_only_where_needed(shape, tn):
+    """N, K and leading dimensions off the multiples of 8, one at a time and together: operands that the kernels read
+    where they lie, operands copied (also rows of fewer than 8 elements), C stored at odd widths, pitches and addresses.
+    Everything around the operands is NaN, and so is everything around C afterwards."""
+    M, N, K = shape
+    name, a, b = wl.exact_family_for(shape, seed=92)
+    ref = orc.hgemm(a, b)
+    bs = np.ascontiguousarray(b.T) if tn else b
+    stream = torch.cuda.current_stream().cuda_stream
+    for pads in ((0, 0, 0), (3, 0, 0), (0, 5, 0), (0, 0, 7), (8 - K % 8, 8 - bs.shape[1] % 8, 8 - N % 8)):
+        for shift in ((0, 0, 0), (0, 0, 1), (1, 3, 5)):
+            def place(x, pad, off):
+                rows, cols = x.shape
+                buf = torch.full((16 + off + (rows + 1) * (cols + pad) + 64,), float("nan"), dtype=torch.float16, device="cuda")
+                view = buf[16 + off:16 + off + rows * (cols + pad)].view(rows, cols + pad)
+                view[:, :cols] = to_dev(x)
+                return buf, view
+            abuf, av = place(a, pads[0], shift[0])
+            bbuf, bv = place(bs, pads[1], shift[1])
+            cbuf, cv = place(np.full((M, N), np.nan, np.float16), pads[2], shift[2])
+            lay = hg.Layouts.make(b_col_major=tn, lda=K + pads[0], ldb=bs.shape[1] + pads[1], ldc=N + pads[2])
+            with hg.Plan(M, N, K, lay) as p:
+                desc = f"{shape} tn={tn} pads={pads} shift={shift} {p.describe()}"
+                for _ in range(2):
+                    cbuf.fill_(float("nan"))
+                    p.run(av.data_ptr(), bv.data_ptr(), cv.data_ptr(), stream)
+                    torch.cuda.synchronize()
+                    assert_bit_exact(to_host(cv[:, :N]), ref, desc)
+                    assert torch.isnan(cv[:, N:]).all() and int(torch.isnan(cbuf).sum()) == cbuf.numel() - M * N, desc + ": wrote outside C"
+
+
+def test_ragged_columns_in_every_way_a_kernel_stores_them():
+    """An odd N (column-major B: nothing is copied) and an unaligned C through every kind of plan that stores C: one
+    tile per workgroup, split-K (planes of padded rows, both reductions), stream-K, persistent, phased, streaming."""
+    stream = torch.cuda.current_stream().cuda_stream
+    base = ["mfma,bm=64,bn=64,bk=64,wm=2,wn=2,st=4,pf=3,sk=1,gm=8", "mfma,bm=128,bn=128,bk=64,wm=2,wn=2,st=2,pf=1,sk=1,gm=8"]
+    specs = base + [s.replace("sk=1", "sk=3") for s in base] + [s.replace("sk=1", "sk=3") + ",fr=1" for s in base] + [base[1] + ",sm=1", base[1] + ",ps=1"]
+    specs += phased_specs()[:1] + phased_specs(sk=2)[:1]
+    for shape in ((64, 520, 1024), (2200, 2056, 256)):
+        M, N, K = shape
+        name, a, b = wl.exact_family_for(shape, seed=93)
+        ref = orc.hgemm(a, b)
+        da, db = to_dev(a), to_dev(b)
+        for spec in specs + (["skinny,sk=1", "skinny,sk=3", "skinny,sk=3,fr=1"] if M <= 64 else []):
+            for off, pad in ((1, 0), (0, 3), (5, 8)):
+                buf = torch.full((16 + off + M * (N + pad) + 64,), float("nan"), dtype=torch.float16, device="cuda")
+                c = buf[16 + off:16 + off + M * (N + pad)].view(M, N + pad)
+                if pad % 8:          # a pitch off the multiples of 8 is the planner's business; C's address is anybody's
+                    plan = hg.Plan(M, N, K, hg.Layouts.make(ldc=N + pad))
+                else:
+                    plan = hg.Plan(M, N, K, hg.Layouts.make(ldc=N + pad), spec)
+                with plan as p:
+                    desc = f"{shape} off={off} pad={pad} {p.describe()}"
+                    p.run(da.data_ptr(), db.data_ptr(), c.data_ptr(), stream)
+                    torch.cuda.synchronize()
+                assert_bit_exact(to_host(c[:, :N]), ref, desc)
+                assert int(torch.isnan(buf).sum()) == buf.numel() - M * N, desc + ": wrote outside C"
