@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -85,52 +86,43 @@ static std::string spec_to_string(const Spec& s)
     return buf;
 }
 
+// Reads a spec string in place: planning a call parses one (a table row), so nothing is allocated here.
 static bool parse_spec(const char* text, Spec* out)
 {
     if (!text) return false;
-    std::string s(text);
-    size_t pos = s.find(',');
-    std::string fam = s.substr(0, pos);
     Spec sp;
-    if (fam == "generic") {
-        sp.fam = FAM_GENERIC;
-    } else if (fam == "mfma") {
-        sp.fam = FAM_MFMA;
-    } else if (fam == "skinny") {
-        sp.fam = FAM_SKINNY;
-    } else {
-        return false;
-    }
-    while (pos != std::string::npos) {
-        size_t next = s.find(',', pos + 1);
-        std::string kv = s.substr(pos + 1, next == std::string::npos ? std::string::npos : next - pos - 1);
-        pos = next;
-        size_t eq = kv.find('=');
-        if (eq == std::string::npos || eq == 0 || eq + 1 >= kv.size()) return false;
-        std::string key = kv.substr(0, eq);
+    const char* p = text;
+    auto word = [&](const char* w) {
+        const size_t n = strlen(w);
+        if (strncmp(p, w, n) || (p[n] != '\0' && p[n] != ',')) return false;
+        p += n;
+        return true;
+    };
+    if (word("mfma")) sp.fam = FAM_MFMA;
+    else if (word("skinny")) sp.fam = FAM_SKINNY;
+    else if (word("generic")) sp.fam = FAM_GENERIC;
+    else return false;
+    int ignored = 0;
+    const struct { char key[4]; int* value; } keys[] = {
+        {"bm", &sp.bm}, {"bn", &sp.bn}, {"bk", &sp.bk}, {"wm", &sp.wm}, {"wn", &sp.wn}, {"st", &sp.st}, {"pf", &sp.pf}, {"sk", &sp.sk},
+        {"gm", &sp.gm}, {"tb", &sp.tb}, {"sm", &sp.sm}, {"fr", &sp.fr}, {"ps", &sp.ps}, {"ac", &sp.ac}, {"mi", &sp.mi}, {"ph", &sp.ph},
+        {"wv", &sp.wv}, {"nr", &sp.nr},
+        {"pad", &ignored},      // reported by hgemm_plan_describe; padding follows from the shape, not from the spec
+    };
+    while (*p) {
+        ++p;                                                   // the comma in front of a key
+        const char* eq = p;
+        while (*eq && *eq != '=' && *eq != ',') ++eq;
+        const size_t len = (size_t)(eq - p);
+        if (*eq != '=' || len == 0 || eq[1] == '\0' || eq[1] == ',') return false;
         char* end = nullptr;
-        long v = strtol(kv.c_str() + eq + 1, &end, 10);
-        if (*end != '\0' || v < 0 || v > (1 << 20)) return false;
-        if (key == "bm") sp.bm = (int)v;
-        else if (key == "bn") sp.bn = (int)v;
-        else if (key == "bk") sp.bk = (int)v;
-        else if (key == "wm") sp.wm = (int)v;
-        else if (key == "wn") sp.wn = (int)v;
-        else if (key == "st") sp.st = (int)v;
-        else if (key == "pf") sp.pf = (int)v;
-        else if (key == "sk") sp.sk = (int)v;
-        else if (key == "gm") sp.gm = (int)v;
-        else if (key == "tb") sp.tb = (int)v;
-        else if (key == "sm") sp.sm = (int)v;
-        else if (key == "fr") sp.fr = (int)v;
-        else if (key == "ps") sp.ps = (int)v;
-        else if (key == "ac") sp.ac = (int)v;
-        else if (key == "mi") sp.mi = (int)v;
-        else if (key == "ph") sp.ph = (int)v;
-        else if (key == "wv") sp.wv = (int)v;
-        else if (key == "nr") sp.nr = (int)v;
-        else if (key == "pad") { /* reported by hgemm_plan_describe; padding follows from the shape, not from the spec */ }
-        else return false;
+        const long v = strtol(eq + 1, &end, 10);
+        if ((*end != '\0' && *end != ',') || v < 0 || v > (1 << 20)) return false;
+        bool known = false;
+        for (const auto& k : keys)
+            if (strlen(k.key) == len && !strncmp(k.key, p, len)) { *k.value = (int)v; known = true; break; }
+        if (!known) return false;
+        p = end;
     }
     if (sp.sk < 1 || sp.tb > 1 || sp.sm > 1 || sp.fr > 1 || sp.ps > 1 || (sp.sm && sp.sk > 1) || (sp.ps && (sp.sk > 1 || sp.sm)))
         return false;
@@ -161,6 +153,8 @@ struct hgemm_plan_s {
     Spec spec;
     const MfmaEntry* entry;     // null for the generic and skinny families
     void (*skinny)(GemmArgs);   // the skinny family's kernel, else null
+    void (*kernel)(GemmArgs);   // the large-tile family's main kernel and its dynamic LDS
+    int kernel_lds;
     GemmArgs args;              // pointers filled in at run time
     void* workspace;            // [transposed B (when spec.tb)] [split-K / stream-K partial sums]
     size_t workspace_bytes;
@@ -294,24 +288,45 @@ Spec heuristic(int64_t M, int64_t N, int64_t K)
 #include "dispatch_table.inc"
 #include "dispatch_table_tn.inc"
 
+// A table's rows in order of their shapes, with the logarithms that neighbour_choice compares: a call that plans (every
+// hgemm_run_static does) looks its row up by bisection instead of walking a thousand rows.
+struct TableIndex {
+    struct Item { int64_t m, n, k; const char* spec; double lm, ln, lk; };
+    std::vector<Item> items;
+    TableIndex(const DispatchRow* rows, size_t count)
+    {
+        for (size_t i = 0; i < count; ++i) {
+            const DispatchRow& r = rows[i];
+            if (r.m > 0 && r.n > 0 && r.k > 0) items.push_back({r.m, r.n, r.k, r.spec, std::log2((double)r.m), std::log2((double)r.n), std::log2((double)r.k)});
+        }
+        std::stable_sort(items.begin(), items.end(), [](const Item& a, const Item& b) { return a.m != b.m ? a.m < b.m : a.n != b.n ? a.n < b.n : a.k < b.k; });
+    }
+    const char* find(int64_t M, int64_t N, int64_t K) const
+    {
+        auto it = std::lower_bound(items.begin(), items.end(), 0,
+                                   [&](const Item& a, int) { return a.m != M ? a.m < M : a.n != N ? a.n < N : a.k < K; });
+        return it != items.end() && it->m == M && it->n == N && it->k == K ? it->spec : nullptr;
+    }
+};
+const TableIndex& table_index(bool b_col_major)
+{
+    static const TableIndex nn(kDispatchTable, sizeof(kDispatchTable) / sizeof(kDispatchTable[0]));
+    static const TableIndex tn(kDispatchTableTN, sizeof(kDispatchTableTN) / sizeof(kDispatchTableTN[0]));
+    return b_col_major ? tn : nn;
+}
+
 // The measured row for a shape: with column-major B the table tuned in that layout first, then (as for
 // row-major B) the table tuned with row-major B, whose tile sizes and split factors carry over.
 bool table_lookup(int64_t M, int64_t N, int64_t K, bool b_col_major, Spec* out)
 {
-    if (b_col_major)
-        for (size_t i = 0; i < sizeof(kDispatchTableTN) / sizeof(kDispatchTableTN[0]); ++i) {
-            const DispatchRow& r = kDispatchTableTN[i];
-            if (r.m == M && r.n == N && r.k == K && r.spec[0] != '\0' && parse_spec(r.spec, out)) return true;
-        }
-    for (size_t i = 0; i < sizeof(kDispatchTable) / sizeof(kDispatchTable[0]); ++i) {
-        const DispatchRow& r = kDispatchTable[i];
-        if (r.m == M && r.n == N && r.k == K) {
-            // a row of the NN table serves a column-major B only if it names the large-tile family (the streaming
-            // family decomposes the two layouts differently: slab and wave counts do not carry over)
-            return r.spec[0] != '\0' && parse_spec(r.spec, out) && !(b_col_major && out->fam != FAM_MFMA);
-        }
+    if (b_col_major) {
+        const char* spec = table_index(true).find(M, N, K);
+        if (spec && spec[0] != '\0' && parse_spec(spec, out)) return true;
     }
-    return false;
+    // a row of the NN table serves a column-major B only if it names the large-tile family (the streaming
+    // family decomposes the two layouts differently: slab and wave counts do not carry over)
+    const char* spec = table_index(false).find(M, N, K);
+    return spec && spec[0] != '\0' && parse_spec(spec, out) && !(b_col_major && out->fam != FAM_MFMA);
 }
 
 // ---------------------------------------------------------------------------
@@ -340,18 +355,24 @@ int64_t effective_splits(int64_t ktiles, int64_t sk)
 }
 
 // Split factors worth considering for a configuration with `t` tiles and `ktiles` K-tiles.
-std::vector<int> split_candidates(int64_t t, int64_t ktiles)
+struct SplitFactors {
+    int n = 0, sk[12];
+    const int* begin() const { return sk; }
+    const int* end() const { return sk + n; }
+};
+SplitFactors split_candidates(int64_t t, int64_t ktiles)
 {
-    std::vector<int> sks = {1};
+    SplitFactors f;
+    f.sk[f.n++] = 1;
     const int64_t kCUs = cu_count();
     if (t < 2 * kCUs) {
         for (int sk : {2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64}) {
             if (ktiles / sk < 2) break;
             if (t * sk > 8 * kCUs) break;
-            sks.push_back(sk);
+            f.sk[f.n++] = sk;
         }
     }
-    return sks;
+    return f;
 }
 
 // Tiles far taller or wider than the problem only waste matrix-core work.
@@ -362,8 +383,13 @@ bool tile_fits_problem(const MfmaEntry& e, int64_t M, int64_t N)
     return true;
 }
 
-// Predicted microseconds of one call (plain or split-K kernel, default tile order).
-double predict_us(int64_t Mi, int64_t Ni, int64_t Ki, int bm, int bn, int bk, int wm, int wn, int st, int pf, int64_t ski)
+// Predicted microseconds of one call (plain or split-K kernel, default tile order); big = predict_big(M, N, K).
+double predict_big(int64_t M, int64_t N, int64_t K)
+{
+    const double flop = 2.0 * (double)M * (double)N * (double)K;
+    return std::min(2.0, std::max(0.0, std::log10(std::max(flop, 1.0)) - 10.0)) / 2.0;
+}
+double predict_us(int64_t Mi, int64_t Ni, int64_t Ki, int bm, int bn, int bk, int wm, int wn, int st, int pf, int64_t ski, double big)
 {
     const PlanModel& g = kModel;
     const int64_t kCUs = cu_count();
@@ -383,8 +409,6 @@ double predict_us(int64_t Mi, int64_t Ni, int64_t Ki, int bm, int bn, int bk, in
     const double w = std::ceil(wgs / (double)kCUs);
     const double co = std::min(occ, w);
     const double rounds = std::ceil(w / co);
-    const double flop = 2.0 * M * N * K;
-    const double big = std::min(2.0, std::max(0.0, std::log10(std::max(flop, 1.0)) - 10.0)) / 2.0;
     double t_mfma = 2.0 * bm * bn * bk / g.F * (1.0 + g.c1 * (double)(tm + tn) / (double)(tm * tn)) * (1.0 + g.cp * big);
     if (pf == 1) t_mfma *= g.q1;
     if (bm == 32) t_mfma *= g.m32;
@@ -475,7 +499,7 @@ std::vector<int> skinny_split_candidates(int64_t N, int64_t K)
     return out;
 }
 
-bool model_choice(int64_t M, int64_t N, int64_t K, Spec* out, bool b_row_major = true)
+bool evaluate_model(int64_t M, int64_t N, int64_t K, Spec* out, bool b_row_major)
 {
     double best = 1e300;
     bool found = false;
@@ -501,6 +525,7 @@ bool model_choice(int64_t M, int64_t N, int64_t K, Spec* out, bool b_row_major =
     // 128-160 MiB the two families are level at M = 1 and the 32-row tiles ahead from M = 16 on (32 x 10240 x 8192:
     // 36 us against 51), so those stay with the model.
     if (found && M <= 32 && 2.0 * (double)K * (double)N >= 256.0 * 1048576.0) return true;
+    const double big = predict_big(M, N, K);
     for (const MfmaEntry& e : registry()) {
         if (e.deep || e.mi != 32) continue;          // the cost model was not fitted to these kernels: the tuner's business
         if (!tile_fits_problem(e, M, N)) continue;
@@ -508,7 +533,7 @@ bool model_choice(int64_t M, int64_t N, int64_t K, Spec* out, bool b_row_major =
         const int64_t ktiles = (K + e.bk - 1) / e.bk;
         for (int sk0 : split_candidates(t, ktiles)) {
             const int64_t sk = effective_splits(ktiles, sk0);
-            double us = predict_us(M, N, K, e.bm, e.bn, e.bk, e.wm, e.wn, e.st, e.pf, sk);
+            double us = predict_us(M, N, K, e.bm, e.bn, e.bk, e.wm, e.wn, e.st, e.pf, sk, big);
             const bool fuse = sk > 1 && fused_delta_us(M, N, sk) < 0.0 && (int64_t)t * (int64_t)sizeof(int) <= (int64_t)kCounterBytes;
             if (fuse) us += fused_delta_us(M, N, sk);
             if (us < best) {
@@ -522,6 +547,25 @@ bool model_choice(int64_t M, int64_t N, int64_t K, Spec* out, bool b_row_major =
         }
     }
     return found;
+}
+
+// The model's pick.  Evaluating it takes some hundred candidates (10-20 us of host time, more than a small call takes on
+// the device), and a program that plans on every call -- hgemm_run_static, the one-call Python wrapper -- comes back with a
+// handful of shapes.  Each thread keeps its last picks, a function of the shape and the layout alone, in a table of fixed
+// size.
+bool model_choice(int64_t M, int64_t N, int64_t K, Spec* out, bool b_row_major = true)
+{
+    struct Pick { int64_t M, N, K; bool row, found; Spec spec; };
+    constexpr size_t kPicks = 64;
+    static thread_local Pick picks[kPicks] = {};
+    const uint64_t h = ((uint64_t)M * 0x9E3779B97F4A7C15ull ^ (uint64_t)N * 0xC2B2AE3D27D4EB4Full ^ (uint64_t)K * 0x165667B19E3779F9ull) + b_row_major;
+    Pick& p = picks[(h ^ (h >> 29)) % kPicks];
+    if (p.M != M || p.N != N || p.K != K || p.row != b_row_major) {
+        p.found = evaluate_model(M, N, K, &p.spec, b_row_major);
+        p.M = M; p.N = N; p.K = K; p.row = b_row_major;
+    }
+    if (p.found) *out = p.spec;
+    return p.found;
 }
 
 // Large problems the table does not hold: the tuned choice of the nearest shape that it does hold.
@@ -544,15 +588,13 @@ double last_round_fill(const Spec& s, int64_t M, int64_t N)
 bool neighbour_choice(int64_t M, int64_t N, int64_t K, bool b_col_major, const Spec& model, Spec* out)
 {
     if (2.0 * (double)M * (double)N * (double)K < 3e10 || std::min(M, N) < 512 || model.fam != FAM_MFMA) return false;
-    const DispatchRow* rows = b_col_major ? kDispatchTableTN : kDispatchTable;
-    const size_t count = b_col_major ? sizeof(kDispatchTableTN) / sizeof(kDispatchTableTN[0]) : sizeof(kDispatchTable) / sizeof(kDispatchTable[0]);
     auto lg = [](int64_t v) { return std::log2((double)std::max<int64_t>(v, 1)); };
+    const double lm = lg(M), ln = lg(N), lk = lg(K);
     double best = 1.5;
-    const DispatchRow* pick = nullptr;
-    for (size_t i = 0; i < count; ++i) {
-        const DispatchRow& r = rows[i];
-        if (r.m <= 0 || r.spec[0] == '\0') continue;
-        const double d = std::fabs(lg(M) - lg(r.m)) + std::fabs(lg(N) - lg(r.n)) + std::fabs(lg(K) - lg(r.k));
+    const TableIndex::Item* pick = nullptr;
+    for (const TableIndex::Item& r : table_index(b_col_major).items) {
+        if (r.spec[0] == '\0') continue;
+        const double d = std::fabs(lm - r.lm) + std::fabs(ln - r.ln) + std::fabs(lk - r.lk);
         if (d <= best) { best = d; pick = &r; }
     }
     Spec near;
@@ -628,6 +670,34 @@ hgemm_status_t acquire_workspace(hgemm_plan_s* p, size_t partial_bytes, size_t c
     return HGEMM_OK;
 }
 
+// The main kernel of a large-tile plan.  Dynamic LDS beyond 64 KiB has to be requested for a kernel function, once per
+// device: a bit per (device, configuration, kernel) keeps a call that plans from asking again.
+bool select_kernel(hgemm_plan_s* p)
+{
+    const MfmaEntry* e = p->entry;
+    const Spec& s = p->spec;
+    const bool split = s.sk > 1;
+    void (*const all[])(GemmArgs) = {e->plain, e->splitk, e->streamk, e->splitk_fused, e->persist, e->acc16, e->phased, e->phased_splitk};
+    void (*const all_tn[])(GemmArgs) = {e->plain_tn, e->splitk_tn, e->streamk_tn, e->splitk_fused_tn, e->persist_tn, e->acc16_tn, e->phased_tn, e->phased_splitk_tn};
+    const int which = s.sm ? 2 : s.ps ? 4 : split && s.fr ? 3 : s.ph ? (split ? 7 : 6) : split ? 1 : s.ac == 16 ? 5 : 0;
+    p->kernel = p->tn_kernel ? all_tn[which] : all[which];
+    p->kernel_lds = s.ph ? e->phased_lds : e->lds_bytes;
+    if (!p->kernel) return false;
+    if (p->kernel_lds <= 64 * 1024) return true;
+    constexpr size_t kMaxEntries = 256;
+    static std::atomic<unsigned> allowed[kMaxDevices][kMaxEntries] = {};
+    const size_t idx = (size_t)(e - registry().data());
+    const unsigned bit = 1u << (which + (p->tn_kernel ? 16 : 0));
+    const bool keep = idx < kMaxEntries && p->device >= 0 && p->device < kMaxDevices;
+    if (keep && (allowed[p->device][idx].load(std::memory_order_acquire) & bit)) return true;
+    if (hipFuncSetAttribute((const void*)p->kernel, hipFuncAttributeMaxDynamicSharedMemorySize, p->kernel_lds) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (keep) allowed[p->device][idx].fetch_or(bit, std::memory_order_release);
+    return true;
+}
+
 hgemm_status_t finish_plan(hgemm_plan_s* p)
 {
     const int64_t M = p->M, N = p->N, K = p->K;
@@ -685,20 +755,6 @@ hgemm_status_t finish_plan(hgemm_plan_s* p)
     if (e->deep && (s.sk > 1 || s.sm || s.ps || s.fr || s.ac == 16)) return HGEMM_ERR_UNSUPPORTED;
     if (s.ac == 16 && !e->acc16) return HGEMM_ERR_UNSUPPORTED;
     if (s.ph && !e->phased) return HGEMM_ERR_UNSUPPORTED;
-    // dynamic LDS beyond 64 KiB has to be requested per kernel function
-    {
-        void (*const kernels[])(GemmArgs) = {e->plain, e->splitk, e->plain_tn, e->splitk_tn, e->streamk, e->streamk_tn, e->splitk_fused,
-                                             e->splitk_fused_tn, e->persist, e->persist_tn, e->acc16, e->acc16_tn};
-        bool ok = true;
-        for (auto k : kernels)
-            if (k && hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, e->lds_bytes) != hipSuccess) ok = false;
-        for (auto k : {e->phased, e->phased_tn, e->phased_splitk, e->phased_splitk_tn})
-            if (k && hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, e->phased_lds) != hipSuccess) ok = false;
-        if (!ok) {
-            (void)hipGetLastError();
-            return HGEMM_ERR_LAUNCH;
-        }
-    }
     GemmArgs& a = p->args;
     a.M = (int)M; a.N = (int)N; a.K = (int)K;
     a.lda = (int)p->lay.lda; a.ldb = s.tb ? (int)K : (int)p->lay.ldb; a.ldc = (int)p->lay.ldc;
@@ -759,6 +815,7 @@ hgemm_status_t finish_plan(hgemm_plan_s* p)
     p->bt_off = ctr_bytes + pad_bytes;
     p->partial_offset = ctr_bytes + pad_bytes + bt_bytes;
     p->workspace_bytes = ctr_bytes + pad_bytes + bt_bytes + partial_bytes;
+    if (!select_kernel(p)) return HGEMM_ERR_LAUNCH;
     return acquire_workspace(p, partial_bytes, ctr_bytes);
 }
 
@@ -1184,37 +1241,19 @@ static hgemm_status_t run_plan(const hgemm_plan_s* plan, const void* A, const vo
         if (hipGetLastError() != hipSuccess) return HGEMM_ERR_LAUNCH;
         a.B = (const _Float16*)((char*)plan->workspace + plan->bt_off);
     }
+    const unsigned grid = plan->spec.sm ? (unsigned)(a.dp_tiles + a.sk_workers) : plan->spec.ps ? (unsigned)std::min<int64_t>(wgs, cu_count()) : wgs;
+    hipLaunchKernelGGL(plan->kernel, dim3(grid, (unsigned)a.splits), dim3(e->threads), plan->kernel_lds, stream, a);
     if (plan->spec.sm) {
-        hipLaunchKernelGGL(plan->tn_kernel ? e->streamk_tn : e->streamk, dim3((unsigned)(a.dp_tiles + a.sk_workers)), dim3(e->threads),
-                           e->lds_bytes, stream, a);
         if (hipGetLastError() != hipSuccess) return HGEMM_ERR_LAUNCH;
         hipLaunchKernelGGL(e->fixup, dim3(wgs - (unsigned)a.dp_tiles, (unsigned)((e->bm * e->bn / 4 + 1023) / 1024)), dim3(256), 0,
                            stream, a);
-    } else if (plan->spec.ps) {
-        hipLaunchKernelGGL(plan->tn_kernel ? e->persist_tn : e->persist, dim3((unsigned)std::min<int64_t>(wgs, cu_count())), dim3(e->threads),
-                           e->lds_bytes, stream, a);
-    } else if (a.splits > 1 && plan->spec.fr) {
-        hipLaunchKernelGGL(plan->tn_kernel ? e->splitk_fused_tn : e->splitk_fused, dim3(wgs, (unsigned)a.splits), dim3(e->threads),
-                           e->lds_bytes, stream, a);
-    } else if (a.splits > 1) {
-        if (plan->spec.ph)
-            hipLaunchKernelGGL(plan->tn_kernel ? e->phased_splitk_tn : e->phased_splitk, dim3(wgs, (unsigned)a.splits), dim3(e->threads), e->phased_lds,
-                               stream, a);
-        else
-            hipLaunchKernelGGL(plan->tn_kernel ? e->splitk_tn : e->splitk, dim3(wgs, (unsigned)a.splits), dim3(e->threads), e->lds_bytes,
-                               stream, a);
+    } else if (a.splits > 1 && !plan->spec.fr) {
         if (hipGetLastError() != hipSuccess) return HGEMM_ERR_LAUNCH;
         const int64_t quads = M * ((N + 3) / 4);
         const int blocks = (int)std::min<int64_t>((quads + 255) / 256, 2048);
         hipLaunchKernelGGL(splitk_reduce_kernel, dim3(blocks), dim3(256), 0, stream,
                            (const float*)((const char*)plan->workspace + plan->partial_offset), (_Float16*)C, (int)M, (int)N,
                            a.part_ld, (int)plan->lay.ldc, a.c_wide, a.splits);
-    } else if (plan->spec.ph) {
-        hipLaunchKernelGGL(plan->tn_kernel ? e->phased_tn : e->phased, dim3(wgs), dim3(e->threads), e->phased_lds, stream, a);
-    } else if (plan->spec.ac == 16) {
-        hipLaunchKernelGGL(plan->tn_kernel ? e->acc16_tn : e->acc16, dim3(wgs), dim3(e->threads), e->lds_bytes, stream, a);
-    } else {
-        hipLaunchKernelGGL(plan->tn_kernel ? e->plain_tn : e->plain, dim3(wgs), dim3(e->threads), e->lds_bytes, stream, a);
     }
     return finish();
 }
@@ -1471,7 +1510,7 @@ hgemm_status_t hgemm_candidates(int64_t M, int64_t N, int64_t K, const hgemm_lay
                 }
                 continue;
             }
-            const std::vector<int> sks = split_candidates(t, ktiles);
+            const SplitFactors sks = split_candidates(t, ktiles);
             if (t % CUS != 0 && ktiles >= 4 && e.bm >= 64 && e.bn >= 64) {
                 Spec s;
                 s.fam = FAM_MFMA; s.bm = e.bm; s.bn = e.bn; s.bk = e.bk; s.wm = e.wm; s.wn = e.wn; s.st = e.st; s.pf = e.pf; s.mi = e.mi; s.sk = 1; s.gm = 8; s.sm = 1;
@@ -1532,7 +1571,7 @@ hgemm_status_t hgemm_predict_us(int64_t M, int64_t N, int64_t K, const char* spe
     }
     if (s.fam != FAM_MFMA || s.sm || s.tb || s.ps || s.ac == 16 || !find_entry(s)) return HGEMM_ERR_UNSUPPORTED;
     const int64_t eff = effective_splits((K + s.bk - 1) / s.bk, s.sk);
-    *us = predict_us(M, N, K, s.bm, s.bn, s.bk, s.wm, s.wn, s.st, s.pf, eff);
+    *us = predict_us(M, N, K, s.bm, s.bn, s.bk, s.wm, s.wn, s.st, s.pf, eff, predict_big(M, N, K));
     if (s.fr && eff > 1) *us += fused_delta_us(M, N, eff);
     return HGEMM_OK;
 }

@@ -148,3 +148,39 @@ def test_plan_choice_names_the_source_of_every_kind_of_plan():
         hg.plan_choice(-1, 8, 8)
     with pytest.raises(hg.HgemmError):
         hg.plan_choice(64, 64, 64, hg.Layouts.make(lda=8))
+
+
+def test_plan_choice_is_the_same_from_every_thread_and_after_many_other_shapes():
+    """The cost model's picks are kept per thread in a table of 64: a shape asked again, asked after many others took its
+    place, and asked from a thread that has never planned gets one answer, in both layouts."""
+    import random
+    import threading
+
+    rnd = random.Random(17)
+    shapes = [(rnd.randint(1, 3000), 8 * rnd.randint(1, 400), 8 * rnd.randint(1, 400), rnd.random() < 0.5) for _ in range(300)]
+
+    def ask(out):
+        for m, n, k, tn in shapes:
+            out.append(hg.plan_choice(m, n, k, hg.Layouts.make(b_col_major=tn)))
+
+    first, again, other = [], [], [[] for _ in range(4)]
+    ask(first)
+    ask(again)
+    threads = [threading.Thread(target=ask, args=(o,)) for o in other]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert first == again and all(o == first for o in other)
+    for i in (0, 150, 299):                                    # asked twice in a row: the second answer comes from the table
+        m, n, k, tn = shapes[i]
+        lay = hg.Layouts.make(b_col_major=tn)
+        assert hg.plan_choice(m, n, k, lay) == hg.plan_choice(m, n, k, lay) == first[i]
+
+
+@pytest.mark.parametrize("spec", ["", "mfma,", "mfma,bm", "mfma,bm=", "mfma,bm=64x", "mfma,=3", "mfma,bm=64,,bn=64", "mfmax", "mfma;bm=64", "skinny,sk=0",
+                                  "mfma,bm=-1", "mfma,zz=1", "mfma,bm=99999999", "skinny,wv=5", "mfma,ph=2", "skinny,ph=1", "mfma,bm=64,"])
+def test_malformed_specs_are_invalid_arguments(spec):
+    with pytest.raises(hg.HgemmError) as e:
+        hg.predict_us(64, 64, 64, spec)
+    assert e.value.status == 1, spec
