@@ -38,6 +38,7 @@ static const std::vector<MfmaEntry>& registry()
 }
 
 void (*skinny_kernel(int mb, bool fused, int waves, int tn_rows))(GemmArgs);      // hgemm_skinny.hip
+void (*skinny_any_b_kernel(int mb, bool fused))(GemmArgs);
 
 constexpr int64_t kSkinnyMaxM = 64;
 
@@ -168,9 +169,11 @@ struct hgemm_plan_s {
     // kernels see them, and the fields below keep the caller's problem.  An operand that can be read where it lies is;
     // its place in the workspace is kept all the same, for calls whose base pointer is not 16-byte aligned.
     // Measured against copying A, B and C always, two bytes per lane (us): 1000 x 1001 x 1003 26.3 -> 10.9 (A and B
-    // copied, in one launch), 16 x 50257 x 4096 with column-major B 383 -> 89 (nothing copied), with row-major B 402 -> 240.
+    // copied, in one launch), 16 x 50257 x 4096 with column-major B 383 -> 89 (nothing copied), with row-major B 402 -> 240
+    // (and 100 by the streaming family, which reads any row-major B where it lies).
     bool padded;
     bool copy_a, copy_b;
+    bool any_b;                 // row-major B off the 16-byte grid that the streaming family reads where it lies (never copied)
     int64_t uN, uK;
     hgemm_layouts_t ulay;
     size_t a_off, b_off;        // byte offsets of the padded copies of A and B inside the workspace
@@ -499,23 +502,42 @@ std::vector<int> skinny_split_candidates(int64_t N, int64_t K)
     return out;
 }
 
+// The streaming family's best slab count for a row-major B under its model, and the prediction.
+double skinny_choice(int64_t M, int64_t N, int64_t K, Spec* out)
+{
+    double best = 1e300;
+    for (int sk : skinny_split_candidates(N, K)) {
+        for (int fr = 0; fr <= (sk > 1 ? 1 : 0); ++fr) {
+            const double us = predict_skinny_us(M, N, K, sk, fr != 0);
+            if (us < best) {
+                best = us;
+                Spec s;
+                s.fam = FAM_SKINNY; s.sk = (int)sk; s.fr = fr;
+                *out = s;
+            }
+        }
+    }
+    return best;
+}
+
+// A row-major B whose rows do not consist of whole aligned 16-byte chunks would have to be copied for the large-tile
+// kernels; the streaming family reads it as it is.  Taken for M <= 32 always, and up to its 64 rows where B is 32 MiB or
+// more: there the copy alone takes longer than the multiplication (40 x 32001 x 2048: copy and 64-row tiles 64 us, streamed 39), below
+// that size the copy stays in the caches and the 64-row tiles are the faster half of the deal.
+bool streams_any_b(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l)
+{
+    if (l.b != HGEMM_ROW_MAJOR || (N % 8 == 0 && l.ldb % 8 == 0) || N < 8 || M > kSkinnyMaxM) return false;
+    if ((K + 512) * l.ldb * 2 >= ((int64_t)1 << 31)) return false;
+    return M <= 32 || 2.0 * (double)K * (double)N >= 32.0 * 1048576.0;
+}
+
 bool evaluate_model(int64_t M, int64_t N, int64_t K, Spec* out, bool b_row_major)
 {
     double best = 1e300;
     bool found = false;
     if (b_row_major && M <= kSkinnyMaxM) {
-        for (int sk : skinny_split_candidates(N, K)) {
-            for (int fr = 0; fr <= (sk > 1 ? 1 : 0); ++fr) {
-                const double us = predict_skinny_us(M, N, K, sk, fr != 0);
-                if (us < best) {
-                    best = us;
-                    found = true;
-                    Spec s;
-                    s.fam = FAM_SKINNY; s.sk = (int)sk; s.fr = fr;
-                    *out = s;
-                }
-            }
-        }
+        best = skinny_choice(M, N, K, out);
+        found = best < 1e300;
     }
     // The large-tile model below was fitted to timings with the operands warm in the last-level cache wherever
     // they fit it, the streaming family's to operands streamed from HBM; the two are not comparable for a few
@@ -614,6 +636,7 @@ bool kernels_can_run(const hgemm_plan_s* p)
 {
     if (!p->padded) return fast_path_ok(p->M, p->N, p->K, p->lay);
     hgemm_layouts_t l = p->lay;
+    if (p->any_b) l.ldb = up8(l.ldb);
     l.ldc = up8(p->N);                      // C is addressed in 64 bits, whatever its leading dimension
     return fast_path_ok(p->M, up8(p->N), p->K, l);
 }
@@ -625,6 +648,7 @@ size_t place_copies(hgemm_plan_s* p)
     if (!p->padded) return 0;
     const size_t N = (size_t)up8(p->N), K = (size_t)p->K;
     p->b_off = up256((size_t)p->M * K * 2);
+    if (p->any_b && !p->static_ws) return p->b_off;
     return p->b_off + up256(K * N * 2);
 }
 
@@ -723,9 +747,10 @@ hgemm_status_t finish_plan(hgemm_plan_s* p)
         s.sk = (int)sk;
         if (sk == 1) s.fr = 0;
         if (!tn && s.nr != 16) return HGEMM_ERR_UNSUPPORTED;
+        if (p->any_b && s.wv != 4) return HGEMM_ERR_UNSUPPORTED;
         const int64_t strips = (N + skinny_cols(s, tn) - 1) / skinny_cols(s, tn);
         if (s.fr && strips * (int64_t)sizeof(int) > (int64_t)kCounterBytes) return HGEMM_ERR_UNSUPPORTED;
-        p->skinny = skinny_kernel(mb, s.fr != 0, s.wv, tn ? s.nr : 0);
+        p->skinny = p->any_b ? skinny_any_b_kernel(mb, s.fr != 0) : skinny_kernel(mb, s.fr != 0, s.wv, tn ? s.nr : 0);
         if (!p->skinny) return HGEMM_ERR_UNSUPPORTED;
         GemmArgs& a = p->args;
         a.M = (int)M; a.N = (int)N; a.K = (int)K;
@@ -840,8 +865,13 @@ bool device_is_gfx950(int dev)
 // it comes from: the layout's dispatch table (packed leading dimensions only), else the cost model, whose pick a
 // large problem trades for the kernel tuned for the nearest shape of the table (neighbour_choice); `fallback` is
 // the model's pick in that last case, should the neighbour's kernel refuse the shape.
-const char* choose_spec(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, bool padded, Spec* first, Spec* fallback)
+// any_b: B is to be streamed where it lies (streams_any_b), which only the streaming family does.
+const char* choose_spec(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, bool padded, bool any_b, Spec* first, Spec* fallback)
 {
+    if (any_b && skinny_choice(M, N, K, first) < 1e300) {
+        *fallback = *first;
+        return "model";
+    }
     const bool tn = l.b == HGEMM_COL_MAJOR;
     const bool packed = l.lda == K && l.ldc == N && l.ldb == (tn ? K : N);
     const char* source = "table";
@@ -889,7 +919,7 @@ hgemm_status_t init_plan(hgemm_plan_s* p, int64_t M, int64_t N, int64_t K, const
     p->M = M; p->N = N; p->K = K; p->lay = l; p->device = dev;
     p->padded = false;
     p->static_ws = static_ws;
-    p->copy_a = p->copy_b = false;
+    p->copy_a = p->copy_b = p->any_b = false;
     p->uN = N; p->uK = K; p->ulay = l;
     p->a_off = p->b_off = p->bt_off = 0;
 
@@ -917,6 +947,8 @@ hgemm_status_t init_plan(hgemm_plan_s* p, int64_t M, int64_t N, int64_t K, const
                 p->copy_a = K % 8 != 0 || !fast_path_ok(M, Np, Kp, la);
                 p->copy_b = (row_b ? N : K) % 8 != 0 || !fast_path_ok(M, Np, Kp, lb);
                 p->padded = true;
+                p->any_b = p->copy_b && streams_any_b(M, N, K, l);
+                if (p->any_b) p->copy_b = false;
                 p->K = K = Kp;
                 p->lay.lda = p->copy_a ? Kp : l.lda;
                 p->lay.ldb = p->copy_b ? lp.ldb : l.ldb;
@@ -932,12 +964,17 @@ hgemm_status_t init_plan(hgemm_plan_s* p, int64_t M, int64_t N, int64_t K, const
             st = finish_plan(p);
         } else {
             Spec fallback;
-            if (!strcmp(choose_spec(M, N, K, l, p->padded, &p->spec, &fallback), "neighbour")) {
+            if (!strcmp(choose_spec(M, N, K, l, p->padded, p->any_b, &p->spec, &fallback), "neighbour")) {
                 if (finish_plan(p) == HGEMM_OK) return HGEMM_OK;
                 p->spec = fallback;
                 if (l.b == HGEMM_COL_MAJOR || p->padded) p->spec.tb = 0;
             }
             st = finish_plan(p);
+            if (st == HGEMM_ERR_UNSUPPORTED && p->any_b) {     // not the streaming family after all: B is copied
+                p->any_b = false;
+                p->copy_b = true;
+                p->lay.ldb = l.ldb;
+            }
             if (st == HGEMM_ERR_UNSUPPORTED) {
                 // a table row naming a kernel this build lacks, or a row of the NN table, consulted for a
                 // column-major B, that names the streaming family (row-major B only): the cost model decides
@@ -950,7 +987,7 @@ hgemm_status_t init_plan(hgemm_plan_s* p, int64_t M, int64_t N, int64_t K, const
                 }
             }
             if (st != HGEMM_OK && st != HGEMM_ERR_WORKSPACE && p->padded) {   // e.g. no memory for the padded copies: the generic kernel needs none
-                p->padded = p->copy_a = p->copy_b = false;
+                p->padded = p->copy_a = p->copy_b = p->any_b = false;
                 p->N = p->uN; p->K = p->uK; p->lay = p->ulay;
                 p->spec = Spec();
                 st = finish_plan(p);
@@ -1102,14 +1139,18 @@ hgemm_status_t hgemm_plan_choice(int64_t M, int64_t N, int64_t K, const hgemm_la
     std::string out;
     const bool nonempty = M > 0 && N > 0 && K > 0;
     bool fast = nonempty && fast_path_ok(M, N, K, l);
-    bool padded = false;
+    bool padded = false, any_b = false;
     if (!fast && nonempty && (double)M * (double)N * (double)K >= kPadMinMacs) {
         const int64_t Kp = (K + 7) / 8 * 8, Np = (N + 7) / 8 * 8;
         hgemm_layouts_t lp = l;
         lp.lda = Kp;
         lp.ldb = (l.b == HGEMM_ROW_MAJOR) ? Np : Kp;
         lp.ldc = Np;
-        if (fast_path_ok(M, Np, Kp, lp) && l.ldc < ((int64_t)1 << 31)) { padded = fast = true; N = Np; K = Kp; l = lp; }
+        if (fast_path_ok(M, Np, Kp, lp) && l.ldc < ((int64_t)1 << 31)) {
+            any_b = streams_any_b(M, N, K, l);
+            padded = fast = true;
+            N = Np; K = Kp; l = lp;
+        }
     }
     int64_t rows = 0, cols = 0;
     bool bt = false;
@@ -1125,7 +1166,7 @@ hgemm_status_t hgemm_plan_choice(int64_t M, int64_t N, int64_t K, const hgemm_la
         out = "generic";
     } else {
         Spec first, fallback;
-        const char* source = choose_spec(M, N, K, l, padded, &first, &fallback);
+        const char* source = choose_spec(M, N, K, l, padded, any_b, &first, &fallback);
         out = std::string(source) + ": " + spec_to_string(first) + (padded ? ",pad=1" : "");
     }
     if (out.size() + 1 > n) { buf[0] = '\0'; return HGEMM_ERR_INVALID_ARG; }
@@ -1171,7 +1212,7 @@ static hgemm_status_t run_plan(const hgemm_plan_s* plan, const void* A, const vo
     int64_t lda = plan->lay.lda, ldb = plan->lay.ldb, b_rows = plan->args.b_rows;
     const bool row_b = plan->lay.b == HGEMM_ROW_MAJOR;
     if (plan->padded && plan->spec.fam != FAM_GENERIC) {
-        const bool copy_a = plan->copy_a || ((uintptr_t)A & 15), copy_b = plan->copy_b || ((uintptr_t)B & 15);
+        const bool copy_a = plan->copy_a || ((uintptr_t)A & 15), copy_b = plan->copy_b || (((uintptr_t)B & 15) && !plan->any_b);
         if (copy_a || copy_b) {
             char* ws = (char*)plan->workspace;
             const int64_t Np = up8(N);
@@ -1193,7 +1234,7 @@ static hgemm_status_t run_plan(const hgemm_plan_s* plan, const void* A, const vo
     auto finish = [&]() -> hgemm_status_t { return hipGetLastError() == hipSuccess ? HGEMM_OK : HGEMM_ERR_LAUNCH; };
 
     // A and B are read in 16-byte chunks; C may start anywhere
-    const bool aligned = ((((uintptr_t)A) | ((uintptr_t)B)) & 15) == 0;
+    const bool aligned = ((((uintptr_t)A) | (plan->any_b ? (uintptr_t)0 : (uintptr_t)B)) & 15) == 0;
     if (plan->spec.fam == FAM_GENERIC || !aligned) {
         if (N > (int64_t)64 * 0x7fffffff || (M + 3) / 4 > 65535) {
             // grid.y limit: fold rows into several launches

@@ -9,6 +9,12 @@ namespace {
 #endif
 constexpr int kDepth = HGEMM_SKINNY_DEPTH;      // steps of loads a wave keeps in flight (4 KiB each)
 
+template <int MB>
+void (*any_b_kernel(bool fused))(GemmArgs)
+{
+    return fused ? skinny_gemm_kernel<MB, true, kDepth, 4, true> : skinny_gemm_kernel<MB, false, kDepth, 4, true>;
+}
+
 template <int WAVES>
 void (*kernel_for(int mb, bool fused))(GemmArgs)
 {
@@ -54,6 +60,12 @@ void (*tn_kernel_for(int mb, bool fused, int nr))(GemmArgs)
     return nullptr;
 }
 }  // namespace
+
+// Row-major B whose rows start at any element: workgroups of 4 waves.
+void (*skinny_any_b_kernel(int mb, bool fused))(GemmArgs)
+{
+    return mb == 1 ? any_b_kernel<1>(fused) : mb == 2 ? any_b_kernel<2>(fused) : mb == 4 ? any_b_kernel<4>(fused) : nullptr;
+}
 
 // Kernel for M <= 16 * mb (mb in {1, 2, 4}) and workgroups of 4, 8 or 16 waves, with or without the fused
 // reduction, for row-major B (tn_rows = 0) or column-major B with tn_rows = 16, 32 or 64 rows of B per workgroup;

@@ -850,12 +850,13 @@ def test_phased_kernels_bit_exact_both_layouts_and_split(shape):
                 hg.Plan(*shape, None, bad)
 
 
-@pytest.mark.parametrize("shape", [(65, 130, 257), (130, 201, 264), (200, 264, 129), (1030, 1031, 5), (17, 4099, 520), (100, 1000, 1003), (512, 1001, 4096)],
+@pytest.mark.parametrize("shape", [(65, 130, 257), (130, 201, 264), (200, 264, 129), (1030, 1031, 5), (17, 4099, 520), (100, 1000, 1003), (512, 1001, 4096),
+                                   (1, 1001, 1100), (32, 4099, 1003), (9, 130, 1029), (40, 33001, 513)],
                          ids=lambda s: "x".join(map(str, s)))
 @pytest.mark.parametrize("tn", [False, True])
 def test_ragged_operands_are_copied_only_where_needed(shape, tn):
     """N, K and leading dimensions off the multiples of 8, one at a time and together: operands that the kernels read
-    where they lie, operands copied (also rows of fewer than 8 elements), C stored at odd widths, pitches and addresses.
+    where they lie (the last four shapes: also a row-major B off the 16-byte grid, by the streaming family), operands copied (also rows of fewer than 8 elements), C stored at odd widths, pitches and addresses.
     Everything around the operands is NaN, and so is everything around C afterwards."""
     M, N, K = shape
     name, a, b = wl.exact_family_for(shape, seed=92)
