@@ -155,6 +155,7 @@ struct hgemm_plan_s {
     const MfmaEntry* entry;     // null for the generic and skinny families
     void (*skinny)(GemmArgs);   // the skinny family's kernel, else null
     void (*kernel)(GemmArgs);   // the large-tile family's main kernel and its dynamic LDS
+    void (*kernel_any)(GemmArgs);   // what runs in its place for a narrow C or a B of fewer rows than K (the same, or its twin)
     int kernel_lds;
     GemmArgs args;              // pointers filled in at run time
     void* workspace;            // [transposed B (when spec.tb)] [split-K / stream-K partial sums]
@@ -705,6 +706,7 @@ bool select_kernel(hgemm_plan_s* p)
     void (*const all_tn[])(GemmArgs) = {e->plain_tn, e->splitk_tn, e->streamk_tn, e->splitk_fused_tn, e->persist_tn, e->acc16_tn, e->phased_tn, e->phased_splitk_tn};
     const int which = s.sm ? 2 : s.ps ? 4 : split && s.fr ? 3 : s.ph ? (split ? 7 : 6) : split ? 1 : s.ac == 16 ? 5 : 0;
     p->kernel = p->tn_kernel ? all_tn[which] : all[which];
+    p->kernel_any = which != 0 ? p->kernel : p->tn_kernel ? e->plain_any_tn : e->plain_any;
     p->kernel_lds = s.ph ? e->phased_lds : e->lds_bytes;
     if (!p->kernel) return false;
     if (p->kernel_lds <= 64 * 1024) return true;
@@ -714,10 +716,11 @@ bool select_kernel(hgemm_plan_s* p)
     const unsigned bit = 1u << (which + (p->tn_kernel ? 16 : 0));
     const bool keep = idx < kMaxEntries && p->device >= 0 && p->device < kMaxDevices;
     if (keep && (allowed[p->device][idx].load(std::memory_order_acquire) & bit)) return true;
-    if (hipFuncSetAttribute((const void*)p->kernel, hipFuncAttributeMaxDynamicSharedMemorySize, p->kernel_lds) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
+    for (auto k : {p->kernel, p->kernel_any})
+        if (hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, p->kernel_lds) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
     if (keep) allowed[p->device][idx].fetch_or(bit, std::memory_order_release);
     return true;
 }
@@ -759,10 +762,9 @@ hgemm_status_t finish_plan(hgemm_plan_s* p)
         a.splits = (int)sk;
         a.k_per_split = (int)(((ksteps + sk - 1) / sk) * step);
         a.b_rows = (int)(p->padded && !p->copy_b ? p->uK : K);
-        a.part_ld = (int)up8(N);
         // workspace: [counters] [padded copies of A and B (problems off the 16-byte grid)] [planes]
         const size_t pad_bytes = place_copies(p);
-        const size_t partial_bytes = sk > 1 ? up256((size_t)sk * (size_t)M * (size_t)a.part_ld * sizeof(float)) : 0;
+        const size_t partial_bytes = sk > 1 ? up256((size_t)sk * (size_t)M * (size_t)part_ld((int)N) * sizeof(float)) : 0;
         const size_t ctr_bytes = (s.fr || (p->static_ws && pad_bytes + partial_bytes > 0)) ? kCounterBytes : 0;
         p->a_off += ctr_bytes; p->b_off += ctr_bytes;
         p->bt_off = ctr_bytes + pad_bytes;
@@ -824,10 +826,9 @@ hgemm_status_t finish_plan(hgemm_plan_s* p)
         }
     }
     a.b_rows = (int)(p->padded && !p->copy_b ? p->uK : K);
-    a.part_ld = (int)up8(N);
     const size_t pad_bytes = place_copies(p);
     size_t bt_bytes = s.tb ? up256((size_t)N * (size_t)K * 2) : 0;
-    size_t partial_bytes = sk > 1 ? (size_t)sk * (size_t)M * (size_t)a.part_ld * sizeof(float) : 0;
+    size_t partial_bytes = sk > 1 ? (size_t)sk * (size_t)M * (size_t)part_ld((int)N) * sizeof(float) : 0;
     if (s.sm) partial_bytes = (size_t)2 * a.sk_workers * e->bm * e->bn * sizeof(float);
     partial_bytes = up256(partial_bytes);
     // fused split-K: one arrival counter per tile in front of everything else.  Counters are zero
@@ -842,6 +843,90 @@ hgemm_status_t finish_plan(hgemm_plan_s* p)
     p->workspace_bytes = ctr_bytes + pad_bytes + bt_bytes + partial_bytes;
     if (!select_kernel(p)) return HGEMM_ERR_LAUNCH;
     return acquire_workspace(p, partial_bytes, ctr_bytes);
+}
+
+// Phased kernels on problems that the table does not hold.  The cost model above was fitted before they existed.  They
+// have a model of their own, fitted (soft-L1 on log time, 850 timings on 240 random problems of at least 3e10 flop, operands
+// rotated through 400 MB, rms 8-13 %): rounds of workgroups over the compute units, a K-tile the slower the larger the share
+// of the chip that works, reads of A and B and the planes of a split at rates of their own.
+struct PhasedTile { const char* spec; int bm, bn; double tk, fixed, busy, tail, bw, plane_bw, reduce, t0; };
+constexpr PhasedTile kPhasedTiles[] = {
+    {"mfma,bm=256,bn=256,bk=64,wm=2,wn=4,st=2,pf=1,sk=1,gm=8,mi=16,ph=1", 256, 256, 0.968, 8.218, 0.475, 1.0, 5.161, 3.986, 4.727, 0.3},
+    {"mfma,bm=256,bn=128,bk=64,wm=2,wn=4,st=3,pf=1,sk=1,gm=8,mi=16,ph=1", 256, 128, 0.452, 4.214, 1.248, 1.0, 4.959, 3.337, 2.092, 4.0},
+    {"mfma,bm=128,bn=256,bk=64,wm=2,wn=4,st=3,pf=1,sk=1,gm=8,mi=16,ph=1", 128, 256, 0.688, 3.758, 0.366, 0.995, 5.311, 3.612, 4.954, 1.557},
+    {"mfma,bm=128,bn=128,bk=64,wm=2,wn=4,st=3,pf=1,sk=1,gm=8,ph=1", 128, 128, 0, 0, 0, 0, 0, 0, 0, 0},      // twins only (below)
+};
+double predict_phased_us(const PhasedTile& c, int64_t M, int64_t N, int64_t K, int64_t sk)
+{
+    const int64_t kt = (K + 63) / 64;
+    sk = effective_splits(kt, sk);
+    const double per = std::ceil((double)kt / (double)sk);
+    const double wgs = (double)(((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) * sk);
+    const double rounds = wgs / (double)cu_count(), full = std::floor(rounds), part = rounds - full;
+    auto round = [&](double share) { return per * c.tk * (1.0 + c.busy * share) + c.fixed; };
+    const double cu = full > 0 ? full * round(1.0) + (part > 0 ? c.tail * round(part) : 0.0) : round(part);
+    const double mem = 2.0 * ((double)M * K + (double)K * N + (double)M * N) / (c.bw * 1e6);
+    const double main = std::pow(std::pow(cu, 6.0) + std::pow(mem, 6.0), 1.0 / 6.0);
+    return c.t0 + main + (sk > 1 ? c.reduce + (double)sk * M * N * 4.0 / (c.plane_bw * 1e6) : 0.0);
+}
+
+bool same_tile(const Spec& s, const PhasedTile& c) { return s.fam == FAM_MFMA && s.bm == c.bm && s.bn == c.bn; }
+
+// A phased kernel in the place of `pick` (the cost model's choice, or the nearest tuned shape's).
+// From 3e10 flop: the phased tile and split with the smallest prediction, if that is below 0.95 of the pick's.  The cost
+// model was fitted with operands in the last-level cache and is 13-16 % below measured times on problems of this size
+// whose operands come from HBM: its predictions count 1.12 times.  A kernel that neither model knows stays.  A pick that
+// needs no workspace is not traded for a split: a program that plans on every call would pay for the allocation
+// (1024 x 2048 x 8192 through the one-call wrapper: 48 us, as a split 96).
+// Below, or where no prediction is low enough: the phased schedule of the pick's own tile and split, if a split is long
+// enough to pay for the longer prologue and epilogue (256 x 256: 128 of K, smaller tiles 384; 128 x 128 at K = 100: 10-20 %
+// slower) and the rows of a row-major B start on cache lines where a unit is one line wide (BN = 128; 776 x 4056 x 2656:
+// 6 % slower otherwise).
+bool phased_choice(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, const Spec& pick, Spec* out)
+{
+    if (pick.fam != FAM_MFMA || pick.ac != 32 || pick.tb) return false;
+    if (pick.mi == 16 && !pick.ph && K / std::max(1, pick.sk) < 512) return false;
+    const int most_sk = pick.sk > 1 || pick.sm ? 8 : 1;
+    const double flop = 2.0 * (double)M * (double)N * (double)K;
+    if (flop >= 3e10 && std::min(M, N) >= 96) {
+        double limit = 0;                            // a kernel that neither model knows stays
+        for (const PhasedTile& c : kPhasedTiles)
+            if (pick.ph && c.tk > 0 && same_tile(pick, c)) limit = 0.95 * predict_phased_us(c, M, N, K, pick.sk);
+        if (!pick.ph && !pick.sm && !pick.ps && pick.mi == 32) {
+            const MfmaEntry* e = find_entry(pick);
+            if (e && !e->deep)
+                limit = 0.95 * 1.12 * predict_us(M, N, K, pick.bm, pick.bn, pick.bk, pick.wm, pick.wn, pick.st, pick.pf,
+                                                 effective_splits((K + pick.bk - 1) / pick.bk, pick.sk), predict_big(M, N, K));
+        }
+        const PhasedTile* best = nullptr;
+        int best_sk = 1;
+        for (const PhasedTile& c : kPhasedTiles) {
+            if (c.tk <= 0 || c.bm >= 2 * M || c.bn >= 2 * N) continue;
+            const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+            for (int sk : {1, 2, 3, 4, 6, 8}) {
+                if (sk > most_sk || (sk > 1 && (tiles * sk > 640 || K / sk < 256))) break;
+                if (2 * tiles * sk < cu_count()) continue;     // half the chip idle: outside what the model was fitted to choose
+                const double us = predict_phased_us(c, M, N, K, sk);
+                if (us < limit) { limit = us; best = &c; best_sk = sk; }
+            }
+        }
+        if (best && parse_spec(best->spec, out)) {
+            out->sk = best_sk;
+            return true;
+        }
+    }
+    if (pick.ph || pick.sm || pick.ps || pick.fr) return false;
+    for (const PhasedTile& c : kPhasedTiles) {
+        if (!same_tile(pick, c)) continue;
+        const int64_t k_split = K / std::max(1, pick.sk);
+        if (k_split < (c.bm == 256 && c.bn == 256 ? 128 : 384)) return false;
+        if (l.b == HGEMM_ROW_MAJOR && c.bn == 128 && l.ldb % 64 != 0) return false;
+        if (!parse_spec(c.spec, out)) return false;
+        out->sk = pick.sk;
+        out->gm = pick.gm;
+        return true;
+    }
+    return false;
 }
 
 // True when device `dev` is a gfx950; the answer is kept per device (hipGetDeviceProperties is slow).
@@ -863,30 +948,42 @@ bool device_is_gfx950(int dev)
 // scratch array and nothing is allocated; otherwise the workspace is hipMalloc'ed and owned by the plan.
 // The specialisation the planner tries first for an aligned problem of less than 2 GiB per operand, and where
 // it comes from: the layout's dispatch table (packed leading dimensions only), else the cost model, whose pick a
-// large problem trades for the kernel tuned for the nearest shape of the table (neighbour_choice); `fallback` is
-// the model's pick in that last case, should the neighbour's kernel refuse the shape.
+// large problem trades for the kernel tuned for the nearest shape of the table (neighbour_choice), and either of them for a
+// phased kernel (phased_choice).
 // any_b: B is to be streamed where it lies (streams_any_b), which only the streaming family does.
-const char* choose_spec(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, bool padded, bool any_b, Spec* first, Spec* fallback)
+// Returns the specialisations to try in order (a later one if the device or the workspace refuses an earlier one) and
+// says where the first comes from.
+struct Choices {
+    const char* source;
+    int n;
+    Spec spec[3];
+};
+Choices choose_spec(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, bool padded, bool any_b)
 {
-    if (any_b && skinny_choice(M, N, K, first) < 1e300) {
-        *fallback = *first;
-        return "model";
-    }
+    Choices c{"table", 1, {}};
     const bool tn = l.b == HGEMM_COL_MAJOR;
-    const bool packed = l.lda == K && l.ldc == N && l.ldb == (tn ? K : N);
-    const char* source = "table";
-    if (!table_lookup(M, N, K, tn, first) || !packed) {
-        source = "model";
-        if (!model_choice(M, N, K, first, !tn)) {
-            *first = heuristic(M, N, K);
-            source = "rules";
-        }
-        *fallback = *first;
-        if (neighbour_choice(M, N, K, tn, *fallback, first)) return "neighbour";
+    if (any_b && skinny_choice(M, N, K, &c.spec[0]) < 1e300) {
+        c.source = "model";
+        return c;
     }
-    if (tn || padded) first->tb = 0;      // B already has K contiguous / is copied once already
-    *fallback = *first;
-    return source;
+    const bool packed = l.lda == K && l.ldc == N && l.ldb == (tn ? K : N);
+    Spec model, near, phased;
+    if (!packed || !table_lookup(M, N, K, tn, &c.spec[0])) {
+        c.source = "model";
+        if (!model_choice(M, N, K, &model, !tn)) {
+            model = heuristic(M, N, K);
+            c.source = "rules";
+        }
+        c.n = 0;
+        const bool neighbour = neighbour_choice(M, N, K, tn, model, &near);
+        if (phased_choice(M, N, K, l, neighbour ? near : model, &phased)) c.spec[c.n++] = phased;
+        else if (neighbour) c.source = "neighbour";
+        if (neighbour) c.spec[c.n++] = near;
+        c.spec[c.n++] = model;
+    }
+    for (int i = 0; i < c.n; ++i)
+        if (tn || padded) c.spec[i].tb = 0;       // B already has K contiguous / is copied once already
+    return c;
 }
 
 hgemm_status_t init_blocked(hgemm_plan_s* p);
@@ -963,13 +1060,12 @@ hgemm_status_t init_plan(hgemm_plan_s* p, int64_t M, int64_t N, int64_t K, const
             p->spec = Spec();
             st = finish_plan(p);
         } else {
-            Spec fallback;
-            if (!strcmp(choose_spec(M, N, K, l, p->padded, p->any_b, &p->spec, &fallback), "neighbour")) {
-                if (finish_plan(p) == HGEMM_OK) return HGEMM_OK;
-                p->spec = fallback;
-                if (l.b == HGEMM_COL_MAJOR || p->padded) p->spec.tb = 0;
+            const Choices c = choose_spec(M, N, K, l, p->padded, p->any_b);
+            for (int i = 0; i < c.n; ++i) {
+                p->spec = c.spec[i];
+                st = finish_plan(p);
+                if (st == HGEMM_OK) return HGEMM_OK;
             }
-            st = finish_plan(p);
             if (st == HGEMM_ERR_UNSUPPORTED && p->any_b) {     // not the streaming family after all: B is copied
                 p->any_b = false;
                 p->copy_b = true;
@@ -1165,9 +1261,8 @@ hgemm_status_t hgemm_plan_choice(int64_t M, int64_t N, int64_t K, const hgemm_la
     } else if (!fast) {
         out = "generic";
     } else {
-        Spec first, fallback;
-        const char* source = choose_spec(M, N, K, l, padded, any_b, &first, &fallback);
-        out = std::string(source) + ": " + spec_to_string(first) + (padded ? ",pad=1" : "");
+        const Choices c = choose_spec(M, N, K, l, padded, any_b);
+        out = std::string(c.source) + ": " + spec_to_string(c.spec[0]) + (padded ? ",pad=1" : "");
     }
     if (out.size() + 1 > n) { buf[0] = '\0'; return HGEMM_ERR_INVALID_ARG; }
     memcpy(buf, out.c_str(), out.size() + 1);
@@ -1269,7 +1364,7 @@ static hgemm_status_t run_plan(const hgemm_plan_s* plan, const void* A, const vo
             const int blocks = (int)std::min<int64_t>((quads + 255) / 256, 2048);
             hipLaunchKernelGGL(splitk_reduce_kernel, dim3(blocks), dim3(256), 0, stream,
                                (const float*)((const char*)plan->workspace + plan->partial_offset), (_Float16*)C, (int)M, (int)N,
-                               a.part_ld, (int)plan->lay.ldc, a.c_wide, a.splits);
+                               part_ld((int)N), (int)plan->lay.ldc, a.c_wide, a.splits);
         }
         return finish();
     }
@@ -1283,7 +1378,7 @@ static hgemm_status_t run_plan(const hgemm_plan_s* plan, const void* A, const vo
         a.B = (const _Float16*)((char*)plan->workspace + plan->bt_off);
     }
     const unsigned grid = plan->spec.sm ? (unsigned)(a.dp_tiles + a.sk_workers) : plan->spec.ps ? (unsigned)std::min<int64_t>(wgs, cu_count()) : wgs;
-    hipLaunchKernelGGL(plan->kernel, dim3(grid, (unsigned)a.splits), dim3(e->threads), plan->kernel_lds, stream, a);
+    hipLaunchKernelGGL(a.c_wide && (plan->tn_kernel || a.b_rows == K) ? plan->kernel : plan->kernel_any, dim3(grid, (unsigned)a.splits), dim3(e->threads), plan->kernel_lds, stream, a);
     if (plan->spec.sm) {
         if (hipGetLastError() != hipSuccess) return HGEMM_ERR_LAUNCH;
         hipLaunchKernelGGL(e->fixup, dim3(wgs - (unsigned)a.dp_tiles, (unsigned)((e->bm * e->bn / 4 + 1023) / 1024)), dim3(256), 0,
@@ -1294,7 +1389,7 @@ static hgemm_status_t run_plan(const hgemm_plan_s* plan, const void* A, const vo
         const int blocks = (int)std::min<int64_t>((quads + 255) / 256, 2048);
         hipLaunchKernelGGL(splitk_reduce_kernel, dim3(blocks), dim3(256), 0, stream,
                            (const float*)((const char*)plan->workspace + plan->partial_offset), (_Float16*)C, (int)M, (int)N,
-                           a.part_ld, (int)plan->lay.ldc, a.c_wide, a.splits);
+                           part_ld((int)N), (int)plan->lay.ldc, a.c_wide, a.splits);
     }
     return finish();
 }
@@ -1611,6 +1706,16 @@ hgemm_status_t hgemm_predict_us(int64_t M, int64_t N, int64_t K, const char* spe
         return HGEMM_OK;
     }
     if (s.fam != FAM_MFMA || s.sm || s.tb || s.ps || s.ac == 16 || !find_entry(s)) return HGEMM_ERR_UNSUPPORTED;
+    if (s.ph) {
+        // the cost model does not know the phased schedule: it counts like the best schedule of its tile that the model knows
+        if (s.fr || !find_entry(s)->phased) return HGEMM_ERR_UNSUPPORTED;
+        *us = 1e300;
+        for (const MfmaEntry& e : registry()) {
+            if (e.bm != s.bm || e.bn != s.bn || e.deep || e.mi != 32) continue;
+            *us = std::min(*us, predict_us(M, N, K, e.bm, e.bn, e.bk, e.wm, e.wn, e.st, e.pf, effective_splits((K + e.bk - 1) / e.bk, s.sk), predict_big(M, N, K)));
+        }
+        return HGEMM_OK;
+    }
     const int64_t eff = effective_splits((K + s.bk - 1) / s.bk, s.sk);
     *us = predict_us(M, N, K, s.bm, s.bn, s.bk, s.wm, s.wn, s.st, s.pf, eff, predict_big(M, N, K));
     if (s.fr && eff > 1) *us += fused_delta_us(M, N, eff);

@@ -78,9 +78,6 @@ struct GemmArgs {
     int* counters;       // fused split-K: one arrival counter per output tile, zero between launches
     int M, N, K;
     int lda, ldb, ldc;   // elements
-    int b_rows;          // rows a row-major B has: K, or fewer where K was rounded up to whole 16-byte chunks (A zero-filled)
-    int part_ld;         // floats per row of a split-K plane: N rounded up to 8
-    int c_wide;          // every row of C starts on 16 bytes and holds whole 16-byte chunks (else store_cols goes narrower)
     int tiles_m, tiles_n;
     int swizzle;         // group height in tiles for the tile order; 0 = row-major
     // divisors of the tile order, fixed per launch (set_tile_map): tiles_n; one band = group * tiles_n
@@ -94,7 +91,13 @@ struct GemmArgs {
     int sk_workers;
     int sk_iters_per_worker;
     int sk_total_iters;  // (tiles - dp_tiles) * ceil(K / BK)
+    // behind the rest: what every kernel needs first is fetched in the fewest loads
+    int b_rows;          // rows a row-major B has: K, or fewer where K was rounded up to whole 16-byte chunks (A zero-filled)
+    int c_wide;          // every row of C starts on 16 bytes and holds whole 16-byte chunks (else store_cols goes narrower)
 };
+
+// Floats per row of a split-K plane: N rounded up to 8, so that every row starts on 16 bytes.
+__host__ __device__ inline int part_ld(int n) { return (n + 7) & ~7; }
 
 // Kernel modes: one full-K tile per workgroup; split-K (grid.y = split) with the reduction in a
 // second launch; stream-K; split-K with the reduction fused into the kernel (the workgroup that
@@ -105,8 +108,11 @@ struct GemmArgs {
 // running sums rounded to fp16 after every matrix-core instruction, i.e. after every 16 products: Section 1
 // of the paper names fp16 accumulators as a valid choice and Section 2.3.2's exact-match test is built
 // for them; the matrix cores of this chip only accumulate in fp32, so the rounding is applied to the
-// fp32 accumulator registers and buys no register space).
-enum { MODE_PLAIN = 0, MODE_SPLITK = 1, MODE_STREAMK = 2, MODE_SPLITK_FUSED = 3, MODE_PERSIST = 4, MODE_ACC16 = 5 };
+// fp32 accumulator registers and buys no register space); and plain for problems off the 16-byte grid: rows of C of any
+// width and alignment, a row-major B of fewer rows than K (GemmArgs::b_rows).  The other modes find that out at run
+// time, but the plain kernels, which short calls run on, are 1-2 % slower for one more argument and both epilogues
+// (1024^3 5.70 -> 5.76 us, 3715 x 1184 x 200 6.93 -> 7.09 us).
+enum { MODE_PLAIN = 0, MODE_SPLITK = 1, MODE_STREAMK = 2, MODE_SPLITK_FUSED = 3, MODE_PERSIST = 4, MODE_ACC16 = 5, MODE_PLAIN_ANY = 6 };
 
 // Stores the first `left` of V's 4 or 8 consecutive columns of C.  `wide` (GemmArgs::c_wide, the same for the whole
 // launch): one aligned store.  Otherwise the row may start at any element: a whole group is still one store (global
@@ -148,7 +154,7 @@ template <int THREADS, int QPR>
 __device__ __forceinline__ void sum_split_planes(const GemmArgs& g, int m0, int n0, int rows, int t)
 {
     constexpr int QU = 4, SU = 4;
-    const size_t plane2 = (size_t)g.M * g.part_ld / 2;              // plane size in 8-byte words
+    const size_t plane2 = (size_t)g.M * part_ld(g.N) / 2;              // plane size in 8-byte words
     const int items = rows * QPR;
     for (int qb = 0; qb < items; qb += QU * THREADS) {
         const unsigned long long* src[QU];
@@ -160,7 +166,7 @@ __device__ __forceinline__ void sum_split_planes(const GemmArgs& g, int m0, int 
             const int q = qb + j * THREADS + t;
             const int m = m0 + q / QPR, n = n0 + (q % QPR) * 4;
             ok[j] = q < items && n < g.N;
-            src[j] = (const unsigned long long*)(g.partial + (ok[j] ? (size_t)m * g.part_ld + n : (size_t)m0 * g.part_ld + n0));
+            src[j] = (const unsigned long long*)(g.partial + (ok[j] ? (size_t)m * part_ld(g.N) + n : (size_t)m0 * part_ld(g.N) + n0));
             dst[j] = g.C + (size_t)m * g.ldc + n;
             sum[j] = float4v{0.f, 0.f, 0.f, 0.f};
         }
@@ -407,7 +413,7 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(GemmArgs g)
     constexpr bool PERSIST = MODE == MODE_PERSIST;
     constexpr bool ACC16 = MODE == MODE_ACC16;
     constexpr bool DEEP = C::DEEP;
-    static_assert(!DEEP || MODE == MODE_PLAIN, "deep-staged configurations run one full-K tile per workgroup");
+    static_assert(!DEEP || MODE == MODE_PLAIN || MODE == MODE_PLAIN_ANY, "deep-staged configurations run one full-K tile per workgroup");
     constexpr int MI = C::MI;
     static_assert(MI == 32 || !ACC16, "the 16-bit accumulator rounds after every 16 products: 32 x 32 x 16 instructions only");
     constexpr int LG = MI == 32 ? 5 : 4;           // lane / MI = the lane's k-chunk within a k-step
@@ -418,7 +424,9 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(GemmArgs g)
     // left to itself the compiler fetches some of them later, inside branches, and every such fetch is
     // another round trip to memory in front of the first copy (short kernels are latency chains).
     asm volatile("" :: "s"(g.A), "s"(g.B), "s"(g.C), "s"(g.M), "s"(g.N), "s"(g.K), "s"(g.lda), "s"(g.ldb), "s"(g.ldc),
-                 "s"(g.tiles_m), "s"(g.tiles_n), "s"(g.swizzle), "s"(g.k_per_split), "s"(g.splits), "s"(g.b_rows), "s"(g.c_wide), "s"(g.part_ld));
+                 "s"(g.tiles_m), "s"(g.tiles_n), "s"(g.swizzle), "s"(g.k_per_split), "s"(g.splits));
+    if constexpr (MODE != MODE_PLAIN && !TN) asm volatile("" :: "s"(g.b_rows));
+    if constexpr (MODE != MODE_PLAIN && MODE != MODE_SPLITK) asm volatile("" :: "s"(g.c_wide));
     asm volatile("" :: "s"(g.by_tiles_n.m), "s"(g.by_tiles_n.l), "s"(g.by_band.m), "s"(g.by_band.l), "s"(g.by_rows.m),
                  "s"(g.by_rows.l), "s"(g.by_last_rows.m), "s"(g.by_last_rows.l));
 
@@ -483,7 +491,7 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(GemmArgs g)
 
     const unsigned OOB = 0x80000000u;        // beyond every num_records the host admits
     const int4v rsrcA = make_rsrc(g.A, (unsigned)min((long long)g.M * g.lda * 2, 0x7fffffffLL));
-    const int4v rsrcB = make_rsrc(g.B, (unsigned)min((long long)(TN ? g.N : min(k_end, g.b_rows)) * g.ldb * 2, 0x7fffffffLL));
+    const int4v rsrcB = make_rsrc(g.B, (unsigned)min((long long)(TN ? g.N : MODE == MODE_PLAIN ? k_end : min(k_end, g.b_rows)) * g.ldb * 2, 0x7fffffffLL));
 
     // ---- global -> LDS addressing (per lane, fixed for the whole K loop) ----
     // A: wave-load q = j*NWAVES + wave covers rows [q*A_RPI, (q+1)*A_RPI); lane i writes LDS slot i,
@@ -845,27 +853,45 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(GemmArgs g)
                     *(half4*)(stage + (lane & (MI - 1)) * ROWB + (tn * MI + vg * 8 + 4 * (lane >> LG)) * 2) = o;
                 }
             }
-            auto store_chunk = [&](int j, bool wide) {
-                const int idx = j * 64 + lane;
-                const int r = idx / CPR, ch = idx % CPR;
-                const half4 lo = *(const half4*)(stage + r * ROWB + ch * 16);
-                const half4 hi = *(const half4*)(stage + r * ROWB + ch * 16 + 8);
-                const int m = m0 + wm * C::WTM + tm * MI + r;
-                const int n = n0 + wn * C::WTN + ch * 8;
-                if (m < g.M && n < g.N) {
-                    half8 v;
+            if constexpr (MODE == MODE_PLAIN) {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) { v[e] = lo[e]; v[4 + e] = hi[e]; }
-                    store_cols(g.C + (size_t)m * g.ldc + n, v, g.N - n, wide);
+                for (int j = 0; j < (MI * CPR) / 64; ++j) {
+                    const int idx = j * 64 + lane;
+                    const int r = idx / CPR, ch = idx % CPR;
+                    const half4 lo = *(const half4*)(stage + r * ROWB + ch * 16);
+                    const half4 hi = *(const half4*)(stage + r * ROWB + ch * 16 + 8);
+                    const int m = m0 + wm * C::WTM + tm * MI + r;
+                    const int n = n0 + wn * C::WTN + ch * 8;
+                    if (m < g.M && n < g.N) {
+                        half8 v;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) { v[e] = lo[e]; v[4 + e] = hi[e]; }
+                        *(half8*)(g.C + (size_t)m * g.ldc + n) = v;
+                    }
                 }
-            };
-            // two loops, the one for narrow rows kept small and out of the way: short kernels pay for the code they fetch
-            if (__builtin_expect(g.c_wide != 0, 1)) {
-#pragma unroll
-                for (int j = 0; j < (MI * CPR) / 64; ++j) store_chunk(j, true);
             } else {
+                auto store_chunk = [&](int j, bool wide) {
+                    const int idx = j * 64 + lane;
+                    const int r = idx / CPR, ch = idx % CPR;
+                    const half4 lo = *(const half4*)(stage + r * ROWB + ch * 16);
+                    const half4 hi = *(const half4*)(stage + r * ROWB + ch * 16 + 8);
+                    const int m = m0 + wm * C::WTM + tm * MI + r;
+                    const int n = n0 + wn * C::WTN + ch * 8;
+                    if (m < g.M && n < g.N) {
+                        half8 v;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) { v[e] = lo[e]; v[4 + e] = hi[e]; }
+                        store_cols(g.C + (size_t)m * g.ldc + n, v, g.N - n, wide);
+                    }
+                };
+                // two loops, the one for narrow rows kept small: short kernels pay for the code they fetch
+                if (MODE != MODE_PLAIN_ANY && __builtin_expect(g.c_wide != 0, 1)) {
+#pragma unroll
+                    for (int j = 0; j < (MI * CPR) / 64; ++j) store_chunk(j, true);
+                } else {
 #pragma unroll 1
-                for (int j = 0; j < (MI * CPR) / 64; ++j) store_chunk(j, false);
+                    for (int j = 0; j < (MI * CPR) / 64; ++j) store_chunk(j, false);
+                }
             }
         }
     } else {
@@ -887,7 +913,7 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(GemmArgs g)
                     if (STREAMK) {
                         *(float4v*)(sk_slot + (row_t + tm * MI) * C::BN + col_t + tn * MI + vg * 8) = o;
                     } else if (m < g.M && n < g.N) {
-                        float* dst = g.partial + ((size_t)split * g.M + m) * g.part_ld + n;
+                        float* dst = g.partial + ((size_t)split * g.M + m) * part_ld(g.N) + n;
                         if (FUSED) {
                             // device-coherent stores: the summing workgroup may sit on another XCD
                             union { float4v f; unsigned long long u[2]; } w;

@@ -61,7 +61,7 @@ __global__ __launch_bounds__(C::THREADS) void phased_gemm_kernel(GemmArgs g)
 {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     asm volatile("" :: "s"(g.A), "s"(g.B), "s"(g.C), "s"(g.M), "s"(g.N), "s"(g.K), "s"(g.lda), "s"(g.ldb), "s"(g.ldc),
-                 "s"(g.tiles_m), "s"(g.tiles_n), "s"(g.swizzle), "s"(g.k_per_split), "s"(g.b_rows), "s"(g.c_wide), "s"(g.part_ld));
+                 "s"(g.tiles_m), "s"(g.tiles_n), "s"(g.swizzle), "s"(g.k_per_split), "s"(g.b_rows), "s"(g.c_wide));
     asm volatile("" :: "s"(g.by_tiles_n.m), "s"(g.by_tiles_n.l), "s"(g.by_band.m), "s"(g.by_band.l), "s"(g.by_rows.m),
                  "s"(g.by_rows.l), "s"(g.by_last_rows.m), "s"(g.by_last_rows.l));
     const int lane = threadIdx.x & 63;
@@ -241,7 +241,7 @@ __global__ __launch_bounds__(C::THREADS) void phased_gemm_kernel(GemmArgs g)
 #pragma unroll
                 for (int tn = 0; tn < C::TN; ++tn) {
                     const int m = m0 + h * C::HM + wm * C::QM + tm * 16 + l16, n = n0 + q * C::HN + wn * C::QN + tn * 16 + 4 * lg;
-                    if (m < g.M && n < g.N) *(float4v*)(g.partial + ((size_t)split * g.M + m) * g.part_ld + n) = acc[h][q][tm][tn];
+                    if (m < g.M && n < g.N) *(float4v*)(g.partial + ((size_t)split * g.M + m) * part_ld(g.N) + n) = acc[h][q][tm][tn];
                 }
         }); });
         return;

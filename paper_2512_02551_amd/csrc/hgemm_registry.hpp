@@ -25,6 +25,9 @@ struct MfmaEntry {
     void (*acc16_tn)(GemmArgs);
     void (*fixup)(GemmArgs);
     int mi = 32;                        // side of the matrix-core output block
+    // the plain kernel for a C whose rows are not whole aligned 16-byte chunks, or a row-major B of fewer rows than K
+    void (*plain_any)(GemmArgs) = nullptr;
+    void (*plain_any_tn)(GemmArgs) = nullptr;
     // the phased schedule of the same tile and waves (null where there is none): plain and two-launch split-K
     void (*phased)(GemmArgs) = nullptr;
     void (*phased_tn)(GemmArgs) = nullptr;
@@ -62,6 +65,8 @@ template <class C> inline MfmaEntry make_entry()
         e.threads = C::THREADS; e.lds_bytes = C::LDS_BYTES; e.deep = C::DEEP; e.mi = C::MI;
         e.plain = mfma_gemm_kernel<C, MODE_PLAIN, false>;
         e.plain_tn = mfma_gemm_kernel<C, MODE_PLAIN, true>;
+        e.plain_any = mfma_gemm_kernel<C, MODE_PLAIN_ANY, false>;
+        e.plain_any_tn = mfma_gemm_kernel<C, MODE_PLAIN_ANY, true>;
         return e;
     } else {
         MfmaEntry e{C::BM, C::BN, C::BK, C::WAVES_M, C::WAVES_N, C::STAGES, C::PF, C::THREADS, C::LDS_BYTES, false,
@@ -73,6 +78,8 @@ template <class C> inline MfmaEntry make_entry()
                          acc16_kernel<C, false>(), acc16_kernel<C, true>(),
                          streamk_fixup_kernel<C::BM, C::BN, C::BK>};
         e.mi = C::MI;
+        e.plain_any = mfma_gemm_kernel<C, MODE_PLAIN_ANY, false>;
+        e.plain_any_tn = mfma_gemm_kernel<C, MODE_PLAIN_ANY, true>;
         if constexpr (has_phased<C>()) {
             typedef PhasedCfg<C::BM, C::BN, C::WAVES_M, C::WAVES_N> P;
             static_assert(P::THREADS == C::THREADS, "the phased schedule keeps the waves");

@@ -210,7 +210,7 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_gemm_kernel(GemmArgs g)
             }
             store_cols(g.C + (size_t)m * g.ldc + n, o, g.N - n, g.c_wide);
         } else {
-            float* dst = g.partial + ((size_t)split * g.M + m) * g.part_ld + n;
+            float* dst = g.partial + ((size_t)split * g.M + m) * part_ld(g.N) + n;
             if (FUSED) {
                 union { float4v f; unsigned long long u[2]; } v0, v1;
                 v0.f = s0;
@@ -359,7 +359,7 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_tn_gemm_kernel(GemmArgs g)
                 for (int e = 0; e < 4; ++e) o[e] = (_Float16)s[e];
                 store_cols(g.C + (size_t)m * g.ldc + n, o, g.N - n, g.c_wide);
             } else {
-                float* dst = g.partial + ((size_t)split * g.M + m) * g.part_ld + n;
+                float* dst = g.partial + ((size_t)split * g.M + m) * part_ld(g.N) + n;
                 if (FUSED) {
                     union { float4v f; unsigned long long u[2]; } v;
                     v.f = s;

@@ -184,3 +184,28 @@ def test_malformed_specs_are_invalid_arguments(spec):
     with pytest.raises(hg.HgemmError) as e:
         hg.predict_us(64, 64, 64, spec)
     assert e.value.status == 1, spec
+
+
+def test_phased_kernels_take_over_large_problems_off_the_table():
+    """A pick of the cost model or of the nearest tuned shape gives way to a phased kernel where one is predicted clearly
+    faster, or keeps its tile and takes the phased schedule; short K and cache-line straddling rows of B keep the pick.
+    No pick that needs no workspace becomes a split."""
+    import random
+    import re
+
+    tn = hg.Layouts.make(b_col_major=True)
+    assert "ph=1" in hg.plan_choice(9306, 2632, 10032, tn) and "ph=1" in hg.plan_choice(2746, 10800, 7456, tn)
+    assert "ph=1" not in hg.plan_choice(1595, 8232, 104) and "ph=1" not in hg.plan_choice(776, 4056, 2656)
+    rnd = random.Random(23)
+    phased = 0
+    for _ in range(1500):
+        m, n, k = rnd.randint(96, 9000), 8 * rnd.randint(12, 1200), 8 * rnd.randint(8, 1200)
+        lay = hg.Layouts.make(b_col_major=rnd.random() < 0.5)
+        spec = hg.plan_choice(m, n, k, lay).split(": ")[1]
+        if "ph=1" not in spec:
+            continue
+        phased += 1
+        kv = {a: int(b) for a, b in re.findall(r"(\w+)=(\d+)", spec)}
+        assert kv["bm"] < 2 * m and kv["bn"] < 2 * n and k // kv["sk"] >= 128, (m, n, k, spec)
+        assert "sm=1" not in spec and "ps=1" not in spec and "fr=1" not in spec and hg.predict_us(m, n, k, spec) > 1.0
+    assert phased > 200
