@@ -649,17 +649,23 @@ size_t place_copies(hgemm_plan_s* p)
     if (!p->padded) return 0;
     const size_t N = (size_t)up8(p->N), K = (size_t)p->K;
     p->b_off = up256((size_t)p->M * K * 2);
-    if (p->any_b && !p->static_ws) return p->b_off;
+    if (p->any_b) return p->b_off;
     return p->b_off + up256(K * N * 2);
 }
 
 // hgemm_run_static accepts a problem by the scratch it would take with padded copies of all three operands: callers
-// size their problems by that rule.
+// size their problems by that rule.  (A B that is streamed where it lies counts as copied; the planes of the slabs, which
+// the large-tile kernels would not have needed, then go without counting, as long as what is really taken fits.)
 bool over_static_scratch(const hgemm_plan_s* p)
 {
-    if (!p->static_ws) return false;
-    const size_t c_copy = p->padded ? up256((size_t)p->M * (size_t)up8(p->N) * 2) : 0;
-    return p->workspace_bytes && p->workspace_bytes + c_copy > kScratchBytes;
+    if (!p->static_ws || !p->workspace_bytes) return false;
+    size_t counted = p->workspace_bytes;
+    if (p->padded) counted += up256((size_t)p->M * (size_t)up8(p->N) * 2);
+    if (p->any_b) {
+        counted += up256((size_t)p->K * (size_t)up8(p->N) * 2);
+        if (p->spec.sk > 1) counted -= up256((size_t)p->spec.sk * (size_t)p->M * (size_t)up8(p->N) * sizeof(float));
+    }
+    return counted > kScratchBytes || p->workspace_bytes > kScratchBytes;
 }
 
 // Gives the plan its workspace of p->workspace_bytes (static scratch or an allocation), points the
@@ -980,6 +986,9 @@ Choices choose_spec(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, b
         else if (neighbour) c.source = "neighbour";
         if (neighbour) c.spec[c.n++] = near;
         c.spec[c.n++] = model;
+    } else if (c.spec[0].ph && c.spec[0].sk > 1) {
+        c.spec[c.n] = c.spec[0];                  // where the planes do not fit: the same tile without a split
+        c.spec[c.n++].sk = 1;
     }
     for (int i = 0; i < c.n; ++i)
         if (tn || padded) c.spec[i].tb = 0;       // B already has K contiguous / is copied once already

@@ -119,3 +119,23 @@ def test_static_entry_point_refuses_what_does_not_fit():
     assert torch.isnan(c).all()
     with pytest.raises(hg.HgemmError):
         hg.run_static(-1, 8, 8, None, 0, 0, 0, 0)
+
+
+def test_static_entry_point_on_an_unaligned_b_that_is_streamed_where_it_lies():
+    # the streaming family reads such a B in place (planes of the slabs in the scratch, nothing copied but A); what is
+    # refused is still counted with a copy of B
+    for shape in [(8, 8001, 1500), (3, 8001, 3801), (1, 1001, 1100)]:
+        M, N, K = shape
+        assert "skinny" in hg.plan_choice(M, N, K)
+        name, a, b = wl.exact_family_for(shape, seed=44)
+        want, _, _, desc = run_hgemm(a, b)
+        assert_bit_exact(_run_static(a, b), want, f"static {shape} {name} {desc}")
+    M, N, K = 3, 8001, 4193
+    a = torch.zeros((M, K), dtype=torch.float16, device="cuda")
+    b = torch.zeros((K, N), dtype=torch.float16, device="cuda")
+    c = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda")
+    with pytest.raises(hg.HgemmError) as e:
+        hg.run_static(M, N, K, None, a.data_ptr(), b.data_ptr(), c.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    assert e.value.status == hg.ERR_WORKSPACE
+    torch.cuda.synchronize()
+    assert torch.isnan(c).all()
