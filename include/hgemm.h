@@ -160,9 +160,10 @@ hgemm_status_t hgemm_run_many(hgemm_plan_t plan, int64_t count, int64_t sets, in
  * HGEMM_STATIC_SCRATCH_BYTES inside the library (one copy per GPU, held until
  * the process ends) instead of a hipMalloc'ed buffer, and the plan itself
  * lives on the call's stack.  A problem whose chosen specialisation needs more
- * scratch than that (an unaligned problem counts with padded copies of A, B
- * and C) returns HGEMM_ERR_WORKSPACE and launches nothing; problems
- * that need no workspace are never refused.  The kernels overwrite every
+ * scratch than that, arrival counters aside, returns HGEMM_ERR_WORKSPACE and
+ * launches nothing.  An unaligned problem counts with padded copies of A, B and
+ * C, whether they are made or not; aligned problems that need no workspace are
+ * never refused.  The kernels overwrite every
  * scratch element they later read, so nothing has to be cleared between calls.
  * All calls on one GPU share that GPU's array: calls whose kernels may overlap
  * in time (different streams, no dependency between them) race on it, and so

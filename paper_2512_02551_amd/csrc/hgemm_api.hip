@@ -198,10 +198,12 @@ struct hgemm_plan_s {
 // copies from this array instead of a hipMalloc'ed workspace.  Every GPU the library runs on holds
 // its own copy at its own address until the process ends.  In host code the array's name is only a
 // stand-in for the symbol: the device address comes from hipGetSymbolAddress(), once per device.
+// The arrival counters in front come on top of the advertised size, so that a workspace of exactly that size fits: the
+// planes of a split in four of 8192 x 512 are 64 MiB, and the same tile without a split takes twice as long.
 // ---------------------------------------------------------------------------
 constexpr size_t kScratchBytes = (size_t)HGEMM_STATIC_SCRATCH_BYTES;
 constexpr size_t kCounterBytes = 64 * 1024;      // arrival counters of fused split-K plans: up to 16384 tiles
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kCounterBytes + kScratchBytes];
 
 namespace {
 
@@ -656,16 +658,17 @@ size_t place_copies(hgemm_plan_s* p)
 // hgemm_run_static accepts a problem by the scratch it would take with padded copies of all three operands: callers
 // size their problems by that rule.  (A B that is streamed where it lies counts as copied; the planes of the slabs, which
 // the large-tile kernels would not have needed, then go without counting, as long as what is really taken fits.)
-bool over_static_scratch(const hgemm_plan_s* p)
+bool over_static_scratch(const hgemm_plan_s* p, size_t ctr_bytes)
 {
     if (!p->static_ws || !p->workspace_bytes) return false;
-    size_t counted = p->workspace_bytes;
+    const size_t taken = p->workspace_bytes - ctr_bytes;
+    size_t counted = taken;
     if (p->padded) counted += up256((size_t)p->M * (size_t)up8(p->N) * 2);
     if (p->any_b) {
         counted += up256((size_t)p->K * (size_t)up8(p->N) * 2);
         if (p->spec.sk > 1) counted -= up256((size_t)p->spec.sk * (size_t)p->M * (size_t)up8(p->N) * sizeof(float));
     }
-    return counted > kScratchBytes || p->workspace_bytes > kScratchBytes;
+    return counted > kScratchBytes || taken > kScratchBytes;
 }
 
 // Gives the plan its workspace of p->workspace_bytes (static scratch or an allocation), points the
@@ -674,7 +677,7 @@ hgemm_status_t acquire_workspace(hgemm_plan_s* p, size_t partial_bytes, size_t c
 {
     GemmArgs& a = p->args;
     if (p->workspace_bytes && p->static_ws) {
-        if (over_static_scratch(p)) { p->workspace_bytes = 0; return HGEMM_ERR_WORKSPACE; }
+        if (over_static_scratch(p, ctr_bytes)) { p->workspace_bytes = 0; return HGEMM_ERR_WORKSPACE; }
         p->workspace = scratch_ptr_for(p->device);
         if (!p->workspace) { p->workspace_bytes = 0; return HGEMM_ERR_LAUNCH; }
         if (partial_bytes) a.partial = (float*)((char*)p->workspace + p->partial_offset);
@@ -987,7 +990,7 @@ Choices choose_spec(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, b
         if (neighbour) c.spec[c.n++] = near;
         c.spec[c.n++] = model;
     } else if (c.spec[0].ph && c.spec[0].sk > 1) {
-        c.spec[c.n] = c.spec[0];                  // where the planes do not fit: the same tile without a split
+        c.spec[c.n] = c.spec[0];                  // where there is no room for the planes: the same tile without a split
         c.spec[c.n++].sk = 1;
     }
     for (int i = 0; i < c.n; ++i)

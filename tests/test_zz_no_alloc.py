@@ -139,3 +139,29 @@ def test_static_entry_point_on_an_unaligned_b_that_is_streamed_where_it_lies():
     assert e.value.status == hg.ERR_WORKSPACE
     torch.cuda.synchronize()
     assert torch.isnan(c).all()
+
+
+@pytest.mark.parametrize("shape", [(512, 8192, 16384), (12288, 256, 16384)], ids=lambda s: "x".join(map(str, s)))
+def test_static_entry_point_on_a_workspace_that_fills_the_scratch(shape):
+    # split-K planes, and stream-K tiles, of exactly HGEMM_STATIC_SCRATCH_BYTES; then a fused split, whose arrival counters
+    # sit in front of them and must still be zero
+    M, N, K = shape
+    g = torch.Generator(device="cuda").manual_seed(7)
+    a = torch.randint(-2, 3, (M, K), generator=g, device="cuda").half()
+    b = torch.randint(-2, 3, (K, N), generator=g, device="cuda").half()
+    want = torch.empty((M, N), dtype=torch.float16, device="cuda")
+    got = torch.full_like(want, float("nan"))
+    stream = torch.cuda.current_stream().cuda_stream
+    with hg.Plan(M, N, K) as p:
+        assert p.workspace_bytes() == hg.STATIC_SCRATCH_BYTES, p.describe()
+        p.run(a.data_ptr(), b.data_ptr(), want.data_ptr(), stream)
+    hg.run_static(M, N, K, None, a.data_ptr(), b.data_ptr(), got.data_ptr(), stream)
+    torch.cuda.synchronize()
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    for j in (0, N // 2, N - 1):                       # sums of integers below 2^24 in fp32, one rounding
+        ref = (a.float() @ b[:, j:j + 1].float()).half()
+        assert torch.equal(want[:, j:j + 1], ref)
+    name, sa, sb = wl.exact_family_for((1, 8192, 8192), seed=45)
+    fused, _, _, desc = run_hgemm(sa, sb)
+    assert "fr=1" in desc
+    assert_bit_exact(_run_static(sa, sb), fused, desc)
