@@ -891,7 +891,7 @@ bool same_tile(const Spec& s, const PhasedTile& c) { return s.fam == FAM_MFMA &&
 // enough to pay for the longer prologue and epilogue (256 x 256: 128 of K, smaller tiles 384; 128 x 128 at K = 100: 10-20 %
 // slower) and the rows of a row-major B start on cache lines where a unit is one line wide (BN = 128; 776 x 4056 x 2656:
 // 6 % slower otherwise).
-bool phased_choice(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, const Spec& pick, Spec* out)
+bool phased_choice(int64_t M, int64_t N, int64_t K, bool row_b, int64_t b_ld, const Spec& pick, Spec* out)
 {
     if (pick.fam != FAM_MFMA || pick.ac != 32 || pick.tb) return false;
     if (pick.mi == 16 && !pick.ph && K / std::max(1, pick.sk) < 512) return false;
@@ -929,7 +929,7 @@ bool phased_choice(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, co
         if (!same_tile(pick, c)) continue;
         const int64_t k_split = K / std::max(1, pick.sk);
         if (k_split < (c.bm == 256 && c.bn == 256 ? 128 : 384)) return false;
-        if (l.b == HGEMM_ROW_MAJOR && c.bn == 128 && l.ldb % 64 != 0) return false;
+        if (row_b && c.bn == 128 && b_ld % 64 != 0) return false;
         if (!parse_spec(c.spec, out)) return false;
         out->sk = pick.sk;
         out->gm = pick.gm;
@@ -962,12 +962,13 @@ bool device_is_gfx950(int dev)
 // any_b: B is to be streamed where it lies (streams_any_b), which only the streaming family does.
 // Returns the specialisations to try in order (a later one if the device or the workspace refuses an earlier one) and
 // says where the first comes from.
+// b_ld: the leading dimension of B as the kernels see it (l describes the packed problem of a padded one).
 struct Choices {
     const char* source;
     int n;
     Spec spec[3];
 };
-Choices choose_spec(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, bool padded, bool any_b)
+Choices choose_spec(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, int64_t b_ld, bool padded, bool any_b)
 {
     Choices c{"table", 1, {}};
     const bool tn = l.b == HGEMM_COL_MAJOR;
@@ -985,7 +986,7 @@ Choices choose_spec(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, b
         }
         c.n = 0;
         const bool neighbour = neighbour_choice(M, N, K, tn, model, &near);
-        if (phased_choice(M, N, K, l, neighbour ? near : model, &phased)) c.spec[c.n++] = phased;
+        if (phased_choice(M, N, K, l.b == HGEMM_ROW_MAJOR, b_ld, neighbour ? near : model, &phased)) c.spec[c.n++] = phased;
         else if (neighbour) c.source = "neighbour";
         if (neighbour) c.spec[c.n++] = near;
         c.spec[c.n++] = model;
@@ -996,6 +997,44 @@ Choices choose_spec(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, b
     for (int i = 0; i < c.n; ++i)
         if (tn || padded) c.spec[i].tb = 0;       // B already has K contiguous / is copied once already
     return c;
+}
+
+// How hgemm_plan takes a problem: on the kernels that read aligned 16-byte chunks (`fast`), with packed zero-filled copies
+// of those operands that cannot be read that way where they lie (`padded`), or neither.
+struct Route {
+    bool fast, padded, copy_a, copy_b, any_b;
+    int64_t N, K;                // the planner's view of the problem: rounded up to 8 where it is padded,
+    hgemm_layouts_t lay;         // its operands packed
+    int64_t lda, ldb;            // leading dimensions of A and B as the kernels see them
+};
+Route route(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l)
+{
+    Route r{false, false, false, false, false, N, K, l, l.lda, l.ldb};
+    if (M <= 0 || N <= 0 || K <= 0) return r;
+    r.fast = fast_path_ok(M, N, K, l);
+    // N, K or a leading dimension is not a multiple of 8.  Above a size where the one-thread-per-element kernel would
+    // take longer than an extra launch, run the matrix-core kernels.
+    if (r.fast || (double)M * (double)N * (double)K < kPadMinMacs) return r;
+    const bool row_b = l.b == HGEMM_ROW_MAJOR;
+    const int64_t Kp = up8(K), Np = up8(N);
+    hgemm_layouts_t lp = l;
+    lp.lda = Kp;
+    lp.ldb = row_b ? Np : Kp;
+    lp.ldc = Np;
+    if (!fast_path_ok(M, Np, Kp, lp) || l.ldc >= ((int64_t)1 << 31)) return r;
+    // readable where it lies: rows of whole aligned chunks, and the kernels' offsets reach all of it
+    hgemm_layouts_t la = lp, lb = lp;
+    la.lda = l.lda;
+    lb.ldb = l.ldb;
+    r.copy_a = K % 8 != 0 || !fast_path_ok(M, Np, Kp, la);
+    r.copy_b = (row_b ? N : K) % 8 != 0 || !fast_path_ok(M, Np, Kp, lb);
+    r.any_b = r.copy_b && streams_any_b(M, N, K, l);
+    if (r.any_b) r.copy_b = false;
+    r.fast = r.padded = true;
+    r.N = Np; r.K = Kp; r.lay = lp;
+    r.lda = r.copy_a ? Kp : l.lda;
+    r.ldb = r.copy_b ? lp.ldb : l.ldb;
+    return r;
 }
 
 hgemm_status_t init_blocked(hgemm_plan_s* p);
@@ -1037,34 +1076,14 @@ hgemm_status_t init_plan(hgemm_plan_s* p, int64_t M, int64_t N, int64_t K, const
         if (!parse_spec(spec_text, &p->spec)) return HGEMM_ERR_INVALID_ARG;
         st = finish_plan(p);
     } else {
-        bool fast = fast_path_ok(M, N, K, l) && M > 0 && N > 0 && K > 0;
-        if (!fast && M > 0 && N > 0 && K > 0 && (double)M * (double)N * (double)K >= kPadMinMacs) {
-            // N, K or a leading dimension is not a multiple of 8.  Above a size where the one-thread-per-
-            // element kernel would take longer than an extra launch, run the matrix-core kernel, with packed
-            // zero-filled copies of those operands that cannot be read in 16-byte chunks where they lie.
-            const int64_t Kp = (K + 7) / 8 * 8, Np = (N + 7) / 8 * 8;
-            hgemm_layouts_t lp = l;
-            lp.lda = Kp;
-            lp.ldb = (l.b == HGEMM_ROW_MAJOR) ? Np : Kp;
-            lp.ldc = Np;
-            if (fast_path_ok(M, Np, Kp, lp) && l.ldc < ((int64_t)1 << 31)) {
-                const bool row_b = l.b == HGEMM_ROW_MAJOR;
-                // readable where it lies: rows of whole aligned chunks, and the kernels' offsets reach all of it
-                hgemm_layouts_t la = lp, lb = lp;
-                la.lda = l.lda;
-                lb.ldb = l.ldb;
-                p->copy_a = K % 8 != 0 || !fast_path_ok(M, Np, Kp, la);
-                p->copy_b = (row_b ? N : K) % 8 != 0 || !fast_path_ok(M, Np, Kp, lb);
-                p->padded = true;
-                p->any_b = p->copy_b && streams_any_b(M, N, K, l);
-                if (p->any_b) p->copy_b = false;
-                p->K = K = Kp;
-                p->lay.lda = p->copy_a ? Kp : l.lda;
-                p->lay.ldb = p->copy_b ? lp.ldb : l.ldb;
-                N = Np;                               // the planner's view of the problem
-                l = lp;
-                fast = true;
-            }
+        const Route r = route(M, N, K, l);
+        const bool fast = r.fast;
+        if (r.padded) {
+            p->padded = true;
+            p->copy_a = r.copy_a; p->copy_b = r.copy_b; p->any_b = r.any_b;
+            p->K = r.K;
+            p->lay.lda = r.lda; p->lay.ldb = r.ldb;
+            N = r.N; K = r.K; l = r.lay;
         }
         const bool dims_aligned = !(N % 8 || K % 8 || l.lda % 8 || l.ldb % 8 || l.ldc % 8) && M < (1 << 24) && N < (1 << 24) && K < (1 << 24);
         if (!fast && !static_ws && M > 0 && N > 0 && K > 0 && dims_aligned && init_blocked(p) == HGEMM_OK) return HGEMM_OK;
@@ -1072,7 +1091,7 @@ hgemm_status_t init_plan(hgemm_plan_s* p, int64_t M, int64_t N, int64_t K, const
             p->spec = Spec();
             st = finish_plan(p);
         } else {
-            const Choices c = choose_spec(M, N, K, l, p->padded, p->any_b);
+            const Choices c = choose_spec(M, N, K, l, r.ldb, p->padded, p->any_b);
             for (int i = 0; i < c.n; ++i) {
                 p->spec = c.spec[i];
                 st = finish_plan(p);
@@ -1246,20 +1265,9 @@ hgemm_status_t hgemm_plan_choice(int64_t M, int64_t N, int64_t K, const hgemm_la
     if (l.lda < K || l.ldc < N || l.ldb < ((l.b == HGEMM_ROW_MAJOR) ? N : K)) return HGEMM_ERR_INVALID_ARG;
     std::string out;
     const bool nonempty = M > 0 && N > 0 && K > 0;
-    bool fast = nonempty && fast_path_ok(M, N, K, l);
-    bool padded = false, any_b = false;
-    if (!fast && nonempty && (double)M * (double)N * (double)K >= kPadMinMacs) {
-        const int64_t Kp = (K + 7) / 8 * 8, Np = (N + 7) / 8 * 8;
-        hgemm_layouts_t lp = l;
-        lp.lda = Kp;
-        lp.ldb = (l.b == HGEMM_ROW_MAJOR) ? Np : Kp;
-        lp.ldc = Np;
-        if (fast_path_ok(M, Np, Kp, lp) && l.ldc < ((int64_t)1 << 31)) {
-            any_b = streams_any_b(M, N, K, l);
-            padded = fast = true;
-            N = Np; K = Kp; l = lp;
-        }
-    }
+    const Route r = route(M, N, K, l);
+    const bool fast = r.fast;
+    N = r.N; K = r.K; l = r.lay;
     int64_t rows = 0, cols = 0;
     bool bt = false;
     hgemm_layouts_t bl;
@@ -1273,8 +1281,8 @@ hgemm_status_t hgemm_plan_choice(int64_t M, int64_t N, int64_t K, const hgemm_la
     } else if (!fast) {
         out = "generic";
     } else {
-        const Choices c = choose_spec(M, N, K, l, padded, any_b);
-        out = std::string(c.source) + ": " + spec_to_string(c.spec[0]) + (padded ? ",pad=1" : "");
+        const Choices c = choose_spec(M, N, K, l, r.ldb, r.padded, r.any_b);
+        out = std::string(c.source) + ": " + spec_to_string(c.spec[0]) + (r.padded ? ",pad=1" : "");
     }
     if (out.size() + 1 > n) { buf[0] = '\0'; return HGEMM_ERR_INVALID_ARG; }
     memcpy(buf, out.c_str(), out.size() + 1);

@@ -209,3 +209,13 @@ def test_phased_kernels_take_over_large_problems_off_the_table():
         assert kv["bm"] < 2 * m and kv["bn"] < 2 * n and k // kv["sk"] >= 128, (m, n, k, spec)
         assert "sm=1" not in spec and "ps=1" not in spec and "fr=1" not in spec and hg.predict_us(m, n, k, spec) > 1.0
     assert phased > 200
+
+
+@pytest.mark.parametrize("m,n,k,ldb,phased", [(2048, 2048, 1008, 2056, False), (2048, 2048, 1003, 2056, False), (2048, 2048, 1003, 2048, True),
+                                              (2048, 2040, 1003, 2048, True), (2048, 2040, 1008, 2048, True), (2048, 2041, 1003, 2056, True),
+                                              (2048, 2033, 1003, 2048, False)])
+def test_phased_choice_looks_at_the_pitch_the_kernel_reads_b_with(m, n, k, ldb, phased):
+    """128 columns of a row-major B are phased where its rows start on cache lines: the caller's pitch where B is read in
+    place, also beside a copied A, else that of its packed copy (2048 for 2041 columns, 2040 for 2033)."""
+    choice = hg.plan_choice(m, n, k, hg.Layouts.make(ldb=ldb))
+    assert "bm=128,bn=128" in choice and ("ph=1" in choice) == phased, choice
