@@ -174,10 +174,11 @@ struct hgemm_plan_s {
     // (and 100 by the streaming family, which reads any row-major B where it lies).
     bool padded;
     bool copy_a, copy_b;
+    bool copy_c;                // C's rows are 2^31 elements apart or more, which the kernels cannot address: stored packed, copied from there
     bool any_b;                 // row-major B off the 16-byte grid that the streaming family reads where it lies (never copied)
     int64_t uN, uK;
     hgemm_layouts_t ulay;
-    size_t a_off, b_off;        // byte offsets of the padded copies of A and B inside the workspace
+    size_t a_off, b_off, c_off; // byte offsets of the padded copies of A and B and of the packed C inside the workspace
     size_t bt_off;              // byte offset of the transposed copy of B (spec.tb)
     bool static_ws;             // the workspace is this device's static scratch array, not an allocation
     // Operands beyond the reach of the kernels' 32-bit buffer offsets (2 GiB per operand): the problem runs
@@ -644,15 +645,15 @@ bool kernels_can_run(const hgemm_plan_s* p)
     return fast_path_ok(p->M, up8(p->N), p->K, l);
 }
 
-// Lays the padded copies of A and B out in the workspace behind the counters and returns their bytes.
+// Lays the padded copies of A and B, and the packed C, out in the workspace behind the counters and returns their bytes.
 size_t place_copies(hgemm_plan_s* p)
 {
-    p->a_off = p->b_off = 0;
+    p->a_off = p->b_off = p->c_off = 0;
     if (!p->padded) return 0;
-    const size_t N = (size_t)up8(p->N), K = (size_t)p->K;
-    p->b_off = up256((size_t)p->M * K * 2);
-    if (p->any_b) return p->b_off;
-    return p->b_off + up256(K * N * 2);
+    const size_t M = (size_t)p->M, N = (size_t)up8(p->N), K = (size_t)p->K;
+    p->b_off = up256(M * K * 2);
+    p->c_off = p->b_off + (p->any_b ? 0 : up256(K * N * 2));
+    return p->c_off + (p->copy_c ? up256(M * N * 2) : 0);
 }
 
 // hgemm_run_static accepts a problem by the scratch it would take with padded copies of all three operands: callers
@@ -663,7 +664,7 @@ bool over_static_scratch(const hgemm_plan_s* p, size_t ctr_bytes)
     if (!p->static_ws || !p->workspace_bytes) return false;
     const size_t taken = p->workspace_bytes - ctr_bytes;
     size_t counted = taken;
-    if (p->padded) counted += up256((size_t)p->M * (size_t)up8(p->N) * 2);
+    if (p->padded && !p->copy_c) counted += up256((size_t)p->M * (size_t)up8(p->N) * 2);
     if (p->any_b) {
         counted += up256((size_t)p->K * (size_t)up8(p->N) * 2);
         if (p->spec.sk > 1) counted -= up256((size_t)p->spec.sk * (size_t)p->M * (size_t)up8(p->N) * sizeof(float));
@@ -775,7 +776,7 @@ hgemm_status_t finish_plan(hgemm_plan_s* p)
         const size_t pad_bytes = place_copies(p);
         const size_t partial_bytes = sk > 1 ? up256((size_t)sk * (size_t)M * (size_t)part_ld((int)N) * sizeof(float)) : 0;
         const size_t ctr_bytes = (s.fr || (p->static_ws && pad_bytes + partial_bytes > 0)) ? kCounterBytes : 0;
-        p->a_off += ctr_bytes; p->b_off += ctr_bytes;
+        p->a_off += ctr_bytes; p->b_off += ctr_bytes; p->c_off += ctr_bytes;
         p->bt_off = ctr_bytes + pad_bytes;
         p->partial_offset = ctr_bytes + pad_bytes;
         p->workspace_bytes = ctr_bytes + pad_bytes + partial_bytes;
@@ -846,7 +847,7 @@ hgemm_status_t finish_plan(hgemm_plan_s* p)
     // (In the static scratch every plan keeps clear of that region, so it stays zero for the fused ones.)
     const size_t ctr_bytes = (s.fr || (p->static_ws && pad_bytes + bt_bytes + partial_bytes > 0)) ? kCounterBytes : 0;
     if (s.fr && (size_t)a.tiles_m * a.tiles_n * sizeof(int) > kCounterBytes) return HGEMM_ERR_UNSUPPORTED;
-    p->a_off += ctr_bytes; p->b_off += ctr_bytes;
+    p->a_off += ctr_bytes; p->b_off += ctr_bytes; p->c_off += ctr_bytes;
     p->bt_off = ctr_bytes + pad_bytes;
     p->partial_offset = ctr_bytes + pad_bytes + bt_bytes;
     p->workspace_bytes = ctr_bytes + pad_bytes + bt_bytes + partial_bytes;
@@ -1002,14 +1003,14 @@ Choices choose_spec(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, i
 // How hgemm_plan takes a problem: on the kernels that read aligned 16-byte chunks (`fast`), with packed zero-filled copies
 // of those operands that cannot be read that way where they lie (`padded`), or neither.
 struct Route {
-    bool fast, padded, copy_a, copy_b, any_b;
+    bool fast, padded, copy_a, copy_b, copy_c, any_b;
     int64_t N, K;                // the planner's view of the problem: rounded up to 8 where it is padded,
     hgemm_layouts_t lay;         // its operands packed
-    int64_t lda, ldb;            // leading dimensions of A and B as the kernels see them
+    int64_t lda, ldb, ldc;       // leading dimensions as the kernels see them
 };
 Route route(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l)
 {
-    Route r{false, false, false, false, false, N, K, l, l.lda, l.ldb};
+    Route r{false, false, false, false, false, false, N, K, l, l.lda, l.ldb, l.ldc};
     if (M <= 0 || N <= 0 || K <= 0) return r;
     r.fast = fast_path_ok(M, N, K, l);
     // N, K or a leading dimension is not a multiple of 8.  Above a size where the one-thread-per-element kernel would
@@ -1021,7 +1022,7 @@ Route route(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l)
     lp.lda = Kp;
     lp.ldb = row_b ? Np : Kp;
     lp.ldc = Np;
-    if (!fast_path_ok(M, Np, Kp, lp) || l.ldc >= ((int64_t)1 << 31)) return r;
+    if (!fast_path_ok(M, Np, Kp, lp)) return r;
     // readable where it lies: rows of whole aligned chunks, and the kernels' offsets reach all of it
     hgemm_layouts_t la = lp, lb = lp;
     la.lda = l.lda;
@@ -1034,6 +1035,10 @@ Route route(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l)
     r.N = Np; r.K = Kp; r.lay = lp;
     r.lda = r.copy_a ? Kp : l.lda;
     r.ldb = r.copy_b ? lp.ldb : l.ldb;
+    if (l.ldc >= ((int64_t)1 << 31)) {           // kernels have the pitch of C in 32 bits
+        r.ldc = Np;
+        r.copy_c = M > 1;
+    }
     return r;
 }
 
@@ -1067,9 +1072,9 @@ hgemm_status_t init_plan(hgemm_plan_s* p, int64_t M, int64_t N, int64_t K, const
     p->M = M; p->N = N; p->K = K; p->lay = l; p->device = dev;
     p->padded = false;
     p->static_ws = static_ws;
-    p->copy_a = p->copy_b = p->any_b = false;
+    p->copy_a = p->copy_b = p->copy_c = p->any_b = false;
     p->uN = N; p->uK = K; p->ulay = l;
-    p->a_off = p->b_off = p->bt_off = 0;
+    p->a_off = p->b_off = p->c_off = p->bt_off = 0;
 
     hgemm_status_t st;
     if (spec_text) {
@@ -1080,9 +1085,9 @@ hgemm_status_t init_plan(hgemm_plan_s* p, int64_t M, int64_t N, int64_t K, const
         const bool fast = r.fast;
         if (r.padded) {
             p->padded = true;
-            p->copy_a = r.copy_a; p->copy_b = r.copy_b; p->any_b = r.any_b;
+            p->copy_a = r.copy_a; p->copy_b = r.copy_b; p->copy_c = r.copy_c; p->any_b = r.any_b;
             p->K = r.K;
-            p->lay.lda = r.lda; p->lay.ldb = r.ldb;
+            p->lay.lda = r.lda; p->lay.ldb = r.ldb; p->lay.ldc = r.ldc;
             N = r.N; K = r.K; l = r.lay;
         }
         const bool dims_aligned = !(N % 8 || K % 8 || l.lda % 8 || l.ldb % 8 || l.ldc % 8) && M < (1 << 24) && N < (1 << 24) && K < (1 << 24);
@@ -1114,7 +1119,7 @@ hgemm_status_t init_plan(hgemm_plan_s* p, int64_t M, int64_t N, int64_t K, const
                 }
             }
             if (st != HGEMM_OK && st != HGEMM_ERR_WORKSPACE && p->padded) {   // e.g. no memory for the padded copies: the generic kernel needs none
-                p->padded = p->copy_a = p->copy_b = p->any_b = false;
+                p->padded = p->copy_a = p->copy_b = p->copy_c = p->any_b = false;
                 p->N = p->uN; p->K = p->uK; p->lay = p->ulay;
                 p->spec = Spec();
                 st = finish_plan(p);
@@ -1346,7 +1351,15 @@ static hgemm_status_t run_plan(const hgemm_plan_s* plan, const void* A, const vo
             if (copy_b) { B = ws + plan->b_off; ldb = row_b ? Np : K; b_rows = K; }
         }
     }
-    auto finish = [&]() -> hgemm_status_t { return hipGetLastError() == hipSuccess ? HGEMM_OK : HGEMM_ERR_LAUNCH; };
+    void* const user_C = C;
+    if (plan->copy_c && plan->spec.fam != FAM_GENERIC) C = (char*)plan->workspace + plan->c_off;
+    auto finish = [&]() -> hgemm_status_t {
+        if (hipGetLastError() != hipSuccess) return HGEMM_ERR_LAUNCH;
+        if (C == user_C) return HGEMM_OK;
+        hipLaunchKernelGGL(copy_back_kernel, dim3((unsigned)((N + 2047) / 2048), (unsigned)std::min<int64_t>(M, 32768)), dim3(256), 0, stream,
+                           (const _Float16*)C, plan->lay.ldc, (_Float16*)user_C, plan->ulay.ldc, M, N);
+        return hipGetLastError() == hipSuccess ? HGEMM_OK : HGEMM_ERR_LAUNCH;
+    };
 
     // A and B are read in 16-byte chunks; C may start anywhere
     const bool aligned = ((((uintptr_t)A) | (plan->any_b ? (uintptr_t)0 : (uintptr_t)B)) & 15) == 0;

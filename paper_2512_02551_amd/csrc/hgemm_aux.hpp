@@ -1,5 +1,5 @@
 // Auxiliary kernels: the generic any-shape GEMM, the split-K reduction, a transposing copy, a padding
-// copy, a fill kernel, and the two roofline calibration kernels.
+// copy, a copy of C into place, a fill kernel, and the two roofline calibration kernels.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -151,6 +151,17 @@ __global__ __launch_bounds__(256) void pad_copy_kernel(PadCopy a, PadCopy b, uns
         else if (d > 0u) o = ull2{(v[j].x >> d) | (v[j].y << (64u - d)), v[j].y >> d};
         *(ull2*)(p.dst + (size_t)q * 8u) = o;
     }
+}
+
+// dst (M x N, rows dst_ld apart, any address) = src (rows src_ld apart, multiple of 8, 16-byte aligned): C from the
+// workspace to a place whose rows are 2^31 elements apart or more.  A lane moves 8 columns.  Rare, and bound by memory.
+__global__ __launch_bounds__(256) void copy_back_kernel(const _Float16* __restrict__ src, int64_t src_ld, _Float16* __restrict__ dst, int64_t dst_ld,
+                                                        int64_t M, int64_t N)
+{
+    const int64_t c = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 8;
+    if (c >= N) return;
+    for (int64_t r = blockIdx.y; r < M; r += gridDim.y)
+        store_cols(dst + r * dst_ld + c, *(const half8*)(src + r * src_ld + c), (int)min(N - c, (int64_t)8), 0);
 }
 
 // C = 0 for K == 0 (the empty sum), any ldc.  A lane clears 8 consecutive columns: with one 16-byte

@@ -94,3 +94,26 @@ def test_blocked_plans_are_not_for_the_entry_point_that_allocates_nothing_and_ex
     with hg.Plan(M, N, K) as p:
         assert p.describe().startswith("blocks,")
         assert p.workspace_bytes() >= 0
+
+
+@pytest.mark.parametrize("tn", [False, True])
+@pytest.mark.parametrize("M,N,K,ldc", [(3, 1001, 1003, (1 << 31) + 3), (2, 4099, 520, (1 << 31) + 8), (3, 1000, 1008, (1 << 31) - 1)],
+                         ids=lambda v: str(v))
+def test_rows_of_c_that_lie_2_to_the_31_elements_apart(M, N, K, ldc, tn):
+    """Stored packed and copied into place, with the pitch just below that stored in place: every element, and nothing around a row."""
+    rng = np.random.default_rng([M, N, K])
+    a, b = wl.integers(rng, M, K, -2, 2), wl.integers(rng, K, N, -2, 2)
+    da, db = to_dev(a), to_dev(np.ascontiguousarray(b.T) if tn else b)
+    buf = torch.empty(64 + (M - 1) * ldc + N + 64, dtype=torch.float16, device="cuda")
+    rows = [buf[r * ldc:r * ldc + N + 128] for r in range(M)]           # C starts at element 64
+    with hg.Plan(M, N, K, hg.Layouts.make(b_col_major=tn, ldc=ldc)) as p:
+        desc = p.describe()
+        assert "generic" not in desc, desc
+        for _ in range(2):
+            for r in rows:
+                r.fill_(float("nan"))
+            p.run(da.data_ptr(), db.data_ptr(), buf.data_ptr() + 128, torch.cuda.current_stream().cuda_stream)
+            torch.cuda.synchronize()
+            got = torch.stack([r[64:64 + N] for r in rows])
+            assert_bit_exact(to_host(got), orc.hgemm(a, b), desc)
+            assert all(bool(torch.isnan(r[:64]).all()) and bool(torch.isnan(r[64 + N:]).all()) for r in rows), desc
