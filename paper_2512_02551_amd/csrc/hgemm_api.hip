@@ -168,12 +168,14 @@ struct hgemm_plan_s {
     // the workspace, packed and zero-filled to multiples of 8 (the zero padding of Section 5.2).  K above is then
     // rounded up to 8 (zero columns of the copy of A make the extra products vanish), lay describes the operands as the
     // kernels see them, and the fields below keep the caller's problem.  An operand that can be read where it lies is;
-    // its place in the workspace is kept all the same, for calls whose base pointer is not 16-byte aligned.
+    // its place in the workspace is kept all the same (`spare`), for calls whose base pointer is not 16-byte aligned, unless
+    // there is no memory for it: such calls then take the generic kernel.
     // Measured against copying A, B and C always, two bytes per lane (us): 1000 x 1001 x 1003 26.3 -> 10.9 (A and B
     // copied, in one launch), 16 x 50257 x 4096 with column-major B 383 -> 89 (nothing copied), with row-major B 402 -> 240
     // (and 100 by the streaming family, which reads any row-major B where it lies).
     bool padded;
     bool copy_a, copy_b;
+    bool spare;                 // the workspace has room for copies of operands that are not copied otherwise
     bool copy_c;                // C's rows are 2^31 elements apart or more, which the kernels cannot address: stored packed, copied from there
     bool any_b;                 // row-major B off the 16-byte grid that the streaming family reads where it lies (never copied)
     int64_t uN, uK;
@@ -651,8 +653,8 @@ size_t place_copies(hgemm_plan_s* p)
     p->a_off = p->b_off = p->c_off = 0;
     if (!p->padded) return 0;
     const size_t M = (size_t)p->M, N = (size_t)up8(p->N), K = (size_t)p->K;
-    p->b_off = up256(M * K * 2);
-    p->c_off = p->b_off + (p->any_b ? 0 : up256(K * N * 2));
+    p->b_off = p->copy_a || p->spare ? up256(M * K * 2) : 0;
+    p->c_off = p->b_off + ((p->copy_b || p->spare) && !p->any_b ? up256(K * N * 2) : 0);
     return p->c_off + (p->copy_c ? up256(M * N * 2) : 0);
 }
 
@@ -1073,6 +1075,7 @@ hgemm_status_t init_plan(hgemm_plan_s* p, int64_t M, int64_t N, int64_t K, const
     p->padded = false;
     p->static_ws = static_ws;
     p->copy_a = p->copy_b = p->copy_c = p->any_b = false;
+    p->spare = true;
     p->uN = N; p->uK = K; p->ulay = l;
     p->a_off = p->b_off = p->c_off = p->bt_off = 0;
 
@@ -1097,10 +1100,14 @@ hgemm_status_t init_plan(hgemm_plan_s* p, int64_t M, int64_t N, int64_t K, const
             st = finish_plan(p);
         } else {
             const Choices c = choose_spec(M, N, K, l, r.ldb, p->padded, p->any_b);
-            for (int i = 0; i < c.n; ++i) {
-                p->spec = c.spec[i];
-                st = finish_plan(p);
-                if (st == HGEMM_OK) return HGEMM_OK;
+            for (const bool spare : {true, false}) {       // no memory: once more without the room that only misaligned calls use
+                p->spare = spare;
+                for (int i = 0; i < c.n; ++i) {
+                    p->spec = c.spec[i];
+                    st = finish_plan(p);
+                    if (st == HGEMM_OK) return HGEMM_OK;
+                }
+                if (st != HGEMM_ERR_ALLOC || !p->padded) break;
             }
             if (st == HGEMM_ERR_UNSUPPORTED && p->any_b) {     // not the streaming family after all: B is copied
                 p->any_b = false;
@@ -1332,7 +1339,8 @@ static hgemm_status_t run_plan(const hgemm_plan_s* plan, const void* A, const vo
     int64_t lda = plan->lay.lda, ldb = plan->lay.ldb, b_rows = plan->args.b_rows;
     const bool row_b = plan->lay.b == HGEMM_ROW_MAJOR;
     if (plan->padded && plan->spec.fam != FAM_GENERIC) {
-        const bool copy_a = plan->copy_a || ((uintptr_t)A & 15), copy_b = plan->copy_b || (((uintptr_t)B & 15) && !plan->any_b);
+        const bool copy_a = plan->copy_a || (plan->spare && ((uintptr_t)A & 15));
+        const bool copy_b = plan->copy_b || (plan->spare && ((uintptr_t)B & 15) && !plan->any_b);
         if (copy_a || copy_b) {
             char* ws = (char*)plan->workspace;
             const int64_t Np = up8(N);
@@ -1364,19 +1372,19 @@ static hgemm_status_t run_plan(const hgemm_plan_s* plan, const void* A, const vo
     // A and B are read in 16-byte chunks; C may start anywhere
     const bool aligned = ((((uintptr_t)A) | (plan->any_b ? (uintptr_t)0 : (uintptr_t)B)) & 15) == 0;
     if (plan->spec.fam == FAM_GENERIC || !aligned) {
+        const int col_b = row_b ? 0 : 1;
+        const int64_t k = plan->uK;                       // of a padded problem too: a copy of A is longer, B need not be
         if (N > (int64_t)64 * 0x7fffffff || (M + 3) / 4 > 65535) {
             // grid.y limit: fold rows into several launches
             for (int64_t mb = 0; mb < M; mb += 4 * 65535) {
                 const int64_t rows = std::min<int64_t>(M - mb, 4 * 65535);
                 hipLaunchKernelGGL(generic_gemm_kernel, dim3((unsigned)((N + 63) / 64), (unsigned)((rows + 3) / 4)), dim3(256), 0,
-                                   stream, (const _Float16*)A + mb * plan->lay.lda, (const _Float16*)B,
-                                   (_Float16*)C + mb * plan->lay.ldc, rows, N, K, plan->lay.lda, plan->lay.ldb, plan->lay.ldc,
-                                   plan->lay.b == HGEMM_COL_MAJOR ? 1 : 0);
+                                   stream, (const _Float16*)A + mb * lda, (const _Float16*)B, (_Float16*)C + mb * plan->lay.ldc, rows, N, k,
+                                   lda, ldb, plan->lay.ldc, col_b);
             }
         } else {
             hipLaunchKernelGGL(generic_gemm_kernel, dim3((unsigned)((N + 63) / 64), (unsigned)((M + 3) / 4)), dim3(256), 0, stream,
-                               (const _Float16*)A, (const _Float16*)B, (_Float16*)C, M, N, K, plan->lay.lda, plan->lay.ldb,
-                               plan->lay.ldc, plan->lay.b == HGEMM_COL_MAJOR ? 1 : 0);
+                               (const _Float16*)A, (const _Float16*)B, (_Float16*)C, M, N, k, lda, ldb, plan->lay.ldc, col_b);
         }
         return finish();
     }

@@ -24,7 +24,8 @@ hipStream_t g_stream = nullptr;
 extern "C" {
 void fake_device_memory(size_t bytes) { g_limit = bytes; }
 size_t fake_live_bytes() { return g_live_bytes; }
-// What was called since the last time, one line each: "malloc BYTES", "malloc BYTES failed", "free", "launch KERNEL GRIDX GRIDY".
+// What was called since the last time, one line each: "malloc BYTES", "malloc BYTES failed", "free", "launch KERNEL GRIDX GRIDY"
+// (the generic kernel: followed by A, B, C, M, N, K, lda, ldb, ldc).
 const char* fake_take_log()
 {
     static std::string out;
@@ -47,9 +48,12 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shared, hi
     *grid = g_grid; *block = g_block; *shared = g_shared; *stream = g_stream;
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void**, size_t, hipStream_t)
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** args, size_t, hipStream_t)
 {
-    g_log += "launch " + g_names[f] + " " + std::to_string(grid.x) + " " + std::to_string(grid.y) + "\n";
+    g_log += "launch " + g_names[f] + " " + std::to_string(grid.x) + " " + std::to_string(grid.y);
+    if (g_names[f].find("generic_gemm_kernel") != std::string::npos)      // (A, B, C, M, N, K, lda, ldb, ldc, col_major): three pointers, six int64
+        for (int i = 0; i < 9; ++i) g_log += " " + std::to_string(*(const int64_t*)args[i]);
+    g_log += "\n";
     return hipSuccess;
 }
 hipError_t hipGetDevice(int* dev) { *dev = 0; return hipSuccess; }

@@ -39,8 +39,8 @@ def kernels(log):
     out = []
     for line in log:
         if line.startswith("launch "):
-            _, name, x, y = line.split()
-            out.append((re.search(r"([a-z0-9_]+_kernel)", re.sub(r"^_ZN5hgemm\d+", "", name))[1], int(x), int(y)))
+            name, x, y, *args = line.split()[1:]
+            out.append((re.search(r"([a-z0-9_]+_kernel)", re.sub(r"^_ZN5hgemm\d+", "", name))[1], int(x), int(y), *map(int, args)))
     return out
 
 
@@ -54,7 +54,45 @@ def test_a_pitch_of_c_beyond_32_bits_keeps_the_matrix_core_kernels(m, n, k, tn):
         if q["M"] * n * k < 1 << 20:
             assert r["describe"] == "generic"
             continue
-        names = [name for name, _, _ in kernels(r["run_log"])]
+        names = [name for name, *_ in kernels(r["run_log"])]
         assert r["run"] == 0 and "generic_gemm_kernel" not in names, (q, names)
         assert ("copy_back_kernel" in names) == (q["M"] > 1 and q["ldc"] >= 1 << 31), (q, names)
         assert r["static"] == 0 and r["static_log"] == r["run_log"], q
+
+
+MIB = 1 << 20
+
+
+@pytest.mark.parametrize("q,needs", [
+    ({"M": 16, "N": 50257, "K": 4096, "tn": True}, 0),                       # nothing is copied
+    ({"M": 300, "N": 4097, "K": 4096, "tn": True, "lda": 4099}, 18 * MIB),   # A is (the rest: planes)
+    ({"M": 2500, "N": 2504, "K": 2501}, 13 * MIB),                           # A is; B, of fewer rows than the copy of A has columns, is not
+], ids=["none", "A", "A, short B"])
+def test_no_memory_for_copies_that_no_aligned_call_needs(q, needs):
+    """The room for copies of operands that can be read where they lie serves misaligned bases only: where the device has no
+    memory for it, the plan keeps the matrix-core kernel, and a misaligned call takes the generic kernel on the caller's operands."""
+    from fake_hip import BASE
+    rich, poor, a_off, b_off, rich_off = ask([q, {**q, "memory": needs}, {**q, "memory": needs, "A": BASE + 2}, {**q, "memory": needs, "B": BASE + 2},
+                                              {**q, "A": BASE + 2, "B": BASE + 2}])
+    assert rich["workspace"] > needs and rich["describe"] == poor["describe"] and "generic" not in poor["describe"]
+    assert poor["workspace"] <= needs and poor["run"] == 0 and poor["run_log"] == rich["run_log"]
+    assert [k[0] for k in kernels(rich_off["run_log"])][0] == "pad_copy_kernel" and "generic_gemm_kernel" not in str(rich_off["run_log"])
+    copies_a = "pad_copy_kernel" in str(rich["run_log"])
+    for r, off in ((a_off, "A"), (b_off, "B")):
+        last = kernels(r["run_log"])[-1]
+        assert r["run"] == 0
+        if off == "A" and copies_a:
+            assert r["run_log"] == poor["run_log"]                 # its copy is made either way
+            continue
+        assert last[0] == "generic_gemm_kernel", r["run_log"]
+        M, N, K, tn = q["M"], q["N"], q["K"], q.get("tn", False)
+        up8 = (K + 7) // 8 * 8
+        assert last[3:] == ((last[3] if copies_a else BASE + 2 * (off == "A")), BASE + 2 * (off == "B"), BASE, M, N, K,
+                            up8 if copies_a else q.get("lda", K), K if tn else N, N), last
+
+
+def test_no_memory_for_the_planes_of_a_phased_split():
+    """... and the same tile runs without a split."""
+    rich, poor = ask([{"M": 512, "N": 8192, "K": 16384}, {"M": 512, "N": 8192, "K": 16384, "memory": 32 * MIB}])
+    assert "sk=4" in rich["describe"] and "ph=1" in rich["describe"] and rich["workspace"] == 64 * MIB
+    assert poor["describe"] == rich["describe"].replace("sk=4", "sk=1") and poor["workspace"] == 0 and poor["run"] == 0
