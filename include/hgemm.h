@@ -110,10 +110,13 @@ hgemm_status_t hgemm_plan_override(hgemm_plan_t* out, int64_t M, int64_t N, int6
  *               in the plan's workspace for zero-padded packed copies of A and
  *               B (Section 5.2's zero padding) and the run makes, in one launch
  *               before the GEMM on the same stream, those that are needed: of
- *               an operand whose rows are not whole aligned chunks.  (A C whose
- *               rows are 2^31 elements apart or more is stored in the workspace
- *               and copied into place by one more launch.)  Problems
- *               below 2^20 multiply-adds with such sizes take a generic
+ *               an operand whose rows are not whole aligned chunks, or whose
+ *               base is not 16-byte aligned.  (Room that only such a base would
+ *               need is left out where the device has no memory for it; the
+ *               generic kernel serves such a base then.)  A C whose rows are
+ *               2^31 elements apart or more is stored in the workspace and
+ *               copied into place by one more launch.  Problems below 2^20
+ *               multiply-adds with such sizes take a generic
  *               one-thread-per-element kernel, as do calls on aligned sizes
  *               whose A or B is not 16-byte aligned.  C is write-only: every
  *               element is overwritten (beta = 0), earlier contents never
