@@ -96,3 +96,12 @@ def test_no_memory_for_the_planes_of_a_phased_split():
     rich, poor = ask([{"M": 512, "N": 8192, "K": 16384}, {"M": 512, "N": 8192, "K": 16384, "memory": 32 * MIB}])
     assert "sk=4" in rich["describe"] and "ph=1" in rich["describe"] and rich["workspace"] == 64 * MIB
     assert poor["describe"] == rich["describe"].replace("sk=4", "sk=1") and poor["workspace"] == 0 and poor["run"] == 0
+
+
+@pytest.mark.parametrize("tn", [False, True])
+def test_no_phased_table_row_has_less_than_two_k_tiles(tn):
+    """The phased schedule copies two K-tiles ahead: with one (12288 x 16384 x 64), half of its copies move zeros and it is 28-35 % slower."""
+    phased = [(shape, spec) for shape, spec in table_rows(tn) if "ph=1" in spec]
+    assert len(phased) > 200
+    for (m, n, k), spec in phased:
+        assert k // int(re.search(r"sk=(\d+)", spec)[1]) >= 128, (m, n, k, spec)

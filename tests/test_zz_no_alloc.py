@@ -141,7 +141,7 @@ def test_static_entry_point_on_an_unaligned_b_that_is_streamed_where_it_lies():
     assert torch.isnan(c).all()
 
 
-@pytest.mark.parametrize("shape", [(512, 8192, 16384), (12288, 256, 16384)], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("shape", [(512, 8192, 16384), (8192, 256, 16384)], ids=lambda s: "x".join(map(str, s)))
 def test_static_entry_point_on_a_workspace_that_fills_the_scratch(shape):
     # split-K planes, and stream-K tiles, of exactly HGEMM_STATIC_SCRATCH_BYTES; then a fused split, whose arrival counters
     # sit in front of them and must still be zero
