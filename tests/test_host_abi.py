@@ -219,3 +219,24 @@ def test_phased_choice_looks_at_the_pitch_the_kernel_reads_b_with(m, n, k, ldb, 
     place, also beside a copied A, else that of its packed copy (2048 for 2041 columns, 2040 for 2033)."""
     choice = hg.plan_choice(m, n, k, hg.Layouts.make(ldb=ldb))
     assert "bm=128,bn=128" in choice and ("ph=1" in choice) == phased, choice
+
+
+def test_a_phased_neighbour_keeps_the_row_by_row_order_on_whole_rounds_of_xcds_only():
+    """gm = 0 is taken over from the nearest tuned shape where the columns of tiles are a multiple of eight."""
+    import random
+    import re
+
+    rnd = random.Random(29)
+    kept = dropped = 0
+    for _ in range(3000):
+        m, n, k = rnd.randint(512, 4000), 8 * rnd.randint(500, 2000), 8 * rnd.randint(40, 700)
+        choice = hg.plan_choice(m, n, k)
+        if not choice.startswith("neighbour") or "ph=1" not in choice:
+            continue
+        kv = {a: int(b) for a, b in re.findall(r"(\w+)=(\d+)", choice)}
+        whole = -(-n // kv["bn"]) % 8 == 0
+        assert kv["gm"] != 0 or whole, (m, n, k, choice)
+        kept += kv["gm"] == 0
+        dropped += not whole
+    assert kept > 10 and dropped > 100
+    assert "gm=8" in hg.plan_choice(1297, 5392, 12336)
