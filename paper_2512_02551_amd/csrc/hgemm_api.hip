@@ -528,13 +528,15 @@ double skinny_choice(int64_t M, int64_t N, int64_t K, Spec* out)
 
 // A row-major B whose rows do not consist of whole aligned 16-byte chunks would have to be copied for the large-tile
 // kernels; the streaming family reads it as it is.  Taken for M <= 32 always, and up to its 64 rows where B is 32 MiB or
-// more: there the copy alone takes longer than the multiplication (40 x 32001 x 2048: copy and 64-row tiles 64 us, streamed 39), below
-// that size the copy stays in the caches and the 64-row tiles are the faster half of the deal.
+// more and K 256: there the copy alone takes longer than the multiplication (40 x 32001 x 2048: copy and 64-row tiles 64 us,
+// streamed 39), below that size the copy stays in the caches and the 64-row tiles are the faster half of the deal, and a
+// shorter K is few steps of the stream per 128 columns of C (62 x 473671 x 48: streamed 83 us, with copies of A, B and C 68;
+// of 220 such problems with K below 64 streamed 1.1 times, copied 0.64 times what three copies take; from K = 256 on 0.54 and 0.58).
 bool streams_any_b(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l)
 {
     if (l.b != HGEMM_ROW_MAJOR || (N % 8 == 0 && l.ldb % 8 == 0) || N < 8 || M > kSkinnyMaxM) return false;
     if ((K + 512) * l.ldb * 2 >= ((int64_t)1 << 31)) return false;
-    return M <= 32 || 2.0 * (double)K * (double)N >= 32.0 * 1048576.0;
+    return M <= 32 || (K >= 256 && 2.0 * (double)K * (double)N >= 32.0 * 1048576.0);
 }
 
 bool evaluate_model(int64_t M, int64_t N, int64_t K, Spec* out, bool b_row_major)

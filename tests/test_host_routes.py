@@ -105,3 +105,12 @@ def test_no_phased_table_row_has_less_than_two_k_tiles(tn):
     assert len(phased) > 200
     for (m, n, k), spec in phased:
         assert k // int(re.search(r"sk=(\d+)", spec)[1]) >= 128, (m, n, k, spec)
+
+
+@pytest.mark.parametrize("m,n,k,streamed", [(62, 473671, 48, False), (33, 80001, 255, False), (33, 80001, 256, True), (64, 8001, 2048, False),
+                                            (32, 80001, 255, True), (32, 4001, 300, True)])
+def test_which_unaligned_row_major_b_is_streamed_where_it_lies(m, n, k, streamed):
+    """Up to 32 rows of A always, up to 64 from 32 MiB of B and K = 256 on; the others are copied."""
+    (r,) = ask([{"M": m, "N": n, "K": k}])
+    reads_any_b = "skinny_gemm_kernel" in str(r["run_log"]) and any("skinny_gemm_kernel" in line and "ELb1EEEvNS_8GemmArgsE" in line for line in r["run_log"])
+    assert r["run"] == 0 and reads_any_b == streamed, r["run_log"]
