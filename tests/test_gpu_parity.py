@@ -886,12 +886,14 @@ def test_ragged_operands_are_copied_only_where_needed(shape, tn):
 
 
 def test_ragged_columns_in_every_way_a_kernel_stores_them():
-    """An odd N (column-major B: nothing is copied) and an unaligned C through every kind of plan that stores C: one
-    tile per workgroup, split-K (planes of padded rows, both reductions), stream-K, persistent, phased, streaming."""
+    """An unaligned C through every kind of plan that stores C: one tile per workgroup, split-K (both reductions), stream-K,
+    persistent, phased in every tile, streaming (pad 3: whatever the planner takes for that pitch).  N is a multiple of 8,
+    explicit specs take no other; odd widths: the test of planned problems off the 16-byte grid, except for stream-K, which
+    the planner does not choose for them."""
     stream = torch.cuda.current_stream().cuda_stream
     base = ["mfma,bm=64,bn=64,bk=64,wm=2,wn=2,st=4,pf=3,sk=1,gm=8", "mfma,bm=128,bn=128,bk=64,wm=2,wn=2,st=2,pf=1,sk=1,gm=8"]
     specs = base + [s.replace("sk=1", "sk=3") for s in base] + [s.replace("sk=1", "sk=3") + ",fr=1" for s in base] + [base[1] + ",sm=1", base[1] + ",ps=1"]
-    specs += phased_specs()[:1] + phased_specs(sk=2)[:1]
+    specs += phased_specs() + phased_specs(sk=2)
     for shape in ((64, 520, 1024), (2200, 2056, 256)):
         M, N, K = shape
         name, a, b = wl.exact_family_for(shape, seed=93)
@@ -911,3 +913,95 @@ def test_ragged_columns_in_every_way_a_kernel_stores_them():
                     torch.cuda.synchronize()
                 assert_bit_exact(to_host(c[:, :N]), ref, desc)
                 assert int(torch.isnan(buf).sum()) == buf.numel() - M * N, desc + ": wrote outside C"
+
+
+# what the planner runs on phased and persistent kernels: tile, and what happens to the operands
+OFF_GRID = [
+    # B is row-major and read where it lies, with fewer rows than the copy of A has columns
+    (2216, 1408, 419, False, "bm=128,bn=128", "ph=1"), (321, 1408, 4927, False, "bm=128,bn=128", "ph=1,split"), (2508, 2496, 389, False, "bm=128,bn=256", "ph=1"),
+    (330, 5760, 3959, False, "bm=128,bn=256", "ph=1,split"), (5611, 1408, 615, False, "bm=256,bn=128", "ph=1"), (5677, 384, 4601, False, "bm=256,bn=128", "ph=1,split"),
+    (3503, 3520, 137, False, "bm=256,bn=256", "ph=1"), (729, 5504, 6885, False, "bm=256,bn=256", "ph=1,split"), (15332, 5184, 189, False, "bm=192,bn=256", "ps=1"),
+    # B is row-major and copied, A too where K is odd; odd rows of C
+    (1236, 2553, 416, False, "bm=128,bn=128", "ph=1"), (4277, 1435, 456, False, "bm=128,bn=256", "ph=1"), (2882, 4525, 137, False, "bm=256,bn=256", "ph=1"),
+    (5641, 1403, 525, False, "bm=256,bn=128", "ph=1"), (14837, 7599, 183, False, "bm=256,bn=256", "ps=1"),
+    # B is column-major; nothing is copied where K is a multiple of 8
+    (527, 5459, 384, True, "bm=128,bn=128", "ph=1"), (3463, 79, 5896, True, "bm=128,bn=128", "ph=1,split"), (272, 2707, 8400, True, "bm=128,bn=256", "ph=1,split"),
+    (3621, 2143, 392, True, "bm=256,bn=128", "ph=1"), (3294, 3885, 144, True, "bm=256,bn=256", "ph=1"), (626, 5312, 6597, True, "bm=256,bn=256", "ph=1,split"),
+    (7737, 5833, 353, True, "bm=256,bn=128", "ps=1"),
+]
+
+
+@pytest.mark.parametrize("M,N,K,tn,tile,kind", OFF_GRID, ids=lambda v: str(v))
+def test_planned_problems_off_the_16_byte_grid_on_phased_and_persistent_kernels(M, N, K, tn, tile, kind):
+    """N or K odd, C at an odd address with an odd pitch, NaN behind the last row of A and B and around C.  Small integers:
+    sums of less than 2^24 in fp32, whatever their order, rounded once."""
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    a = torch.randint(-2, 3, (M, K), generator=g, device="cuda").half()
+    b = torch.randint(-2, 3, (N, K) if tn else (K, N), generator=g, device="cuda").half()
+    ref = (a.double() @ (b.double().t().contiguous() if tn else b.double())).half()
+    abuf, bbuf = (torch.cat([x.flatten(), torch.full((4096,), float("nan"), dtype=torch.float16, device="cuda")]) for x in (a, b))
+    ldc, off = N + 5, 3
+    cbuf = torch.empty(off + M * ldc + 64, dtype=torch.float16, device="cuda")
+    c = cbuf[off:off + M * ldc].view(M, ldc)
+    with hg.Plan(M, N, K, hg.Layouts.make(b_col_major=tn, ldc=ldc)) as p:
+        desc = p.describe()
+        assert tile in desc and kind.split(",")[0] in desc and "pad=1" in desc and ("sk=1," in desc) != ("split" in kind), desc
+        for _ in range(2):
+            cbuf.fill_(float("nan"))
+            p.run(abuf.data_ptr(), bbuf.data_ptr(), c.data_ptr(), torch.cuda.current_stream().cuda_stream)
+            torch.cuda.synchronize()
+            assert torch.equal(c[:, :N], ref), f"{desc}: {int((c[:, :N] != ref).sum())} elements differ"
+            assert int(torch.isnan(cbuf).sum()) == cbuf.numel() - M * N, desc + ": wrote outside C"
+
+
+@pytest.mark.parametrize("tn", [False, True])
+def test_phased_kernels_inside_wider_buffers(tn):
+    """Leading dimensions longer than the rows of A, B and C; NaN between the rows."""
+    M, N, K = 300, 520, 328
+    name, a, b = wl.exact_family_for((M, N, K), seed=94)
+    ref = orc.hgemm(a, b)
+    bs = np.ascontiguousarray(b.T) if tn else b
+    lda, ldb, ldc = K + 24, bs.shape[1] + 40, N + 8
+    A = torch.full((M, lda), float("nan"), dtype=torch.float16, device="cuda")
+    B = torch.full((bs.shape[0], ldb), float("nan"), dtype=torch.float16, device="cuda")
+    C = torch.empty((M, ldc), dtype=torch.float16, device="cuda")
+    A[:, :K] = to_dev(a)
+    B[:, :bs.shape[1]] = to_dev(bs)
+    for spec in phased_specs() + phased_specs(sk=3):
+        with hg.Plan(M, N, K, hg.Layouts.make(b_col_major=tn, lda=lda, ldb=ldb, ldc=ldc), spec) as p:
+            C.fill_(float("nan"))
+            p.run(A.data_ptr(), B.data_ptr(), C.data_ptr(), torch.cuda.current_stream().cuda_stream)
+            torch.cuda.synchronize()
+        out = to_host(C)
+        assert_bit_exact(out[:, :N], ref, f"{name} {spec}")
+        assert np.isnan(out[:, N:]).all(), spec
+
+
+def test_phased_kernels_non_finite_and_subnormal_values():
+    """NaN and infinities reach exactly the elements of C the definition gives them -- not those that a tile's zero fill, the
+    copies past the last K-tile or another phase's registers would add -- and subnormal inputs and results are kept."""
+    M, N, K = 300, 264, 200
+    a, b = wl.small_int_inputs((M, N, K), seed=9)
+    a, b = a.copy(), b.copy()
+    a[3, 5] = np.nan
+    a[290, 199] = np.nan
+    a[130, 64] = np.inf
+    b[64, 7] = 0              # inf * 0 = NaN at C[130, 7]
+    b[17, 130] = np.inf
+    b[199, 263] = -np.inf
+    b[127, 40] = np.nan
+    ref = orc.hgemm(a, b)
+    assert np.isnan(ref).any() and np.isinf(ref).any() and np.isfinite(ref).sum() > M * N // 2
+    rng = np.random.default_rng(78)
+    a2 = (rng.integers(-3, 4, size=(M, K)).astype(np.float64) * 2.0 ** -24).astype(np.float16)
+    b2 = wl.integers(rng, K, N, -2, 2)
+    ref2 = orc.hgemm(a2, b2)
+    assert (np.abs(ref2.astype(np.float64)) < 2.0 ** -14).all() and np.count_nonzero(ref2) > M * N // 2
+    for spec in phased_specs() + phased_specs(sk=2):
+        for tn in (False, True):
+            c, _, _, desc = run_hgemm(a, np.ascontiguousarray(b.T) if tn else b, spec=spec, b_col_major=tn)
+            assert np.array_equal(np.isnan(c), np.isnan(ref)), desc
+            fin = ~np.isnan(ref)
+            assert np.array_equal(c[fin].astype(np.float64), ref[fin].astype(np.float64)), desc
+            c2, _, _, desc = run_hgemm(a2, np.ascontiguousarray(b2.T) if tn else b2, spec=spec, b_col_major=tn)
+            assert_bit_exact(c2, ref2, "subnormal A: " + desc)
