@@ -235,7 +235,10 @@ hgemm_status_t hgemm_plan_choice(int64_t M, int64_t N, int64_t K,
  * tb/sm) on an M x N x K problem.  hgemm_plan() picks the compiled configuration and split factor
  * with the smallest prediction when its measured table has no row for the shape (Section 6 reads
  * such trends -- tile size against M and N, stages against K -- off the paper's winners; here they
- * are a fitted model of one launch).  Host only.  Errors: INVALID_ARG, UNSUPPORTED.            */
+ * are a fitted model of one launch).  The model does not know the phased schedule: a spec with ph=1
+ * counts like the best schedule of its tile that the model knows, and is not what the planner
+ * weighs phased kernels by (it has a model of their own for problems of 3e10 flop and more).
+ * Host only.  Errors: INVALID_ARG, UNSUPPORTED.                                                */
 hgemm_status_t hgemm_predict_us(int64_t M, int64_t N, int64_t K, const char* spec, double* us);
 
 /* Tile-count arithmetic of the zero-padding technique (Section 5.2): number

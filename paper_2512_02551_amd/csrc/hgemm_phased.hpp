@@ -34,7 +34,7 @@
 namespace hgemm {
 
 template <int BM_, int BN_, int WAVES_M_, int WAVES_N_>
-struct PhasedCfg {      // LDS: two buffers of four units, 128 KiB at 256 x 256; 64 KiB at 128 x 128, two workgroups per compute unit
+struct PhasedCfg {      // LDS: two buffers of four units or, where that is more, the epilogue's tile: 132 KiB at 256 x 256; 64 at 128 x 128, two workgroups per compute unit
     static constexpr int BM = BM_, BN = BN_, BK = 64, WAVES_M = WAVES_M_, WAVES_N = WAVES_N_;
     static constexpr int NWAVES = WAVES_M * WAVES_N, THREADS = 64 * NWAVES;
     static constexpr int HM = BM / 2, HN = BN / 2;                       // rows / columns of a unit
