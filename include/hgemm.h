@@ -136,10 +136,11 @@ hgemm_status_t hgemm_run(hgemm_plan_t plan, const void* A, const void* B, void* 
  * `hip_stream` (Section 2.4.2's offline mode: the same kernel executed
  * consecutively, without pauses).  Call i works on operand set j = (first + i)
  * % sets, C[j] = A[j] * B[j]; the result is that of `count` calls of hgemm_run
- * in a loop.  The
+ * in a loop, bit for bit.  The
  * loop runs inside the library so that a caller in an interpreted language
  * pays its per-call overhead once per batch: kernels of 2-3 us are otherwise
- * enqueued more slowly than the GPU executes them.
+ * enqueued more slowly than the GPU executes them.  Consecutive small calls of
+ * which none writes what another reads or writes share one launch.
  *   count       number of calls, >= 0
  *   sets        number of operand sets, >= 1
  *   first       set of the first call, 0 <= first < sets (a caller that cycles

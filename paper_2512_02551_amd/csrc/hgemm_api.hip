@@ -137,6 +137,14 @@ static bool parse_spec(const char* text, Spec* out)
     return true;
 }
 
+// The configuration with square tiles of this side that also takes several problems in one launch.
+static const MfmaEntry* batch_entry(int tile)
+{
+    for (const MfmaEntry& e : registry())
+        if (e.batch && e.bm == tile && e.bn == tile) return &e;
+    return nullptr;
+}
+
 static const MfmaEntry* find_entry(const Spec& s)
 {
     for (const MfmaEntry& e : registry())
@@ -183,6 +191,7 @@ struct hgemm_plan_s {
     size_t a_off, b_off, c_off; // byte offsets of the padded copies of A and B and of the packed C inside the workspace
     size_t bt_off;              // byte offset of the transposed copy of B (spec.tb)
     bool static_ws;             // the workspace is this device's static scratch array, not an allocation
+    bool planned;               // the library chose the specialisation (hgemm_plan, not hgemm_plan_override)
     // Operands beyond the reach of the kernels' 32-bit buffer offsets (2 GiB per operand): the problem runs
     // as a grid of row blocks of A and C by column panels of B and C, each an ordinary plan of its own on
     // offset pointers.  A row-major B of that size cannot be cut into panels that way (a panel still spans
@@ -1082,6 +1091,7 @@ hgemm_status_t init_plan(hgemm_plan_s* p, int64_t M, int64_t N, int64_t K, const
     p->static_ws = static_ws;
     p->copy_a = p->copy_b = p->copy_c = p->any_b = false;
     p->spare = true;
+    p->planned = spec_text == nullptr;
     p->uN = N; p->uK = K; p->ulay = l;
     p->a_off = p->b_off = p->c_off = p->bt_off = 0;
 
@@ -1447,17 +1457,97 @@ hgemm_status_t hgemm_run(hgemm_plan_t plan, const void* A, const void* B, void* 
     return run_plan(plan, A, B, C, hip_stream);
 }
 
+// The kernel that runs up to `calls` calls of a plan in one launch (null: each call is a launch of its own).  A launch costs a
+// call 2.4 us whatever it computes, and one small problem fills a fraction of the chip.
+//   * Only kernels that form and add the products in the plan's own order -- unsplit, 32 x 32 x 16 instructions, k ascending,
+//     whatever the tile -- so that every result has the bits that hgemm_run gives it; not those of a specialisation that the
+//     caller chose, which is to run as it was asked for.
+//   * Operands and result of a call up to 8 MiB: 8 x 256^3 22.4 -> 3.9 us, 16 x 512 x 512 x 1024 106 -> 12, 8 x 1024^3 48 -> 20;
+//     above, a call takes 12 us and more and the launch little of it (4 x 1536^3 49.9 -> 43).
+//   * Tiles of 128 x 128 where they give every compute unit one (8 x 1024 x 1024 x 256: 8.6 us, in 64 x 64 tiles 11.1; 8 x 768^3
+//     12.1 against 13.9), else 64 x 64 (4 x 512 x 512 x 1024, 64 tiles of 128: 5.5 us against 8.8).
+static const MfmaEntry* merged_entry(const hgemm_plan_s* p, int64_t calls)
+{
+    const Spec& s = p->spec;
+    if (!p->planned || p->blocked || p->padded || !p->entry || s.sk > 1 || s.sm || s.ps || s.ph || s.tb || s.ac != 32 || s.mi != 32) return nullptr;
+    if (2.0 * ((double)p->M * p->K + (double)p->K * p->N + (double)p->M * p->N) > 8.0 * 1048576.0) return nullptr;
+    static const MfmaEntry* const large = batch_entry(128);
+    static const MfmaEntry* const small = batch_entry(64);
+    const int64_t tiles128 = ((p->M + 127) / 128) * ((p->N + 127) / 128);
+    return std::min<int64_t>(calls, kBatchSets) * tiles128 >= cu_count() ? large : small;
+}
+
+// A call's operands as address ranges: calls that share a launch must not write what another of them reads or writes.
+struct CallRanges {
+    uintptr_t a0, a1, b0, b1, c0, c1;
+};
+static bool independent(const CallRanges& x, const CallRanges& y)
+{
+    auto apart = [](uintptr_t p0, uintptr_t p1, uintptr_t q0, uintptr_t q1) { return p1 <= q0 || q1 <= p0; };
+    return apart(x.c0, x.c1, y.c0, y.c1) && apart(x.c0, x.c1, y.a0, y.a1) && apart(x.c0, x.c1, y.b0, y.b1) && apart(y.c0, y.c1, x.a0, x.a1) &&
+           apart(y.c0, y.c1, x.b0, x.b1);
+}
+
 hgemm_status_t hgemm_run_many(hgemm_plan_t plan, int64_t count, int64_t sets, int64_t first, const void* const* A,
                               const void* const* B, void* const* C, void* hip_stream)
 {
     if (!plan || count < 0 || sets < 1 || first < 0 || first >= sets || !A || !B || !C) return HGEMM_ERR_INVALID_ARG;
+    const MfmaEntry* e = count > 1 && sets > 1 ? merged_entry(plan, std::min(count, sets)) : nullptr;
+    if (!e) {
+        int64_t set = first;
+        for (int64_t i = 0; i < count; ++i) {
+            const hgemm_status_t st = run_plan(plan, A[set], B[set], C[set], hip_stream);
+            if (st != HGEMM_OK) return st;
+            if (++set == sets) set = 0;
+        }
+        return HGEMM_OK;
+    }
+    BatchArgs g;
+    static_cast<GemmArgs&>(g) = plan->args;
+    g.tiles_m = (g.M + e->bm - 1) / e->bm;
+    g.tiles_n = (g.N + e->bn - 1) / e->bn;
+    g.swizzle = g.tiles_m * g.tiles_n <= 16 ? 0 : plan->spec.gm;
+    set_tile_map(g);
+    const hgemm_layouts_t& l = plan->lay;
+    const size_t a_bytes = ((size_t)(plan->M - 1) * l.lda + plan->K) * 2, c_bytes = ((size_t)(plan->M - 1) * l.ldc + plan->N) * 2;
+    const size_t b_bytes = l.b == HGEMM_ROW_MAJOR ? ((size_t)(plan->K - 1) * l.ldb + plan->N) * 2 : ((size_t)(plan->N - 1) * l.ldb + plan->K) * 2;
+    CallRanges group[kBatchSets];
+    int n = 0;
+    auto flush = [&]() -> hgemm_status_t {
+        if (n == 0) return HGEMM_OK;
+        hgemm_status_t st = HGEMM_OK;
+        if (n == 1) {
+            st = run_plan(plan, g.set[0].A, g.set[0].B, g.set[0].C, hip_stream);
+        } else {
+            hipLaunchKernelGGL(plan->tn_kernel ? e->batch_tn : e->batch, dim3((unsigned)n, (unsigned)(g.tiles_m * g.tiles_n)), dim3(e->threads), e->lds_bytes,
+                               (hipStream_t)hip_stream, g);
+            if (hipGetLastError() != hipSuccess) st = HGEMM_ERR_LAUNCH;
+        }
+        n = 0;
+        return st;
+    };
     int64_t set = first;
     for (int64_t i = 0; i < count; ++i) {
-        const hgemm_status_t st = run_plan(plan, A[set], B[set], C[set], hip_stream);
-        if (st != HGEMM_OK) return st;
+        const uintptr_t a = (uintptr_t)A[set], b = (uintptr_t)B[set], c = (uintptr_t)C[set];
+        const bool wide = a && b && c && ((a | b | c) & 15) == 0 && plan->N % 8 == 0 && l.ldc % 8 == 0;
+        const CallRanges r{a, a + a_bytes, b, b + b_bytes, c, c + c_bytes};
+        bool joins = wide && n < kBatchSets;
+        for (int j = 0; joins && j < n; ++j) joins = independent(r, group[j]);
+        if (!joins) {
+            const hgemm_status_t st = flush();
+            if (st != HGEMM_OK) return st;
+        }
+        if (wide) {
+            group[n] = r;               // one more call of the next launch
+            g.set[n] = {(const _Float16*)A[set], (const _Float16*)B[set], (_Float16*)C[set]};
+            ++n;
+        } else {
+            const hgemm_status_t st = run_plan(plan, A[set], B[set], C[set], hip_stream);
+            if (st != HGEMM_OK) return st;
+        }
         if (++set == sets) set = 0;
     }
-    return HGEMM_OK;
+    return flush();
 }
 
 hgemm_status_t hgemm_run_static(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t* layouts, const void* A, const void* B,

@@ -96,6 +96,15 @@ struct GemmArgs {
     int c_wide;          // every row of C starts on 16 bytes and holds whole 16-byte chunks (else store_cols goes narrower)
 };
 
+// Several problems of one shape and layout in one launch (MODE_BATCH): workgroup (x, y) takes tile y of problem x, whose
+// operands are set[x]; A, B and C of the base are not used.  Problems run along x because workgroup ids are dealt round-robin
+// to the XCDs: with eight problems (or a multiple) each stays on one XCD and comes into one L2 once.  Eight of 256^3 take as
+// long as one does, 3.9 us with the launch: what bounds them is the launch and one trip to memory.
+constexpr int kBatchSets = 32;
+struct BatchArgs : GemmArgs {
+    struct { const _Float16* A; const _Float16* B; _Float16* C; } set[kBatchSets];
+};
+
 // Floats per row of a split-K plane: N rounded up to 8, so that every row starts on 16 bytes.
 __host__ __device__ inline int part_ld(int n) { return (n + 7) & ~7; }
 
@@ -111,8 +120,8 @@ __host__ __device__ inline int part_ld(int n) { return (n + 7) & ~7; }
 // fp32 accumulator registers and buys no register space); and plain for problems off the 16-byte grid: rows of C of any
 // width and alignment, a row-major B of fewer rows than K (GemmArgs::b_rows).  The other modes find that out at run
 // time, but the plain kernels, which short calls run on, are 1-2 % slower for one more argument and both epilogues
-// (1024^3 5.70 -> 5.76 us, 3715 x 1184 x 200 6.93 -> 7.09 us).
-enum { MODE_PLAIN = 0, MODE_SPLITK = 1, MODE_STREAMK = 2, MODE_SPLITK_FUSED = 3, MODE_PERSIST = 4, MODE_ACC16 = 5, MODE_PLAIN_ANY = 6 };
+// (1024^3 5.70 -> 5.76 us, 3715 x 1184 x 200 6.93 -> 7.09 us).  Batch: plain, for several problems (BatchArgs).
+enum { MODE_PLAIN = 0, MODE_SPLITK = 1, MODE_STREAMK = 2, MODE_SPLITK_FUSED = 3, MODE_PERSIST = 4, MODE_ACC16 = 5, MODE_PLAIN_ANY = 6, MODE_BATCH = 7 };
 
 // Stores the first `left` of V's 4 or 8 consecutive columns of C.  `wide` (GemmArgs::c_wide, the same for the whole
 // launch): one aligned store.  Otherwise the row may start at any element: a whole group is still one store (global
@@ -403,10 +412,11 @@ template <int N, class F> __device__ __forceinline__ void static_for(F&& f)
     static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
-template <class C, int MODE, bool TN>
-__global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(GemmArgs g)
+template <class C, int MODE, bool TN, class ARGS = GemmArgs>
+__global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(ARGS g)
 {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
+    constexpr bool BATCH = MODE == MODE_BATCH;
     constexpr bool FUSED = MODE == MODE_SPLITK_FUSED;
     constexpr bool SPLITK = MODE == MODE_SPLITK || FUSED;
     constexpr bool STREAMK = MODE == MODE_STREAMK;
@@ -423,10 +433,21 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(GemmArgs g)
     // All arguments the set-up reads are pulled into scalar registers here, in one batch of loads:
     // left to itself the compiler fetches some of them later, inside branches, and every such fetch is
     // another round trip to memory in front of the first copy (short kernels are latency chains).
-    asm volatile("" :: "s"(g.A), "s"(g.B), "s"(g.C), "s"(g.M), "s"(g.N), "s"(g.K), "s"(g.lda), "s"(g.ldb), "s"(g.ldc),
+    const _Float16 *gA, *gB;
+    _Float16* gC;
+    if constexpr (BATCH) {
+        gA = g.set[blockIdx.x].A;
+        gB = g.set[blockIdx.x].B;
+        gC = g.set[blockIdx.x].C;
+    } else {
+        gA = g.A;
+        gB = g.B;
+        gC = g.C;
+    }
+    asm volatile("" :: "s"(gA), "s"(gB), "s"(gC), "s"(g.M), "s"(g.N), "s"(g.K), "s"(g.lda), "s"(g.ldb), "s"(g.ldc),
                  "s"(g.tiles_m), "s"(g.tiles_n), "s"(g.swizzle), "s"(g.k_per_split), "s"(g.splits));
-    if constexpr (MODE != MODE_PLAIN && !TN) asm volatile("" :: "s"(g.b_rows));
-    if constexpr (MODE != MODE_PLAIN && MODE != MODE_SPLITK) asm volatile("" :: "s"(g.c_wide));
+    if constexpr (MODE != MODE_PLAIN && !BATCH && !TN) asm volatile("" :: "s"(g.b_rows));
+    if constexpr (MODE != MODE_PLAIN && !BATCH && MODE != MODE_SPLITK) asm volatile("" :: "s"(g.c_wide));
     asm volatile("" :: "s"(g.by_tiles_n.m), "s"(g.by_tiles_n.l), "s"(g.by_band.m), "s"(g.by_band.l), "s"(g.by_rows.m),
                  "s"(g.by_rows.l), "s"(g.by_last_rows.m), "s"(g.by_last_rows.l));
 
@@ -471,7 +492,7 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(GemmArgs g)
         to_partial = !(kt0 == 0 && kt1 == kt_per_tile);
         sk_iter += kt1 - kt0;
     } else {
-        tile_id = blockIdx.x;
+        tile_id = BATCH ? blockIdx.y : blockIdx.x;
         k_begin = split * g.k_per_split;
         k_end = min(g.K, k_begin + g.k_per_split);
     }
@@ -490,8 +511,8 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(GemmArgs g)
     const int KT = (k_end - k_begin + C::BK - 1) / C::BK;
 
     const unsigned OOB = 0x80000000u;        // beyond every num_records the host admits
-    const int4v rsrcA = make_rsrc(g.A, (unsigned)min((long long)g.M * g.lda * 2, 0x7fffffffLL));
-    const int4v rsrcB = make_rsrc(g.B, (unsigned)min((long long)(TN ? g.N : MODE == MODE_PLAIN ? k_end : min(k_end, g.b_rows)) * g.ldb * 2, 0x7fffffffLL));
+    const int4v rsrcA = make_rsrc(gA, (unsigned)min((long long)g.M * g.lda * 2, 0x7fffffffLL));
+    const int4v rsrcB = make_rsrc(gB, (unsigned)min((long long)(TN ? g.N : MODE == MODE_PLAIN || BATCH ? k_end : min(k_end, g.b_rows)) * g.ldb * 2, 0x7fffffffLL));
 
     // ---- global -> LDS addressing (per lane, fixed for the whole K loop) ----
     // A: wave-load q = j*NWAVES + wave covers rows [q*A_RPI, (q+1)*A_RPI); lane i writes LDS slot i,
@@ -853,7 +874,7 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(GemmArgs g)
                     *(half4*)(stage + (lane & (MI - 1)) * ROWB + (tn * MI + vg * 8 + 4 * (lane >> LG)) * 2) = o;
                 }
             }
-            if constexpr (MODE == MODE_PLAIN) {
+            if constexpr (MODE == MODE_PLAIN || BATCH) {
 #pragma unroll
                 for (int j = 0; j < (MI * CPR) / 64; ++j) {
                     const int idx = j * 64 + lane;
@@ -866,7 +887,7 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(GemmArgs g)
                         half8 v;
 #pragma unroll
                         for (int e = 0; e < 4; ++e) { v[e] = lo[e]; v[4 + e] = hi[e]; }
-                        *(half8*)(g.C + (size_t)m * g.ldc + n) = v;
+                        *(half8*)(gC + (size_t)m * g.ldc + n) = v;
                     }
                 }
             } else {
@@ -881,7 +902,7 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(GemmArgs g)
                         half8 v;
 #pragma unroll
                         for (int e = 0; e < 4; ++e) { v[e] = lo[e]; v[4 + e] = hi[e]; }
-                        store_cols(g.C + (size_t)m * g.ldc + n, v, g.N - n, wide);
+                        store_cols(gC + (size_t)m * g.ldc + n, v, g.N - n, wide);
                     }
                 };
                 // two loops, the one for narrow rows kept small: short kernels pay for the code they fetch

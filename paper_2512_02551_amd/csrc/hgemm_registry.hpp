@@ -34,6 +34,9 @@ struct MfmaEntry {
     void (*phased_splitk)(GemmArgs) = nullptr;
     void (*phased_splitk_tn)(GemmArgs) = nullptr;
     int phased_lds = 0;
+    // several problems in one launch (null where there is none)
+    void (*batch)(BatchArgs) = nullptr;
+    void (*batch_tn)(BatchArgs) = nullptr;
 };
 
 template <class C> constexpr bool has_phased()
@@ -41,6 +44,15 @@ template <class C> constexpr bool has_phased()
     return false
 #define HGEMM_PHASED(bm, bn, wm, wn, st, mi) \
     || (C::BM == bm && C::BN == bn && C::BK == 64 && C::WAVES_M == wm && C::WAVES_N == wn && C::STAGES == st && C::PF == 1 && C::MI == mi)
+#include "hgemm_configs.inc"
+        ;
+}
+
+template <class C> constexpr bool has_batch()
+{
+    return false
+#define HGEMM_BATCH(bm, bn, bk, wm, wn, st, pf) \
+    || (C::BM == bm && C::BN == bn && C::BK == bk && C::WAVES_M == wm && C::WAVES_N == wn && C::STAGES == st && C::PF == pf && C::MI == 32)
 #include "hgemm_configs.inc"
         ;
 }
@@ -88,6 +100,10 @@ template <class C> inline MfmaEntry make_entry()
             e.phased_splitk = phased_gemm_kernel<P, true, false>;
             e.phased_splitk_tn = phased_gemm_kernel<P, true, true>;
             e.phased_lds = P::LDS_BYTES;
+        }
+        if constexpr (has_batch<C>()) {
+            e.batch = mfma_gemm_kernel<C, MODE_BATCH, false, BatchArgs>;
+            e.batch_tn = mfma_gemm_kernel<C, MODE_BATCH, true, BatchArgs>;
         }
         return e;
     }

@@ -2,7 +2,8 @@
 hgemm_plan and hgemm_run_static decide, allocate and launch, on a machine without a GPU.
 
     ask([{"M": 8, "N": 8, "K": 8, ...}, ...]) -> one dict per question: status, description, workspace bytes and log of
-    hgemm_plan + hgemm_run, and status and log of hgemm_run_static, on operands at the addresses asked for."""
+    hgemm_plan + hgemm_run (and of hgemm_run_many, where operand sets are given), and status and log of hgemm_run_static, on
+    operands at the addresses asked for."""
 import ctypes
 import json
 import os
@@ -44,6 +45,10 @@ def _answer(fake, lib, q):
         assert lib.hgemm_plan_describe(plan, text, ctypes.c_size_t(512)) == 0
         r["describe"], r["workspace"] = text.value.decode(), lib.hgemm_plan_workspace_bytes(plan)
         r["run"], r["run_log"] = lib.hgemm_run(plan, *at, None), log()
+        if "many" in q:         # (A, B, C) per operand set
+            arrays = [(vp * len(q["many"]))(*column) for column in zip(*q["many"])]
+            r["many"] = lib.hgemm_run_many(plan, i64(q.get("count", len(q["many"]))), i64(len(q["many"])), i64(q.get("first", 0)), *arrays, None)
+            r["many_log"] = log()
         lib.hgemm_destroy(plan)
         assert fake.fake_live_bytes() == 0, "the plan's memory was not given back"
     log()

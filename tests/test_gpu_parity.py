@@ -355,6 +355,45 @@ def test_run_many_equals_a_loop_of_runs_and_rotates_operand_sets():
                 p.run_many(1, [(sets[0][0].data_ptr(), sets[0][1].data_ptr(), 0)], sh, 1)      # first >= sets
 
 
+@pytest.mark.parametrize("shape,count,tn,gap", [((1, 8, 8), 3, False, 0), ((64, 64, 128), 8, True, 0), ((65, 72, 136), 5, False, 24), ((16, 512, 1000), 16, True, 8),
+                                                ((257, 120, 264), 33, False, 0), ((512, 504, 72), 16, True, 64), ((500, 512, 520), 17, False, 0), ((130, 136, 8), 32, True, 0)])
+def test_calls_that_share_a_launch_give_the_bits_of_single_calls(shape, count, tn, gap):
+    """hgemm_run_many on small problems, tiles of 64 and (where there are enough calls) 128: every set bit for bit what hgemm_run
+    gives, nothing written beside it; the last set reads the first one's result."""
+    M, N, K = shape
+    g = torch.Generator(device="cuda").manual_seed(M * N + K)
+    sh = torch.cuda.current_stream().cuda_stream
+    sets = []
+    for i in range(count):
+        a = torch.randn((M, K + gap), generator=g, device="cuda").half()
+        b = torch.randn((N, K) if tn else (K, N), generator=g, device="cuda").half()
+        if i == 1:
+            a[M // 2, K // 2] = float("inf")
+            b[0, 0] = float("nan")
+        sets.append([a, b, torch.full((M + 2, N + 8), float("nan"), dtype=torch.float16, device="cuda")])
+    if N >= K + gap and count > 2:
+        sets[-1][0] = sets[0][2]
+    lay = hg.Layouts.make(b_col_major=tn, lda=K + gap, ldc=N + 8)
+    if N >= K + gap and count > 2:
+        lay = hg.Layouts.make(b_col_major=tn, lda=N + 8, ldc=N + 8)
+        for s in sets[:-1]:
+            s[0] = torch.nn.functional.pad(s[0], (0, N + 8 - K - gap)).contiguous()
+    with hg.Plan(M, N, K, lay) as p:
+        for a, b, c in sets:
+            p.run(a.data_ptr(), b.data_ptr(), c.data_ptr(), sh)
+        want = [s[2].clone() for s in sets]
+        for s in sets:
+            s[2].fill_(float("nan"))
+        for _ in range(2):
+            p.run_many(count, [tuple(t.data_ptr() for t in s) for s in sets], sh)
+        torch.cuda.synchronize()
+    for i, (s, w) in enumerate(zip(sets, want)):
+        assert torch.equal(s[2].view(torch.int16), w.view(torch.int16)), f"set {i}"
+    a, b, _ = sets[0]
+    ref = a[:, :K].float().cpu() @ (b.float().cpu().t() if tn else b.float().cpu())
+    assert_close(to_host(want[0][:M, :N]), ref.half().numpy(), "set 0")
+
+
 def skinny_specs(M, N, K):
     out = [c for c in hg.candidates(M, N, K) if c.startswith("skinny")]
     assert out

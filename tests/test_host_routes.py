@@ -114,3 +114,43 @@ def test_which_unaligned_row_major_b_is_streamed_where_it_lies(m, n, k, streamed
     (r,) = ask([{"M": m, "N": n, "K": k}])
     reads_any_b = "skinny_gemm_kernel" in str(r["run_log"]) and any("skinny_gemm_kernel" in line and "ELb1EEEvNS_8GemmArgsE" in line for line in r["run_log"])
     assert r["run"] == 0 and reads_any_b == streamed, r["run_log"]
+
+
+def batch_sets(n, m, nn, k, lda=0):
+    """n sets of packed operands (rows of A lda apart), one behind the other with nothing between them."""
+    from fake_hip import BASE
+    a, b, c = 2 * m * (lda or k), 2 * k * nn, 2 * m * nn
+    return [(BASE + i * (a + b + c), BASE + i * (a + b + c) + a, BASE + i * (a + b + c) + a + b) for i in range(n)]
+
+
+def many(sets, m=256, n=256, k=256, **more):
+    (r,) = ask([{"M": m, "N": n, "K": k, "many": sets, **more}])
+    return r["many"], [int(line.split()[2]) if "BatchArgs" in line else 1 for line in r["many_log"] if line.startswith("launch ")]
+
+
+def test_small_calls_of_a_batch_share_launches_where_none_depends_on_another():
+    """Problems per launch of hgemm_run_many.  Calls join a launch as long as no call of it writes what another reads or writes."""
+    s = batch_sets(8, 256, 256, 256)
+    assert many(s) == (0, [8])
+    assert many(batch_sets(70, 256, 256, 256)) == (0, [32, 32, 6])
+    assert many(batch_sets(33, 256, 256, 256)) == (0, [32, 1])
+    assert many(s, count=19, first=3) == (0, [8, 8, 3])                               # a set's C comes round again
+    assert many(s[:1], count=4) == (0, [1] * 4)
+    chain = [(s[0][0], s[0][1], s[0][2]), (s[0][2], s[1][1], s[1][2]), (s[2][0], s[2][1], s[2][2]), (s[1][0], s[2][2], s[3][2])]
+    assert many(chain) == (0, [1, 2, 1])                                              # A is the C of the call before; B is
+    assert many([s[0], (s[1][0], s[0][1], s[1][2]), (s[1][0], s[0][1], s[2][2])]) == (0, [3])     # operands that are only read may be shared
+    assert many([s[0], (s[1][0], s[1][1], s[0][0]), s[2]]) == (0, [1, 2])             # C is an A of the call before
+    assert many([s[0], (s[1][0], s[1][1], s[0][2] + 2 * 256 * 255 + 2 * 248), s[2]]) == (0, [1, 2])   # the last 16 bytes of its C
+    assert many([s[0], (s[1][0], s[1][1] + 2, s[1][2]), s[2], s[3]]) == (0, [1, 1, 2])            # a misaligned B goes its own way
+    status, launches = many([s[0], s[1], (s[2][0], None, s[2][2]), s[3]])
+    assert status != 0 and launches == [2]                                            # calls in front of the one that fails are enqueued
+
+
+def test_which_plans_share_launches():
+    """Small unsplit problems in both layouts and in wider buffers; not large ones, split ones or those off the 16-byte grid."""
+    assert many(batch_sets(4, 16, 64, 64), 16, 64, 64, tn=True) == (0, [4])
+    assert many(batch_sets(5, 100, 200, 304, lda=512), 100, 200, 304, lda=512) == (0, [5])
+    assert many(batch_sets(3, 1536, 1536, 1536), 1536, 1536, 1536) == (0, [1] * 3)
+    assert sum(many(batch_sets(3, 64, 64, 16384), 64, 64, 16384)[1]) >= 3             # split: two launches or fused, one call each
+    assert max(many(batch_sets(3, 64, 64, 16384), 64, 64, 16384)[1]) == 1
+    assert max(many(batch_sets(3, 200, 201, 203), 200, 201, 203)[1]) == 1
