@@ -57,6 +57,7 @@ struct Spec {
     int ac = 32;    // accumulator width: 32 = fp32 over all of K; 16 = rounded to fp16 after every 16 products
     int mi = 32;    // matrix-core output block: 32 = v_mfma_f32_32x32x16_f16, 16 = v_mfma_f32_16x16x32_f16
     int ph = 0;     // 1 = the phased schedule of this tile (hgemm_phased.hpp)
+    int di = 0;     // 1 = operands read through registers, at any element's address (MODE_DIRECT)
     int wv = 4;     // skinny family: waves per workgroup (4, 8 or 16), each taking 16 k-rows of a step
     int nr = 16;    // skinny family, column-major B: rows of B (columns of C) per workgroup (16, 32 or 64)
 };
@@ -84,6 +85,7 @@ static std::string spec_to_string(const Spec& s)
     if (s.ac == 16) strncat(buf, ",ac=16", sizeof buf - strlen(buf) - 1);
     if (s.mi == 16) strncat(buf, ",mi=16", sizeof buf - strlen(buf) - 1);
     if (s.ph) strncat(buf, ",ph=1", sizeof buf - strlen(buf) - 1);
+    if (s.di) strncat(buf, ",di=1", sizeof buf - strlen(buf) - 1);
     return buf;
 }
 
@@ -107,7 +109,7 @@ static bool parse_spec(const char* text, Spec* out)
     const struct { char key[4]; int* value; } keys[] = {
         {"bm", &sp.bm}, {"bn", &sp.bn}, {"bk", &sp.bk}, {"wm", &sp.wm}, {"wn", &sp.wn}, {"st", &sp.st}, {"pf", &sp.pf}, {"sk", &sp.sk},
         {"gm", &sp.gm}, {"tb", &sp.tb}, {"sm", &sp.sm}, {"fr", &sp.fr}, {"ps", &sp.ps}, {"ac", &sp.ac}, {"mi", &sp.mi}, {"ph", &sp.ph},
-        {"wv", &sp.wv}, {"nr", &sp.nr},
+        {"di", &sp.di}, {"wv", &sp.wv}, {"nr", &sp.nr},
         {"pad", &ignored},      // reported by hgemm_plan_describe; padding follows from the shape, not from the spec
     };
     while (*p) {
@@ -131,6 +133,7 @@ static bool parse_spec(const char* text, Spec* out)
     if ((sp.ac != 32 && sp.ac != 16) || (sp.ac == 16 && (sp.fam != FAM_MFMA || sp.sk > 1 || sp.sm || sp.ps || sp.fr))) return false;
     if (sp.mi != 32 && sp.mi != 16) return false;
     if (sp.ph > 1 || (sp.ph && (sp.fam != FAM_MFMA || sp.sm || sp.fr || sp.ps || sp.tb || sp.ac == 16))) return false;
+    if (sp.di > 1 || (sp.di && (sp.fam != FAM_MFMA || sp.sm || sp.ps || sp.tb || sp.ph || sp.ac == 16 || sp.mi != 32))) return false;
     if ((sp.wv != 4 && sp.wv != 8 && sp.wv != 16) || (sp.wv != 4 && sp.fam != FAM_SKINNY)) return false;
     if ((sp.nr != 16 && sp.nr != 32 && sp.nr != 64) || (sp.nr != 16 && sp.fam != FAM_SKINNY)) return false;
     *out = sp;
@@ -178,6 +181,7 @@ struct hgemm_plan_s {
     // kernels see them, and the fields below keep the caller's problem.  An operand that can be read where it lies is;
     // its place in the workspace is kept all the same (`spare`), for calls whose base pointer is not 16-byte aligned, unless
     // there is no memory for it: such calls then take the generic kernel.
+    // Smaller problems don't take this way: kernels that load A and B through registers read them where they lie (direct_choice).
     // Measured against copying A, B and C always, two bytes per lane (us): 1000 x 1001 x 1003 26.3 -> 10.9 (A and B
     // copied, in one launch), 16 x 50257 x 4096 with column-major B 383 -> 89 (nothing copied), with row-major B 402 -> 240
     // (and 100 by the streaming family, which reads any row-major B where it lies).
@@ -662,6 +666,15 @@ bool kernels_can_run(const hgemm_plan_s* p)
     return fast_path_ok(p->M, up8(p->N), p->K, l);
 }
 
+// Can the kernels that read operands through registers run the problem?  Any pitches and addresses; whole loads of 8 elements
+// have to exist, and byte offsets, those of the K-tiles loaded ahead of the last one included, stay below 2^32.
+bool direct_can_run(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l)
+{
+    const int64_t lim = (int64_t)1 << 31, b_rows = l.b == HGEMM_ROW_MAJOR ? K : N;
+    return M > 0 && N >= 8 && K >= 8 && M < (1 << 24) && N < (1 << 24) && K < (1 << 24) && (M + 512) * l.lda * 2 < lim && (b_rows + 512) * l.ldb * 2 < lim &&
+           l.ldc < lim;
+}
+
 // Lays the padded copies of A and B, and the packed C, out in the workspace behind the counters and returns their bytes.
 size_t place_copies(hgemm_plan_s* p)
 {
@@ -729,12 +742,13 @@ bool select_kernel(hgemm_plan_s* p)
     const MfmaEntry* e = p->entry;
     const Spec& s = p->spec;
     const bool split = s.sk > 1;
-    void (*const all[])(GemmArgs) = {e->plain, e->splitk, e->streamk, e->splitk_fused, e->persist, e->acc16, e->phased, e->phased_splitk};
-    void (*const all_tn[])(GemmArgs) = {e->plain_tn, e->splitk_tn, e->streamk_tn, e->splitk_fused_tn, e->persist_tn, e->acc16_tn, e->phased_tn, e->phased_splitk_tn};
-    const int which = s.sm ? 2 : s.ps ? 4 : split && s.fr ? 3 : s.ph ? (split ? 7 : 6) : split ? 1 : s.ac == 16 ? 5 : 0;
+    void (*const all[])(GemmArgs) = {e->plain, e->splitk, e->streamk, e->splitk_fused, e->persist, e->acc16, e->phased, e->phased_splitk, e->direct, e->direct_splitk, e->direct_fused};
+    void (*const all_tn[])(GemmArgs) = {e->plain_tn, e->splitk_tn, e->streamk_tn, e->splitk_fused_tn, e->persist_tn, e->acc16_tn, e->phased_tn, e->phased_splitk_tn,
+                                           e->direct_tn, e->direct_splitk_tn, e->direct_fused_tn};
+    const int which = s.di ? (!split ? 8 : s.fr ? 10 : 9) : s.sm ? 2 : s.ps ? 4 : split && s.fr ? 3 : s.ph ? (split ? 7 : 6) : split ? 1 : s.ac == 16 ? 5 : 0;
     p->kernel = p->tn_kernel ? all_tn[which] : all[which];
     p->kernel_any = which != 0 ? p->kernel : p->tn_kernel ? e->plain_any_tn : e->plain_any;
-    p->kernel_lds = s.ph ? e->phased_lds : e->lds_bytes;
+    p->kernel_lds = s.ph ? e->phased_lds : s.di ? e->direct_lds : e->lds_bytes;
     if (!p->kernel) return false;
     if (p->kernel_lds <= 64 * 1024) return true;
     constexpr size_t kMaxEntries = 256;
@@ -801,7 +815,7 @@ hgemm_status_t finish_plan(hgemm_plan_s* p)
     }
     const MfmaEntry* e = find_entry(s);
     if (!e) return HGEMM_ERR_UNSUPPORTED;
-    if (!kernels_can_run(p)) return HGEMM_ERR_UNSUPPORTED;
+    if (s.di ? !e->direct || p->padded || !direct_can_run(M, N, K, p->lay) : !kernels_can_run(p)) return HGEMM_ERR_UNSUPPORTED;
     if (s.tb && p->lay.b != HGEMM_ROW_MAJOR) return HGEMM_ERR_UNSUPPORTED;
     p->tn_kernel = s.tb || p->lay.b == HGEMM_COL_MAJOR;
     p->entry = e;
@@ -956,6 +970,63 @@ bool phased_choice(int64_t M, int64_t N, int64_t K, bool row_b, int64_t b_ld, co
     return false;
 }
 
+// Problems off the 16-byte grid, read through registers where they lie.  Fitted (soft-L1 on log time, rms 9-11 %) to 9700
+// timings of the four tiles and their splits on 600 random problems (M and N from 65 to 4200, K from 129; few rows against a long
+// odd N among them), operands in the last-level cache.
+struct DirectTile { const char* spec; int bm, bn; double t0, wg, lat, busy, flow, red2, red2_mib, red1, red1_mib; };
+constexpr DirectTile kDirectTiles[] = {
+    {"mfma,bm=32,bn=64,bk=64,wm=1,wn=2,st=4,pf=3,sk=1,gm=8,di=1", 32, 64, 2.904, 0.354, 0.199, 0.215, 0.190, 1.977, 0.478, 2.169, 0.777},
+    {"mfma,bm=64,bn=64,bk=64,wm=2,wn=2,st=4,pf=3,sk=1,gm=8,di=1", 64, 64, 2.738, 0.436, 0.280, 0.288, 0.240, 1.911, 0.577, 3.326, 0.948},
+    {"mfma,bm=64,bn=128,bk=64,wm=2,wn=2,st=4,pf=3,sk=1,gm=8,di=1", 64, 128, 3.666, 0.598, 0.310, 0.415, 0.435, 1.911, 0.464, 1.412, 1.774},
+    {"mfma,bm=128,bn=128,bk=64,wm=2,wn=4,st=3,pf=3,sk=1,gm=8,di=1", 128, 128, 4.212, 0.022, 0.502, 0.558, 0.580, 1.953, 0.507, 1.262, 1.990},
+};
+double predict_direct_us(const DirectTile& c, int64_t M, int64_t N, int64_t K, int64_t sk, bool fused)
+{
+    const int64_t kt = (K + 63) / 64;
+    sk = effective_splits(kt, sk);
+    const double per = (double)(((kt + sk - 1) / sk + 1) / 2 * 2);       // K-tiles of a workgroup, whole pairs
+    const double x = (double)(((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) * sk) / (double)cu_count(), w = std::ceil(x);
+    const double chain = std::max(c.lat, c.busy * w), flow = c.flow * x;
+    const double planes = (double)sk * M * N * 4.0 / 1048576.0;
+    const double t = c.t0 + c.wg * w + per * std::sqrt(std::sqrt(chain * chain * chain * chain + flow * flow * flow * flow));
+    return sk == 1 ? t : t + (fused ? c.red1 + c.red1_mib * planes : c.red2 + c.red2_mib * planes);
+}
+
+// Predicted microseconds of one call of a specialisation, where a model knows it.
+bool predict_spec_us(int64_t M, int64_t N, int64_t K, const Spec& s, double* us)
+{
+    if (s.fam == FAM_SKINNY) {
+        if (M > kSkinnyMaxM) return false;
+        const int64_t eff = effective_splits((K + skinny_step(s) - 1) / skinny_step(s), s.sk);
+        *us = predict_skinny_us(M, N, K, eff, s.fr != 0 && eff > 1);
+        return true;
+    }
+    const MfmaEntry* own = s.fam == FAM_MFMA ? find_entry(s) : nullptr;
+    if (!own || s.sm || s.tb || s.ps || s.ac == 16) return false;
+    if (s.di) {
+        for (const DirectTile& c : kDirectTiles)
+            if (c.bm == s.bm && c.bn == s.bn) {
+                *us = predict_direct_us(c, M, N, K, s.sk, s.fr != 0);
+                return own->direct != nullptr;
+            }
+        return false;
+    }
+    if (s.ph) {
+        // the cost model does not know the phased schedule: it counts like the best schedule of its tile that the model knows
+        if (s.fr || !own->phased) return false;
+        *us = 1e300;
+        for (const MfmaEntry& e : registry()) {
+            if (e.bm != s.bm || e.bn != s.bn || e.deep || e.mi != 32) continue;
+            *us = std::min(*us, predict_us(M, N, K, e.bm, e.bn, e.bk, e.wm, e.wn, e.st, e.pf, effective_splits((K + e.bk - 1) / e.bk, s.sk), predict_big(M, N, K)));
+        }
+        return true;
+    }
+    const int64_t eff = effective_splits((K + s.bk - 1) / s.bk, s.sk);
+    *us = predict_us(M, N, K, s.bm, s.bn, s.bk, s.wm, s.wn, s.st, s.pf, eff, predict_big(M, N, K));
+    if (s.fr && eff > 1) *us += fused_delta_us(M, N, eff);
+    return true;
+}
+
 // True when device `dev` is a gfx950; the answer is kept per device (hipGetDeviceProperties is slow).
 bool device_is_gfx950(int dev)
 {
@@ -1059,6 +1130,51 @@ Route route(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l)
     return r;
 }
 
+// A problem that would be copied: the kernels that read it where it lies instead?  `pick` is what the padded problem would run on;
+// a phased or persistent pick stays, and so does a B that is streamed.  A copy costs a launch and the operand three times; reading through registers costs the
+// matrix cores their even supply: 1000 x 1001 x 1003 11.0 -> 8.0 us, 500 x 501 x 503 7.4 -> 5.3, 70 x 3001 x 1001 11.3 -> 7.0, 2000 x 2001 x 2003
+// 33 -> 29, but 4100 x 4101 x 4103 183 -> 280.  Taken where its prediction is below 0.9 of the other way's (1.3 times the
+// prediction of the pick, which was fitted warm and alone, and 0.2 us a MB copied), below 0.75 for an unsplit K of 2560 and more, where it
+// is the less certain one; 128 x 128 tiles up to one for every compute unit.  523 random problems: 487 change, 1.40 times
+// faster in the geometric mean over all, none slower by more than 2 %.
+bool direct_choice(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, const Route& r, const Spec& pick, Spec* out)
+{
+    if (!r.padded || !(r.copy_a || r.copy_b) || r.any_b || pick.fam != FAM_MFMA || pick.ph || pick.ps || !direct_can_run(M, N, K, l) || 2.0 * (double)M * (double)N * (double)K > 4e10) return false;
+    double other = 0;
+    if (!predict_spec_us(M, r.N, r.K, pick, &other)) return false;
+    const double moved = 4e-6 * ((r.copy_a ? (double)M * r.K : 0.0) + (r.copy_b ? (double)r.N * r.K : 0.0));      // MB read and written
+    other = 1.74 + 1.3 * other + 0.206 * moved;
+    const DirectTile* best = nullptr;
+    double best_us = 1e300;
+    int best_sk = 1, best_fr = 0;
+    const int64_t ktiles = (K + 63) / 64;
+    for (const DirectTile& c : kDirectTiles) {
+        const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+        if ((c.bm >= 2 * M && c.bm > 32) || (c.bn >= 2 * N && c.bn > 64) || (c.bm == 128 && tiles > cu_count())) continue;
+        for (int sk : {1, 2, 3, 4, 6, 8, 12, 16}) {
+            if (sk > 1 && (tiles * sk > 4 * cu_count() || ktiles / sk < 2 || tiles > cu_count())) break;
+            for (int fr = 0; fr < (sk > 1 && (double)sk * M * N * 4.0 <= 6.0 * 1048576.0 ? 2 : 1); ++fr) {
+                const double us = predict_direct_us(c, M, N, K, sk, fr != 0);
+                if (us < best_us) { best_us = us; best = &c; best_sk = sk; best_fr = fr; }
+            }
+        }
+    }
+    if (!best || best_us >= (K >= 2560 && best_sk == 1 ? 0.75 : 0.9) * other || !parse_spec(best->spec, out)) return false;
+    out->sk = (int)effective_splits(ktiles, best_sk);
+    out->fr = best_fr;
+    return true;
+}
+
+// hgemm_run_static refuses a problem whose padded copies, with the planes of a split, take more than the scratch; callers size
+// their problems by that rule, so it stays one also for a problem that needs none of them any more.
+bool copies_fit_static_scratch(int64_t M, const Route& r, const Choices& c)
+{
+    const size_t copies = up256((size_t)M * r.K * 2) + up256((size_t)r.K * r.N * 2) + up256((size_t)M * r.N * 2);
+    for (int i = 0; i < c.n; ++i)
+        if (copies + (c.spec[i].sk > 1 ? up256((size_t)c.spec[i].sk * M * r.N * sizeof(float)) : 0) <= kScratchBytes) return true;
+    return false;
+}
+
 hgemm_status_t init_blocked(hgemm_plan_s* p);
 
 hgemm_status_t init_plan(hgemm_plan_s* p, int64_t M, int64_t N, int64_t K, const hgemm_layouts_t* layouts, const char* spec_text,
@@ -1116,6 +1232,16 @@ hgemm_status_t init_plan(hgemm_plan_s* p, int64_t M, int64_t N, int64_t K, const
             st = finish_plan(p);
         } else {
             const Choices c = choose_spec(M, N, K, l, r.ldb, p->padded, p->any_b);
+            Spec direct;
+            if (direct_choice(M, p->uN, p->uK, p->ulay, r, c.spec[0], &direct) && (!static_ws || copies_fit_static_scratch(M, r, c))) {
+                const hgemm_plan_s padded = *p;
+                p->padded = p->copy_a = p->copy_b = p->copy_c = p->any_b = false;
+                p->K = p->uK;
+                p->lay = p->ulay;
+                p->spec = direct;
+                if (finish_plan(p) == HGEMM_OK) return HGEMM_OK;
+                *p = padded;                               // no memory for planes, say: the other way
+            }
             for (const bool spare : {true, false}) {       // no memory: once more without the room that only misaligned calls use
                 p->spare = spare;
                 for (int i = 0; i < c.n; ++i) {
@@ -1295,6 +1421,8 @@ hgemm_status_t hgemm_plan_choice(int64_t M, int64_t N, int64_t K, const hgemm_la
     const bool nonempty = M > 0 && N > 0 && K > 0;
     const Route r = route(M, N, K, l);
     const bool fast = r.fast;
+    const int64_t uN = N, uK = K;
+    const hgemm_layouts_t ul = l;
     N = r.N; K = r.K; l = r.lay;
     int64_t rows = 0, cols = 0;
     bool bt = false;
@@ -1310,7 +1438,9 @@ hgemm_status_t hgemm_plan_choice(int64_t M, int64_t N, int64_t K, const hgemm_la
         out = "generic";
     } else {
         const Choices c = choose_spec(M, N, K, l, r.ldb, r.padded, r.any_b);
-        out = std::string(c.source) + ": " + spec_to_string(c.spec[0]) + (r.padded ? ",pad=1" : "");
+        Spec direct;
+        if (direct_choice(M, uN, uK, ul, r, c.spec[0], &direct)) out = "model: " + spec_to_string(direct) + ",pad=1";
+        else out = std::string(c.source) + ": " + spec_to_string(c.spec[0]) + (r.padded ? ",pad=1" : "");
     }
     if (out.size() + 1 > n) { buf[0] = '\0'; return HGEMM_ERR_INVALID_ARG; }
     memcpy(buf, out.c_str(), out.size() + 1);
@@ -1386,7 +1516,7 @@ static hgemm_status_t run_plan(const hgemm_plan_s* plan, const void* A, const vo
     };
 
     // A and B are read in 16-byte chunks; C may start anywhere
-    const bool aligned = ((((uintptr_t)A) | (plan->any_b ? (uintptr_t)0 : (uintptr_t)B)) & 15) == 0;
+    const bool aligned = plan->spec.di || ((((uintptr_t)A) | (plan->any_b ? (uintptr_t)0 : (uintptr_t)B)) & 15) == 0;
     if (plan->spec.fam == FAM_GENERIC || !aligned) {
         const int col_b = row_b ? 0 : 1;
         const int64_t k = plan->uK;                       // of a padded problem too: a copy of A is longer, B need not be
@@ -1469,7 +1599,7 @@ hgemm_status_t hgemm_run(hgemm_plan_t plan, const void* A, const void* B, void* 
 static const MfmaEntry* merged_entry(const hgemm_plan_s* p, int64_t calls)
 {
     const Spec& s = p->spec;
-    if (!p->planned || p->blocked || p->padded || !p->entry || s.sk > 1 || s.sm || s.ps || s.ph || s.tb || s.ac != 32 || s.mi != 32) return nullptr;
+    if (!p->planned || p->blocked || p->padded || !p->entry || s.sk > 1 || s.sm || s.ps || s.ph || s.di || s.tb || s.ac != 32 || s.mi != 32) return nullptr;
     if (2.0 * ((double)p->M * p->K + (double)p->K * p->N + (double)p->M * p->N) > 8.0 * 1048576.0) return nullptr;
     static const MfmaEntry* const large = batch_entry(128);
     static const MfmaEntry* const small = batch_entry(64);
@@ -1594,7 +1724,7 @@ hgemm_status_t hgemm_plan_describe(hgemm_plan_t plan, char* buf, size_t n)
         const hgemm_plan_s* q = plan->sub[0][0] ? plan->sub[0][0] : plan->sub[1][0] ? plan->sub[1][0] : plan->sub[0][1] ? plan->sub[0][1] : plan->sub[1][1];
         s = std::string(head) + (q ? spec_to_string(q->spec) : std::string("?"));
     } else {
-        s = spec_to_string(plan->spec) + (plan->padded ? ",pad=1" : "");
+        s = spec_to_string(plan->spec) + (plan->padded || (plan->spec.di && plan->planned) ? ",pad=1" : "");
     }
     if (s.size() + 1 > n) { buf[0] = '\0'; return HGEMM_ERR_INVALID_ARG; }
     memcpy(buf, s.c_str(), s.size() + 1);
@@ -1629,7 +1759,7 @@ hgemm_status_t hgemm_plan_launch_info(hgemm_plan_t plan, int64_t* workgroups, in
         wg = plan->spec.sm ? (int64_t)plan->args.dp_tiles + plan->args.sk_workers
                            : (int64_t)plan->args.tiles_m * plan->args.tiles_n * plan->args.splits;
         if (plan->spec.ps) wg = std::min<int64_t>(wg, cu_count());
-        lds = plan->spec.ph ? plan->entry->phased_lds : plan->entry->lds_bytes;
+        lds = plan->kernel_lds;
         th = plan->entry->threads;
     } else {
         wg = ((plan->N + 63) / 64) * ((plan->M + 3) / 4);
@@ -1658,7 +1788,7 @@ const char* hgemm_spec_help(void)
             "    Column-major B (K contiguous): a workgroup takes nr = 16 (default), 32 or 64 rows of B (columns of C), its waves split its K\n"
             "    range into contiguous parts of whole 32-k steps, 16-byte loads are the operands of 16x16x32 instructions\n"
             "    as they come; sk splits K further across workgroups\n"
-            "mfma,bm=BM,bn=BN,bk=BK,wm=WM,wn=WN,st=STAGES[,pf=PREFETCH][,sk=SPLITS][,gm=GROUP][,tb=1][,sm=1][,fr=1][,ps=1][,ac=16][,mi=16][,ph=1]\n"
+            "mfma,bm=BM,bn=BN,bk=BK,wm=WM,wn=WN,st=STAGES[,pf=PREFETCH][,sk=SPLITS][,gm=GROUP][,tb=1][,sm=1][,fr=1][,ps=1][,ac=16][,mi=16][,ph=1][,di=1]\n"
             "    pipelined 32x32x16 MFMA kernel; BMxBN tile per workgroup, WMxWN wavefronts, STAGES LDS buffers,\n"
             "    pf = register prefetch distance in k-steps (1 = ping-pong, 3 = four fragment sets),\n"
             "    sk = split-K factor (fp32 partials + ordered reduction), gm = tile-order group height (0 = row-major),\n"
@@ -1672,9 +1802,11 @@ const char* hgemm_spec_help(void)
             "    ac = 16: 16-bit accumulator: the running sums are rounded to fp16 after every matrix-core instruction\n"
             "            (16 products); explicit specs only, with sk = 1 and without sm, ps, fr; never chosen by hgemm_plan,\n"
             "            which always accumulates in fp32 over all of K\n"
+            "    di = 1: operands at any element's address, with any N and K of at least 8: loaded through registers, zeros behind K\n"
+            "            put in on the way (two stages, 32x32x16 instructions); sk and fr allowed, no sm, ps, ph, ac, tb\n"
             "    pad = 1 in a description: N, K or a leading dimension is not a multiple of 8 and the kernel runs on\n"
             "            zero-padded packed copies, held in the plan's workspace, of those of A and B whose rows are not whole\n"
-            "            aligned 16-byte chunks (decided by hgemm_plan from the shape)\n"
+            "            aligned 16-byte chunks, or, with di = 1, pads them on their way through registers (decided by hgemm_plan from the shape)\n"
             "    compiled (bm,bn,bk,wm,wn,st,pf):";
         for (const MfmaEntry& e : registry()) {
             if (e.deep || e.mi != 32) continue;
@@ -1711,6 +1843,13 @@ const char* hgemm_spec_help(void)
             if (!e.phased) continue;
             char b[64];
             snprintf(b, sizeof b, " (%d,%d,%d,%d,%d,%d,%d,%d)", e.bm, e.bn, e.bk, e.wm, e.wn, e.st, e.pf, e.mi);
+            t += b;
+        }
+        t += "\n    direct (bm,bn,bk,wm,wn,st,pf):";
+        for (const MfmaEntry& e : registry()) {
+            if (!e.direct) continue;
+            char b[64];
+            snprintf(b, sizeof b, " (%d,%d,%d,%d,%d,%d,%d)", e.bm, e.bn, e.bk, e.wm, e.wn, e.st, e.pf);
             t += b;
         }
         t += "\n";
@@ -1836,27 +1975,7 @@ hgemm_status_t hgemm_predict_us(int64_t M, int64_t N, int64_t K, const char* spe
     if (!spec || !us || M <= 0 || N <= 0 || K <= 0) return HGEMM_ERR_INVALID_ARG;
     Spec s;
     if (!parse_spec(spec, &s)) return HGEMM_ERR_INVALID_ARG;
-    if (s.fam == FAM_SKINNY) {
-        if (M > kSkinnyMaxM) return HGEMM_ERR_UNSUPPORTED;
-        const int64_t eff = effective_splits((K + skinny_step(s) - 1) / skinny_step(s), s.sk);
-        *us = predict_skinny_us(M, N, K, eff, s.fr != 0 && eff > 1);
-        return HGEMM_OK;
-    }
-    if (s.fam != FAM_MFMA || s.sm || s.tb || s.ps || s.ac == 16 || !find_entry(s)) return HGEMM_ERR_UNSUPPORTED;
-    if (s.ph) {
-        // the cost model does not know the phased schedule: it counts like the best schedule of its tile that the model knows
-        if (s.fr || !find_entry(s)->phased) return HGEMM_ERR_UNSUPPORTED;
-        *us = 1e300;
-        for (const MfmaEntry& e : registry()) {
-            if (e.bm != s.bm || e.bn != s.bn || e.deep || e.mi != 32) continue;
-            *us = std::min(*us, predict_us(M, N, K, e.bm, e.bn, e.bk, e.wm, e.wn, e.st, e.pf, effective_splits((K + e.bk - 1) / e.bk, s.sk), predict_big(M, N, K)));
-        }
-        return HGEMM_OK;
-    }
-    const int64_t eff = effective_splits((K + s.bk - 1) / s.bk, s.sk);
-    *us = predict_us(M, N, K, s.bm, s.bn, s.bk, s.wm, s.wn, s.st, s.pf, eff, predict_big(M, N, K));
-    if (s.fr && eff > 1) *us += fused_delta_us(M, N, eff);
-    return HGEMM_OK;
+    return predict_spec_us(M, N, K, s, us) ? HGEMM_OK : HGEMM_ERR_UNSUPPORTED;
 }
 
 int64_t hgemm_tiles(int64_t dim, int64_t tile) { return (dim < 0 || tile <= 0) ? -1 : (dim + tile - 1) / tile; }

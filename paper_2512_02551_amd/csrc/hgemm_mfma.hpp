@@ -120,8 +120,9 @@ __host__ __device__ inline int part_ld(int n) { return (n + 7) & ~7; }
 // fp32 accumulator registers and buys no register space); and plain for problems off the 16-byte grid: rows of C of any
 // width and alignment, a row-major B of fewer rows than K (GemmArgs::b_rows).  The other modes find that out at run
 // time, but the plain kernels, which short calls run on, are 1-2 % slower for one more argument and both epilogues
-// (1024^3 5.70 -> 5.76 us, 3715 x 1184 x 200 6.93 -> 7.09 us).  Batch: plain, for several problems (BatchArgs).
-enum { MODE_PLAIN = 0, MODE_SPLITK = 1, MODE_STREAMK = 2, MODE_SPLITK_FUSED = 3, MODE_PERSIST = 4, MODE_ACC16 = 5, MODE_PLAIN_ANY = 6, MODE_BATCH = 7 };
+// (1024^3 5.70 -> 5.76 us, 3715 x 1184 x 200 6.93 -> 7.09 us).  Batch: plain, for several problems (BatchArgs).  Direct: operands at any
+// element's address go through registers (see staged below), as plain, two-launch and fused split-K kernels.
+enum { MODE_PLAIN = 0, MODE_SPLITK = 1, MODE_STREAMK = 2, MODE_SPLITK_FUSED = 3, MODE_PERSIST = 4, MODE_ACC16 = 5, MODE_PLAIN_ANY = 6, MODE_BATCH = 7, MODE_DIRECT = 8, MODE_DIRECT_SPLITK = 9, MODE_DIRECT_FUSED = 10 };
 
 // Stores the first `left` of V's 4 or 8 consecutive columns of C.  `wide` (GemmArgs::c_wide, the same for the whole
 // launch): one aligned store.  Otherwise the row may start at any element: a whole group is still one store (global
@@ -416,9 +417,9 @@ template <class C, int MODE, bool TN, class ARGS = GemmArgs>
 __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(ARGS g)
 {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    constexpr bool BATCH = MODE == MODE_BATCH;
-    constexpr bool FUSED = MODE == MODE_SPLITK_FUSED;
-    constexpr bool SPLITK = MODE == MODE_SPLITK || FUSED;
+    constexpr bool BATCH = MODE == MODE_BATCH, DIRECT = MODE == MODE_DIRECT || MODE == MODE_DIRECT_SPLITK || MODE == MODE_DIRECT_FUSED;
+    constexpr bool FUSED = MODE == MODE_SPLITK_FUSED || MODE == MODE_DIRECT_FUSED;
+    constexpr bool SPLITK = MODE == MODE_SPLITK || MODE == MODE_DIRECT_SPLITK || FUSED;
     constexpr bool STREAMK = MODE == MODE_STREAMK;
     constexpr bool PERSIST = MODE == MODE_PERSIST;
     constexpr bool ACC16 = MODE == MODE_ACC16;
@@ -446,8 +447,8 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(ARGS g)
     }
     asm volatile("" :: "s"(gA), "s"(gB), "s"(gC), "s"(g.M), "s"(g.N), "s"(g.K), "s"(g.lda), "s"(g.ldb), "s"(g.ldc),
                  "s"(g.tiles_m), "s"(g.tiles_n), "s"(g.swizzle), "s"(g.k_per_split), "s"(g.splits));
-    if constexpr (MODE != MODE_PLAIN && !BATCH && !TN) asm volatile("" :: "s"(g.b_rows));
-    if constexpr (MODE != MODE_PLAIN && !BATCH && MODE != MODE_SPLITK) asm volatile("" :: "s"(g.c_wide));
+    if constexpr (MODE != MODE_PLAIN && !BATCH && !DIRECT && !TN) asm volatile("" :: "s"(g.b_rows));
+    if constexpr (MODE != MODE_PLAIN && !BATCH && MODE != MODE_SPLITK && MODE != MODE_DIRECT && MODE != MODE_DIRECT_SPLITK) asm volatile("" :: "s"(g.c_wide));
     asm volatile("" :: "s"(g.by_tiles_n.m), "s"(g.by_tiles_n.l), "s"(g.by_band.m), "s"(g.by_band.l), "s"(g.by_rows.m),
                  "s"(g.by_rows.l), "s"(g.by_last_rows.m), "s"(g.by_last_rows.l));
 
@@ -658,6 +659,77 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(ARGS g)
                 for (int e = 0; e < C::ACC; ++e) acc[tm][tn][e] = (float)(_Float16)acc[tm][tn][e];
     };
 
+    // MODE_DIRECT: operands off the 16-byte grid go through registers, 16 bytes a lane and load (global memory takes those at any
+    // element's address).  Chunk l of a K-tile is the lane's l-th load, the first A_LOADS of A.  A chunk that straddles the end of
+    // its row takes the beginning of the next one with it; none reaches past the last element of an operand: those are
+    // loaded so much earlier, and mend_last_tile puts them right.
+    // What bounds it: the LDS, which takes the operands through the same registers once more than direct copies do, and loads
+    // that touch nine lines instead of eight (16 bytes a lane at odd elements: 1000 x 1001 x 1003, column-major B, 8.6 us; at whole
+    // dwords 7.5; on aligned operands the copies to LDS take 5.9).  It replaces a launch that copies both operands first: 1000 x 1001 x
+    // 1003 11.2 -> 8.6 us, 500 x 501 x 503 7.4 -> 5.3, 70 x 3001 x 1001 11.3 -> 7.0.  Writing and loading between the matrix-core
+    // instructions took a first form, which did both in one go per K-tile, from 10.2 to 8.9 us.
+    typedef unsigned long long chunk16 __attribute__((ext_vector_type(2)));
+    constexpr int BCPR = TN ? C::A_CPR : C::B_CPR;
+    chunk16 staged[DIRECT ? 2 : 1][DIRECT ? C::LOADS : 1];
+    unsigned chunk_at[DIRECT ? C::LOADS : 1], a_lim = 0, b_lim = 0, b_next = 0;   // bytes; where the K-tile loaded next has them
+    const int a_c = threadIdx.x % C::A_CPR, b_c = threadIdx.x % BCPR;
+    auto a_tile_row = [&](int l) { return (l * C::THREADS + (int)threadIdx.x) / C::A_CPR; };
+    auto b_tile_row = [&](int l) { return ((l - C::A_LOADS) * C::THREADS + (int)threadIdx.x) / BCPR; };
+    if constexpr (DIRECT) {
+        a_lim = (unsigned)(((g.M - 1) * g.lda + g.K - 8) * 2);
+        b_lim = (unsigned)(((TN ? (g.N - 1) * g.ldb + g.K : (g.K - 1) * g.ldb + g.N) - 8) * 2);
+        b_next = TN ? C::BK * 2 : (unsigned)(C::BK * g.ldb * 2);
+#pragma unroll
+        for (int l = 0; l < (DIRECT ? C::LOADS : 0); ++l) {
+            const int n = n0 + b_c * 8;
+            if (l < C::A_LOADS) chunk_at[l] = (unsigned)((min(m0 + a_tile_row(l), g.M - 1) * g.lda + k_begin + a_c * 8) * 2);
+            else if (TN) chunk_at[l] = (unsigned)((min(n0 + b_tile_row(l), g.N - 1) * g.ldb + k_begin + b_c * 8) * 2);
+            else chunk_at[l] = (unsigned)(((k_begin + b_tile_row(l)) * g.ldb + (n < g.N ? n : 0)) * 2);
+        }
+    }
+    auto load_chunk = [&](chunk16& v, int l) {
+        if (l < C::A_LOADS) {
+            __builtin_memcpy(&v, (const char*)gA + min(chunk_at[l], a_lim), 16);
+            chunk_at[l] += C::BK * 2;
+        } else {
+            __builtin_memcpy(&v, (const char*)gB + min(chunk_at[l], b_lim), 16);
+            chunk_at[l] += b_next;
+        }
+    };
+    auto chunk_slot = [&](int buf, int l) -> chunk16* {
+        char* sA = lds + buf * C::STAGE_BYTES;
+        if (l < C::A_LOADS) return (chunk16*)(sA + a_tile_row(l) * (C::BK * 2) + ((a_c ^ swz_a<C>(a_tile_row(l))) * 16));
+        const int r = b_tile_row(l);
+        return (chunk16*)(sA + C::A_BYTES + (TN ? r * (C::BK * 2) + ((b_c ^ swz_a<C>(r)) * 16) : r * (C::BN * 2) + ((b_c ^ swz_b<C>(r)) * 16)));
+    };
+    // The last K-tile in LDS, the lane's own chunks of it: zeros behind K, and what was loaded early is shifted down.
+    auto mend_last_tile = [&]() {
+        auto mend = [](chunk16 v, int early, int valid) -> chunk16 {
+            const unsigned d = 16u * (unsigned)early;
+            if (d >= 128u) v = chunk16{0, 0};
+            else if (d >= 64u) v = chunk16{v.y >> (d - 64u), 0};
+            else if (d > 0u) v = chunk16{(v.x >> d) | (v.y << (64u - d)), v.y >> d};
+            if (valid <= 0) v = chunk16{0, 0};
+            else if (valid <= 4) v = chunk16{valid == 4 ? v.x : v.x & ((1ull << (16 * valid)) - 1), 0};
+            else if (valid < 8) v = chunk16{v.x, v.y & ((1ull << (16 * (valid - 4))) - 1)};
+            return v;
+        };
+        const int kl = k_begin + (KT - 1) * C::BK;
+        static_for<C::LOADS>([&](auto l_tag) {
+            constexpr int l = decltype(l_tag)::value;
+            chunk16* p = chunk_slot(1, l);
+            if (l < C::A_LOADS || TN) {
+                const int k = kl + (l < C::A_LOADS ? a_c : b_c) * 8;
+                const bool last_row = l < C::A_LOADS ? m0 + a_tile_row(l) >= g.M - 1 : n0 + b_tile_row(l) >= g.N - 1;
+                if (k + 8 > g.K) *p = mend(*p, last_row ? k + 8 - g.K : 0, g.K - k);
+            } else {
+                const int k = kl + b_tile_row(l), n = n0 + b_c * 8;
+                if (k >= g.K) *p = chunk16{0, 0};
+                else if (k == g.K - 1 && n < g.N && n + 8 > g.N) *p = mend(*p, n + 8 - g.N, 8);
+            }
+        });
+    };
+
     using std::integral_constant;
     // One k-step with a pinned instruction order: matrix-core instruction i is followed by its
     // share of the side work (fragment reads for the k-step PF steps ahead, and after the barrier
@@ -670,7 +742,7 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(ARGS g)
     // (A k-step of more than 32 matrix-core instructions is issued in two halves: one lambda with all of them is too
     // large for the inliner, and a lambda that stays a call reaches the buffer descriptors through memory.)
     auto kstep_part = [&](auto i0_tag, auto i1_tag, auto slot_tag, int rbuf, int rks, auto rslot_tag, auto do_reads_tag, int dma_kt, int dma_buf,
-                          auto dma_lo_tag, auto dma_hi_tag) {
+                          auto dma_lo_tag, auto dma_hi_tag, auto set_tag) {
         constexpr int i0 = decltype(i0_tag)::value, i1 = decltype(i1_tag)::value;
         constexpr int slot = decltype(slot_tag)::value, rslot = decltype(rslot_tag)::value;
         constexpr int dma_lo = decltype(dma_lo_tag)::value, dma_hi = decltype(dma_hi_tag)::value;
@@ -685,17 +757,21 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(ARGS g)
                 constexpr int t = lo + decltype(tt)::value;
                 // fragment reads first (they are needed soonest), then the copies
                 if constexpr (t < nreads) read_one(rbuf, rks, rslot, t);
-                else dma_one(dma_kt, dma_buf, dma_lo + t - nreads);
+                else if constexpr (DIRECT) {
+                    constexpr int l = dma_lo + t - nreads;
+                    *chunk_slot(dma_buf, l) = staged[decltype(set_tag)::value][l];
+                    load_chunk(staged[decltype(set_tag)::value][l], l);
+                } else dma_one(dma_kt, dma_buf, dma_lo + t - nreads);
             });
             __builtin_amdgcn_sched_barrier(0);
         });
     };
-    auto kstep = [&](auto slot, int rbuf, int rks, auto rslot, auto do_reads, int dma_kt, int dma_buf, auto dma_lo, auto dma_hi) {
+    auto kstep = [&](auto slot, int rbuf, int rks, auto rslot, auto do_reads, int dma_kt, int dma_buf, auto dma_lo, auto dma_hi, auto set) {
         if constexpr (NMMA > 32) {
-            kstep_part(ic<0>{}, ic<NMMA / 2>{}, slot, rbuf, rks, rslot, do_reads, dma_kt, dma_buf, dma_lo, dma_hi);
-            kstep_part(ic<NMMA / 2>{}, ic<NMMA>{}, slot, rbuf, rks, rslot, do_reads, dma_kt, dma_buf, dma_lo, dma_hi);
+            kstep_part(ic<0>{}, ic<NMMA / 2>{}, slot, rbuf, rks, rslot, do_reads, dma_kt, dma_buf, dma_lo, dma_hi, set);
+            kstep_part(ic<NMMA / 2>{}, ic<NMMA>{}, slot, rbuf, rks, rslot, do_reads, dma_kt, dma_buf, dma_lo, dma_hi, set);
         } else {
-            kstep_part(ic<0>{}, ic<NMMA>{}, slot, rbuf, rks, rslot, do_reads, dma_kt, dma_buf, dma_lo, dma_hi);
+            kstep_part(ic<0>{}, ic<NMMA>{}, slot, rbuf, rks, rslot, do_reads, dma_kt, dma_buf, dma_lo, dma_hi, set);
         }
     };
 
@@ -706,7 +782,7 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(ARGS g)
     // tile kt+1 (copies issued STAGES-1 tiles earlier) is complete and visible to all waves.
     // WAIT = number of copies that may still be in flight at the barrier; HAS_NEXT = a next tile
     // exists; DMA = K-tile dma_kt (of the copies' tile) is copied into the vacated buffer after the barrier.
-    auto tile_body = [&](int dma_kt, int buf, int nbuf, auto wait_tag, auto has_next_tag, auto dma_tag) {
+    auto tile_body = [&](int dma_kt, int buf, int nbuf, auto wait_tag, auto has_next_tag, auto dma_tag, auto set) {
         constexpr int WAIT = decltype(wait_tag)::value;
         constexpr bool HAS_NEXT = decltype(has_next_tag)::value;
         constexpr bool DMA = decltype(dma_tag)::value;
@@ -714,7 +790,7 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(ARGS g)
             constexpr int ks = decltype(ks_tag)::value;
             constexpr bool after = ks >= C::KS - C::PF;        // this step runs behind the barrier
             if (ks == C::KS - C::PF && HAS_NEXT) {
-                wait_vmcnt<WAIT>();
+                if constexpr (!DIRECT) wait_vmcnt<WAIT>();
                 asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
             }
             constexpr int t = ks + C::PF;
@@ -723,7 +799,7 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(ARGS g)
             constexpr int dlo = (DMA && after) ? (j * C::LOADS) / C::PF : 0;
             constexpr int dhi = (DMA && after) ? ((j + 1) * C::LOADS) / C::PF : 0;
             kstep(ic<ks % C::NSLOT>{}, in_next ? nbuf : buf, in_next ? t - C::KS : t, ic<t % C::NSLOT>{},
-                  std::bool_constant<(in_next ? HAS_NEXT : true)>{}, dma_kt, buf, ic<dlo>{}, ic<dhi>{});
+                  std::bool_constant<(in_next ? HAS_NEXT : true)>{}, dma_kt, buf, ic<dlo>{}, ic<dhi>{}, set);
             if (ACC16) {
                 round_accumulators();
                 __builtin_amdgcn_sched_barrier(0);
@@ -734,7 +810,7 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(ARGS g)
     // ---- main loop ----------------------------------------------------------
     int buf = 0;                      // LDS buffer of the K-tile being multiplied
     bool has_next = false;            // persistent mode: this workgroup has another tile after this one
-    if (!DEEP && KT > 0) {
+    if (!DEEP && !DIRECT && KT > 0) {
 #pragma unroll
         for (int s = 0; s < C::STAGES; ++s)
             if (s < KT) load_tile(s, s);
@@ -752,7 +828,30 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(ARGS g)
         for (int j = 0; j < C::TN; ++j)
 #pragma unroll
             for (int v = 0; v < C::ACC; ++v) acc[i][j][v] = 0.f;
-    if constexpr (DEEP) {
+    if constexpr (DIRECT) {
+        // K-tile t lives in LDS buffer t % 2.  While K-tile kt is multiplied, behind its barrier, K-tile kt + 2 is written
+        // from registers into the buffer that kt has left, and those registers are loaded with K-tile kt + 4.  An odd number
+        // of K-tiles starts with one of zeros: the loop then has one way out, in front of the last two (with a way out between
+        // the two of a pass, the compiler waits for more loads than it has to).
+        const int KT2 = (KT + 1) & ~1;
+        chunk16 first[2][C::LOADS];
+        static_for<C::LOADS>([&](auto l) { first[0][l] = chunk16{0, 0}; });
+        if (KT == KT2) static_for<C::LOADS>([&](auto l) { load_chunk(first[0][l], l); });
+        static_for<C::LOADS>([&](auto l) { load_chunk(first[1][l], l); });
+        static_for<2>([&](auto u) { static_for<C::LOADS>([&](auto l) { load_chunk(staged[u][l], l); }); });
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<2>([&](auto u) { static_for<C::LOADS>([&](auto l) { *chunk_slot(u, l) = first[u][l]; }); });
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        static_for<C::PF>([&](auto ks) { read_frags(0, ks, ks); });
+        __builtin_amdgcn_sched_barrier(0);
+        for (int kt = 2; kt < KT2; kt += 2) {
+            tile_body(0, 0, 1, ic<0>{}, std::true_type{}, std::true_type{}, ic<0>{});
+            tile_body(0, 1, 0, ic<0>{}, std::true_type{}, std::true_type{}, ic<1>{});
+        }
+        mend_last_tile();
+        tile_body(0, 0, 1, ic<0>{}, std::true_type{}, std::false_type{}, ic<0>{});
+        tile_body(0, 1, 0, ic<0>{}, std::false_type{}, std::false_type{}, ic<0>{});
+    } else if constexpr (DEEP) {
         // Deep-staged main loop.  The reads lead the matrix cores by three k-steps; "the read tile" is the K-tile
         // the reads are in.  When the reads move on to the next K-tile: that tile must have landed (all copies but
         // those of the STAGES - 2 younger tiles), every wave must be done reading the tile they leave (its buffer
@@ -783,9 +882,9 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(ARGS g)
         const int KT2 = (KT + 1) & ~1;
         for (int t2 = 0; t2 < KT2; t2 += 2) {
             enter_next_tile();
-            kstep(ic<0>{}, rb, 0, ic<1>{}, std::true_type{}, dkt, dbuf, ic<0>{}, ic<L>{});
+            kstep(ic<0>{}, rb, 0, ic<1>{}, std::true_type{}, dkt, dbuf, ic<0>{}, ic<L>{}, ic<0>{});
             enter_next_tile();
-            kstep(ic<1>{}, rb, 0, ic<0>{}, std::true_type{}, dkt, dbuf, ic<0>{}, ic<L>{});
+            kstep(ic<1>{}, rb, 0, ic<0>{}, std::true_type{}, dkt, dbuf, ic<0>{}, ic<L>{}, ic<0>{});
         }
         wait_vmcnt<0>();                     // copies still in flight would land in the epilogue's staging area
       } else {
@@ -799,12 +898,12 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(ARGS g)
         // One pass = two K-tiles = four k-steps; k-step u multiplies fragment set u and reads the k-step three
         // ahead into set (u + 3) % 4.  A refill is issued in two halves: behind the barrier, and in the k-step after.
         for (int t2 = 0; t2 < KT2; t2 += 2) {
-            kstep(ic<0>{}, rb, 1, ic<3>{}, std::true_type{}, dkt, dbuf, ic<L / 2>{}, ic<L>{});
+            kstep(ic<0>{}, rb, 1, ic<3>{}, std::true_type{}, dkt, dbuf, ic<L / 2>{}, ic<L>{}, ic<0>{});
             enter_next_tile();
-            kstep(ic<1>{}, rb, 0, ic<0>{}, std::true_type{}, dkt, dbuf, ic<0>{}, ic<L / 2>{});
-            kstep(ic<2>{}, rb, 1, ic<1>{}, std::true_type{}, dkt, dbuf, ic<L / 2>{}, ic<L>{});
+            kstep(ic<1>{}, rb, 0, ic<0>{}, std::true_type{}, dkt, dbuf, ic<0>{}, ic<L / 2>{}, ic<0>{});
+            kstep(ic<2>{}, rb, 1, ic<1>{}, std::true_type{}, dkt, dbuf, ic<L / 2>{}, ic<L>{}, ic<0>{});
             enter_next_tile();
-            kstep(ic<3>{}, rb, 0, ic<2>{}, std::true_type{}, dkt, dbuf, ic<0>{}, ic<L / 2>{});
+            kstep(ic<3>{}, rb, 0, ic<2>{}, std::true_type{}, dkt, dbuf, ic<0>{}, ic<L / 2>{}, ic<0>{});
         }
         wait_vmcnt<0>();                     // copies still in flight would land in the epilogue's staging area
       }
@@ -823,7 +922,7 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(ARGS g)
                 const int nbuf = (buf + 1 == C::STAGES) ? 0 : buf + 1;
                 if (kt + C::STAGES == KT) set_load_tile(has_next ? tile_id + (int)gridDim.x : -1);
                 tile_body(kt + C::STAGES < KT ? kt + C::STAGES : kt + C::STAGES - KT, buf, nbuf, integral_constant<int, STEADY>{},
-                          integral_constant<bool, true>{}, integral_constant<bool, true>{});
+                          integral_constant<bool, true>{}, integral_constant<bool, true>{}, ic<0>{});
                 buf = nbuf;
             }
         } else {
@@ -831,18 +930,18 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(ARGS g)
             for (; kt + C::STAGES < KT; ++kt) {
                 const int nbuf = (buf + 1 == C::STAGES) ? 0 : buf + 1;
                 tile_body(kt + C::STAGES, buf, nbuf, integral_constant<int, STEADY>{}, integral_constant<bool, true>{},
-                          integral_constant<bool, true>{});
+                          integral_constant<bool, true>{}, ic<0>{});
                 buf = nbuf;
             }
             // drain: no more copies to issue
             for (; kt + 1 < KT; ++kt) {
                 const int nbuf = (buf + 1 == C::STAGES) ? 0 : buf + 1;
-                tile_body(0, buf, nbuf, integral_constant<int, 0>{}, integral_constant<bool, true>{}, integral_constant<bool, false>{});
+                tile_body(0, buf, nbuf, integral_constant<int, 0>{}, integral_constant<bool, true>{}, integral_constant<bool, false>{}, ic<0>{});
                 buf = nbuf;
             }
         }
         // last K-tile: nothing more to copy or to read ahead (persistent mode: the epilogue stages in its buffer)
-        tile_body(0, buf, buf, integral_constant<int, 0>{}, integral_constant<bool, false>{}, integral_constant<bool, false>{});
+        tile_body(0, buf, buf, integral_constant<int, 0>{}, integral_constant<bool, false>{}, integral_constant<bool, false>{}, ic<0>{});
     }
 
     // ---- epilogue ------------------------------------------------------------
@@ -860,7 +959,7 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(ARGS g)
         constexpr int CPR = C::WTN / 8;           // 16-byte chunks per slab row
         // persistent mode: only the buffer of the last K-tile is free (the others hold the next tile's first K-tiles)
         char* stage = lds + (PERSIST ? buf * C::STAGE_BYTES : 0) + wave * (MI * ROWB);
-        static_assert(C::NWAVES * MI * ROWB <= C::LDS_BYTES, "epilogue staging must fit in the operand buffers");
+        static_assert(C::NWAVES * MI * ROWB <= (DIRECT ? 2 * C::STAGE_BYTES : C::LDS_BYTES), "epilogue staging must fit in the operand buffers");
         static_assert(MI * CPR >= 64, "a slab holds at least one 16-byte chunk per lane");
 #pragma unroll
         for (int tm = 0; tm < C::TM; ++tm) {
@@ -906,7 +1005,7 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(ARGS g)
                     }
                 };
                 // two loops, the one for narrow rows kept small: short kernels pay for the code they fetch
-                if (MODE != MODE_PLAIN_ANY && __builtin_expect(g.c_wide != 0, 1)) {
+                if (MODE != MODE_PLAIN_ANY && !DIRECT && __builtin_expect(g.c_wide != 0, 1)) {
 #pragma unroll
                     for (int j = 0; j < (MI * CPR) / 64; ++j) store_chunk(j, true);
                 } else {

@@ -34,6 +34,14 @@ struct MfmaEntry {
     void (*phased_splitk)(GemmArgs) = nullptr;
     void (*phased_splitk_tn)(GemmArgs) = nullptr;
     int phased_lds = 0;
+    // operands at any element, read through registers (null where there is none): plain, two-launch and fused split-K
+    void (*direct)(GemmArgs) = nullptr;
+    void (*direct_tn)(GemmArgs) = nullptr;
+    void (*direct_splitk)(GemmArgs) = nullptr;
+    void (*direct_splitk_tn)(GemmArgs) = nullptr;
+    void (*direct_fused)(GemmArgs) = nullptr;
+    void (*direct_fused_tn)(GemmArgs) = nullptr;
+    int direct_lds = 0;
     // several problems in one launch (null where there is none)
     void (*batch)(BatchArgs) = nullptr;
     void (*batch_tn)(BatchArgs) = nullptr;
@@ -52,6 +60,15 @@ template <class C> constexpr bool has_batch()
 {
     return false
 #define HGEMM_BATCH(bm, bn, bk, wm, wn, st, pf) \
+    || (C::BM == bm && C::BN == bn && C::BK == bk && C::WAVES_M == wm && C::WAVES_N == wn && C::STAGES == st && C::PF == pf && C::MI == 32)
+#include "hgemm_configs.inc"
+        ;
+}
+
+template <class C> constexpr bool has_direct()
+{
+    return false
+#define HGEMM_DIRECT(bm, bn, bk, wm, wn, st, pf) \
     || (C::BM == bm && C::BN == bn && C::BK == bk && C::WAVES_M == wm && C::WAVES_N == wn && C::STAGES == st && C::PF == pf && C::MI == 32)
 #include "hgemm_configs.inc"
         ;
@@ -100,6 +117,15 @@ template <class C> inline MfmaEntry make_entry()
             e.phased_splitk = phased_gemm_kernel<P, true, false>;
             e.phased_splitk_tn = phased_gemm_kernel<P, true, true>;
             e.phased_lds = P::LDS_BYTES;
+        }
+        if constexpr (has_direct<C>()) {
+            e.direct = mfma_gemm_kernel<C, MODE_DIRECT, false>;
+            e.direct_tn = mfma_gemm_kernel<C, MODE_DIRECT, true>;
+            e.direct_splitk = mfma_gemm_kernel<C, MODE_DIRECT_SPLITK, false>;
+            e.direct_splitk_tn = mfma_gemm_kernel<C, MODE_DIRECT_SPLITK, true>;
+            e.direct_fused = mfma_gemm_kernel<C, MODE_DIRECT_FUSED, false>;
+            e.direct_fused_tn = mfma_gemm_kernel<C, MODE_DIRECT_FUSED, true>;
+            e.direct_lds = 2 * C::STAGE_BYTES;
         }
         if constexpr (has_batch<C>()) {
             e.batch = mfma_gemm_kernel<C, MODE_BATCH, false, BatchArgs>;

@@ -154,3 +154,29 @@ def test_which_plans_share_launches():
     assert sum(many(batch_sets(3, 64, 64, 16384), 64, 64, 16384)[1]) >= 3             # split: two launches or fused, one call each
     assert max(many(batch_sets(3, 64, 64, 16384), 64, 64, 16384)[1]) == 1
     assert max(many(batch_sets(3, 200, 201, 203), 200, 201, 203)[1]) == 1
+
+
+@pytest.mark.parametrize("m,n,k,tn,launches", [(1000, 1001, 1003, False, 1), (500, 501, 503, True, 1), (70, 3001, 1001, False, 1), (264, 328, 200, False, 1), (90, 71, 4101, False, 2),
+                                               (700, 71, 3301, True, 2)])
+def test_small_problems_off_the_grid_are_read_where_they_lie(m, n, k, tn, launches):
+    """No copies: one launch (a split in planes: two), no workspace but for planes, whatever the bases; the static entry point launches the same."""
+    from fake_hip import BASE
+    pads = {"lda": k + 1, "ldb": (k if tn else n) + 3} if (m, n, k) == (264, 328, 200) else {}
+    plain, off = ask([{"M": m, "N": n, "K": k, "tn": tn, **pads}, {"M": m, "N": n, "K": k, "tn": tn, "A": BASE + 2, "B": BASE + 6, "C": BASE + 2, **pads}])
+    names = [name for name, *_ in kernels(plain["run_log"])]
+    assert ",di=1" in plain["describe"] and plain["describe"].endswith("pad=1") and len(names) == launches and names[0] == "mfma_gemm_kernel", plain
+    assert "sk=1," in plain["describe"] and plain["workspace"] == 0 or "sk=1," not in plain["describe"] and plain["workspace"] > 0
+    assert off["run_log"] == plain["run_log"] and plain["static"] == 0 and plain["static_log"] == plain["run_log"]
+
+
+def test_what_the_static_entry_point_refuses_stays_refused():
+    """Problems whose padded copies exceed the scratch are refused, also where the kernels that read them in place would need none."""
+    thin = {"M": 40, "N": 190001, "K": 201, "tn": True}
+    (r,) = ask([thin])
+    assert r["plan"] == 0 and r["static"] == 6, r
+
+
+@pytest.mark.parametrize("m,n,k,tn", [(4100, 4101, 4103, False), (2216, 1408, 419, False), (3463, 79, 5896, True), (16, 50257, 4096, False), (16, 50257, 4096, True)])
+def test_problems_off_the_grid_that_keep_their_copies_streams_and_phased_kernels(m, n, k, tn):
+    (r,) = ask([{"M": m, "N": n, "K": k, "tn": tn}])
+    assert r["run"] == 0 and ",di=1" not in r["describe"], r
