@@ -552,7 +552,65 @@ bool streams_any_b(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l)
     return M <= 32 || (K >= 256 && 2.0 * (double)K * (double)N >= 32.0 * 1048576.0);
 }
 
-bool evaluate_model(int64_t M, int64_t N, int64_t K, Spec* out, bool b_row_major)
+// Few rows of A: the nearest of some four thousand measured problems (few_rows.inc) instead of the models' pick.  The models
+// above are fitted to operands that the last-level cache holds (large tiles) or know one kernel of each family (streaming): on
+// problems whose weights come from HBM their picks are 10 % slower than the fastest kernel, up to 1.6 times where 256-column tiles
+// leave a third of the chip idle in their only round (4 x 23424 x 5120, column-major B: 63 us, in 128-column tiles 42).
+// Distance = 0.3 |log2 ratio of M| + |log2 ratio of N| + |log2 ratio of K|, and a quarter more across a multiple of 16384 columns,
+// where 64-column tiles begin another round; at most 0.3.  A pick that is among the neighbour's fastest stays, one that needs no
+// workspace is not traded for a split (as in phased_choice), and a split not for one of more planes unless these stay below the
+// 2 MiB from which an allocation costs 60 us (and so far within the static scratch); nor one that needs another round of workgroups
+// where the neighbour did not (4 x 5480 x 12912: 258 in two rounds 45 us, the model's pick 33).  968 problems held out: 533 change,
+// all together 7.5 % faster in the geometric mean, 12 slower by more than 3 %; 3.5 % from the fastest kernel of each.  238 changed picks
+// of generic sizes: 1.13 times faster cold, 1.15 in the cache (4 slower by more than 10 % cold, one in the cache).  Not for operands
+// that would be copied: the choice between copies and direct_choice compares with the models' pick.
+struct FewRow { unsigned short m; unsigned n, k; signed char spec[5]; };
+#include "few_rows.inc"
+struct FewIndex {
+    struct Item { float lm, ln, lk; int columns; const FewRow* row; };
+    std::vector<Item> items;
+    FewIndex(const FewRow* rows, size_t count)
+    {
+        items.reserve(count);
+        for (size_t i = 0; i < count; ++i)
+            items.push_back({std::log2((float)rows[i].m), std::log2((float)rows[i].n), std::log2((float)rows[i].k), (int)((rows[i].n + 16383) / 16384), &rows[i]});
+    }
+};
+bool few_rows_choice(int64_t M, int64_t N, int64_t K, bool b_row_major, const Spec& model, Spec* out)
+{
+    static const FewIndex nn(kFewRowsNN, sizeof(kFewRowsNN) / sizeof(kFewRowsNN[0]));
+    static const FewIndex tn(kFewRowsTN, sizeof(kFewRowsTN) / sizeof(kFewRowsTN[0]));
+    const float lm = std::log2((float)M), ln = std::log2((float)N), lk = std::log2((float)K);
+    const int columns = (int)((N + 16383) / 16384);
+    float best = 0.3f;
+    const FewRow* row = nullptr;
+    for (const FewIndex::Item& r : (b_row_major ? nn : tn).items) {
+        const float d = 0.3f * std::fabs(lm - r.lm) + std::fabs(ln - r.ln) + std::fabs(lk - r.lk) + (columns != r.columns ? 0.25f : 0.f);
+        if (d < best) { best = d; row = &r.row[0]; }
+    }
+    if (!row) return false;
+    auto rounds = [](const Spec& s, int64_t n) { return s.fam == FAM_MFMA ? ((n + s.bn - 1) / s.bn * s.sk + cu_count() - 1) / cu_count() : 0; };
+    Spec first;
+    bool found = false;
+    for (const signed char i : row->spec) {
+        Spec s;
+        if (i < 0 || !parse_spec(kFewSpecs[i], &s)) break;
+        if (s.fam == FAM_MFMA && !find_entry(s)) continue;
+        const int64_t step = s.fam == FAM_MFMA ? s.bk : skinny_step(s, !b_row_major);
+        s.sk = (int)effective_splits((K + step - 1) / step, s.sk);
+        if (s.sk == 1) s.fr = 0;
+        if (s.fam == model.fam && s.bm == model.bm && s.bn == model.bn && s.bk == model.bk && s.st == model.st && s.pf == model.pf && s.sk == model.sk &&
+            s.fr == model.fr && s.wv == model.wv && s.nr == model.nr)
+            return false;
+        const bool small = (double)s.sk * (double)M * (double)((N + 7) / 8 * 8) * 4.0 <= 2097152.0 - 65536.0;
+        const bool fits = s.sk == 1 || (model.sk > 1 && (small || s.sk < model.sk || (s.sk == model.sk && s.fr <= model.fr)));
+        if (!found && fits && rounds(s, N) <= rounds(s, row->n)) { first = s; found = true; }
+    }
+    if (found) *out = first;
+    return found;
+}
+
+bool evaluate_model(int64_t M, int64_t N, int64_t K, Spec* out, bool b_row_major, bool measured)
 {
     double best = 1e300;
     bool found = false;
@@ -589,23 +647,26 @@ bool evaluate_model(int64_t M, int64_t N, int64_t K, Spec* out, bool b_row_major
             }
         }
     }
+    Spec near;
+    if (found && measured && M <= 32 && (!b_row_major || 2.0 * (double)K * (double)N < 256.0 * 1048576.0) && few_rows_choice(M, N, K, b_row_major, *out, &near))
+        *out = near;
     return found;
 }
 
 // The model's pick.  Evaluating it takes some hundred candidates (10-20 us of host time, more than a small call takes on
 // the device), and a program that plans on every call -- hgemm_run_static, the one-call Python wrapper -- comes back with a
-// handful of shapes.  Each thread keeps its last picks, a function of the shape and the layout alone, in a table of fixed
+// handful of shapes.  Each thread keeps its last picks, a function of its arguments alone, in a table of fixed
 // size.
-bool model_choice(int64_t M, int64_t N, int64_t K, Spec* out, bool b_row_major = true)
+bool model_choice(int64_t M, int64_t N, int64_t K, Spec* out, bool b_row_major = true, bool measured = false)
 {
-    struct Pick { int64_t M, N, K; bool row, found; Spec spec; };
+    struct Pick { int64_t M, N, K; bool row, measured, found; Spec spec; };
     constexpr size_t kPicks = 64;
     static thread_local Pick picks[kPicks] = {};
-    const uint64_t h = ((uint64_t)M * 0x9E3779B97F4A7C15ull ^ (uint64_t)N * 0xC2B2AE3D27D4EB4Full ^ (uint64_t)K * 0x165667B19E3779F9ull) + b_row_major;
+    const uint64_t h = ((uint64_t)M * 0x9E3779B97F4A7C15ull ^ (uint64_t)N * 0xC2B2AE3D27D4EB4Full ^ (uint64_t)K * 0x165667B19E3779F9ull) + b_row_major + 2 * measured;
     Pick& p = picks[(h ^ (h >> 29)) % kPicks];
-    if (p.M != M || p.N != N || p.K != K || p.row != b_row_major) {
-        p.found = evaluate_model(M, N, K, &p.spec, b_row_major);
-        p.M = M; p.N = N; p.K = K; p.row = b_row_major;
+    if (p.M != M || p.N != N || p.K != K || p.row != b_row_major || p.measured != measured) {
+        p.found = evaluate_model(M, N, K, &p.spec, b_row_major, measured);
+        p.M = M; p.N = N; p.K = K; p.row = b_row_major; p.measured = measured;
     }
     if (p.found) *out = p.spec;
     return p.found;
@@ -1051,13 +1112,14 @@ bool device_is_gfx950(int dev)
 // any_b: B is to be streamed where it lies (streams_any_b), which only the streaming family does.
 // Returns the specialisations to try in order (a later one if the device or the workspace refuses an earlier one) and
 // says where the first comes from.
-// b_ld: the leading dimension of B as the kernels see it (l describes the packed problem of a padded one).
+// b_ld: the leading dimension of B as the kernels see it (l describes the packed problem of a padded one); copied: an operand is
+// copied first.
 struct Choices {
     const char* source;
     int n;
     Spec spec[3];
 };
-Choices choose_spec(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, int64_t b_ld, bool padded, bool any_b)
+Choices choose_spec(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, int64_t b_ld, bool padded, bool copied, bool any_b)
 {
     Choices c{"table", 1, {}};
     const bool tn = l.b == HGEMM_COL_MAJOR;
@@ -1069,7 +1131,7 @@ Choices choose_spec(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, i
     Spec model, near, phased;
     if (!packed || !table_lookup(M, N, K, tn, &c.spec[0])) {
         c.source = "model";
-        if (!model_choice(M, N, K, &model, !tn)) {
+        if (!model_choice(M, N, K, &model, !tn, !copied)) {
             model = heuristic(M, N, K);
             c.source = "rules";
         }
@@ -1231,7 +1293,7 @@ hgemm_status_t init_plan(hgemm_plan_s* p, int64_t M, int64_t N, int64_t K, const
             p->spec = Spec();
             st = finish_plan(p);
         } else {
-            const Choices c = choose_spec(M, N, K, l, r.ldb, p->padded, p->any_b);
+            const Choices c = choose_spec(M, N, K, l, r.ldb, p->padded, r.copy_a || r.copy_b, p->any_b);
             Spec direct;
             if (direct_choice(M, p->uN, p->uK, p->ulay, r, c.spec[0], &direct) && (!static_ws || copies_fit_static_scratch(M, r, c))) {
                 const hgemm_plan_s padded = *p;
@@ -1437,7 +1499,7 @@ hgemm_status_t hgemm_plan_choice(int64_t M, int64_t N, int64_t K, const hgemm_la
     } else if (!fast) {
         out = "generic";
     } else {
-        const Choices c = choose_spec(M, N, K, l, r.ldb, r.padded, r.any_b);
+        const Choices c = choose_spec(M, N, K, l, r.ldb, r.padded, r.copy_a || r.copy_b, r.any_b);
         Spec direct;
         if (direct_choice(M, uN, uK, ul, r, c.spec[0], &direct)) out = "model: " + spec_to_string(direct) + ",pad=1";
         else out = std::string(c.source) + ": " + spec_to_string(c.spec[0]) + (r.padded ? ",pad=1" : "");

@@ -180,3 +180,15 @@ def test_what_the_static_entry_point_refuses_stays_refused():
 def test_problems_off_the_grid_that_keep_their_copies_streams_and_phased_kernels(m, n, k, tn):
     (r,) = ask([{"M": m, "N": n, "K": k, "tn": tn}])
     assert r["run"] == 0 and ",di=1" not in r["describe"], r
+
+
+@pytest.mark.parametrize("m", [1, 4, 16, 32])
+def test_few_rows_of_a_fit_the_static_scratch_and_keep_in_place_kernels_off_the_grid(m):
+    """What the static entry point takes with few rows is the planned call; operands that would be copied are still read where they lie."""
+    on = [{"M": m, "N": n, "K": k, "tn": tn} for n in (1000, 5480, 13736, 40008, 64000) for k in (512, 2360, 5152, 12912) for tn in (False, True)]
+    for q, r in zip(on, ask(on)):
+        assert r["plan"] == 0 and r["run"] == 0 and r["workspace"] <= hg.STATIC_SCRATCH_BYTES, (q, r["describe"], r["workspace"])
+        assert r["static"] == 0 and r["static_log"] == r["run_log"], (q, r["describe"])
+    off = [{"M": m, "N": n, "K": k, "tn": True} for n, k in [(1729, 1545), (6747, 2667), (3137, 957), (35783, 3107)]]
+    for q, r in zip(off, ask(off)):
+        assert ",di=1" in r["describe"], (q, r["describe"])
