@@ -39,6 +39,7 @@ static const std::vector<MfmaEntry>& registry()
 
 void (*skinny_kernel(int mb, bool fused, int waves, int tn_rows))(GemmArgs);      // hgemm_skinny.hip
 void (*skinny_any_b_kernel(int mb, bool fused))(GemmArgs);
+void (*skinny_strips(int mb, int64_t K))(GemmArgs);
 
 constexpr int64_t kSkinnyMaxM = 64;
 
@@ -60,6 +61,7 @@ struct Spec {
     int di = 0;     // 1 = operands read through registers, at any element's address (MODE_DIRECT)
     int wv = 4;     // skinny family: waves per workgroup (4, 8 or 16), each taking 16 k-rows of a step
     int nr = 16;    // skinny family, column-major B: rows of B (columns of C) per workgroup (16, 32 or 64)
+    int ra = 0;     // skinny family, column-major B: 1 = A resident in registers, one workgroup per compute unit walks strips of B
 };
 
 // k-rows a workgroup of the skinny family takes per step (K slabs are whole numbers of steps) and the columns of C
@@ -75,6 +77,7 @@ static std::string spec_to_string(const Spec& s)
         snprintf(buf, sizeof buf, "skinny,sk=%d%s", s.sk, s.fr ? ",fr=1" : "");
         if (s.wv != 4) snprintf(buf + strlen(buf), sizeof buf - strlen(buf), ",wv=%d", s.wv);
         if (s.nr != 16) snprintf(buf + strlen(buf), sizeof buf - strlen(buf), ",nr=%d", s.nr);
+        if (s.ra) snprintf(buf + strlen(buf), sizeof buf - strlen(buf), ",ra=1");
         return buf;
     }
     snprintf(buf, sizeof buf, "mfma,bm=%d,bn=%d,bk=%d,wm=%d,wn=%d,st=%d,pf=%d,sk=%d,gm=%d%s", s.bm, s.bn, s.bk, s.wm, s.wn,
@@ -109,7 +112,7 @@ static bool parse_spec(const char* text, Spec* out)
     const struct { char key[4]; int* value; } keys[] = {
         {"bm", &sp.bm}, {"bn", &sp.bn}, {"bk", &sp.bk}, {"wm", &sp.wm}, {"wn", &sp.wn}, {"st", &sp.st}, {"pf", &sp.pf}, {"sk", &sp.sk},
         {"gm", &sp.gm}, {"tb", &sp.tb}, {"sm", &sp.sm}, {"fr", &sp.fr}, {"ps", &sp.ps}, {"ac", &sp.ac}, {"mi", &sp.mi}, {"ph", &sp.ph},
-        {"di", &sp.di}, {"wv", &sp.wv}, {"nr", &sp.nr},
+        {"di", &sp.di}, {"wv", &sp.wv}, {"nr", &sp.nr}, {"ra", &sp.ra},
         {"pad", &ignored},      // reported by hgemm_plan_describe; padding follows from the shape, not from the spec
     };
     while (*p) {
@@ -136,6 +139,7 @@ static bool parse_spec(const char* text, Spec* out)
     if (sp.di > 1 || (sp.di && (sp.fam != FAM_MFMA || sp.sm || sp.ps || sp.tb || sp.ph || sp.ac == 16 || sp.mi != 32))) return false;
     if ((sp.wv != 4 && sp.wv != 8 && sp.wv != 16) || (sp.wv != 4 && sp.fam != FAM_SKINNY)) return false;
     if ((sp.nr != 16 && sp.nr != 32 && sp.nr != 64) || (sp.nr != 16 && sp.fam != FAM_SKINNY)) return false;
+    if (sp.ra > 1 || (sp.ra && (sp.fam != FAM_SKINNY || sp.wv != kStripWaves || sp.nr != 16 || sp.sk > 1))) return false;
     *out = sp;
     return true;
 }
@@ -554,16 +558,17 @@ bool streams_any_b(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l)
 
 // Few rows of A: the nearest of some four thousand measured problems (few_rows.inc) instead of the models' pick.  The models
 // above are fitted to operands that the last-level cache holds (large tiles) or know one kernel of each family (streaming): on
-// problems whose weights come from HBM their picks are 10 % slower than the fastest kernel, up to 1.6 times where 256-column tiles
+// problems whose weights come from HBM their picks are 12 % slower than the fastest kernel, up to 1.6 times where 256-column tiles
 // leave a third of the chip idle in their only round (4 x 23424 x 5120, column-major B: 63 us, in 128-column tiles 42).
-// Distance = 0.3 |log2 ratio of M| + |log2 ratio of N| + |log2 ratio of K|, and a quarter more across a multiple of 16384 columns,
-// where 64-column tiles begin another round; at most 0.3.  A pick that is among the neighbour's fastest stays, one that needs no
+// Distance = 0.3 |log2 ratio of M| + |log2 ratio of N| + |log2 ratio of K|, and a quarter more across 16384 and 32768 columns, where
+// 64-column tiles begin another round; at most 0.3.  A pick that is among the neighbour's fastest stays, one that needs no
 // workspace is not traded for a split (as in phased_choice), and a split not for one of more planes unless these stay below the
-// 2 MiB from which an allocation costs 60 us (and so far within the static scratch); nor one that needs another round of workgroups
-// where the neighbour did not (4 x 5480 x 12912: 258 in two rounds 45 us, the model's pick 33).  968 problems held out: 533 change,
-// all together 7.5 % faster in the geometric mean, 12 slower by more than 3 %; 3.5 % from the fastest kernel of each.  238 changed picks
-// of generic sizes: 1.13 times faster cold, 1.15 in the cache (4 slower by more than 10 % cold, one in the cache).  Not for operands
-// that would be copied: the choice between copies and direct_choice compares with the models' pick.
+// 2 MiB from which an allocation costs 60 us (and so far within the static scratch); nor one that needs more rounds of workgroups
+// than the neighbour did, other than by its more columns (4 x 5480 x 12912: 258 in two rounds 45 us, the model's pick 33).
+// 976 problems held out: 594 change, all together 8.9 % faster in the geometric mean (column-major B 12.7 %), 12 slower by more than
+// 3 %; 3.1 % from the fastest kernel of each.  The strips of resident A stand in rows of K >= 1200 only: on a shorter K they win less
+// than 5 % cold and lose as much from the cache (1 x 18352 x 808: 10.3 -> 8.2 us cold, 4.9 -> 6.3 warm).
+// Not for operands that would be copied: the choice between copies and direct_choice compares with the models' pick.
 struct FewRow { unsigned short m; unsigned n, k; signed char spec[5]; };
 #include "few_rows.inc"
 struct FewIndex {
@@ -573,7 +578,7 @@ struct FewIndex {
     {
         items.reserve(count);
         for (size_t i = 0; i < count; ++i)
-            items.push_back({std::log2((float)rows[i].m), std::log2((float)rows[i].n), std::log2((float)rows[i].k), (int)((rows[i].n + 16383) / 16384), &rows[i]});
+            items.push_back({std::log2((float)rows[i].m), std::log2((float)rows[i].n), std::log2((float)rows[i].k), std::min(3, (int)((rows[i].n + 16383) / 16384)), &rows[i]});
     }
 };
 bool few_rows_choice(int64_t M, int64_t N, int64_t K, bool b_row_major, const Spec& model, Spec* out)
@@ -581,7 +586,7 @@ bool few_rows_choice(int64_t M, int64_t N, int64_t K, bool b_row_major, const Sp
     static const FewIndex nn(kFewRowsNN, sizeof(kFewRowsNN) / sizeof(kFewRowsNN[0]));
     static const FewIndex tn(kFewRowsTN, sizeof(kFewRowsTN) / sizeof(kFewRowsTN[0]));
     const float lm = std::log2((float)M), ln = std::log2((float)N), lk = std::log2((float)K);
-    const int columns = (int)((N + 16383) / 16384);
+    const int columns = (int)std::min<int64_t>(3, (N + 16383) / 16384);
     float best = 0.3f;
     const FewRow* row = nullptr;
     for (const FewIndex::Item& r : (b_row_major ? nn : tn).items) {
@@ -589,22 +594,27 @@ bool few_rows_choice(int64_t M, int64_t N, int64_t K, bool b_row_major, const Sp
         if (d < best) { best = d; row = &r.row[0]; }
     }
     if (!row) return false;
-    auto rounds = [](const Spec& s, int64_t n) { return s.fam == FAM_MFMA ? ((n + s.bn - 1) / s.bn * s.sk + cu_count() - 1) / cu_count() : 0; };
+    auto rounds = [](const Spec& s, int64_t n) {
+        const int64_t cus = cu_count();
+        if (s.fam != FAM_MFMA) return s.ra ? ((n + 15) / 16 + cus - 1) / cus : 0;
+        return ((n + s.bn - 1) / s.bn * s.sk + cus - 1) / cus;
+    };
     Spec first;
     bool found = false;
     for (const signed char i : row->spec) {
         Spec s;
         if (i < 0 || !parse_spec(kFewSpecs[i], &s)) break;
-        if (s.fam == FAM_MFMA && !find_entry(s)) continue;
+        if (s.fam == FAM_MFMA ? !find_entry(s) : s.ra && !skinny_strips(M <= 16 ? 1 : 2, K)) continue;
         const int64_t step = s.fam == FAM_MFMA ? s.bk : skinny_step(s, !b_row_major);
         s.sk = (int)effective_splits((K + step - 1) / step, s.sk);
         if (s.sk == 1) s.fr = 0;
         if (s.fam == model.fam && s.bm == model.bm && s.bn == model.bn && s.bk == model.bk && s.st == model.st && s.pf == model.pf && s.sk == model.sk &&
-            s.fr == model.fr && s.wv == model.wv && s.nr == model.nr)
+            s.fr == model.fr && s.wv == model.wv && s.nr == model.nr && s.ra == model.ra)
             return false;
         const bool small = (double)s.sk * (double)M * (double)((N + 7) / 8 * 8) * 4.0 <= 2097152.0 - 65536.0;
         const bool fits = s.sk == 1 || (model.sk > 1 && (small || s.sk < model.sk || (s.sk == model.sk && s.fr <= model.fr)));
-        if (!found && fits && rounds(s, N) <= rounds(s, row->n)) { first = s; found = true; }
+        const int64_t here = rounds(s, N), there = rounds(s, row->n);
+        if (!found && fits && (here <= there || 20 * here * row->n <= 21 * there * N)) { first = s; found = true; }
     }
     if (found) *out = first;
     return found;
@@ -853,16 +863,18 @@ hgemm_status_t finish_plan(hgemm_plan_s* p)
         if (sk == 1) s.fr = 0;
         if (!tn && s.nr != 16) return HGEMM_ERR_UNSUPPORTED;
         if (p->any_b && s.wv != 4) return HGEMM_ERR_UNSUPPORTED;
-        const int64_t strips = (N + skinny_cols(s, tn) - 1) / skinny_cols(s, tn);
+        if (s.ra && (!tn || M > 32)) return HGEMM_ERR_UNSUPPORTED;
+        // with A resident, one workgroup per compute unit (a multiple of the 8 XCDs) walks the strips
+        const int64_t strips = s.ra ? std::max<int64_t>(8, cu_count() / 8 * 8) : (N + skinny_cols(s, tn) - 1) / skinny_cols(s, tn);
         if (s.fr && strips * (int64_t)sizeof(int) > (int64_t)kCounterBytes) return HGEMM_ERR_UNSUPPORTED;
-        p->skinny = p->any_b ? skinny_any_b_kernel(mb, s.fr != 0) : skinny_kernel(mb, s.fr != 0, s.wv, tn ? s.nr : 0);
+        p->skinny = s.ra ? skinny_strips(mb, K) : p->any_b ? skinny_any_b_kernel(mb, s.fr != 0) : skinny_kernel(mb, s.fr != 0, s.wv, tn ? s.nr : 0);
         if (!p->skinny) return HGEMM_ERR_UNSUPPORTED;
         GemmArgs& a = p->args;
         a.M = (int)M; a.N = (int)N; a.K = (int)K;
         a.lda = (int)p->lay.lda; a.ldb = (int)p->lay.ldb; a.ldc = (int)p->lay.ldc;
         a.tiles_m = 1; a.tiles_n = (int)strips;
         a.splits = (int)sk;
-        a.k_per_split = (int)(((ksteps + sk - 1) / sk) * step);
+        a.k_per_split = s.ra ? (int)(ksteps * 32) : (int)(((ksteps + sk - 1) / sk) * step);      // of a wave, else of a slab
         a.b_rows = (int)(p->padded && !p->copy_b ? p->uK : K);
         // workspace: [counters] [padded copies of A and B (problems off the 16-byte grid)] [planes]
         const size_t pad_bytes = place_copies(p);
@@ -1815,7 +1827,7 @@ hgemm_status_t hgemm_plan_launch_info(hgemm_plan_t plan, int64_t* workgroups, in
     int64_t wg, lds, th;
     if (plan->skinny) {
         wg = (int64_t)plan->args.tiles_n * plan->args.splits;
-        lds = plan->tn_kernel ? plan->spec.wv * (plan->M <= 16 ? 1 : plan->M <= 32 ? 2 : 4) * (plan->spec.nr / 16) * 1024 : 4 * 16 * (kSkinnyCols + 4) * 4;
+        lds = plan->tn_kernel ? (plan->spec.ra ? 2 : 1) * plan->spec.wv * (plan->M <= 16 ? 1 : plan->M <= 32 ? 2 : 4) * (plan->spec.nr / 16) * 1024 : 4 * 16 * (kSkinnyCols + 4) * 4;
         th = 64 * plan->spec.wv;
     } else if (plan->entry) {
         wg = plan->spec.sm ? (int64_t)plan->args.dp_tiles + plan->args.sk_workers
@@ -1841,7 +1853,7 @@ const char* hgemm_spec_help(void)
         std::string t =
             "generic\n"
             "    one thread per element, any shape, alignment and layout\n"
-            "skinny,sk=SPLITS[,fr=1][,wv=WAVES][,nr=ROWS]\n"
+            "skinny,sk=SPLITS[,fr=1][,wv=WAVES][,nr=ROWS][,ra=1]\n"
             "    memory-bound kernel for M <= 64 rows of A (row-major B): workgroups of wv = 4 (default), 8 or 16 waves\n"
             "    take 128 columns and a K slab each and stream it in steps of 16 * wv rows; a wave takes 16 rows of a\n"
             "    step, transposes its 4 x 8 blocks in registers for 16x16x16 matrix-core instructions (M on a 16-wide\n"
@@ -1849,7 +1861,8 @@ const char* hgemm_spec_help(void)
             "    slab order by the split-K reduction launch or, with fr = 1, by the workgroup that arrives last.\n"
             "    Column-major B (K contiguous): a workgroup takes nr = 16 (default), 32 or 64 rows of B (columns of C), its waves split its K\n"
             "    range into contiguous parts of whole 32-k steps, 16-byte loads are the operands of 16x16x32 instructions\n"
-            "    as they come; sk splits K further across workgroups\n"
+            "    as they come; sk splits K further across workgroups.  ra = 1 (with sk = 1, wv = 8; M <= 32, K <= 8192, above 16 rows 4096): A stays\n"
+            "    in registers, one workgroup per compute unit walks strips of 16 rows of B\n"
             "mfma,bm=BM,bn=BN,bk=BK,wm=WM,wn=WN,st=STAGES[,pf=PREFETCH][,sk=SPLITS][,gm=GROUP][,tb=1][,sm=1][,fr=1][,ps=1][,ac=16][,mi=16][,ph=1][,di=1]\n"
             "    pipelined 32x32x16 MFMA kernel; BMxBN tile per workgroup, WMxWN wavefronts, STAGES LDS buffers,\n"
             "    pf = register prefetch distance in k-steps (1 = ping-pong, 3 = four fragment sets),\n"
@@ -1969,6 +1982,7 @@ hgemm_status_t hgemm_candidates(int64_t M, int64_t N, int64_t K, const hgemm_lay
                     }
                 }
         }
+        if (l.b == HGEMM_COL_MAJOR && M <= 32 && N >= 16 * CUS && skinny_strips(M <= 16 ? 1 : 2, K)) out += "skinny,sk=1,wv=8,ra=1\n";
         for (const MfmaEntry& e : registry()) {
             if (!tile_fits_problem(e, M, N)) continue;
             const int64_t t = ((M + e.bm - 1) / e.bm) * ((N + e.bn - 1) / e.bn);

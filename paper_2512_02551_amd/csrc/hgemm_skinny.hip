@@ -80,4 +80,26 @@ void (*skinny_kernel(int mb, bool fused, int waves, int tn_rows))(GemmArgs)
     return nullptr;
 }
 
+// Column-major B, A resident: the instance with the fewest registers whose eight waves hold all of K, for M <= 16 * mb (mb 1 or 2); null where
+// none does.  Wider instances are slower on a K that a narrower one holds (32001 x 2048: 23.3 us, for 3072 24.5), two parts of
+// K slower than one.
+void (*skinny_strips(int mb, int64_t K))(GemmArgs)
+{
+    const int64_t steps = (K + 32 * kStripWaves - 1) / (32 * kStripWaves);
+    if (mb == 1) {
+        if (steps <= 6) return skinny_strips_kernel<1, 6, 1>;
+        if (steps <= 8) return skinny_strips_kernel<1, 8, 1>;
+        if (steps <= 12) return skinny_strips_kernel<1, 12, 1>;
+        if (steps <= 16) return skinny_strips_kernel<1, 16, 1>;
+        if (steps <= 20) return skinny_strips_kernel<1, 10, 2>;
+        if (steps <= 32) return skinny_strips_kernel<1, 16, 2>;
+    } else if (mb == 2) {
+        if (steps <= 6) return skinny_strips_kernel<2, 6, 1>;
+        if (steps <= 8) return skinny_strips_kernel<2, 8, 1>;
+        if (steps <= 12) return skinny_strips_kernel<2, 12, 1>;
+        if (steps <= 16) return skinny_strips_kernel<2, 8, 2>;
+    }
+    return nullptr;
+}
+
 }  // namespace hgemm

@@ -387,4 +387,90 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_tn_gemm_kernel(GemmArgs g)
     sum_split_planes<64 * WAVES, NR / 4>(g, 0, n0, g.M, t);
 }
 
+// The same for a long column-major B (an output head, a wide projection) and up to 32 rows of A: A stays in registers.  One workgroup
+// of eight waves per compute unit walks strips of 16 rows of B.  The waves split K; each keeps its part of A as operands of its
+// instructions (S of 32 k, P times), loads its part of a strip with 16-byte loads, asks for the next as soon as one is multiplied,
+// and the eight sums of a strip meet in LDS, added in wave order by one wave (they take turns) while the others go on.
+// The kernel above reads A as often as B through the L1s and has its workgroups' starts and ends in the open.
+// Strips are dealt so that the 32 workgroups of an XCD (workgroup ids go round the XCDs) hold adjacent ones: a strip is 32 bytes of a
+// row of C, and lines of C whose parts come from several L2s cost 5 us (16 x 50257 x 4096: 78.9 -> 73.3; a contiguous run of strips for
+// each workgroup: 81).  More strips in flight than one are slower (32001 x 2048: 23.4, with two 24.7, three 26.7).
+// 16 x 50257 x 4096 84 -> 72.8 us, 1 x 50257 x 4096 81 -> 68.8, 16 x 32000 x 4096 55.9 -> 47.1, 1 x 32001 x 2048 29.9 -> 23.3,
+// 32 x 32001 x 2048 31.0 -> 27.7.  What bounds it: the stream of B, 5.6-6.0 TB/s where a kernel that only reads gets 6.2; and 2 us until A is there.
+constexpr int kStripWaves = 8;
+template <int MB, int S, int P>
+__global__ __launch_bounds__(64 * kStripWaves, 2) void skinny_strips_kernel(GemmArgs g)
+{
+    typedef unsigned int uint4v __attribute__((ext_vector_type(4)));
+    __shared__ __attribute__((aligned(16))) float red[2][kStripWaves * MB * 256];
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int kw = wave * g.k_per_split, kw_hi = min(g.K, kw + g.k_per_split);      // this wave's part of K: a multiple of 32, at most 32 * S * P
+    const int strips = (g.N + 15) / 16, stride = gridDim.x;                         // the grid is a multiple of 8
+    const int first = (int)((blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8);
+    const unsigned OOB = 0x80000000u;
+    const __amdgpu_buffer_rsrc_t rsrcA =
+        __builtin_amdgcn_make_buffer_rsrc((void*)g.A, 0, (int)min((long long)g.M * g.lda * 2, 0x7fffffffLL), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsrcB =
+        __builtin_amdgcn_make_buffer_rsrc((void*)g.B, 0, (int)min((long long)g.N * g.ldb * 2, 0x7fffffffLL), 0x00020000);
+    const int c16 = lane & 15, grp = lane >> 4;
+    const int k0 = kw + 8 * grp;                              // K is a multiple of 8: the eight k of a lane are in range together or not at all
+    uint4v bq[S];
+    union { uint4v u; half8 h; } fa[MB][P][S];
+    auto load_b = [&](int strip, int part) {
+        const int n = strip * 16 + c16;
+        const int left = n < g.N ? kw_hi - k0 : 0;            // one comparison a load: two become branches
+        const unsigned off = ((unsigned)n * (unsigned)g.ldb + (unsigned)k0) * 2u;
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const int k = (part * S + s) * 32;
+            bq[s] = __builtin_amdgcn_raw_buffer_load_b128(rsrcB, k < left ? off + 2u * k : OOB, 0, 0);
+        }
+    };
+    load_b(first, 0);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+        const int m = 16 * mb + c16;
+        const int left = m < g.M ? kw_hi - k0 : 0;
+        const unsigned off = ((unsigned)m * (unsigned)g.lda + (unsigned)k0) * 2u;
+#pragma unroll
+        for (int s = 0; s < S * P; ++s) fa[mb][s / S][s % S].u = __builtin_amdgcn_raw_buffer_load_b128(rsrcA, 32 * s < left ? off + 64u * s : OOB, 0, 0);
+    }
+    for (int strip = first, turn = 0; strip < strips; strip += stride, ++turn) {
+        float4v acc[MB];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) acc[mb] = float4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                union { uint4v i; half8 h; } b;
+                b.i = bq[s];
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) acc[mb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(b.h, fa[mb][p][s].h, acc[mb], 0, 0, 0);
+            }
+            load_b(p + 1 < P ? strip : strip + stride, (p + 1) % P);
+        }
+        // acc[mb][r] belongs to C[16 mb + c16][16 strip + 4 grp + r].  Two sets of sums: the one written here was last read before the
+        // barrier of the strip in between.
+        float* sums = red[turn & 1];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) *(float4v*)(sums + ((wave * MB + mb) * 64 + lane) * 4) = acc[mb];
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");      // not __syncthreads(): the next strips' loads stay in flight
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            if ((turn * MB + mb) % kStripWaves != wave) continue;
+            float4v sum = float4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < kStripWaves; ++w) sum += *(const float4v*)(sums + ((w * MB + mb) * 64 + lane) * 4);
+            const int m = 16 * mb + c16, n = strip * 16 + 4 * grp;
+            if (m >= g.M || n >= g.N) continue;
+            half4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = (_Float16)sum[e];
+            store_cols(g.C + (size_t)m * g.ldc + n, o, g.N - n, g.c_wide);
+        }
+    }
+}
+
 }  // namespace hgemm
