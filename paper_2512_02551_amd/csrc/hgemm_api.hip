@@ -571,7 +571,7 @@ bool streams_any_b(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l)
 // Not for operands that would be copied: the choice between copies and direct_choice compares with the models' pick.
 struct FewRow { unsigned short m; unsigned n, k; signed char spec[5]; };
 #include "few_rows.inc"
-struct FewIndex {
+struct FewIndex {                 // in order of N: a search looks at the rows within reach of its N, a tenth of them
     struct Item { float lm, ln, lk; int columns; const FewRow* row; };
     std::vector<Item> items;
     FewIndex(const FewRow* rows, size_t count)
@@ -579,6 +579,7 @@ struct FewIndex {
         items.reserve(count);
         for (size_t i = 0; i < count; ++i)
             items.push_back({std::log2((float)rows[i].m), std::log2((float)rows[i].n), std::log2((float)rows[i].k), std::min(3, (int)((rows[i].n + 16383) / 16384)), &rows[i]});
+        std::sort(items.begin(), items.end(), [](const Item& x, const Item& y) { return x.ln != y.ln ? x.ln < y.ln : x.row < y.row; });
     }
 };
 bool few_rows_choice(int64_t M, int64_t N, int64_t K, bool b_row_major, const Spec& model, Spec* out)
@@ -589,9 +590,11 @@ bool few_rows_choice(int64_t M, int64_t N, int64_t K, bool b_row_major, const Sp
     const int columns = (int)std::min<int64_t>(3, (N + 16383) / 16384);
     float best = 0.3f;
     const FewRow* row = nullptr;
-    for (const FewIndex::Item& r : (b_row_major ? nn : tn).items) {
-        const float d = 0.3f * std::fabs(lm - r.lm) + std::fabs(ln - r.ln) + std::fabs(lk - r.lk) + (columns != r.columns ? 0.25f : 0.f);
-        if (d < best) { best = d; row = &r.row[0]; }
+    const std::vector<FewIndex::Item>& items = (b_row_major ? nn : tn).items;
+    for (auto r = std::lower_bound(items.begin(), items.end(), ln - best, [](const FewIndex::Item& x, float v) { return x.ln < v; });
+         r != items.end() && r->ln < ln + best; ++r) {
+        const float d = 0.3f * std::fabs(lm - r->lm) + std::fabs(ln - r->ln) + std::fabs(lk - r->lk) + (columns != r->columns ? 0.25f : 0.f);
+        if (d < best) { best = d; row = r->row; }
     }
     if (!row) return false;
     auto rounds = [](const Spec& s, int64_t n) {
