@@ -111,9 +111,10 @@ hgemm_status_t hgemm_plan_override(hgemm_plan_t* out, int64_t M, int64_t N, int6
  *               B (Section 5.2's zero padding) and the run makes, in one launch
  *               before the GEMM on the same stream, those that are needed: of
  *               an operand whose rows are not whole aligned chunks, or whose
- *               base is not 16-byte aligned.  (Room that only such a base would
- *               need is left out where the device has no memory for it; the
- *               generic kernel serves such a base then.)  A C whose rows are
+ *               base is not 16-byte aligned; smaller problems (",di=1" in the
+ *               description) are read where they lie.  (Room that only
+ *               such a base would need is left out where the device has no
+ *               memory for it; the generic kernel serves such a base then.)  A C whose rows are
  *               2^31 elements apart or more is stored in the workspace and
  *               copied into place by one more launch.  Problems below 2^20
  *               multiply-adds with such sizes take a generic
@@ -221,11 +222,13 @@ hgemm_status_t hgemm_candidates(int64_t M, int64_t N, int64_t K,
  *                      configuration per (M,N,K), here from timed runs)
  *   "neighbour: SPEC"  a large problem the table does not hold: the kernel
  *                      tuned for the nearest shape it does hold
- *   "model: SPEC"      the fitted cost model's pick;  "rules: SPEC" its last
- *                      resort
+ *   "model: SPEC"      the fitted cost model's pick, or with few rows of A
+ *                      that of the nearest measured problem;  "rules: SPEC"
+ *                      its last resort
  *   "blocks,rows=R,cols=C[,bt=1]"   operands of 2 GiB and more
  *   "generic"          unaligned and too small to pad;  "empty"  M, N or K = 0
- * with ",pad=1" appended when the kernel would run on zero-padded copies.
+ * with ",pad=1" appended when N, K or a leading dimension is not a multiple
+ * of 8 (zero-padded copies, or with ",di=1" none).
  * hgemm_plan() then still has to set the choice up on the device; where that
  * fails (a kernel this build lacks, no memory) it falls back as documented
  * there.  Errors: INVALID_ARG (also when buf is too small), UNSUPPORTED.    */
