@@ -571,28 +571,28 @@ bool streams_any_b(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l)
 // Not for operands that would be copied: the choice between copies and direct_choice compares with the models' pick.
 struct FewRow { unsigned short m; unsigned n, k; signed char spec[5]; };
 #include "few_rows.inc"
-struct FewIndex {                 // in order of N: a search looks at the rows within reach of its N, a tenth of them
-    struct Item { float lm, ln, lk; int columns; const FewRow* row; };
-    std::vector<Item> items;
-    FewIndex(const FewRow* rows, size_t count)
+struct FewItem { float lm, ln, lk; int columns; const FewRow* row; };
+template <size_t COUNT>
+struct FewIndex {                 // in order of N: a search looks at the rows within reach of its N, a tenth of them.  Nothing is allocated.
+    FewItem items[COUNT];
+    explicit FewIndex(const FewRow (&rows)[COUNT])
     {
-        items.reserve(count);
-        for (size_t i = 0; i < count; ++i)
-            items.push_back({std::log2((float)rows[i].m), std::log2((float)rows[i].n), std::log2((float)rows[i].k), std::min(3, (int)((rows[i].n + 16383) / 16384)), &rows[i]});
-        std::sort(items.begin(), items.end(), [](const Item& x, const Item& y) { return x.ln != y.ln ? x.ln < y.ln : x.row < y.row; });
+        for (size_t i = 0; i < COUNT; ++i)
+            items[i] = {std::log2((float)rows[i].m), std::log2((float)rows[i].n), std::log2((float)rows[i].k), std::min(3, (int)((rows[i].n + 16383) / 16384)), &rows[i]};
+        std::sort(items, items + COUNT, [](const FewItem& x, const FewItem& y) { return x.ln != y.ln ? x.ln < y.ln : x.row < y.row; });
     }
 };
 bool few_rows_choice(int64_t M, int64_t N, int64_t K, bool b_row_major, const Spec& model, Spec* out)
 {
-    static const FewIndex nn(kFewRowsNN, sizeof(kFewRowsNN) / sizeof(kFewRowsNN[0]));
-    static const FewIndex tn(kFewRowsTN, sizeof(kFewRowsTN) / sizeof(kFewRowsTN[0]));
+    static const FewIndex nn(kFewRowsNN);
+    static const FewIndex tn(kFewRowsTN);
+    const FewItem* const items = b_row_major ? nn.items : tn.items;
+    const FewItem* const end = items + (b_row_major ? std::size(kFewRowsNN) : std::size(kFewRowsTN));
     const float lm = std::log2((float)M), ln = std::log2((float)N), lk = std::log2((float)K);
     const int columns = (int)std::min<int64_t>(3, (N + 16383) / 16384);
     float best = 0.3f;
     const FewRow* row = nullptr;
-    const std::vector<FewIndex::Item>& items = (b_row_major ? nn : tn).items;
-    for (auto r = std::lower_bound(items.begin(), items.end(), ln - best, [](const FewIndex::Item& x, float v) { return x.ln < v; });
-         r != items.end() && r->ln < ln + best; ++r) {
+    for (const FewItem* r = std::lower_bound(items, end, ln - best, [](const FewItem& x, float v) { return x.ln < v; }); r != end && r->ln < ln + best; ++r) {
         const float d = 0.3f * std::fabs(lm - r->lm) + std::fabs(ln - r->ln) + std::fabs(lk - r->lk) + (columns != r->columns ? 0.25f : 0.f);
         if (d < best) { best = d; row = r->row; }
     }
