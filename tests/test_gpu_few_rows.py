@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
     (10, 7944, 2248, False, "mfma,bm=32,bn=128,bk=64"), (7, 10592, 5880, False, "mfma,bm=32,bn=192,bk=64"), (23, 11960, 6120, False, "mfma,bm=32,bn=256,bk=64"),
     (1, 1072, 936, True, "skinny"), (15, 1035, 928, True, "mfma,bm=32,bn=64,bk=64"), (12, 4088, 952, True, "skinny,sk=1,wv=8,nr=32"), (4, 4720, 1200, True, "skinny,sk=1,nr=32"),
     (2, 845, 3768, True, "mfma,bm=32,bn=64,bk=64"), (14, 6029, 1552, True, "skinny,sk=1,wv=8,ra=1"), (16, 50257, 4096, True, "skinny,sk=1,wv=8,ra=1"), (8, 16761, 1032, True, "mfma,bm=32,bn=128,bk=128"),
-    (3, 2837, 8344, True, "mfma,bm=32,bn=128,bk=64"), (3, 6776, 6384, True, "mfma,bm=32,bn=192,bk=64"), (32, 40005, 1304, True, "skinny,sk=1,wv=8,ra=1")], ids=str)
+    (3, 2837, 8344, True, "mfma,bm=32,bn=128,bk=64"), (3, 6776, 6384, True, "mfma,bm=32,bn=192,bk=64"), (32, 40005, 1304, True, "skinny,sk=1,wv=8,ra=1"),
+    (16, 16384, 1200, True, "skinny,sk=1,wv=8,ra=1"), (1, 20001, 4096, True, "skinny,sk=1,wv=8,ra=1"), (16, 16392, 4104, True, "mfma")], ids=str)
 def test_the_measured_pick_is_exact_on_small_integers_and_stays_inside_c(m, n, k, tn, kernel):
     assert check(None, m, n, k, tn).startswith(kernel)
 
