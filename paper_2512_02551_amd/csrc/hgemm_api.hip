@@ -1057,12 +1057,13 @@ bool phased_choice(int64_t M, int64_t N, int64_t K, bool row_b, int64_t b_ld, co
 // Problems off the 16-byte grid, read through registers where they lie.  Fitted (soft-L1 on log time, rms 9-11 %) to 9700
 // timings of the four tiles and their splits on 600 random problems (M and N from 65 to 4200, K from 129; few rows against a long
 // odd N among them), operands in the last-level cache.
-struct DirectTile { const char* spec; int bm, bn; double t0, wg, lat, busy, flow, red2, red2_mib, red1, red1_mib; };
+// late: what a K-tile takes longer when its operands come from HBM, loads being no more than two K-tiles ahead (90th percentile).
+struct DirectTile { const char* spec; int bm, bn; double t0, wg, lat, busy, flow, red2, red2_mib, red1, red1_mib, late; };
 constexpr DirectTile kDirectTiles[] = {
-    {"mfma,bm=32,bn=64,bk=64,wm=1,wn=2,st=4,pf=3,sk=1,gm=8,di=1", 32, 64, 2.904, 0.354, 0.199, 0.215, 0.190, 1.977, 0.478, 2.169, 0.777},
-    {"mfma,bm=64,bn=64,bk=64,wm=2,wn=2,st=4,pf=3,sk=1,gm=8,di=1", 64, 64, 2.738, 0.436, 0.280, 0.288, 0.240, 1.911, 0.577, 3.326, 0.948},
-    {"mfma,bm=64,bn=128,bk=64,wm=2,wn=2,st=4,pf=3,sk=1,gm=8,di=1", 64, 128, 3.666, 0.598, 0.310, 0.415, 0.435, 1.911, 0.464, 1.412, 1.774},
-    {"mfma,bm=128,bn=128,bk=64,wm=2,wn=4,st=3,pf=3,sk=1,gm=8,di=1", 128, 128, 4.212, 0.022, 0.502, 0.558, 0.580, 1.953, 0.507, 1.262, 1.990},
+    {"mfma,bm=32,bn=64,bk=64,wm=1,wn=2,st=4,pf=3,sk=1,gm=8,di=1", 32, 64, 2.904, 0.354, 0.199, 0.215, 0.190, 1.977, 0.478, 2.169, 0.777, 0.08},
+    {"mfma,bm=64,bn=64,bk=64,wm=2,wn=2,st=4,pf=3,sk=1,gm=8,di=1", 64, 64, 2.738, 0.436, 0.280, 0.288, 0.240, 1.911, 0.577, 3.326, 0.948, 0.20},
+    {"mfma,bm=64,bn=128,bk=64,wm=2,wn=2,st=4,pf=3,sk=1,gm=8,di=1", 64, 128, 3.666, 0.598, 0.310, 0.415, 0.435, 1.911, 0.464, 1.412, 1.774, 0.23},
+    {"mfma,bm=128,bn=128,bk=64,wm=2,wn=4,st=3,pf=3,sk=1,gm=8,di=1", 128, 128, 4.212, 0.022, 0.502, 0.558, 0.580, 1.953, 0.507, 1.262, 1.990, 0.31},
 };
 double predict_direct_us(const DirectTile& c, int64_t M, int64_t N, int64_t K, int64_t sk, bool fused)
 {
@@ -1218,10 +1219,15 @@ Route route(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l)
 // A problem that would be copied: the kernels that read it where it lies instead?  `pick` is what the padded problem would run on;
 // a phased or persistent pick stays, and so does a B that is streamed.  A copy costs a launch and the operand three times; reading through registers costs the
 // matrix cores their even supply: 1000 x 1001 x 1003 11.0 -> 8.0 us, 500 x 501 x 503 7.4 -> 5.3, 70 x 3001 x 1001 11.3 -> 7.0, 2000 x 2001 x 2003
-// 33 -> 29, but 4100 x 4101 x 4103 183 -> 280.  Taken where its prediction is below 0.9 of the other way's (1.3 times the
-// prediction of the pick, which was fitted warm and alone, and 0.2 us a MB copied), below 0.75 for an unsplit K of 2560 and more, where it
-// is the less certain one; 128 x 128 tiles up to one for every compute unit.  523 random problems: 487 change, 1.40 times
-// faster in the geometric mean over all, none slower by more than 2 %.
+// 33 -> 29 (operands in the last-level cache), but 4100 x 4101 x 4103 183 -> 280.  Taken where its prediction, with what operands from
+// HBM add (in full from 16 MB on), is below 0.9 of the other way's (1.3 times the prediction of the pick, which was fitted warm and
+// alone, and 0.2 us a MB copied), without that addition below 0.75 for an unsplit K of 2560 and more, where it is the less certain
+// one; 128 x 128 tiles up to one for every compute unit.  Two ranges keep their copies: a C of more than 4M elements with at most two
+// K-tiles, where storing C takes most of the time (1980 x 13416 x 104 23 us, in place 33; 99 such problems 1.1 times slower), and a B
+// beyond the cache that is not copied anyway, in more than one round of workgroups (53 x 53440 x 3213 64 us, in place 74).
+// 6955 problems that the rule without the addition takes, a third of them random and the others where it was in doubt: from HBM 1.30 times
+// faster than the copies but 440 slower by more than 3 % (up to 1.6 times); of the 5184 that this one keeps 12 are, by 6 % at most, and
+// none from the cache (1.39 and 1.46 times faster).
 bool direct_choice(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, const Route& r, const Spec& pick, Spec* out)
 {
     if (!r.padded || !(r.copy_a || r.copy_b) || r.any_b || pick.fam != FAM_MFMA || pick.ph || pick.ps || !direct_can_run(M, N, K, l) || 2.0 * (double)M * (double)N * (double)K > 4e10) return false;
@@ -1244,8 +1250,14 @@ bool direct_choice(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, co
             }
         }
     }
-    if (!best || best_us >= (K >= 2560 && best_sk == 1 ? 0.75 : 0.9) * other || !parse_spec(best->spec, out)) return false;
-    out->sk = (int)effective_splits(ktiles, best_sk);
+    if (!best || ((double)M * (double)N > 4e6 && K <= 128)) return false;
+    best_sk = (int)effective_splits(ktiles, best_sk);
+    const double bytes = 2.0 * ((double)M * l.lda + (double)(l.b == HGEMM_ROW_MAJOR ? K : N) * l.ldb);
+    const int64_t groups = ((M + best->bm - 1) / best->bm) * ((N + best->bn - 1) / best->bn) * best_sk;
+    if (!r.copy_b && bytes > 128e6 && groups > cu_count()) return false;
+    const double late = best->late * (double)(((ktiles + best_sk - 1) / best_sk + 1) / 2 * 2) * std::min(1.0, bytes / 16e6);
+    if (best_us + late >= 0.9 * other || (K >= 2560 && best_sk == 1 && best_us >= 0.75 * other) || !parse_spec(best->spec, out)) return false;
+    out->sk = best_sk;
     out->fr = best_fr;
     return true;
 }

@@ -182,6 +182,19 @@ def test_problems_off_the_grid_that_keep_their_copies_streams_and_phased_kernels
     assert r["run"] == 0 and ",di=1" not in r["describe"], r
 
 
+@pytest.mark.parametrize("q,in_place", [
+    ({"M": 1980, "N": 13416, "K": 104, "tn": True, "lda": 124}, False), ({"M": 3992, "N": 1311, "K": 71, "tn": True}, False),     # storing C is most of it
+    ({"M": 2801, "N": 1427, "K": 71}, True), ({"M": 1720, "N": 2342, "K": 243}, True),                                          # up to 4M elements; four K-tiles
+    ({"M": 53, "N": 53440, "K": 3213}, False), ({"M": 64, "N": 51160, "K": 4317}, False),              # a B from HBM that no copy would touch, two rounds of workgroups
+    ({"M": 40, "N": 30976, "K": 7889}, True), ({"M": 40, "N": 63977, "K": 1001, "tn": True}, True),                  # ... one round; a B that would be copied
+    ({"M": 395, "N": 1831, "K": 3883}, False), ({"M": 2000, "N": 1901, "K": 2001}, False), ({"M": 315, "N": 2007, "K": 2299, "tn": True}, False),   # long unsplit K from HBM
+    ({"M": 395, "N": 1831, "K": 383}, True)])
+def test_in_place_off_the_grid_only_where_it_is_not_slower_from_memory_either(q, in_place):
+    """Problems that reading in place made up to 1.6 times slower once their operands are not in the cache keep their copies."""
+    (r,) = ask([q])
+    assert r["run"] == 0 and (",di=1" in r["describe"]) == in_place, r["describe"]
+
+
 @pytest.mark.parametrize("m", [1, 4, 16, 32])
 def test_few_rows_of_a_fit_the_static_scratch_and_keep_in_place_kernels_off_the_grid(m):
     """What the static entry point takes with few rows is the planned call; operands that would be copied are still read where they lie."""
