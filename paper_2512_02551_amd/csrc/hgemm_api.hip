@@ -1691,8 +1691,8 @@ hgemm_status_t hgemm_run(hgemm_plan_t plan, const void* A, const void* B, void* 
 //     caller chose, which is to run as it was asked for.
 //   * Operands and result of a call up to 8 MiB: 8 x 256^3 22.4 -> 3.9 us, 16 x 512 x 512 x 1024 106 -> 12, 8 x 1024^3 48 -> 20;
 //     above, a call takes 12 us and more and the launch little of it (4 x 1536^3 49.9 -> 43).
-//   * Tiles of 128 x 128 where they give every compute unit one (8 x 1024 x 1024 x 256: 8.6 us, in 64 x 64 tiles 11.1; 8 x 768^3
-//     12.1 against 13.9), else 64 x 64 (4 x 512 x 512 x 1024, 64 tiles of 128: 5.5 us against 8.8).
+//   * Tiles of 128 x 128 where the calls of the launch give every compute unit one (8 x 1024 x 1024 x 256: 8.6 us, in 64 x 64 tiles 11.1;
+//     8 x 768^3 12.1 against 13.9), else 64 x 64 (4 x 512 x 512 x 1024, 64 tiles of 128: 5.5 us against 8.8).
 static const MfmaEntry* merged_entry(const hgemm_plan_s* p, int64_t calls)
 {
     const Spec& s = p->spec;
@@ -1701,7 +1701,7 @@ static const MfmaEntry* merged_entry(const hgemm_plan_s* p, int64_t calls)
     static const MfmaEntry* const large = batch_entry(128);
     static const MfmaEntry* const small = batch_entry(64);
     const int64_t tiles128 = ((p->M + 127) / 128) * ((p->N + 127) / 128);
-    return std::min<int64_t>(calls, kBatchSets) * tiles128 >= cu_count() ? large : small;
+    return calls * tiles128 >= cu_count() ? large : small;
 }
 
 // A call's operands as address ranges: calls that share a launch must not write what another of them reads or writes.
@@ -1719,8 +1719,7 @@ hgemm_status_t hgemm_run_many(hgemm_plan_t plan, int64_t count, int64_t sets, in
                               const void* const* B, void* const* C, void* hip_stream)
 {
     if (!plan || count < 0 || sets < 1 || first < 0 || first >= sets || !A || !B || !C) return HGEMM_ERR_INVALID_ARG;
-    const MfmaEntry* e = count > 1 && sets > 1 ? merged_entry(plan, std::min(count, sets)) : nullptr;
-    if (!e) {
+    if (count <= 1 || sets <= 1 || !merged_entry(plan, 2)) {
         int64_t set = first;
         for (int64_t i = 0; i < count; ++i) {
             const hgemm_status_t st = run_plan(plan, A[set], B[set], C[set], hip_stream);
@@ -1731,10 +1730,6 @@ hgemm_status_t hgemm_run_many(hgemm_plan_t plan, int64_t count, int64_t sets, in
     }
     BatchArgs g;
     static_cast<GemmArgs&>(g) = plan->args;
-    g.tiles_m = (g.M + e->bm - 1) / e->bm;
-    g.tiles_n = (g.N + e->bn - 1) / e->bn;
-    g.swizzle = g.tiles_m * g.tiles_n <= 16 ? 0 : plan->spec.gm;
-    set_tile_map(g);
     const hgemm_layouts_t& l = plan->lay;
     const size_t a_bytes = ((size_t)(plan->M - 1) * l.lda + plan->K) * 2, c_bytes = ((size_t)(plan->M - 1) * l.ldc + plan->N) * 2;
     const size_t b_bytes = l.b == HGEMM_ROW_MAJOR ? ((size_t)(plan->K - 1) * l.ldb + plan->N) * 2 : ((size_t)(plan->N - 1) * l.ldb + plan->K) * 2;
@@ -1746,6 +1741,11 @@ hgemm_status_t hgemm_run_many(hgemm_plan_t plan, int64_t count, int64_t sets, in
         if (n == 1) {
             st = run_plan(plan, g.set[0].A, g.set[0].B, g.set[0].C, hip_stream);
         } else {
+            const MfmaEntry* e = merged_entry(plan, n);
+            g.tiles_m = (g.M + e->bm - 1) / e->bm;
+            g.tiles_n = (g.N + e->bn - 1) / e->bn;
+            g.swizzle = g.tiles_m * g.tiles_n <= 16 ? 0 : plan->spec.gm;
+            set_tile_map(g);
             hipLaunchKernelGGL(plan->tn_kernel ? e->batch_tn : e->batch, dim3((unsigned)n, (unsigned)(g.tiles_m * g.tiles_n)), dim3(e->threads), e->lds_bytes,
                                (hipStream_t)hip_stream, g);
             if (hipGetLastError() != hipSuccess) st = HGEMM_ERR_LAUNCH;

@@ -146,6 +146,22 @@ def test_small_calls_of_a_batch_share_launches_where_none_depends_on_another():
     assert status != 0 and launches == [2]                                            # calls in front of the one that fails are enqueued
 
 
+def test_the_tiles_of_a_shared_launch_follow_from_the_calls_it_holds():
+    """500 x 512 x 520 has 16 tiles of 128 x 128 and 64 of 64 x 64: the wide ones where the launch's own calls give each of 256 compute units
+    one, not where a later launch of the batch holds fewer calls, or calls that depend on each other cut it short."""
+    def launches(sets):
+        (r,) = ask([{"M": 500, "N": 512, "K": 520, "many": sets}])
+        assert r["many"] == 0
+        return [(x, y) for _, x, y, *_ in kernels(r["many_log"])]
+
+    s = batch_sets(40, 500, 512, 520)
+    assert launches(s) == [(32, 16), (8, 64)]
+    assert launches(s[:16]) == [(16, 16)] and launches(s[:15]) == [(15, 64)]
+    assert launches(batch_sets(34, 500, 512, 520)) == [(32, 16), (2, 64)]
+    pairs = [(a, b, s[i // 2 % 2][2]) if i % 2 else (a, b, c) for i, (a, b, c) in enumerate(s[2:22])]      # two places for C come round in every second call
+    assert [x for x, y in launches(pairs)] == [5, 4, 4, 4, 3] and {y for _, y in launches(pairs)} == {64}
+
+
 def test_which_plans_share_launches():
     """Small unsplit problems in both layouts and in wider buffers; not large ones, split ones or those off the 16-byte grid."""
     assert many(batch_sets(4, 16, 64, 64), 16, 64, 64, tn=True) == (0, [4])
