@@ -2,7 +2,7 @@
 hgemm_plan and hgemm_run_static decide, allocate and launch, on a machine without a GPU.
 
     ask([{"M": 8, "N": 8, "K": 8, ...}, ...]) -> one dict per question: status, description, workspace bytes and log of
-    hgemm_plan + hgemm_run (and of hgemm_run_many, where operand sets are given), and status and log of hgemm_run_static, on
+    hgemm_plan (hgemm_plan_override, where a spec is given) + hgemm_run (and of hgemm_run_many, where operand sets are given), and status and log of hgemm_run_static, on
     operands at the addresses asked for."""
 import ctypes
 import json
@@ -39,7 +39,8 @@ def _answer(fake, lib, q):
     fake.fake_device_memory(ctypes.c_size_t(q.get("memory", 1 << 40)))
     plan = vp()
     log()
-    r = {"plan": lib.hgemm_plan(ctypes.byref(plan), *dims, ctypes.byref(lay)), "plan_log": log()}
+    spec = [q["spec"].encode()] if "spec" in q else []
+    r = {"plan": (lib.hgemm_plan_override if spec else lib.hgemm_plan)(ctypes.byref(plan), *dims, ctypes.byref(lay), *spec), "plan_log": log()}
     if r["plan"] == 0:
         text = ctypes.create_string_buffer(512)
         assert lib.hgemm_plan_describe(plan, text, ctypes.c_size_t(512)) == 0

@@ -162,6 +162,32 @@ def test_the_tiles_of_a_shared_launch_follow_from_the_calls_it_holds():
     assert [x for x, y in launches(pairs)] == [5, 4, 4, 4, 3] and {y for _, y in launches(pairs)} == {64}
 
 
+def test_bench_times_the_kernel_that_its_row_names():
+    """A row over rotating operand sets runs the planned kernel once a call, not shared launches of another one."""
+    import bench
+
+    class FakePlan:
+        def __init__(self, m, n, k, layouts, spec):
+            (self.r,) = ask([{"M": m, "N": n, "K": k, "many": batch_sets(6, m, n, k), **({"spec": spec} if spec else {})}])
+            assert self.r["plan"] == 0
+
+        def describe(self):
+            return self.r["describe"]
+
+        def destroy(self):
+            pass
+
+    class Library:
+        Plan = FakePlan
+
+    for shape in ((512, 512, 512), (64, 512, 256), (200, 201, 203)):
+        planned = FakePlan(*shape, None, None)
+        timed = bench.plan_to_time(Library, shape, None, None, 6)
+        assert timed.describe() == planned.describe()
+        assert timed.r["many_log"] == 6 * planned.r["run_log"], timed.r["many_log"]
+        assert bench.plan_to_time(Library, shape, None, None, 1).r["run_log"] == planned.r["run_log"]
+
+
 def test_which_plans_share_launches():
     """Small unsplit problems in both layouts and in wider buffers; not large ones, split ones or those off the 16-byte grid."""
     assert many(batch_sets(4, 16, 64, 64), 16, 64, 64, tn=True) == (0, [4])
