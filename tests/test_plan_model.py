@@ -67,6 +67,13 @@ def test_predict_us_rejects_what_the_model_does_not_cover():
         hg.predict_us(256, 256, 256, "mfma,bm=96,bn=128,bk=64,wm=2,wn=2,st=3,pf=3,sk=1,gm=8")
 
 
+def test_predict_us_rejects_resident_a():
+    """The streaming model describes workgroups that take a slab of K each; strips that walk past a resident A are none of these."""
+    assert hg.predict_us(16, 50264, 4096, "skinny,sk=1,wv=8") > 0
+    with pytest.raises(hg.HgemmError):
+        hg.predict_us(16, 50264, 4096, "skinny,sk=1,wv=8,ra=1")
+
+
 def test_model_prefers_split_k_for_skinny_long_k_and_big_tiles_for_big_squares():
     def pick(M, N, K):
         cands = [s for s in hg.candidates(M, N, K) if "sm=1" not in s and "tb=1" not in s and "ps=1" not in s and "gm=8" in s]
