@@ -356,7 +356,8 @@ def test_run_many_equals_a_loop_of_runs_and_rotates_operand_sets():
 
 
 @pytest.mark.parametrize("shape,count,tn,gap", [((1, 8, 8), 3, False, 0), ((64, 64, 128), 8, True, 0), ((65, 72, 136), 5, False, 24), ((16, 512, 1000), 16, True, 8),
-                                                ((257, 120, 264), 33, False, 0), ((512, 504, 72), 16, True, 64), ((500, 512, 520), 17, False, 0), ((130, 136, 8), 32, True, 0)])
+                                                ((257, 120, 264), 33, False, 0), ((512, 504, 72), 16, True, 64), ((500, 512, 520), 17, False, 0), ((500, 512, 520), 40, True, 0),
+                                                ((130, 136, 8), 32, True, 0)])
 def test_calls_that_share_a_launch_give_the_bits_of_single_calls(shape, count, tn, gap):
     """hgemm_run_many on small problems, tiles of 64 and (where there are enough calls) 128: every set bit for bit what hgemm_run
     gives, nothing written beside it; the last set reads the first one's result."""
@@ -382,13 +383,13 @@ def test_calls_that_share_a_launch_give_the_bits_of_single_calls(shape, count, t
         for a, b, c in sets:
             p.run(a.data_ptr(), b.data_ptr(), c.data_ptr(), sh)
         want = [s[2].clone() for s in sets]
-        for s in sets:
-            s[2].fill_(float("nan"))
         for _ in range(2):
+            for s in sets:
+                s[2].fill_(float("nan"))        # each time: what the last set must not read, nor leave from the time before
             p.run_many(count, [tuple(t.data_ptr() for t in s) for s in sets], sh)
-        torch.cuda.synchronize()
-    for i, (s, w) in enumerate(zip(sets, want)):
-        assert torch.equal(s[2].view(torch.int16), w.view(torch.int16)), f"set {i}"
+            torch.cuda.synchronize()
+            for i, (s, w) in enumerate(zip(sets, want)):
+                assert torch.equal(s[2].view(torch.int16), w.view(torch.int16)), f"set {i}"
     a, b, _ = sets[0]
     ref = a[:, :K].float().cpu() @ (b.float().cpu().t() if tn else b.float().cpu())
     assert_close(to_host(want[0][:M, :N]), ref.half().numpy(), "set 0")
