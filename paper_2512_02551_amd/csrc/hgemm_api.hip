@@ -1054,26 +1054,34 @@ bool phased_choice(int64_t M, int64_t N, int64_t K, bool row_b, int64_t b_ld, co
     return false;
 }
 
-// Problems off the 16-byte grid, read through registers where they lie.  Fitted (soft-L1 on log time, rms 9-11 %) to 9700
-// timings of the four tiles and their splits on 600 random problems (M and N from 65 to 4200, K from 129; few rows against a long
-// odd N among them), operands in the last-level cache.
-// late: what a K-tile takes longer when its operands come from HBM, loads being no more than two K-tiles ahead (90th percentile).
-struct DirectTile { const char* spec; int bm, bn; double t0, wg, lat, busy, flow, red2, red2_mib, red1, red1_mib, late; };
+// Problems off the 16-byte grid, read through registers where they lie.  Fitted (soft-L1 on log time; direct_model.py, which has the
+// timings) to the four tiles and their splits on 588 random problems (M and N from 65 to 4200, K from 129; few rows against a long
+// odd N among them), operands in the last-level cache.  late: what a K-tile takes longer when its operands come from HBM, loads being
+// no more than two K-tiles ahead (90th percentile over the problems of 8 MB and more).
+struct DirectTile { const char* spec; int bm, bn; double t0, wg, busy, flow, red2, red2_mib, red1, red1_mib, late; };
 constexpr DirectTile kDirectTiles[] = {
-    {"mfma,bm=32,bn=64,bk=64,wm=1,wn=2,st=4,pf=3,sk=1,gm=8,di=1", 32, 64, 2.904, 0.354, 0.199, 0.215, 0.190, 1.977, 0.478, 2.169, 0.777, 0.08},
-    {"mfma,bm=64,bn=64,bk=64,wm=2,wn=2,st=4,pf=3,sk=1,gm=8,di=1", 64, 64, 2.738, 0.436, 0.280, 0.288, 0.240, 1.911, 0.577, 3.326, 0.948, 0.20},
-    {"mfma,bm=64,bn=128,bk=64,wm=2,wn=2,st=4,pf=3,sk=1,gm=8,di=1", 64, 128, 3.666, 0.598, 0.310, 0.415, 0.435, 1.911, 0.464, 1.412, 1.774, 0.23},
-    {"mfma,bm=128,bn=128,bk=64,wm=2,wn=4,st=3,pf=3,sk=1,gm=8,di=1", 128, 128, 4.212, 0.022, 0.502, 0.558, 0.580, 1.953, 0.507, 1.262, 1.990, 0.31},
+#define DIRECT_TILE(...) {__VA_ARGS__},
+#define DIRECT_COPIES(...)
+#include "direct_model.inc"
+#undef DIRECT_TILE
+#undef DIRECT_COPIES
 };
+// Copies: a launch, the pick's prediction (warm and alone) this many times, and us for a MB read and written.
+struct DirectCopies { double launch, kernel, mb; };
+constexpr DirectCopies kDirectCopies =
+#define DIRECT_TILE(...)
+#define DIRECT_COPIES(...) {__VA_ARGS__};
+#include "direct_model.inc"
+#undef DIRECT_TILE
+#undef DIRECT_COPIES
+int64_t direct_ktiles(int64_t K, int64_t sk) { const int64_t kt = (K + 63) / 64; return ((kt + sk - 1) / sk + 1) / 2 * 2; }      // of a workgroup: whole pairs
 double predict_direct_us(const DirectTile& c, int64_t M, int64_t N, int64_t K, int64_t sk, bool fused)
 {
-    const int64_t kt = (K + 63) / 64;
-    sk = effective_splits(kt, sk);
-    const double per = (double)(((kt + sk - 1) / sk + 1) / 2 * 2);       // K-tiles of a workgroup, whole pairs
+    sk = effective_splits((K + 63) / 64, sk);
     const double x = (double)(((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) * sk) / (double)cu_count(), w = std::ceil(x);
-    const double chain = std::max(c.lat, c.busy * w), flow = c.flow * x;
+    const double chain = c.busy * w, flow = c.flow * x;
     const double planes = (double)sk * M * N * 4.0 / 1048576.0;
-    const double t = c.t0 + c.wg * w + per * std::sqrt(std::sqrt(chain * chain * chain * chain + flow * flow * flow * flow));
+    const double t = c.t0 + c.wg * w + (double)direct_ktiles(K, sk) * std::sqrt(std::sqrt(chain * chain * chain * chain + flow * flow * flow * flow));
     return sk == 1 ? t : t + (fused ? c.red1 + c.red1_mib * planes : c.red2 + c.red2_mib * planes);
 }
 
@@ -1226,15 +1234,15 @@ Route route(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l)
 // K-tiles, where storing C takes most of the time (1980 x 13416 x 104 23 us, in place 33; 99 such problems 1.1 times slower), and a B
 // beyond the cache that is not copied anyway, in more than one round of workgroups (53 x 53440 x 3213 64 us, in place 74).
 // 6955 problems that the rule without the addition takes, a third of them random and the others where it was in doubt: from HBM 1.30 times
-// faster than the copies but 440 slower by more than 3 % (up to 1.6 times); of the 5184 that this one keeps 12 are, by 6 % at most, and
-// none from the cache (1.39 and 1.46 times faster).
+// faster than the copies but 440 slower by more than 3 % (up to 1.64 times); of the 5114 that this one keeps 11 are, by 6 % at most, and
+// none from the cache (1.39 and 1.46 times faster; `direct_model.py evaluate`).
 bool direct_choice(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, const Route& r, const Spec& pick, Spec* out)
 {
     if (!r.padded || !(r.copy_a || r.copy_b) || r.any_b || pick.fam != FAM_MFMA || pick.ph || pick.ps || !direct_can_run(M, N, K, l) || 2.0 * (double)M * (double)N * (double)K > 4e10) return false;
     double other = 0;
     if (!predict_spec_us(M, r.N, r.K, pick, &other)) return false;
     const double moved = 4e-6 * ((r.copy_a ? (double)M * r.K : 0.0) + (r.copy_b ? (double)r.N * r.K : 0.0));      // MB read and written
-    other = 1.74 + 1.3 * other + 0.206 * moved;
+    other = kDirectCopies.launch + kDirectCopies.kernel * other + kDirectCopies.mb * moved;
     const DirectTile* best = nullptr;
     double best_us = 1e300;
     int best_sk = 1, best_fr = 0;
@@ -1255,7 +1263,7 @@ bool direct_choice(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, co
     const double bytes = 2.0 * ((double)M * l.lda + (double)(l.b == HGEMM_ROW_MAJOR ? K : N) * l.ldb);
     const int64_t groups = ((M + best->bm - 1) / best->bm) * ((N + best->bn - 1) / best->bn) * best_sk;
     if (!r.copy_b && bytes > 128e6 && groups > cu_count()) return false;
-    const double late = best->late * (double)(((ktiles + best_sk - 1) / best_sk + 1) / 2 * 2) * std::min(1.0, bytes / 16e6);
+    const double late = best->late * (double)direct_ktiles(K, best_sk) * std::min(1.0, bytes / 16e6);
     if (best_us + late >= 0.9 * other || (K >= 2560 && best_sk == 1 && best_us >= 0.75 * other) || !parse_spec(best->spec, out)) return false;
     out->sk = best_sk;
     out->fr = best_fr;
