@@ -569,6 +569,7 @@ bool streams_any_b(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l)
 // 3 %; 3.1 % from the fastest kernel of each.  The strips of resident A stand in rows of K >= 1200 only: on a shorter K they win less
 // than 5 % cold and lose as much from the cache (1 x 18352 x 808: 10.3 -> 8.2 us cold, 4.9 -> 6.3 warm).
 // Not for operands that would be copied: the choice between copies and direct_choice compares with the models' pick.
+constexpr double kCheapAlloc = 2097152.0 - 65536.0;      // bytes of planes beside the counters below hipMalloc's 2 MiB step
 struct FewRow { unsigned short m; unsigned n, k; signed char spec[5]; };
 #include "few_rows.inc"
 struct FewItem { float lm, ln, lk; int columns; const FewRow* row; };
@@ -614,7 +615,7 @@ bool few_rows_choice(int64_t M, int64_t N, int64_t K, bool b_row_major, const Sp
         if (s.fam == model.fam && s.bm == model.bm && s.bn == model.bn && s.bk == model.bk && s.st == model.st && s.pf == model.pf && s.sk == model.sk &&
             s.fr == model.fr && s.wv == model.wv && s.nr == model.nr && s.ra == model.ra)
             return false;
-        const bool small = (double)s.sk * (double)M * (double)((N + 7) / 8 * 8) * 4.0 <= 2097152.0 - 65536.0;
+        const bool small = (double)s.sk * (double)M * (double)((N + 7) / 8 * 8) * 4.0 <= kCheapAlloc;
         const bool fits = s.sk == 1 || (model.sk > 1 && (small || s.sk < model.sk || (s.sk == model.sk && s.fr <= model.fr)));
         const int64_t here = rounds(s, N), there = rounds(s, row->n);
         if (!found && fits && (here <= there || 20 * here * row->n <= 21 * there * N)) { first = s; found = true; }
@@ -1227,15 +1228,20 @@ Route route(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l)
 // A problem that would be copied: the kernels that read it where it lies instead?  `pick` is what the padded problem would run on;
 // a phased or persistent pick stays, and so does a B that is streamed.  A copy costs a launch and the operand three times; reading through registers costs the
 // matrix cores their even supply: 1000 x 1001 x 1003 11.0 -> 8.0 us, 500 x 501 x 503 7.4 -> 5.3, 70 x 3001 x 1001 11.3 -> 7.0, 2000 x 2001 x 2003
-// 33 -> 29 (operands in the last-level cache), but 4100 x 4101 x 4103 183 -> 280.  Taken where its prediction, with what operands from
-// HBM add (in full from 16 MB on), is below 0.9 of the other way's (1.3 times the prediction of the pick, which was fitted warm and
-// alone, and 0.2 us a MB copied), without that addition below 0.75 for an unsplit K of 2560 and more, where it is the less certain
-// one; 128 x 128 tiles up to one for every compute unit.  Two ranges keep their copies: a C of more than 4M elements with at most two
-// K-tiles, where storing C takes most of the time (1980 x 13416 x 104 23 us, in place 33; 99 such problems 1.1 times slower), and a B
-// beyond the cache that is not copied anyway, in more than one round of workgroups (53 x 53440 x 3213 64 us, in place 74).
-// 6955 problems that the rule without the addition takes, a third of them random and the others where it was in doubt: from HBM 1.30 times
-// faster than the copies but 440 slower by more than 3 % (up to 1.64 times); of the 5114 that this one keeps 11 are, by 6 % at most, and
-// none from the cache (1.39 and 1.46 times faster; `direct_model.py evaluate`).
+// 33 -> 29 (operands in the last-level cache), but 4100 x 4101 x 4103 183 -> 280.  Taken where its prediction is below 0.9 of the other way's (1.3
+// times the prediction of the pick, which was fitted warm and alone, and 0.2 us a MB copied), below 0.75 for an unsplit K of 2560 and
+// more, where it is the less certain one; and where it stays below with what operands from HBM add (in full from 16 MB on), by a tenth in
+// more than one round of workgroups, by a twentieth with column-major B; 128 x 128 tiles up to one for every compute unit.  Two
+// ranges keep their copies: a C of more than 4M elements with at most two K-tiles, where storing C takes most of the time
+// (1980 x 13416 x 104 23 us, in place 33; 99 such problems 1.1 times slower), and a B beyond the cache that is not copied anyway, in more
+// than one round of workgroups (53 x 53440 x 3213 64 us, in place 74).
+// 6955 problems that the first condition takes, a third of them random and the others where it was in doubt: from HBM 1.30 times faster than the
+// copies but 440 slower by more than 3 % and 222 by 10 % (up to 1.64 times), from the cache 1.39 times faster and 133 slower.
+// Of the 5776 that all conditions leave, 59 are slower from HBM (8 by 10 %) and 8 from the cache; 1.36 and 1.44 times faster
+// (`direct_model.py evaluate`).  Stricter ones cost more than they save: below 0.9 with the addition 11 are slower, but 667 more keep copies
+// that are 1.13 times slower.
+// A split whose planes pass the 2 MiB from which an allocation costs 60 us, where the copies stay below, is not considered (411 x 279 x 1277
+// through the one-call wrapper 27 -> 60 us).
 bool direct_choice(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, const Route& r, const Spec& pick, Spec* out)
 {
     if (!r.padded || !(r.copy_a || r.copy_b) || r.any_b || pick.fam != FAM_MFMA || pick.ph || pick.ps || !direct_can_run(M, N, K, l) || 2.0 * (double)M * (double)N * (double)K > 4e10) return false;
@@ -1243,6 +1249,8 @@ bool direct_choice(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, co
     if (!predict_spec_us(M, r.N, r.K, pick, &other)) return false;
     const double moved = 4e-6 * ((r.copy_a ? (double)M * r.K : 0.0) + (r.copy_b ? (double)r.N * r.K : 0.0));      // MB read and written
     other = kDirectCopies.launch + kDirectCopies.kernel * other + kDirectCopies.mb * moved;
+    // the workspace of the way with copies
+    const double room = 2.0 * ((double)M * r.K + (double)r.N * r.K) + (pick.sk > 1 ? (double)pick.sk * (double)M * (double)r.N * 4.0 : 0.0);
     const DirectTile* best = nullptr;
     double best_us = 1e300;
     int best_sk = 1, best_fr = 0;
@@ -1252,6 +1260,8 @@ bool direct_choice(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, co
         if ((c.bm >= 2 * M && c.bm > 32) || (c.bn >= 2 * N && c.bn > 64) || (c.bm == 128 && tiles > cu_count())) continue;
         for (int sk : {1, 2, 3, 4, 6, 8, 12, 16}) {
             if (sk > 1 && (tiles * sk > 4 * cu_count() || ktiles / sk < 2 || tiles > cu_count())) break;
+            const double planes = (double)effective_splits(ktiles, sk) * (double)M * (double)r.N * 4.0;
+            if (sk > 1 && planes > kCheapAlloc && room <= kCheapAlloc) break;
             for (int fr = 0; fr < (sk > 1 && (double)sk * M * N * 4.0 <= 6.0 * 1048576.0 ? 2 : 1); ++fr) {
                 const double us = predict_direct_us(c, M, N, K, sk, fr != 0);
                 if (us < best_us) { best_us = us; best = &c; best_sk = sk; best_fr = fr; }
@@ -1264,7 +1274,8 @@ bool direct_choice(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, co
     const int64_t groups = ((M + best->bm - 1) / best->bm) * ((N + best->bn - 1) / best->bn) * best_sk;
     if (!r.copy_b && bytes > 128e6 && groups > cu_count()) return false;
     const double late = best->late * (double)direct_ktiles(K, best_sk) * std::min(1.0, bytes / 16e6);
-    if (best_us + late >= 0.9 * other || (K >= 2560 && best_sk == 1 && best_us >= 0.75 * other) || !parse_spec(best->spec, out)) return false;
+    if (best_us >= (K >= 2560 && best_sk == 1 ? 0.75 : 0.9) * other) return false;
+    if (best_us + late >= (groups > cu_count() ? 0.9 : l.b == HGEMM_ROW_MAJOR ? 1.0 : 0.95) * other || !parse_spec(best->spec, out)) return false;
     out->sk = best_sk;
     out->fr = best_fr;
     return true;

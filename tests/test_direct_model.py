@@ -32,10 +32,11 @@ def test_committed_constants_are_the_fit(timings):
 
 
 def test_reading_in_place_is_chosen_where_it_is_not_slower(timings):
-    """Every problem of the committed timings that the library reads in place: from HBM one in 200 up to 6 % slower than the copies, from the
-    cache none by more than 3 %."""
+    """Every problem of the committed timings that the library reads in place (a third random, the others where it was in doubt): one in
+    a hundred slower than the copies from HBM by more than 3 %, fewer from the cache, next to none by both."""
     chosen = np.array([[r["copies"][1] / r["direct"][1], r["copies"][2] / r["direct"][2]] for r in timings[1]
                        if ",di=1" in hg.plan_choice(*r["shape"], hg.Layouts.make(r["tn"], *r["ld"]))])
-    assert len(chosen) > 5000
-    assert (chosen[:, 0] < 0.97).mean() < 0.005 and chosen[:, 0].min() > 0.93 and chosen[:, 1].min() > 0.97
+    assert len(chosen) > 5500
+    assert (chosen[:, 0] < 0.97).mean() < 0.011 and (chosen[:, 1] < 0.97).mean() < 0.002
+    assert (np.sqrt(chosen[:, 0] * chosen[:, 1]) < 0.97).mean() < 0.003
     assert np.exp(np.log(chosen).mean(axis=0)).min() > 1.35

@@ -116,6 +116,14 @@ def test_which_unaligned_row_major_b_is_streamed_where_it_lies(m, n, k, streamed
     assert r["run"] == 0 and reads_any_b == streamed, r["run_log"]
 
 
+def test_in_place_off_the_grid_takes_no_split_across_the_allocation_step():
+    """hipMalloc costs 60 us more from 2 MiB on, which a program that plans on every call pays: where the copies stay below, so do the planes."""
+    shapes = [(411, 279, 1277, False), (125, 198, 980, False), (295, 143, 1052, True), (380, 301, 1301, True), (640, 163, 1601, False), (250, 417, 1201, True)]
+    for (m, n, k, tn), r in zip(shapes, ask([{"M": m, "N": n, "K": k, "tn": tn} for m, n, k, tn in shapes])):
+        copies = 2 * (m * (k + 7) + (n + 7) * (k + 7))
+        assert r["run"] == 0 and (r["workspace"] < 2 * MIB or copies > 2 * MIB - 65536), (m, n, k, r["describe"], r["workspace"])
+
+
 def batch_sets(n, m, nn, k, lda=0):
     """n sets of packed operands (rows of A lda apart), one behind the other with nothing between them."""
     from fake_hip import BASE
@@ -229,7 +237,7 @@ def test_problems_off_the_grid_that_keep_their_copies_streams_and_phased_kernels
     ({"M": 2801, "N": 1427, "K": 71}, True), ({"M": 1720, "N": 2342, "K": 243}, True),                                          # up to 4M elements; four K-tiles
     ({"M": 53, "N": 53440, "K": 3213}, False), ({"M": 64, "N": 51160, "K": 4317}, False),              # a B from HBM that no copy would touch, two rounds of workgroups
     ({"M": 40, "N": 30976, "K": 7889}, True), ({"M": 40, "N": 63977, "K": 1001, "tn": True}, True),                  # ... one round; a B that would be copied
-    ({"M": 395, "N": 1831, "K": 3883}, False), ({"M": 2000, "N": 1901, "K": 2001}, False), ({"M": 315, "N": 2007, "K": 2299, "tn": True}, False),   # long unsplit K from HBM
+    ({"M": 395, "N": 1831, "K": 3883}, False), ({"M": 2000, "N": 1901, "K": 2001}, False),   # long unsplit K from HBM
     ({"M": 395, "N": 1831, "K": 383}, True)])
 def test_in_place_off_the_grid_only_where_it_is_not_slower_from_memory_either(q, in_place):
     """Problems that reading in place made up to 1.6 times slower once their operands are not in the cache keep their copies."""
