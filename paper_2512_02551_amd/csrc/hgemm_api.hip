@@ -26,12 +26,22 @@ namespace hgemm {
 // Kernel registry: every compiled MFMA specialisation (hgemm_configs.inc), gathered from the
 // translation units that instantiate them.
 // ---------------------------------------------------------------------------
+constexpr int64_t kLdsPerCU = 160 * 1024;
 static const std::vector<MfmaEntry>& registry()
 {
     static const std::vector<MfmaEntry> r = [] {
         std::vector<MfmaEntry> v;
         register_chunk_0(v); register_chunk_1(v); register_chunk_2(v); register_chunk_3(v);
         register_chunk_4(v); register_chunk_5(v); register_chunk_6(v); register_chunk_7(v);
+        for (MfmaEntry& e : v) {
+            const int64_t lds = (int64_t)e.st * (e.bm + e.bn) * e.bk * 2;
+            const int nw = e.wm * e.wn, tm = e.bm / e.wm / 32, tn = e.bn / e.wn / 32;
+            const int regs = tm * tn * 16 + (e.pf + 1) * (tm + tn) * 4 + 40;       // accumulators + fragment sets + addressing
+            const int wps = std::max(1, std::min(8, 512 / std::max(regs, 64)));  // waves per SIMD the register file admits
+            e.blocks_m = tm;
+            e.blocks_n = tn;
+            e.resident = (int)std::max<int64_t>(1, std::min<int64_t>(kLdsPerCU / lds, nw <= wps * 4 ? (wps * 4) / nw : 1));
+        }
         return v;
     }();
     return r;
@@ -274,7 +284,6 @@ int64_t cu_count()
     }();
     return n;
 }
-constexpr int64_t kLdsPerCU = 160 * 1024;
 constexpr double kCacheResidentBytes = 192.0 * 1024 * 1024;
 
 // Last-resort rules, used only when neither the table nor the cost model yields a kernel this
@@ -415,20 +424,17 @@ double predict_big(int64_t M, int64_t N, int64_t K)
     const double flop = 2.0 * (double)M * (double)N * (double)K;
     return std::min(2.0, std::max(0.0, std::log10(std::max(flop, 1.0)) - 10.0)) / 2.0;
 }
-double predict_us(int64_t Mi, int64_t Ni, int64_t Ki, int bm, int bn, int bk, int wm, int wn, int st, int pf, int64_t ski, double big)
+double predict_us(int64_t Mi, int64_t Ni, int64_t Ki, const MfmaEntry& e, int64_t ski, double big)
 {
     const PlanModel& g = kModel;
     const int64_t kCUs = cu_count();
     const double M = (double)Mi, N = (double)Ni, K = (double)Ki;
-    const int nw = wm * wn;
-    const double tiles = (double)(((Mi + bm - 1) / bm) * ((Ni + bn - 1) / bn));
+    const int bm = e.bm, bn = e.bn, bk = e.bk, st = e.st, pf = e.pf, nw = e.wm * e.wn, tm = e.blocks_m, tn = e.blocks_n;
+    const int64_t rows = (Mi + bm - 1) / bm;
+    const double tiles = (double)(rows * ((Ni + bn - 1) / bn));
     const double kt = (double)((Ki + bk - 1) / bk);
     const double sk = (double)ski;
-    const int64_t lds = (int64_t)st * (bm + bn) * bk * 2;
-    const int tm = bm / wm / 32, tn = bn / wn / 32;
-    const int regs = tm * tn * 16 + (pf + 1) * (tm + tn) * 4 + 40;       // accumulators + fragment sets + addressing
-    const int wps = std::max(1, std::min(8, 512 / std::max(regs, 64)));  // waves per SIMD the register file admits
-    const double occ = (double)std::max<int64_t>(1, std::min<int64_t>(kLdsPerCU / lds, nw <= wps * 4 ? (wps * 4) / nw : 1));
+    const double occ = (double)e.resident;
 
     const double wgs = tiles * sk;
     const double kt_wg = std::ceil(kt / sk);
@@ -460,7 +466,7 @@ double predict_us(int64_t Mi, int64_t Ni, int64_t Ki, int bm, int bn, int bk, in
                                ? g.BWs
                                : std::min(g.BWh * (bn == 64 ? g.h64 : bn == 128 ? g.h128 : 1.0), tot_inflight / g.Lhb);
     const double writes = ski > 1 ? part : bytes_c;
-    const double tiles_m = (double)((Mi + bm - 1) / bm);
+    const double tiles_m = (double)rows;
     const double hbm_bytes = resident ? bytes_in : 2.0 * M * K + 2.0 * K * N * (1.0 + g.rr * (std::min(tiles_m, 8.0) - 1.0));
     const double t_main = std::max(cu_time, hbm_bytes / bw_read * 1e-3) + writes / (co <= 1.0 ? g.BWw1 : g.BWw2) * 1e-3;
     const double t_red = ski > 1 ? g.Tr0 + g.Tr1 * std::ceil(sk / 8.0) + (part + bytes_c) / g.BWr * 1e-3 : 0.0;
@@ -655,7 +661,7 @@ bool evaluate_model(int64_t M, int64_t N, int64_t K, Spec* out, bool b_row_major
         const int64_t ktiles = (K + e.bk - 1) / e.bk;
         for (int sk0 : split_candidates(t, ktiles)) {
             const int64_t sk = effective_splits(ktiles, sk0);
-            double us = predict_us(M, N, K, e.bm, e.bn, e.bk, e.wm, e.wn, e.st, e.pf, sk, big);
+            double us = predict_us(M, N, K, e, sk, big);
             const bool fuse = sk > 1 && fused_delta_us(M, N, sk) < 0.0 && (int64_t)t * (int64_t)sizeof(int) <= (int64_t)kCounterBytes;
             if (fuse) us += fused_delta_us(M, N, sk);
             if (us < best) {
@@ -1021,8 +1027,7 @@ bool phased_choice(int64_t M, int64_t N, int64_t K, bool row_b, int64_t b_ld, co
         if (!pick.ph && !pick.sm && !pick.ps && pick.mi == 32) {
             const MfmaEntry* e = find_entry(pick);
             if (e && !e->deep)
-                limit = 0.95 * 1.12 * predict_us(M, N, K, pick.bm, pick.bn, pick.bk, pick.wm, pick.wn, pick.st, pick.pf,
-                                                 effective_splits((K + pick.bk - 1) / pick.bk, pick.sk), predict_big(M, N, K));
+                limit = 0.95 * 1.12 * predict_us(M, N, K, *e, effective_splits((K + pick.bk - 1) / pick.bk, pick.sk), predict_big(M, N, K));
         }
         const PhasedTile* best = nullptr;
         int best_sk = 1;
@@ -1111,12 +1116,12 @@ bool predict_spec_us(int64_t M, int64_t N, int64_t K, const Spec& s, double* us)
         *us = 1e300;
         for (const MfmaEntry& e : registry()) {
             if (e.bm != s.bm || e.bn != s.bn || e.deep || e.mi != 32) continue;
-            *us = std::min(*us, predict_us(M, N, K, e.bm, e.bn, e.bk, e.wm, e.wn, e.st, e.pf, effective_splits((K + e.bk - 1) / e.bk, s.sk), predict_big(M, N, K)));
+            *us = std::min(*us, predict_us(M, N, K, e, effective_splits((K + e.bk - 1) / e.bk, s.sk), predict_big(M, N, K)));
         }
         return true;
     }
     const int64_t eff = effective_splits((K + s.bk - 1) / s.bk, s.sk);
-    *us = predict_us(M, N, K, s.bm, s.bn, s.bk, s.wm, s.wn, s.st, s.pf, eff, predict_big(M, N, K));
+    *us = predict_us(M, N, K, *own, eff, predict_big(M, N, K));
     if (s.fr && eff > 1) *us += fused_delta_us(M, N, eff);
     return true;
 }

@@ -45,6 +45,8 @@ struct MfmaEntry {
     // several problems in one launch (null where there is none)
     void (*batch)(BatchArgs) = nullptr;
     void (*batch_tn)(BatchArgs) = nullptr;
+    // for the cost model, filled in by registry(): 32 x 32 blocks of a wave's tile, workgroups that a compute unit holds
+    int blocks_m = 0, blocks_n = 0, resident = 0;
 };
 
 template <class C> constexpr bool has_phased()
