@@ -562,59 +562,94 @@ bool streams_any_b(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l)
     return M <= 32 || (K >= 256 && 2.0 * (double)K * (double)N >= 32.0 * 1048576.0);
 }
 
-// Few rows of A: the nearest of some four thousand measured problems (few_rows.inc) instead of the models' pick.  The models
-// above are fitted to operands that the last-level cache holds (large tiles) or know one kernel of each family (streaming): on
-// problems whose weights come from HBM their picks are 12 % slower than the fastest kernel, up to 1.6 times where 256-column tiles
-// leave a third of the chip idle in their only round (4 x 23424 x 5120, column-major B: 63 us, in 128-column tiles 42).
+// Few rows of A: the nearest of some six thousand measured problems (few_rows.inc; few_rows.py gathers, builds and evaluates them) instead
+// of the models' pick.  The models above are fitted to operands that the last-level cache holds (large tiles) or know one kernel of each
+// family (streaming): their picks are 12 % slower than the fastest kernel from HBM and 14 % from the cache, up to 1.6 times where
+// 256-column tiles leave a third of the chip idle in their only round (4 x 23424 x 5120, column-major B: 63 us, in 128-column tiles 42).
+// A row lists what is within 5 % of the best: up to 32 MiB of weights by the geometric mean of the times from HBM and from the cache, where
+// a list from HBM alone loses in the other state; above, by the time from HBM (up to 64 MiB by the mean: 27 of the picks below more
+// than 10 % slower from HBM, not 19: 64-column tiles of full K, 14 % slower from HBM and 20 % faster from the cache than split ones).
 // Distance = 0.3 |log2 ratio of M| + |log2 ratio of N| + |log2 ratio of K|, and a quarter more across 16384 and 32768 columns, where
-// 64-column tiles begin another round; at most 0.3.  A pick that is among the neighbour's fastest stays, one that needs no
-// workspace is not traded for a split (as in phased_choice), and a split not for one of more planes unless these stay below the
-// 2 MiB from which an allocation costs 60 us (and so far within the static scratch); nor one that needs more rounds of workgroups
-// than the neighbour did, other than by its more columns (4 x 5480 x 12912: 258 in two rounds 45 us, the model's pick 33).
-// 976 problems held out: 594 change, all together 8.9 % faster in the geometric mean (column-major B 12.7 %), 12 slower by more than
-// 3 %; 3.1 % from the fastest kernel of each.  The strips of resident A stand in rows of K >= 1200 only: on a shorter K they win less
-// than 5 % cold and lose as much from the cache (1 x 18352 x 808: 10.3 -> 8.2 us cold, 4.9 -> 6.3 warm).
+// 64-column tiles begin another round; at most 0.3.  A pick that is on the list stays.  One that needs no workspace is not traded for a
+// split (as in phased_choice), and a split not for one of more planes unless these stay below the 2 MiB from which an allocation
+// costs 60 us (and so far within the static scratch); nor is a large tile taken that needs more rounds of workgroups than the neighbour's
+// did, other than in proportion to its columns (within 5 %; 4 x 5480 x 12912: 258 in two rounds 45 us, the model's pick 33).  A fused
+// reduction in the place of two launches is 5 % faster from HBM and 7 % from the cache where it is taken, but clears its counters in
+// every new plan: 5 x 3840 x 3840 through the one-call wrapper 20.7 us, with counters 24.5.  The other way, a launch more, only from 16 MiB
+// of weights on: below, the launches are most of a call (12 x 1200 x 5360 from the cache up to 1.8 times, 3 x 1920 x 1920 1.4).
+// Where no measured problem of column-major B is near -- beyond 65536 columns they are few -- up to 16 rows, from 16384 columns and for
+// 1200 <= K <= 4096 take resident A: 54 problems of more columns than that 1.33 times faster than the model's picks, 1.15 than the
+// best other kernel.
+// 4877 problems of two seeds that the rows did not come from: 2509 choices differ from the models', 1.17 times faster from HBM and 1.15 from the
+// cache; 96 and 184 of them are slower by more than 3 %, 19 and 54 by 10 % (`few_rows.py build --without`, `evaluate --against`).
 // Not for operands that would be copied: the choice between copies and direct_choice compares with the models' pick.
 constexpr double kCheapAlloc = 2097152.0 - 65536.0;      // bytes of planes beside the counters below hipMalloc's 2 MiB step
-struct FewRow { unsigned short m; unsigned n, k; signed char spec[5]; };
+struct FewRow { unsigned short m; unsigned n, k; signed char spec[8]; };
 #include "few_rows.inc"
-struct FewItem { float lm, ln, lk; int columns; const FewRow* row; };
+struct FewItem { float ln, lk, lm; int columns; };
+// Rows stand in quarters of an octave of N and by K in each, so that a search looks at those within reach in both: some sixty of four
+// thousand.  Nothing is allocated.
+int columns_quarter(int64_t n)
+{
+    const int top = 63 - __builtin_clzll((unsigned long long)n);
+    return 4 * top + (int)((n << 2 >> top) & 3);
+}
 template <size_t COUNT>
-struct FewIndex {                 // in order of N: a search looks at the rows within reach of its N, a tenth of them.  Nothing is allocated.
+struct FewIndex {
     FewItem items[COUNT];
+    unsigned short start[4 * 32 + 1] = {};       // of a quarter's rows
     explicit FewIndex(const FewRow (&rows)[COUNT])
     {
-        for (size_t i = 0; i < COUNT; ++i)
-            items[i] = {std::log2((float)rows[i].m), std::log2((float)rows[i].n), std::log2((float)rows[i].k), std::min(3, (int)((rows[i].n + 16383) / 16384)), &rows[i]};
-        std::sort(items, items + COUNT, [](const FewItem& x, const FewItem& y) { return x.ln != y.ln ? x.ln < y.ln : x.row < y.row; });
+        for (size_t i = 0; i < COUNT; ++i) {
+            items[i] = {std::log2((float)rows[i].n), std::log2((float)rows[i].k), std::log2((float)rows[i].m), std::min(3, (int)((rows[i].n + 16383) / 16384))};
+            ++start[columns_quarter(rows[i].n) + 1];
+        }
+        for (size_t q = 1; q < std::size(start); ++q) start[q] += start[q - 1];
     }
 };
-bool few_rows_choice(int64_t M, int64_t N, int64_t K, bool b_row_major, const Spec& model, Spec* out)
+struct FewKernels {
+    Spec spec[std::size(kFewSpecs)];
+    bool ok[std::size(kFewSpecs)];
+    FewKernels()
+    {
+        for (size_t i = 0; i < std::size(kFewSpecs); ++i) ok[i] = parse_spec(kFewSpecs[i], &spec[i]) && (spec[i].fam != FAM_MFMA || find_entry(spec[i]));
+    }
+};
+const FewRow* nearest_few_row(int64_t M, int64_t N, int64_t K, bool b_row_major)
 {
     static const FewIndex nn(kFewRowsNN);
     static const FewIndex tn(kFewRowsTN);
     const FewItem* const items = b_row_major ? nn.items : tn.items;
-    const FewItem* const end = items + (b_row_major ? std::size(kFewRowsNN) : std::size(kFewRowsTN));
+    const unsigned short* const start = b_row_major ? nn.start : tn.start;
     const float lm = std::log2((float)M), ln = std::log2((float)N), lk = std::log2((float)K);
     const int columns = (int)std::min<int64_t>(3, (N + 16383) / 16384);
     float best = 0.3f;
-    const FewRow* row = nullptr;
-    for (const FewItem* r = std::lower_bound(items, end, ln - best, [](const FewItem& x, float v) { return x.ln < v; }); r != end && r->ln < ln + best; ++r) {
-        const float d = 0.3f * std::fabs(lm - r->lm) + std::fabs(ln - r->ln) + std::fabs(lk - r->lk) + (columns != r->columns ? 0.25f : 0.f);
-        if (d < best) { best = d; row = r->row; }
+    const FewItem* item = nullptr;
+    for (int q = columns_quarter(std::max<int64_t>(1, (int64_t)((double)N * 0.8122))); q <= columns_quarter((int64_t)((double)N * 1.2312)); ++q) {      // 2^-0.3, 2^0.3
+        const FewItem* const end = items + start[q + 1];
+        for (const FewItem* r = std::lower_bound(items + start[q], end, lk - best, [](const FewItem& x, float v) { return x.lk < v; }); r != end && r->lk < lk + best; ++r) {
+            const float d = 0.3f * std::fabs(lm - r->lm) + std::fabs(ln - r->ln) + std::fabs(lk - r->lk) + (columns != r->columns ? 0.25f : 0.f);
+            if (d < best) { best = d; item = r; }
+        }
     }
-    if (!row) return false;
+    return item ? (b_row_major ? kFewRowsNN : kFewRowsTN) + (item - items) : nullptr;
+}
+bool few_rows_choice(int64_t M, int64_t N, int64_t K, bool b_row_major, const Spec& model, Spec* out)
+{
+    static const FewKernels kernels;
+    const FewRow* const row = nearest_few_row(M, N, K, b_row_major);
+    if (!row) return !b_row_major && M <= 16 && N >= 16384 && K >= 1200 && K <= 4096 && parse_spec("skinny,sk=1,wv=8,ra=1", out);
     auto rounds = [](const Spec& s, int64_t n) {
         const int64_t cus = cu_count();
-        if (s.fam != FAM_MFMA) return s.ra ? ((n + 15) / 16 + cus - 1) / cus : 0;
+        if (s.fam != FAM_MFMA) return (int64_t)0;
         return ((n + s.bn - 1) / s.bn * s.sk + cus - 1) / cus;
     };
-    Spec first;
     bool found = false;
     for (const signed char i : row->spec) {
-        Spec s;
-        if (i < 0 || !parse_spec(kFewSpecs[i], &s)) break;
-        if (s.fam == FAM_MFMA ? !find_entry(s) : s.ra && !skinny_strips(M <= 16 ? 1 : 2, K)) continue;
+        if (i < 0) break;
+        if (!kernels.ok[i]) continue;
+        Spec s = kernels.spec[i];
+        if (s.ra && !skinny_strips(M <= 16 ? 1 : 2, K)) continue;
         const int64_t step = s.fam == FAM_MFMA ? s.bk : skinny_step(s, !b_row_major);
         s.sk = (int)effective_splits((K + step - 1) / step, s.sk);
         if (s.sk == 1) s.fr = 0;
@@ -622,20 +657,13 @@ bool few_rows_choice(int64_t M, int64_t N, int64_t K, bool b_row_major, const Sp
             s.fr == model.fr && s.wv == model.wv && s.nr == model.nr && s.ra == model.ra)
             return false;
         const bool small = (double)s.sk * (double)M * (double)((N + 7) / 8 * 8) * 4.0 <= kCheapAlloc;
-        const bool fits = s.sk == 1 || (model.sk > 1 && (small || s.sk < model.sk || (s.sk == model.sk && s.fr <= model.fr)));
+        const bool launch_more = s.sk > 1 && s.fr < model.fr && (double)N * (double)K * 2.0 <= 16.0 * 1048576.0;
+        const bool fits = s.sk == 1 || (model.sk > 1 && !launch_more && (small || s.sk < model.sk || (s.sk == model.sk && s.fr <= model.fr)));
         const int64_t here = rounds(s, N), there = rounds(s, row->n);
-        if (!found && fits && (here <= there || 20 * here * row->n <= 21 * there * N)) { first = s; found = true; }
+        if (!found && fits && (here <= there || 20 * here * row->n <= 21 * there * N)) { *out = s; found = true; }
     }
-    if (found) *out = first;
     return found;
 }
-
-// Long column-major B and up to 16 rows, 1200 <= K <= 4096, from 16384 columns (four rounds of strips): A resident outright.  There it is
-// the fastest kernel on most of the 273 measured problems of that range, 1.10 times faster than the best other one in the geometric mean
-// and 1.18 times than the models' picks (two slower than the best other one by more than 8 %), and the measured rows lie too far apart
-// to reach all of it (1 x 32000 x 4096: 63.9 -> 43.7 us, 16 x 32000 x 4096 55.9 -> 47.1).  Fewer columns leave the last round
-// emptier (0.98-1.01 times the best other), a longer K goes through the registers in two parts (0.95).
-constexpr char kResidentA[] = "skinny,sk=1,wv=8,ra=1";
 
 bool evaluate_model(int64_t M, int64_t N, int64_t K, Spec* out, bool b_row_major, bool measured)
 {
@@ -676,8 +704,7 @@ bool evaluate_model(int64_t M, int64_t N, int64_t K, Spec* out, bool b_row_major
     }
     if (!found || !measured || M > 32) return found;
     Spec near;
-    if (!b_row_major && M <= 16 && N >= 16384 && K >= 1200 && K <= 4096 && parse_spec(kResidentA, &near)) *out = near;
-    else if ((!b_row_major || 2.0 * (double)K * (double)N < 256.0 * 1048576.0) && few_rows_choice(M, N, K, b_row_major, *out, &near)) *out = near;
+    if ((!b_row_major || 2.0 * (double)K * (double)N < 256.0 * 1048576.0) && few_rows_choice(M, N, K, b_row_major, *out, &near)) *out = near;
     return found;
 }
 

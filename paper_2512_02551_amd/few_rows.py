@@ -1,0 +1,301 @@
+"""Measured problems behind hgemm_plan()'s choice for up to 32 rows of A that are not in the dispatch table.
+
+Decoding multiplies a handful of rows by weights that come from HBM.  The cost model of plan_model.py is fitted to operands in
+the last-level cache and to one schedule of each family; here random problems of that kind are timed with every kernel that may be
+the fastest, from HBM and from the cache, and csrc/few_rows.inc holds for each the kernels that are close to the fastest.
+few_rows_choice() in csrc/hgemm_api.hip looks up the nearest.
+
+    python -m paper_2512_02551_amd.few_rows gather --seed 1 --seconds 500 --out FILE [--against LIB]   # on the GPU
+    python -m paper_2512_02551_amd.few_rows build [--without SEED] [FILE ...]          # CPU; rewrites csrc/few_rows.inc
+    python -m paper_2512_02551_amd.few_rows evaluate [--seed SEED] [--against LIB] [FILE ...]     # CPU; the built library's choices
+
+Timing files are JSON lines {"seed": S, "shape": [M, N, K], "tn": B column-major, "cands": [[spec, us from HBM, us from the cache], ...]}
+with the kernels whose first timing was within a fifth of the fastest and the choices of the library and of those it is compared with; csrc/few_rows_timings.jsonl.gz is the set the committed rows were
+built from.  `build --without 4` leaves the problems of seed 4 out; with the library built from that, `evaluate --seed 4` tells how
+far its choices on problems it has not seen are from the fastest, and with --against what another build of the library (of an earlier
+commit, say) would have taken.
+"""
+from __future__ import annotations
+
+import argparse
+import ctypes
+import gzip
+import json
+import math
+import os
+import re
+import sys
+
+import numpy as np
+
+_HERE = os.path.dirname(os.path.abspath(__file__))
+DATA = os.path.join(_HERE, "csrc", "few_rows_timings.jsonl.gz")
+INC = os.path.join(_HERE, "csrc", "few_rows.inc")
+
+# Tiles of 32 rows; the streaming family's kernels come from hgemm_candidates().
+TILES = ["bm=32,bn=64,bk=64,wm=1,wn=2,st=4,pf=3", "bm=32,bn=128,bk=64,wm=1,wn=4,st=4,pf=3", "bm=32,bn=128,bk=128,wm=1,wn=4,st=4,pf=3",
+         "bm=32,bn=192,bk=64,wm=1,wn=2,st=4,pf=3", "bm=32,bn=256,bk=64,wm=1,wn=4,st=4,pf=3"]
+RESIDENT_A = "skinny,sk=1,wv=8,ra=1"
+
+
+def number(spec: str, key: str, default: int = 0) -> int:
+    m = re.search(rf"\b{key}=(\d+)", spec)
+    return int(m[1]) if m else default
+
+
+def problem(rng):
+    """Half the products of a transformer layer and a quarter output heads, at widths in use, and a quarter any multiples of 8."""
+    def size(lo, hi, step=1):
+        return int(min(max(round(lo * (hi / lo) ** rng.random() / step) * step, lo), hi))
+
+    M, tn, kind = size(1, 32), rng.random() < 0.5, rng.random()
+    if kind < 0.5:
+        w = size(1024, 8192, 128)
+        up = int(w * rng.uniform(2.5, 4.0)) // 128 * 128
+        N, K = rng.choice([(w, w), (up, w), (w, up), (up + w, w)])
+    elif kind < 0.75:
+        N, K = size(8000, 160000, 8), size(512, 8192, 8)
+    else:
+        N, K = size(512, 65536, 8), size(512, 16384, 8)
+    return (M, N, K, tn) if N * K <= 1 << 29 else problem(rng)
+
+
+def choice(path, M, N, K, tn):
+    """What a build of the library runs the problem on (None: the package's own build)."""
+    import paper_2512_02551_amd as hg
+
+    lay = hg.Layouts.make(b_col_major=tn)
+    if path is None:
+        return hg.plan_choice(M, N, K, lay).split(": ", 1)[1]
+    hg.load()          # binds the HIP runtime that both builds then share
+    i64, buf = ctypes.c_int64, ctypes.create_string_buffer(512)
+    assert ctypes.CDLL(os.path.abspath(path)).hgemm_plan_choice(i64(M), i64(N), i64(K), ctypes.byref(lay), buf, ctypes.c_size_t(512)) == 0
+    return buf.value.decode().split(": ", 1)[1]
+
+
+def specs_to_time(hg, M, N, K, tn):
+    out = []
+    for t in TILES:
+        tiles, ksteps = -(-N // number(t, "bn")), -(-K // number(t, "bk"))
+        for sk in (1, 2, 3, 4, 6, 8, 12, 16):
+            if sk > 1 and (ksteps // sk < 2 or tiles * sk > 2048 or sk * M * N * 4 > 24 << 20):
+                break
+            out.append(f"mfma,{t},sk={sk},gm=8")
+            if sk > 1 and sk * M * N * 4 <= 3 << 20:
+                out.append(out[-1] + ",fr=1")
+    out += [s for s in hg.candidates(M, N, K, hg.Layouts.make(b_col_major=tn)) if s.startswith("skinny") and "wv=16" not in s and (not tn or number(s, "sk") == 1)]
+    return out
+
+
+def gather(seed: int, seconds: float, path: str, against):
+    import random
+    import time
+
+    import torch
+
+    import paper_2512_02551_amd as hg
+
+    hg.load()
+    sh = torch.cuda.current_stream().cuda_stream
+    rng = random.Random(seed)
+    pool = torch.empty(3 << 28, dtype=torch.float16, device="cuda")           # operand sets are cut from here
+    part = torch.randn(1 << 26, device="cuda").mul_(0.02).half()
+    for i in range(0, pool.numel(), part.numel()):
+        pool[i:i + part.numel()] = part
+    c = torch.empty(32 * 160000, dtype=torch.float16, device="cuda")
+
+    def timed(p, sets, reps):
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record()
+        p.run_many(reps, sets, sh)          # all sets have one C: every call is a launch of its own
+        e1.record()
+        e1.synchronize()
+        return e0.elapsed_time(e1) / reps * 1e3
+
+    t0, done = time.time(), 0
+    with open(path, "w") as f:
+        while time.time() - t0 < seconds:
+            M, N, K, tn = problem(rng)
+            lay = hg.Layouts.make(b_col_major=tn)
+            elems = (M * K + 127) // 128 * 128 + N * K
+            n = max(1, min(64, pool.numel() // elems, int(6e8 // (2 * elems)) + 1))
+            assert n * elems <= pool.numel() and M * N <= c.numel(), (M, N, K)
+            base = pool.data_ptr()
+            sets = [(base + 2 * i * elems, base + 2 * (i * elems + elems - N * K), c.data_ptr()) for i in range(n)]
+            first, plans = {}, {}
+            chosen = [choice(lib, M, N, K, tn) for lib in [None] + against]
+            for s in dict.fromkeys(chosen + specs_to_time(hg, M, N, K, tn)):
+                try:
+                    p = hg.Plan(M, N, K, lay, s)
+                except hg.HgemmError:
+                    continue
+                if p.describe() == s:
+                    timed(p, sets, 2)
+                    first[s] = timed(p, sets, 12)
+                    if s in chosen or first[s] <= 1.2 * min(first.values()):
+                        plans[s] = p
+                        continue
+                p.destroy()
+            near = [s for s in plans if s in chosen or first[s] <= 1.2 * min(first.values())]
+            times = {s: ([], []) for s in near}
+            reps = max(4, min(60, int(300 / min(first.values()))))
+            for _ in range(5):
+                for s in near:
+                    times[s][0].append(timed(plans[s], sets, reps))
+            for _ in range(5):
+                for s in near:
+                    times[s][1].append(timed(plans[s], sets[:1], reps))
+            for p in plans.values():
+                p.destroy()
+            cands = [[s] + [round(float(np.median(v[1:])), 2) for v in times[s]] for s in near]
+            f.write(json.dumps({"seed": seed, "shape": [M, N, K], "tn": tn, "cands": cands}) + "\n")
+            f.flush()
+            done += 1
+            if done % 50 == 0:
+                print(f"{done} problems, {time.time() - t0:.0f} s", flush=True)
+
+
+def load(paths):
+    rows = []
+    for p in paths:
+        with (gzip.open if p.endswith(".gz") else open)(p, "rt") as f:
+            rows += [json.loads(line) for line in f if line.strip()]
+    for r in rows:          # slower from the cache than from HBM: the host was late with a launch
+        r["cands"] = [[s, a, min(a, b)] for s, a, b in r["cands"]]
+    return rows
+
+
+# The rows.  Up to 32 MiB of weights a kernel's score on a problem is the geometric mean of its time from HBM and its time from the cache, each
+# over the shortest: calls come with operands in either place, and a rule fitted to one of them loses in the other.  Above, the time from
+# HBM alone: no program that does anything else between two calls finds so much in the cache again.
+NEIGHBOURS, WITHIN, LISTED, MISSING, REACH, CACHED = 10, 1.05, 8, 1.3, 0.3, 32 << 20
+
+
+def columns(n):
+    return np.minimum(3, -(-n // 16384))
+
+
+def distances(shape, shapes):
+    """few_rows_choice()'s measure: a third of an octave of M counts as a tenth of N or K, and crossing 16384 or 32768 columns a quarter."""
+    d = np.abs(np.log2(shapes[:, 0]) - math.log2(shape[0])) * 0.3 + np.abs(np.log2(shapes[:, 1]) - math.log2(shape[1])) + np.abs(np.log2(shapes[:, 2]) - math.log2(shape[2]))
+    return d + 0.25 * (columns(shapes[:, 1]) != columns(shape[1]))
+
+
+def scores(row):
+    cold, warm = min(c[1] for c in row["cands"]), min(c[2] for c in row["cands"])
+    both = 2 * row["shape"][1] * row["shape"][2] <= CACHED
+    return {s: min(MISSING, math.sqrt(a / cold * b / warm) if both else a / cold) for s, a, b in row["cands"]}
+
+
+def can_run(spec, shape):
+    """Resident A is compiled for as much of K as its registers hold."""
+    return spec != RESIDENT_A or shape[2] <= (8192 if shape[0] <= 16 else 4096)
+
+
+def build(rows):
+    """Per layout: [(shape, [specs, best first])].  The list of a problem comes from its nearest neighbours, itself among them: what
+    they score, nearer ones weighted more.  Problems that a kept neighbour speaks for are left out."""
+    import random
+
+    out = {}
+    for tn in (False, True):
+        sel = [r for r in rows if r["tn"] == tn]
+        shapes = np.array([r["shape"] for r in sel], dtype=np.int64)
+        points = [scores(r) for r in sel]
+        lists = []
+        for r in sel:
+            d = distances(r["shape"], shapes)
+            near = np.argsort(d, kind="stable")[:NEIGHBOURS]
+            total = {}
+            for s in set().union(*(points[j] for j in near)):
+                w = {j: 1.0 / (0.05 + d[j]) for j in near if can_run(s, sel[j]["shape"])}
+                total[s] = sum(wj * points[j].get(s, MISSING) for j, wj in w.items()) / sum(w.values())
+            best = min(total.values())
+            lists.append(sorted((s for s in total if total[s] <= best * WITHIN), key=lambda s: (total[s], s))[:LISTED])
+        order = list(range(len(sel)))
+        random.Random(3).shuffle(order)
+        kept = []
+        for i in order:
+            if not tn and 2.0 * sel[i]["shape"][1] * sel[i]["shape"][2] >= 2 ** (28 + REACH):
+                continue                    # a row-major B of 256 MiB and more is streamed: no lookup reaches this far
+            if kept:
+                d = distances(sel[i]["shape"], shapes[kept])
+                j = kept[int(np.argmin(d))]
+                if d.min() < 0.2 and lists[j][0] == lists[i][0] and 2 * len(set(lists[i]) & set(lists[j])) >= min(len(lists[i]), len(lists[j])):
+                    continue
+            kept.append(i)
+        out[tn] = sorted((tuple(sel[i]["shape"]), lists[i]) for i in kept)
+    return out
+
+
+def columns_quarter(n):
+    """The order the rows are searched in: quarters of an octave of N, K in each."""
+    top = n.bit_length() - 1
+    return 4 * top + ((n << 2 >> top) & 3)
+
+
+def write(table, note, path=INC):
+    specs = sorted({s for rows in table.values() for _, l in rows for s in l})
+    text = ["// Problems of up to 32 rows of A that were timed: rows, columns, K, and the specialisations within 5 % of the best, best first (numbers of",
+            "// kFewSpecs, -1: none).  Written by `python -m paper_2512_02551_amd.few_rows build`; do not edit by hand.", f"// {note}",
+            "static const char* const kFewSpecs[] = {", *(f'    "{s}",' for s in specs), "};"]
+    for tn, name in ((False, "kFewRowsNN"), (True, "kFewRowsTN")):
+        text.append(f"static const FewRow {name}[] = {{")
+        line = "   "
+        for (m, n, k), l in sorted(table[tn], key=lambda r: (columns_quarter(r[0][1]), r[0][2], r[0])):
+            item = f" {{{m}, {n}, {k}, {{{', '.join(str(specs.index(s)) for s in l)}{', -1' * (LISTED - len(l))}}}}},"
+            if len(line) + len(item) > 150:
+                text.append(line)
+                line = "   "
+            line += item
+        text += [line, "};"]
+    with open(path, "w") as f:
+        f.write("\n".join(text) + "\n")
+
+
+def mean(v):
+    return math.exp(float(np.mean(np.log(v)))) if len(v) else float("nan")
+
+
+def report(rows, chosen, before):
+    """`chosen` and `before`: per problem a spec, or None.  Times of the one over the other, and over the fastest."""
+    for w, name in ((1, "from HBM"), (2, "from the cache")):
+        best, gain = [], []
+        for r, s, b in zip(rows, chosen, before):
+            t = {c[0]: c[w] for c in r["cands"]}
+            if s not in t or b not in t:
+                continue
+            best.append(t[s] / min(t.values()))
+            if s != b:
+                gain.append(t[b] / t[s])
+        slow = [sum(g < x for g in gain) for x in (0.97, 0.9)]
+        print(f"{name}: {len(best)} problems, {mean(best):.4f} of the fastest; {len(gain)} choices differ, {mean(gain):.4f} times faster, {slow[0]} slower by more than 3 %, {slow[1]} by 10 %")
+
+
+if __name__ == "__main__":
+    ap = argparse.ArgumentParser()
+    sub = ap.add_subparsers(dest="cmd", required=True)
+    g_ = sub.add_parser("gather")
+    g_.add_argument("--seed", type=int, required=True)
+    g_.add_argument("--seconds", type=float, default=500)
+    g_.add_argument("--out", required=True)
+    g_.add_argument("--against", action="append", default=[], metavar="LIB")
+    b_ = sub.add_parser("build")
+    b_.add_argument("--without", type=int, default=None, metavar="SEED")
+    b_.add_argument("files", nargs="*", default=[DATA])
+    e_ = sub.add_parser("evaluate")
+    e_.add_argument("--seed", type=int, default=None)
+    e_.add_argument("--against", default=None, metavar="LIB")
+    e_.add_argument("files", nargs="*", default=[DATA])
+    args = ap.parse_args()
+    if args.cmd == "build":
+        rows = [r for r in load(args.files) if r["seed"] != args.without]
+        table = build(rows)
+        write(table, f"From {len(rows)} random problems, each row the mean of the {NEIGHBOURS} nearest; problems that a kept neighbour speaks for are left out.")
+        print(len(rows), "problems,", {("tn" if t else "nn"): len(v) for t, v in table.items()}, "rows")
+    elif args.cmd == "evaluate":
+        rows = [r for r in load(args.files) if args.seed in (None, r["seed"])]
+        chosen = [choice(None, *r["shape"], r["tn"]) for r in rows]
+        report(rows, chosen, [choice(args.against, *r["shape"], r["tn"]) for r in rows] if args.against else chosen)
+    elif args.cmd == "gather":
+        gather(args.seed, args.seconds, args.out, args.against)
