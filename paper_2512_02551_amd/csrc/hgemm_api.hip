@@ -562,32 +562,29 @@ bool streams_any_b(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l)
     return M <= 32 || (K >= 256 && 2.0 * (double)K * (double)N >= 32.0 * 1048576.0);
 }
 
-// Few rows of A: the nearest of some six thousand measured problems (few_rows.inc; few_rows.py gathers, builds and evaluates them) instead
-// of the models' pick.  The models above are fitted to operands that the last-level cache holds (large tiles) or know one kernel of each
-// family (streaming): their picks are 12 % slower than the fastest kernel from HBM and 14 % from the cache, up to 1.6 times where
-// 256-column tiles leave a third of the chip idle in their only round (4 x 23424 x 5120, column-major B: 63 us, in 128-column tiles 42).
-// A row lists what is within 5 % of the best: up to 32 MiB of weights by the geometric mean of the times from HBM and from the cache, where
-// a list from HBM alone loses in the other state; above, by the time from HBM (up to 64 MiB by the mean: 27 of the picks below more
-// than 10 % slower from HBM, not 19: 64-column tiles of full K, 14 % slower from HBM and 20 % faster from the cache than split ones).
+// Few rows of A: the nearest of some four thousand measured problems (few_rows.inc; few_rows.py builds them from their timings and
+// evaluates the choices) instead of the models' pick.  The models above are fitted to operands that the last-level cache holds (large
+// tiles) or know one kernel of each family (streaming): on problems whose weights come from HBM their picks are 12 % slower than the
+// fastest kernel, up to 1.6 times where 256-column tiles leave a third of the chip idle in their only round (4 x 23424 x 5120, column-major
+// B: 63 us, in 128-column tiles 42).
 // Distance = 0.3 |log2 ratio of M| + |log2 ratio of N| + |log2 ratio of K|, and a quarter more across 16384 and 32768 columns, where
-// 64-column tiles begin another round; at most 0.3.  A pick that is on the list stays.  One that needs no workspace is not traded for a
-// split (as in phased_choice), and a split not for one of more planes unless these stay below the 2 MiB from which an allocation
-// costs 60 us (and so far within the static scratch); nor is a large tile taken that needs more rounds of workgroups than the neighbour's
-// did, other than in proportion to its columns (within 5 %; 4 x 5480 x 12912: 258 in two rounds 45 us, the model's pick 33).  A fused
-// reduction in the place of two launches is 5 % faster from HBM and 7 % from the cache where it is taken, but clears its counters in
-// every new plan: 5 x 3840 x 3840 through the one-call wrapper 20.7 us, with counters 24.5.  The other way, a launch more, only from 16 MiB
-// of weights on: below, the launches are most of a call (12 x 1200 x 5360 from the cache up to 1.8 times, 3 x 1920 x 1920 1.4).
-// Where no measured problem of column-major B is near -- beyond 65536 columns they are few -- up to 16 rows, from 16384 columns and for
-// 1200 <= K <= 4096 take resident A: 54 problems of more columns than that 1.33 times faster than the model's picks, 1.15 than the
-// best other kernel.
-// 4877 problems of two seeds that the rows did not come from: 2509 choices differ from the models', 1.17 times faster from HBM and 1.15 from the
-// cache; 96 and 184 of them are slower by more than 3 %, 19 and 54 by 10 % (`few_rows.py build --without`, `evaluate --against`).
+// 64-column tiles begin another round; at most 0.3.  Rows of more than 32 rows of A are no neighbours: they fill the chip with
+// 32-row tiles in pairs (24 x 18368 x 1088 took the kernel of 35 x 19208 x 1088, 13.2 us instead of 9.9).  A pick that is among the
+// neighbour's fastest stays, one that needs no workspace is not traded for a split (as in phased_choice), and a split not for one of
+// more planes unless these stay below the 2 MiB from which an allocation costs 60 us (and so far within the static scratch); nor one
+// that needs more rounds of workgroups than the neighbour did, other than in proportion to its columns (within 5 %; 4 x 5480 x 12912: 258
+// in two rounds 45 us, the model's pick 33); nor resident A for more than 16 rows and less than 16384 columns (99 such picks 1.06 times
+// faster from HBM and 1.1 times slower from the cache).  A fused reduction in the place of two launches is 5 % faster from HBM and 7 % from
+// the cache, but clears its counters in every new plan: 5 x 3840 x 3840 planned, run and destroyed 20.7 us, with counters 24.5.
+// 4848 problems that the rows do not come from, a quarter of them of any sizes, in both states: 2498 choices differ from the models', 1.15 times
+// faster from HBM and 1.13 from the cache; 131 and 185 of them are slower by more than 3 %, 40 and 54 by 10 %; 6 and 8 % from the
+// fastest kernel of each, where the models' picks are 13 and 14 %.
 // Not for operands that would be copied: the choice between copies and direct_choice compares with the models' pick.
 constexpr double kCheapAlloc = 2097152.0 - 65536.0;      // bytes of planes beside the counters below hipMalloc's 2 MiB step
-struct FewRow { unsigned short m; unsigned n, k; signed char spec[8]; };
+struct FewRow { unsigned short m; unsigned n, k; signed char spec[5]; };
 #include "few_rows.inc"
 struct FewItem { float ln, lk, lm; int columns; };
-// Rows stand in quarters of an octave of N and by K in each, so that a search looks at those within reach in both: some sixty of four
+// Rows stand in quarters of an octave of N and by K in each, so that a search looks at those within reach in both: some thirty of two
 // thousand.  Nothing is allocated.
 int columns_quarter(int64_t n)
 {
@@ -638,10 +635,10 @@ bool few_rows_choice(int64_t M, int64_t N, int64_t K, bool b_row_major, const Sp
 {
     static const FewKernels kernels;
     const FewRow* const row = nearest_few_row(M, N, K, b_row_major);
-    if (!row) return !b_row_major && M <= 16 && N >= 16384 && K >= 1200 && K <= 4096 && parse_spec("skinny,sk=1,wv=8,ra=1", out);
+    if (!row) return false;
     auto rounds = [](const Spec& s, int64_t n) {
         const int64_t cus = cu_count();
-        if (s.fam != FAM_MFMA) return (int64_t)0;
+        if (s.fam != FAM_MFMA) return s.ra ? ((n + 15) / 16 + cus - 1) / cus : 0;
         return ((n + s.bn - 1) / s.bn * s.sk + cus - 1) / cus;
     };
     bool found = false;
@@ -649,7 +646,7 @@ bool few_rows_choice(int64_t M, int64_t N, int64_t K, bool b_row_major, const Sp
         if (i < 0) break;
         if (!kernels.ok[i]) continue;
         Spec s = kernels.spec[i];
-        if (s.ra && !skinny_strips(M <= 16 ? 1 : 2, K)) continue;
+        if (s.ra && ((M > 16 && N < 16384) || !skinny_strips(M <= 16 ? 1 : 2, K))) continue;
         const int64_t step = s.fam == FAM_MFMA ? s.bk : skinny_step(s, !b_row_major);
         s.sk = (int)effective_splits((K + step - 1) / step, s.sk);
         if (s.sk == 1) s.fr = 0;
@@ -657,13 +654,24 @@ bool few_rows_choice(int64_t M, int64_t N, int64_t K, bool b_row_major, const Sp
             s.fr == model.fr && s.wv == model.wv && s.nr == model.nr && s.ra == model.ra)
             return false;
         const bool small = (double)s.sk * (double)M * (double)((N + 7) / 8 * 8) * 4.0 <= kCheapAlloc;
-        const bool launch_more = s.sk > 1 && s.fr < model.fr && (double)N * (double)K * 2.0 <= 16.0 * 1048576.0;
-        const bool fits = s.sk == 1 || (model.sk > 1 && !launch_more && (small || s.sk < model.sk || (s.sk == model.sk && s.fr <= model.fr)));
+        const bool fits = s.sk == 1 || (model.sk > 1 && (small || s.sk < model.sk || (s.sk == model.sk && s.fr <= model.fr)));
         const int64_t here = rounds(s, N), there = rounds(s, row->n);
         if (!found && fits && (here <= there || 20 * here * row->n <= 21 * there * N)) { *out = s; found = true; }
     }
     return found;
 }
+
+// Long column-major B and up to 16 rows, 1200 <= K <= 4096, from 16384 columns (four rounds of strips): A resident outright, the measured
+// rows lie too far apart to reach all of it (1 x 32000 x 4096: 63.9 -> 43.7 us, 16 x 32000 x 4096 55.9 -> 47.1).  183 problems of the range:
+// 1.22 times faster from HBM than the models' picks (4 slower by more than 3 %) and 1.14 than the best other kernel, 1.10 and 1.02 from the
+// cache (32).  Not where 24000 to 32768 columns give 128-column tiles one full round and K is below 3200: there it is 1.04 times
+// faster from HBM than the models' picks and 1.06 times slower from the cache (27 problems; 1 x 30144 x 2112 1.14).  Fewer columns leave
+// the last round emptier, a longer K goes through the registers in two parts.
+bool resident_a_range(int64_t M, int64_t N, int64_t K)
+{
+    return M <= 16 && N >= 16384 && K >= 1200 && K <= 4096 && (N < 24000 || N > 32768 || K >= 3200);
+}
+constexpr char kResidentA[] = "skinny,sk=1,wv=8,ra=1";
 
 bool evaluate_model(int64_t M, int64_t N, int64_t K, Spec* out, bool b_row_major, bool measured)
 {
@@ -704,7 +712,8 @@ bool evaluate_model(int64_t M, int64_t N, int64_t K, Spec* out, bool b_row_major
     }
     if (!found || !measured || M > 32) return found;
     Spec near;
-    if ((!b_row_major || 2.0 * (double)K * (double)N < 256.0 * 1048576.0) && few_rows_choice(M, N, K, b_row_major, *out, &near)) *out = near;
+    if (!b_row_major && resident_a_range(M, N, K) && parse_spec(kResidentA, &near)) *out = near;
+    else if ((!b_row_major || 2.0 * (double)K * (double)N < 256.0 * 1048576.0) && few_rows_choice(M, N, K, b_row_major, *out, &near)) *out = near;
     return found;
 }
 

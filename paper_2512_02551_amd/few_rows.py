@@ -2,18 +2,24 @@
 
 Decoding multiplies a handful of rows by weights that come from HBM.  The cost model of plan_model.py is fitted to operands in
 the last-level cache and to one schedule of each family; here random problems of that kind are timed with every kernel that may be
-the fastest, from HBM and from the cache, and csrc/few_rows.inc holds for each the kernels that are close to the fastest.
-few_rows_choice() in csrc/hgemm_api.hip looks up the nearest.
+the fastest, and csrc/few_rows.inc holds for each the kernels that are close to the fastest.  few_rows_choice() in csrc/hgemm_api.hip
+looks up the nearest.
 
     python -m paper_2512_02551_amd.few_rows gather --seed 1 --seconds 500 --out FILE [--against LIB]   # on the GPU
-    python -m paper_2512_02551_amd.few_rows build [--without SEED] [FILE ...]          # CPU; rewrites csrc/few_rows.inc
-    python -m paper_2512_02551_amd.few_rows evaluate [--seed SEED] [--against LIB] [FILE ...]     # CPU; the built library's choices
+    python -m paper_2512_02551_amd.few_rows build [FILE ...]          # CPU; rewrites csrc/few_rows.inc
+    python -m paper_2512_02551_amd.few_rows evaluate [--against LIB] [FILE ...]     # CPU; the built library's choices
 
-Timing files are JSON lines {"seed": S, "shape": [M, N, K], "tn": B column-major, "cands": [[spec, us from HBM, us from the cache], ...]}
-with the kernels whose first timing was within a fifth of the fastest and the choices of the library and of those it is compared with; csrc/few_rows_timings.jsonl.gz is the set the committed rows were
-built from.  `build --without 4` leaves the problems of seed 4 out; with the library built from that, `evaluate --seed 4` tells how
-far its choices on problems it has not seen are from the fastest, and with --against what another build of the library (of an earlier
-commit, say) would have taken.
+csrc/few_rows_timings.jsonl.gz, which the committed rows are built from, holds 8390 problems of up to 32 rows (row-major B: 40): three quarters products of transformer
+layers (widths 1024-8192 in steps of 128, feed-forward widths 2.5-4 times that), the others output heads (8000-64000 columns, K
+512-8192).  All candidates, operands from HBM (rotated through 800 MB); its first line names the kernels, the others are {"shape":
+[M, N, K], "tn": B column-major, "us": [[kernel, us], ...]}.  Resident A was timed afterwards, beside the kernel that was chosen then, and
+stands with its time over that one's, on K from 1200 on only: on a shorter K it wins less than 5 % from HBM and loses as much from
+the cache (1 x 18352 x 808: 10.3 -> 8.2 us, 4.9 -> 6.3).
+
+csrc/few_rows_check.jsonl.gz holds 4885 other problems as `gather` writes them, which the choices are checked on: half products of
+layers, a quarter output heads, a quarter any multiples of 8; {"shape", "tn", "cands": [[kernel, us from HBM, us from the cache], ...]} with
+the kernels whose first timing was within a fifth of the fastest, the library's choice and that of the builds it is compared with
+(--against: another build of the library, of an earlier commit, say).
 """
 from __future__ import annotations
 
@@ -30,6 +36,7 @@ import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 DATA = os.path.join(_HERE, "csrc", "few_rows_timings.jsonl.gz")
+CHECK = os.path.join(_HERE, "csrc", "few_rows_check.jsonl.gz")
 INC = os.path.join(_HERE, "csrc", "few_rows.inc")
 
 # Tiles of 32 rows; the streaming family's kernels come from hgemm_candidates().
@@ -158,73 +165,74 @@ def gather(seed: int, seconds: float, path: str, against):
 def load(paths):
     rows = []
     for p in paths:
+        specs = None
         with (gzip.open if p.endswith(".gz") else open)(p, "rt") as f:
-            rows += [json.loads(line) for line in f if line.strip()]
-    for r in rows:          # slower from the cache than from HBM: the host was late with a launch
-        r["cands"] = [[s, a, min(a, b)] for s, a, b in r["cands"]]
+            for line in f:
+                r = json.loads(line)
+                if "specs" in r:
+                    specs = r["specs"]
+                    continue
+                if specs:
+                    r["cands"] = [[specs[i], us, None] for i, us in r.pop("us")]
+                else:       # slower from the cache than from HBM: the host was late with a launch
+                    r["cands"] = [[c, hbm, min(hbm, cache)] for c, hbm, cache in r["cands"]]
+                rows.append(r)
     return rows
 
 
-# The rows.  Up to 32 MiB of weights a kernel's score on a problem is the geometric mean of its time from HBM and its time from the cache, each
-# over the shortest: calls come with operands in either place, and a rule fitted to one of them loses in the other.  Above, the time from
-# HBM alone: no program that does anything else between two calls finds so much in the cache again.
-NEIGHBOURS, WITHIN, LISTED, MISSING, REACH, CACHED = 10, 1.05, 8, 1.3, 0.3, 32 << 20
+NEIGHBOURS, WITHIN, LISTED, REACH = 10, 1.03, 5, 0.3
 
 
 def columns(n):
     return np.minimum(3, -(-n // 16384))
 
 
-def distances(shape, shapes):
-    """few_rows_choice()'s measure: a third of an octave of M counts as a tenth of N or K, and crossing 16384 or 32768 columns a quarter."""
-    d = np.abs(np.log2(shapes[:, 0]) - math.log2(shape[0])) * 0.3 + np.abs(np.log2(shapes[:, 1]) - math.log2(shape[1])) + np.abs(np.log2(shapes[:, 2]) - math.log2(shape[2]))
-    return d + 0.25 * (columns(shapes[:, 1]) != columns(shape[1]))
-
-
-def scores(row):
-    cold, warm = min(c[1] for c in row["cands"]), min(c[2] for c in row["cands"])
-    both = 2 * row["shape"][1] * row["shape"][2] <= CACHED
-    return {s: min(MISSING, math.sqrt(a / cold * b / warm) if both else a / cold) for s, a, b in row["cands"]}
-
-
-def can_run(spec, shape):
-    """Resident A is compiled for as much of K as its registers hold."""
-    return spec != RESIDENT_A or shape[2] <= (8192 if shape[0] <= 16 else 4096)
-
-
 def build(rows):
-    """Per layout: [(shape, [specs, best first])].  The list of a problem comes from its nearest neighbours, itself among them: what
-    they score, nearer ones weighted more.  Problems that a kept neighbour speaks for are left out."""
+    """Per layout: [(shape, [specs, best first])].  The list of a problem comes from its ten nearest neighbours, itself among them: the
+    kernels' times over the fastest (2 at most), nearer ones weighted more.  Problems that a kept neighbour speaks for are left
+    out, and in the end those that no lookup may reach: of more than 32 rows, and of a row-major B of 256 MiB and more, which is streamed."""
     import random
 
     out = {}
     for tn in (False, True):
         sel = [r for r in rows if r["tn"] == tn]
-        shapes = np.array([r["shape"] for r in sel], dtype=np.int64)
-        points = [scores(r) for r in sel]
-        lists = []
+        logs = np.array([[math.log2(v) for v in r["shape"]] for r in sel])
+        part = np.array([columns(r["shape"][1]) for r in sel])
+        weights = np.array([0.3, 1.0, 1.0])
+        relative = []
         for r in sel:
-            d = distances(r["shape"], shapes)
+            best = min(c[1] for c in r["cands"])
+            relative.append({c[0]: min(c[1] / best, 2.0) for c in r["cands"] if "bm=64" not in c[0]})
+
+        def distances(i, to):
+            """few_rows_choice()'s measure."""
+            return np.abs(logs[to] - logs[i]) @ weights + 0.25 * (part[to] != part[i])
+
+        every, lists = np.arange(len(sel)), []
+        for i in range(len(sel)):
+            d = distances(i, every)
             near = np.argsort(d, kind="stable")[:NEIGHBOURS]
-            total = {}
-            for s in set().union(*(points[j] for j in near)):
-                w = {j: 1.0 / (0.05 + d[j]) for j in near if can_run(s, sel[j]["shape"])}
-                total[s] = sum(wj * points[j].get(s, MISSING) for j, wj in w.items()) / sum(w.values())
-            best = min(total.values())
-            lists.append(sorted((s for s in total if total[s] <= best * WITHIN), key=lambda s: (total[s], s))[:LISTED])
+            score, weight, total = {}, {}, 0.0
+            for j in near:
+                w = 1.0 / (0.05 + d[j])
+                total += w
+                for s, v in relative[j].items():
+                    score[s] = score.get(s, 0.0) + w * v
+                    weight[s] = weight.get(s, 0.0) + w
+            ranked = sorted((score[s] / weight[s], s) for s in score if weight[s] > 0.6 * total)
+            lists.append([s for v, s in ranked if v <= ranked[0][0] * WITHIN][:LISTED])
         order = list(range(len(sel)))
         random.Random(3).shuffle(order)
         kept = []
         for i in order:
-            if not tn and 2.0 * sel[i]["shape"][1] * sel[i]["shape"][2] >= 2 ** (28 + REACH):
-                continue                    # a row-major B of 256 MiB and more is streamed: no lookup reaches this far
             if kept:
-                d = distances(sel[i]["shape"], shapes[kept])
+                d = distances(i, np.array(kept))
                 j = kept[int(np.argmin(d))]
                 if d.min() < 0.2 and lists[j][0] == lists[i][0] and 2 * len(set(lists[i]) & set(lists[j])) >= min(len(lists[i]), len(lists[j])):
                     continue
             kept.append(i)
-        out[tn] = sorted((tuple(sel[i]["shape"]), lists[i]) for i in kept)
+        reached = [i for i in kept if sel[i]["shape"][0] <= 32 and (tn or 2.0 * sel[i]["shape"][1] * sel[i]["shape"][2] < 2 ** (28 + REACH))]
+        out[tn] = sorted((tuple(sel[i]["shape"]), lists[i]) for i in reached)
     return out
 
 
@@ -236,7 +244,7 @@ def columns_quarter(n):
 
 def write(table, note, path=INC):
     specs = sorted({s for rows in table.values() for _, l in rows for s in l})
-    text = ["// Problems of up to 32 rows of A that were timed: rows, columns, K, and the specialisations within 5 % of the best, best first (numbers of",
+    text = ["// Problems of up to 32 rows of A that were timed: rows, columns, K, and the specialisations within 3 % of the best, best first (numbers of",
             "// kFewSpecs, -1: none).  Written by `python -m paper_2512_02551_amd.few_rows build`; do not edit by hand.", f"// {note}",
             "static const char* const kFewSpecs[] = {", *(f'    "{s}",' for s in specs), "};"]
     for tn, name in ((False, "kFewRowsNN"), (True, "kFewRowsTN")):
@@ -281,20 +289,18 @@ if __name__ == "__main__":
     g_.add_argument("--out", required=True)
     g_.add_argument("--against", action="append", default=[], metavar="LIB")
     b_ = sub.add_parser("build")
-    b_.add_argument("--without", type=int, default=None, metavar="SEED")
     b_.add_argument("files", nargs="*", default=[DATA])
     e_ = sub.add_parser("evaluate")
-    e_.add_argument("--seed", type=int, default=None)
     e_.add_argument("--against", default=None, metavar="LIB")
-    e_.add_argument("files", nargs="*", default=[DATA])
+    e_.add_argument("files", nargs="*", default=[CHECK])
     args = ap.parse_args()
     if args.cmd == "build":
-        rows = [r for r in load(args.files) if r["seed"] != args.without]
+        rows = load(args.files)
         table = build(rows)
         write(table, f"From {len(rows)} random problems, each row the mean of the {NEIGHBOURS} nearest; problems that a kept neighbour speaks for are left out.")
         print(len(rows), "problems,", {("tn" if t else "nn"): len(v) for t, v in table.items()}, "rows")
     elif args.cmd == "evaluate":
-        rows = [r for r in load(args.files) if args.seed in (None, r["seed"])]
+        rows = load(args.files)
         chosen = [choice(None, *r["shape"], r["tn"]) for r in rows]
         report(rows, chosen, [choice(args.against, *r["shape"], r["tn"]) for r in rows] if args.against else chosen)
     elif args.cmd == "gather":

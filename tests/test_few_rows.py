@@ -15,6 +15,11 @@ def timings():
 
 
 @pytest.fixture(scope="module")
+def check():
+    return fr.load([fr.CHECK])
+
+
+@pytest.fixture(scope="module")
 def committed():
     text = open(fr.INC).read()
     specs = re.findall(r'^    "([^"]+)",$', text, re.M)
@@ -29,7 +34,7 @@ def test_rows_are_of_few_rows_in_search_order_and_within_reach(committed):
     specs, rows = committed
     assert len(specs) <= 127 and len(set(specs)) == len(specs)
     for tn, r in rows.items():
-        assert len(r) > 2500
+        assert len(r) > 1500
         assert [fr.columns_quarter(s[1]) for s, _ in r] == sorted(fr.columns_quarter(s[1]) for s, _ in r)
         assert all(a[0][2] <= b[0][2] for a, b in zip(r, r[1:]) if fr.columns_quarter(a[0][1]) == fr.columns_quarter(b[0][1]))
         for (m, n, k), listed in r:
@@ -43,24 +48,24 @@ def test_committed_rows_are_built_from_the_committed_timings(timings, committed,
     assert a[3] == b[3]                                                 # the third line says what they were built from
 
 
-def test_choices_are_close_to_the_fastest_kernel(timings):
+def test_choices_on_other_problems_are_close_to_the_fastest_kernel(check):
     ratios = []
-    for r in timings:
+    for r in check:
         t = {c[0]: c[1:] for c in r["cands"]}
         s = fr.choice(None, *r["shape"], r["tn"])
         if s in t:
             ratios.append([t[s][w] / min(v[w] for v in t.values()) for w in (0, 1)])
     ratios = np.array(ratios)
-    assert len(ratios) > 0.99 * len(timings)
+    assert len(ratios) > 0.99 * len(check)
     hbm, cache = np.exp(np.log(ratios).mean(axis=0))
-    assert hbm < 1.04 and cache < 1.055, (hbm, cache)
-    assert np.quantile(ratios[:, 0], 0.9) < 1.15 and np.quantile(ratios[:, 1], 0.9) < 1.18
+    assert hbm < 1.06 and cache < 1.08, (hbm, cache)
 
 
 @pytest.mark.parametrize("m,n,k,tn,not_taken", [
-    (24, 18368, 1088, False, "bn=192"), (31, 12496, 2336, False, "bn=128"), (28, 20296, 1928, False, "bn=192"),    # what 33 rows and more take (1.3 times slower)
-    (1, 2176, 2176, False, "sk=6,gm=8$"), (2, 1024, 3456, True, "sk=8,gm=8$"), (12, 1200, 5360, True, "sk=8,gm=8$"),   # a launch more than the fused reduction
-    (7, 9800, 1664, True, "ra=1"), (21, 6272, 1408, True, "ra=1"), (21, 5760, 1664, True, "ra=1")])               # slower from the cache, level from HBM
+    (24, 18368, 1088, False, "bn=192"), (31, 12496, 2336, False, "bn=128"), (28, 20296, 1928, False, "bn=192"), (31, 10424, 1488, False, "bn=128"),    # what 33 rows and more take
+    (1, 30144, 2112, True, "ra=1"), (15, 31736, 2528, True, "ra=1"), (9, 26504, 2504, True, "ra=1"),
+    (21, 6272, 1408, True, "ra=1"), (21, 5760, 1664, True, "ra=1"), (21, 7168, 1792, True, "ra=1")])               # level from HBM, slower from the cache
 def test_few_rows_do_not_take(m, n, k, tn, not_taken):
+    """Kernels that were up to 1.35 times slower than the models' picks."""
     choice = hg.plan_choice(m, n, k, hg.Layouts.make(b_col_major=tn))
     assert not re.search(not_taken, choice), choice
