@@ -1268,7 +1268,7 @@ Route route(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l)
 
 // A problem that would be copied: the kernels that read it where it lies instead?  `pick` is what the padded problem would run on;
 // a phased or persistent pick stays, and so does a B that is streamed.  A copy costs a launch and the operand three times; reading through registers costs the
-// matrix cores their even supply: 1000 x 1001 x 1003 11.0 -> 8.0 us, 500 x 501 x 503 7.4 -> 5.3, 70 x 3001 x 1001 11.3 -> 7.0, 2000 x 2001 x 2003
+// matrix cores their even supply: 1000 x 1001 x 1003 11.1 -> 8.6 us, 500 x 501 x 503 7.4 -> 5.3, 70 x 3001 x 1001 11.3 -> 7.0, 2000 x 2001 x 2003
 // 33 -> 29 (operands in the last-level cache), but 4100 x 4101 x 4103 183 -> 280.  Taken where its prediction is below 0.9 of the other way's (1.3
 // times the prediction of the pick, which was fitted warm and alone, and 0.2 us a MB copied), below 0.75 for an unsplit K of 2560 and
 // more, where it is the less certain one; and where it stays below with what operands from HBM add (in full from 16 MB on), by a tenth in
@@ -1749,7 +1749,7 @@ hgemm_status_t hgemm_run(hgemm_plan_t plan, const void* A, const void* B, void* 
 //   * Only kernels that form and add the products in the plan's own order -- unsplit, 32 x 32 x 16 instructions, k ascending,
 //     whatever the tile -- so that every result has the bits that hgemm_run gives it; not those of a specialisation that the
 //     caller chose, which is to run as it was asked for.
-//   * Operands and result of a call up to 8 MiB: 8 x 256^3 22.4 -> 3.9 us, 16 x 512 x 512 x 1024 106 -> 12, 8 x 1024^3 48 -> 20;
+//   * Operands and result of a call up to 8 MiB: 8 x 256^3 27.7 -> 4.4 us, 16 x 512 x 512 x 1024 106 -> 12, 8 x 1024^3 48 -> 20;
 //     above, a call takes 12 us and more and the launch little of it (4 x 1536^3 49.9 -> 43).
 //   * Tiles of 128 x 128 where the calls of the launch give every compute unit one (8 x 1024 x 1024 x 256: 8.6 us, in 64 x 64 tiles 11.1;
 //     8 x 768^3 12.1 against 13.9), else 64 x 64 (4 x 512 x 512 x 1024, 64 tiles of 128: 5.5 us against 8.8).

@@ -99,7 +99,7 @@ struct GemmArgs {
 // Several problems of one shape and layout in one launch (MODE_BATCH): workgroup (x, y) takes tile y of problem x, whose
 // operands are set[x]; A, B and C of the base are not used.  Problems run along x because workgroup ids are dealt round-robin
 // to the XCDs: with eight problems (or a multiple) each stays on one XCD and comes into one L2 once.  Eight of 256^3 take as
-// long as one does, 3.9 us with the launch: what bounds them is the launch and one trip to memory.
+// long as one does, 4.4 us with the launch: what bounds them is the launch and one trip to memory.
 constexpr int kBatchSets = 32;
 struct BatchArgs : GemmArgs {
     struct { const _Float16* A; const _Float16* B; _Float16* C; } set[kBatchSets];
@@ -666,7 +666,7 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(ARGS g)
     // What bounds it: the LDS, which takes the operands through the same registers once more than direct copies do, and loads
     // that touch nine lines instead of eight (16 bytes a lane at odd elements: 1000 x 1001 x 1003, column-major B, 8.6 us; at whole
     // dwords 7.5; on aligned operands the copies to LDS take 5.9).  It replaces a launch that copies both operands first: 1000 x 1001 x
-    // 1003 11.2 -> 8.6 us, 500 x 501 x 503 7.4 -> 5.3, 70 x 3001 x 1001 11.3 -> 7.0.  Writing and loading between the matrix-core
+    // 1003 11.1 -> 8.6 us, 500 x 501 x 503 7.4 -> 5.3, 70 x 3001 x 1001 11.3 -> 7.0.  Writing and loading between the matrix-core
     // instructions took a first form, which did both in one go per K-tile, from 10.2 to 8.9 us.
     typedef unsigned long long chunk16 __attribute__((ext_vector_type(2)));
     constexpr int BCPR = TN ? C::A_CPR : C::B_CPR;

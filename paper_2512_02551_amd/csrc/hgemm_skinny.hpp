@@ -396,7 +396,9 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_tn_gemm_kernel(GemmArgs g)
 // row of C, and lines of C whose parts come from several L2s cost 5 us (16 x 50257 x 4096: 78.9 -> 73.3; a contiguous run of strips for
 // each workgroup: 81).  More strips in flight than one are slower (32001 x 2048: 23.4, with two 24.7, three 26.7).
 // 16 x 50257 x 4096 84 -> 72.8 us, 1 x 50257 x 4096 81 -> 68.8, 16 x 32000 x 4096 55.9 -> 47.1, 1 x 32001 x 2048 29.9 -> 23.3,
-// 32 x 32001 x 2048 31.0 -> 27.7.  What bounds it: the stream of B, 5.6-6.0 TB/s where a kernel that only reads gets 6.2; and 2 us until A is there.
+// 32 x 32001 x 2048 31.0 -> 27.7.  What bounds it up to 16 rows: the stream of B, 5.6-6.0 TB/s where a kernel that only reads gets 6.2, and
+// 2 us until A is there.  With two blocks of rows B comes at 4.7 TB/s: a strip has twice the sums that meet in LDS and twice the 32-byte
+// pieces of C, between the same barriers (which of the two it is was not told apart).
 constexpr int kStripWaves = 8;
 template <int MB, int S, int P>
 __global__ __launch_bounds__(64 * kStripWaves, 2) void skinny_strips_kernel(GemmArgs g)

@@ -9,12 +9,13 @@ looks up the nearest.
     python -m paper_2512_02551_amd.few_rows build [FILE ...]          # CPU; rewrites csrc/few_rows.inc
     python -m paper_2512_02551_amd.few_rows evaluate [--against LIB] [FILE ...]     # CPU; the built library's choices
 
-csrc/few_rows_timings.jsonl.gz, which the committed rows are built from, holds 8390 problems of up to 32 rows (row-major B: 40): three quarters products of transformer
-layers (widths 1024-8192 in steps of 128, feed-forward widths 2.5-4 times that), the others output heads (8000-64000 columns, K
-512-8192).  All candidates, operands from HBM (rotated through 800 MB); its first line names the kernels, the others are {"shape":
-[M, N, K], "tn": B column-major, "us": [[kernel, us], ...]}.  Resident A was timed afterwards, beside the kernel that was chosen then, and
-stands with its time over that one's, on K from 1200 on only: on a shorter K it wins less than 5 % from HBM and loses as much from
-the cache (1 x 18352 x 808: 10.3 -> 8.2 us, 4.9 -> 6.3).
+csrc/few_rows_timings.jsonl.gz, which the committed rows are built from, holds 8390 problems of up to 32 rows (row-major B: 40; those of
+more than 32 count as neighbours in a mean, but make no rows): three quarters products of transformer layers (widths 1024-8192 in
+steps of 128, feed-forward widths 2.5-4 times that), the others output heads (8000-64000 columns, K 512-8192).  All candidates,
+operands from HBM (rotated through 800 MB); its first line names the kernels, the others are {"shape": [M, N, K], "tn": B column-major,
+"us": [[kernel, us], ...]}.  Resident A was timed afterwards, beside the kernel that was chosen then, and stands with its time over that
+one's, on K from 1200 on only: on a shorter K it wins less than 5 % from HBM and loses as much from the cache (1 x 18352 x 808:
+10.3 -> 8.2 us, 4.9 -> 6.3).
 
 csrc/few_rows_check.jsonl.gz holds 4885 other problems as `gather` writes them, which the choices are checked on: half products of
 layers, a quarter output heads, a quarter any multiples of 8; {"shape", "tn", "cands": [[kernel, us from HBM, us from the cache], ...]} with
@@ -30,7 +31,6 @@ import json
 import math
 import os
 import re
-import sys
 
 import numpy as np
 
@@ -42,7 +42,6 @@ INC = os.path.join(_HERE, "csrc", "few_rows.inc")
 # Tiles of 32 rows; the streaming family's kernels come from hgemm_candidates().
 TILES = ["bm=32,bn=64,bk=64,wm=1,wn=2,st=4,pf=3", "bm=32,bn=128,bk=64,wm=1,wn=4,st=4,pf=3", "bm=32,bn=128,bk=128,wm=1,wn=4,st=4,pf=3",
          "bm=32,bn=192,bk=64,wm=1,wn=2,st=4,pf=3", "bm=32,bn=256,bk=64,wm=1,wn=4,st=4,pf=3"]
-RESIDENT_A = "skinny,sk=1,wv=8,ra=1"
 
 
 def number(spec: str, key: str, default: int = 0) -> int:
