@@ -154,6 +154,24 @@ __device__ inline unsigned long long load_agent(const unsigned long long* p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The counting half of the fused split-K reduction: true for the workgroup of a tile that arrives last (all threads; `word`: one
+// int of LDS that nobody uses any more).  A wave's plane stores have to be performed before its workgroup is counted.  A workgroup barrier
+// does not see to that -- its fences order what the workgroup's own waves see of each other, for which stores on their way to
+// memory need no wait, and relaxed atomics order nothing else -- so every wave waits for its own here.  (An agent-scope
+// release would write the whole L2 back on top of it; these stores go through it as they are.)
+__device__ __forceinline__ bool last_to_arrive(int* counter, int splits, int* word, bool first_thread)
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (first_thread) {
+        const int arrived = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (arrived == splits - 1) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // clean for the next launch
+        *word = arrived;
+    }
+    __syncthreads();
+    return *word == splits - 1;
+}
+
 // The summing half of the fused split-K reduction: the workgroup that arrived last at a tile adds the
 // tile's S fp32 planes in split order, rounds once and stores fp16.  A lane owns groups of 4 columns
 // (QPR groups per tile row).  The loads are device-coherent and each costs a trip to memory, so a lane
@@ -1049,21 +1067,11 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(ARGS g)
         }
         if (FUSED) {
             // Fused reduction.  Every workgroup of a tile stores its fp32 plane with device-coherent
-            // stores, waits until they are performed (the release half of the barrier waits for all of
-            // the wave's outstanding stores), then counts itself in.  The workgroup that finds all
+            // stores, waits until they are performed, then counts itself in.  The workgroup that finds all
             // others already counted -- whichever split it is -- re-reads the S planes in split order,
             // so the sum does not depend on arrival order, rounds once and stores the tile of C.
             // Nobody waits for anybody: a workgroup that is not last simply exits.
-            __syncthreads();
-            int* flag = (int*)lds;
-            if (threadIdx.x == 0) {
-                int* ctr = g.counters + tile_id;
-                const int arrived = __hip_atomic_fetch_add(ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (arrived == g.splits - 1) __hip_atomic_store(ctr, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // clean for the next launch
-                *flag = arrived;
-            }
-            __syncthreads();
-            if (*flag != g.splits - 1) return;
+            if (!last_to_arrive(g.counters + tile_id, g.splits, (int*)lds, threadIdx.x == 0)) return;
             sum_split_planes<C::THREADS, C::BN / 4>(g, m0, n0, min(C::BM, g.M - m0), (int)threadIdx.x);
         }
     }

@@ -230,16 +230,7 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_gemm_kernel(GemmArgs g)
     // Fused reduction over the K slabs of this strip: device-coherent plane stores above, then the
     // workgroup that arrives last re-reads all planes in slab order (the result does not depend on who
     // is last), rounds once and stores.  Nobody waits for anybody.
-    __syncthreads();
-    int* flag = (int*)red;
-    if (t == 0) {
-        int* ctr = g.counters + blockIdx.x;
-        const int arrived = __hip_atomic_fetch_add(ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (arrived == g.splits - 1) __hip_atomic_store(ctr, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        *flag = arrived;
-    }
-    __syncthreads();
-    if (*flag != g.splits - 1) return;
+    if (!last_to_arrive(g.counters + blockIdx.x, g.splits, (int*)red, t == 0)) return;
     sum_split_planes<64 * WAVES, kSkinnyCols / 4>(g, 0, n0, g.M, t);
 }
 
@@ -374,16 +365,7 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_tn_gemm_kernel(GemmArgs g)
     if (!FUSED || direct) return;
 
     // fused reduction over the K slabs of these columns, as in skinny_gemm_kernel
-    __syncthreads();
-    int* flag = (int*)red;
-    if (t == 0) {
-        int* ctr = g.counters + blockIdx.x;
-        const int arrived = __hip_atomic_fetch_add(ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (arrived == g.splits - 1) __hip_atomic_store(ctr, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        *flag = arrived;
-    }
-    __syncthreads();
-    if (*flag != g.splits - 1) return;
+    if (!last_to_arrive(g.counters + blockIdx.x, g.splits, (int*)red, t == 0)) return;
     sum_split_planes<64 * WAVES, NR / 4>(g, 0, n0, g.M, t);
 }
 
