@@ -506,9 +506,11 @@ double predict_skinny_us(int64_t M, int64_t N, int64_t K, int64_t sk, bool fused
 }
 
 // The cheapest compiled configuration and split factor under the model.
-// Split-K with the reduction fused into the kernel against the two-launch form, as measured on skinny
-// shapes: the second launch (its dispatch gap and its own round trip) goes away, the planes are stored
-// device-coherently (slower per byte) and the last workgroup's re-read is a serial tail.
+// Split-K with the reduction fused into the kernel against the two-launch form, as fitted to skinny
+// shapes (M = 1 and 16): the second launch (its dispatch gap and its own round trip) goes away, the planes are stored
+// device-coherently (slower per byte) and the last workgroup's re-read is a serial tail.  Too kind to the fused form: what it chooses
+// takes, enqueued or replayed, 0.6-0.7 us longer than its two launches up to 32 rows (13 492 problems, 9-10 %) and 1.4 us beyond
+// (5138, 20 %); 2 % of it is the wait for the planes' stores in last_to_arrive().
 double fused_delta_us(int64_t M, int64_t N, int64_t sk)
 {
     const double planes_mib = (double)sk * (double)M * (double)N * 4.0 / 1048576.0;
@@ -574,8 +576,9 @@ bool streams_any_b(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l)
 // more planes unless these stay below the 2 MiB from which an allocation costs 60 us (and so far within the static scratch); nor one
 // that needs more rounds of workgroups than the neighbour did, other than in proportion to its columns (within 5 %; 4 x 5480 x 12912: 258
 // in two rounds 45 us, the model's pick 33); nor resident A for more than 16 rows and less than 16384 columns (99 such picks 1.06 times
-// faster from HBM and 1.1 times slower from the cache).  A fused reduction in the place of two launches is 5 % faster from HBM and 7 % from
-// the cache, but clears its counters in every new plan: 5 x 3840 x 3840 planned, run and destroyed 20.7 us, with counters 24.5.
+// faster from HBM and 1.1 times slower from the cache).  Where a fused reduction was timed as the fastest of a problem, its two launches take
+// 1.2 % longer from HBM and 0.5 % from the cache (692 problems), but it clears its counters in every new plan: 5 x 3840 x 3840 planned,
+// run and destroyed 20.7 us, with counters 24.5.
 // 4848 problems that the rows do not come from, a quarter of them of any sizes, in both states: 2498 choices differ from the models', 1.15 times
 // faster from HBM and 1.13 from the cache; 131 and 185 of them are slower by more than 3 %, 40 and 54 by 10 %; 6 and 8 % from the
 // fastest kernel of each, where the models' picks are 13 and 14 %.
