@@ -47,7 +47,8 @@ static const std::vector<MfmaEntry>& registry()
     return r;
 }
 
-void (*skinny_kernel(int mb, bool fused, int waves, int tn_rows))(GemmArgs);      // hgemm_skinny.hip
+void (*skinny_kernel(int mb, bool fused, int waves))(GemmArgs);                   // hgemm_skinny.hip
+SkinnyTnKernel skinny_tn_kernel(int mb, bool fused, int waves, int nr);
 void (*skinny_any_b_kernel(int mb, bool fused))(GemmArgs);
 void (*skinny_strips(int mb, int64_t K))(GemmArgs);
 
@@ -70,14 +71,22 @@ struct Spec {
     int ph = 0;     // 1 = the phased schedule of this tile (hgemm_phased.hpp)
     int di = 0;     // 1 = operands read through registers, at any element's address (MODE_DIRECT)
     int wv = 4;     // skinny family: waves per workgroup (4, 8 or 16), each taking 16 k-rows of a step
-    int nr = 16;    // skinny family, column-major B: rows of B (columns of C) per workgroup (16, 32 or 64)
+    int nr = 0;     // skinny family, column-major B: rows of B (columns of C) per workgroup (16, 32, 48 or 64; 0 = as strip_rows() has it)
     int ra = 0;     // skinny family, column-major B: 1 = A resident in registers, one workgroup per compute unit walks strips of B
 };
 
 // k-rows a workgroup of the skinny family takes per step (K slabs are whole numbers of steps) and the columns of C
 // it owns: row-major B 16 rows per wave and 128 columns, column-major B 32 k per wave and 16 columns
 static int64_t skinny_step(const Spec& s, bool tn = false) { return (tn ? 32 : 16) * s.wv; }
-static int64_t skinny_cols(const Spec& s, bool tn) { return tn ? s.nr : kSkinnyCols; }
+// Rows of a column-major B per workgroup where a spec does not say: one strip for every compute unit as far as that goes.  Few rows of A from HBM, all
+// four widths timed on some 80 problems of each range: 16 rows up to 4096 columns (the others leave compute units idle); 4097-8192 32 rows 0.92 of
+// the time of 16; 8193-12288 48 rows 0.89; 12289-16384 32 rows 0.95 (48 1.12, 64 level with 32); beyond, in several rounds, 32 rows 1.02.
+static int strip_rows(const Spec& s, int64_t N)
+{
+    if (s.nr || s.sk > 1) return s.nr ? s.nr : 16;
+    return N <= 4096 ? 16 : N <= 8192 ? 32 : N <= 12288 ? 48 : N <= 16384 ? 32 : 16;
+}
+static int64_t skinny_cols(const Spec& s, bool tn, int64_t N) { return tn ? strip_rows(s, N) : kSkinnyCols; }
 
 static std::string spec_to_string(const Spec& s)
 {
@@ -86,7 +95,7 @@ static std::string spec_to_string(const Spec& s)
     if (s.fam == FAM_SKINNY) {
         snprintf(buf, sizeof buf, "skinny,sk=%d%s", s.sk, s.fr ? ",fr=1" : "");
         if (s.wv != 4) snprintf(buf + strlen(buf), sizeof buf - strlen(buf), ",wv=%d", s.wv);
-        if (s.nr != 16) snprintf(buf + strlen(buf), sizeof buf - strlen(buf), ",nr=%d", s.nr);
+        if (s.nr) snprintf(buf + strlen(buf), sizeof buf - strlen(buf), ",nr=%d", s.nr);
         if (s.ra) snprintf(buf + strlen(buf), sizeof buf - strlen(buf), ",ra=1");
         return buf;
     }
@@ -119,6 +128,7 @@ static bool parse_spec(const char* text, Spec* out)
     else if (word("generic")) sp.fam = FAM_GENERIC;
     else return false;
     int ignored = 0;
+    sp.nr = -1;                                                // not given
     const struct { char key[4]; int* value; } keys[] = {
         {"bm", &sp.bm}, {"bn", &sp.bn}, {"bk", &sp.bk}, {"wm", &sp.wm}, {"wn", &sp.wn}, {"st", &sp.st}, {"pf", &sp.pf}, {"sk", &sp.sk},
         {"gm", &sp.gm}, {"tb", &sp.tb}, {"sm", &sp.sm}, {"fr", &sp.fr}, {"ps", &sp.ps}, {"ac", &sp.ac}, {"mi", &sp.mi}, {"ph", &sp.ph},
@@ -148,8 +158,9 @@ static bool parse_spec(const char* text, Spec* out)
     if (sp.ph > 1 || (sp.ph && (sp.fam != FAM_MFMA || sp.sm || sp.fr || sp.ps || sp.tb || sp.ac == 16))) return false;
     if (sp.di > 1 || (sp.di && (sp.fam != FAM_MFMA || sp.sm || sp.ps || sp.tb || sp.ph || sp.ac == 16 || sp.mi != 32))) return false;
     if ((sp.wv != 4 && sp.wv != 8 && sp.wv != 16) || (sp.wv != 4 && sp.fam != FAM_SKINNY)) return false;
-    if ((sp.nr != 16 && sp.nr != 32 && sp.nr != 64) || (sp.nr != 16 && sp.fam != FAM_SKINNY)) return false;
-    if (sp.ra > 1 || (sp.ra && (sp.fam != FAM_SKINNY || sp.wv != kStripWaves || sp.nr != 16 || sp.sk > 1))) return false;
+    if (sp.nr != -1 && (sp.nr < 16 || sp.nr > 64 || sp.nr % 16 || (sp.nr != 16 && sp.fam != FAM_SKINNY))) return false;
+    if (sp.nr == -1 || sp.fam != FAM_SKINNY) sp.nr = 0;
+    if (sp.ra > 1 || (sp.ra && (sp.fam != FAM_SKINNY || sp.wv != kStripWaves || (sp.nr != 0 && sp.nr != 16) || sp.sk > 1))) return false;
     *out = sp;
     return true;
 }
@@ -178,7 +189,8 @@ struct hgemm_plan_s {
     hgemm_layouts_t lay;        // with packed leading dimensions resolved
     Spec spec;
     const MfmaEntry* entry;     // null for the generic and skinny families
-    void (*skinny)(GemmArgs);   // the skinny family's kernel, else null
+    void (*skinny)(GemmArgs);   // the skinny family's kernel, else null, and its dynamic LDS
+    int skinny_lds;
     void (*kernel)(GemmArgs);   // the large-tile family's main kernel and its dynamic LDS
     void (*kernel_any)(GemmArgs);   // what runs in its place for a narrow C or a B of fewer rows than K (the same, or its twin)
     int kernel_lds;
@@ -580,8 +592,8 @@ bool streams_any_b(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l)
 // 1.2 % longer from HBM and 0.5 % from the cache (692 problems), but it clears its counters in every new plan: 5 x 3840 x 3840 planned,
 // run and destroyed 20.7 us, with counters 24.5.
 // 4848 problems that the rows do not come from, a quarter of them of any sizes, in both states: 2498 choices differ from the models', 1.15 times
-// faster from HBM and 1.13 from the cache; 131 and 185 of them are slower by more than 3 %, 40 and 54 by 10 %; 6 and 8 % from the
-// fastest kernel of each, where the models' picks are 13 and 14 %.
+// faster from HBM and 1.13 from the cache; 131 and 185 of them are slower by more than 3 %, 40 and 54 by 10 %.  (Timed when a column-major B was
+// loaded as operands; 983 of them go to strips_choice since.)
 // Not for operands that would be copied: the choice between copies and direct_choice compares with the models' pick.
 constexpr double kCheapAlloc = 2097152.0 - 65536.0;      // bytes of planes beside the counters below hipMalloc's 2 MiB step
 struct FewRow { unsigned short m; unsigned n, k; signed char spec[5]; };
@@ -675,6 +687,39 @@ bool resident_a_range(int64_t M, int64_t N, int64_t K)
     return M <= 16 && N >= 16384 && K >= 1200 && K <= 4096 && (N < 24000 || N > 32768 || K >= 3200);
 }
 constexpr char kResidentA[] = "skinny,sk=1,wv=8,ra=1";
+
+// Does hgemm_run_many put calls of this pick into one launch?
+bool joins_launches(const Spec& s, int64_t M, int64_t N, int64_t K)
+{
+    return s.fam == FAM_MFMA && s.sk == 1 && !s.sm && !s.ps && !s.ph && !s.di && !s.tb && s.ac == 32 && s.mi == 32 &&
+           2.0 * ((double)M * K + (double)K * N + (double)M * N) <= 8.0 * 1048576.0;
+}
+
+// Column-major B, up to 32 rows of A and 12288 columns: one strip of 16, 32 or 48 rows of B for every compute unit, K split among its
+// waves only, so that there are no planes and no second launch (skinny_tn_gemm_kernel).  Timed against the choices made without it,
+// table rows among them, on 10 424 problems of 1 to 32 rows (widths of layers, and any multiples of 16 and 8): on the 5955 that this takes 0.83 of their
+// time from HBM (109 slower by more than 3 %, 22 by 10 %) and 0.72 from the cache (92, 5); on 983 others (few_rows_check.jsonl.gz) 0.85 (39, 8) and 0.75 (33, 3).
+// Where it ends, as time from HBM / from the cache against those choices:
+//  * more than 12288 columns: strips of 64 rows 0.98-1.06 up to 16384 columns, several rounds of strips level beyond;
+//  * K below 16 nr: a strip ends before its copies flow (nr = 32: K 256 1.0 / 0.95, 512 0.91 / 0.8; nr = 48: 512 0.98 / 0.9, 768 0.96 / 0.83);
+//  * a long K on strips for few compute units, which a split spreads over more of them, sooner with more rows of A, whose bytes every
+//    strip reads: up to 1024 columns K 8192 0.9 / 0.85 at M = 2, 1.3 / 0.9 at 16; 4097-5120 columns K 4096 0.92 / 0.83 at M = 4, 6144 1.16 /
+//    0.85 at 16; 3073-4096 columns K 8192-16384 0.85-0.98 / 0.84 up to 16 rows, 1.13 / 0.87 at 24.
+//  * picks whose calls share launches stay: 16 calls in one take what two take here;
+//  * columns that are no whole strip of 16 keep the measured neighbours' kernels.
+bool strips_choice(int64_t M, int64_t N, int64_t K, const Spec& pick, Spec* out)
+{
+    if (M > 32 || N % 16 || N < 64 || N > 12288 || joins_launches(pick, M, N, K)) return false;
+    const int64_t blocks = (N + 4095) / 4096;
+    if (K < 256 * blocks) return false;
+    const double filled = (double)N / (4096.0 * (double)blocks);
+    const double work = (double)K * (double)(M + 8);
+    if (filled <= 0.75 ? work > (filled <= 0.25 ? 100e3 : filled <= 0.625 ? 125e3 : 190e3) : M > 16 && blocks < 3 && work > 200e3) return false;
+    *out = Spec();
+    out->fam = FAM_SKINNY;
+    if (blocks > 1) out->nr = (int)(16 * blocks);
+    return true;
+}
 
 bool evaluate_model(int64_t M, int64_t N, int64_t K, Spec* out, bool b_row_major, bool measured)
 {
@@ -894,6 +939,21 @@ bool select_kernel(hgemm_plan_s* p)
     return true;
 }
 
+// More than 64 KiB of dynamic LDS: asked for once per kernel and device.
+bool admit_skinny_lds(int dev, int instance, const SkinnyTnKernel& k)
+{
+    if (k.lds <= 64 * 1024) return true;
+    static std::atomic<bool> allowed[kMaxDevices][3 * 3 * 4 * 2] = {};
+    const bool keep = dev >= 0 && dev < kMaxDevices;
+    if (keep && allowed[dev][instance].load(std::memory_order_acquire)) return true;
+    if (hipFuncSetAttribute((const void*)k.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, k.lds) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (keep) allowed[dev][instance].store(true, std::memory_order_release);
+    return true;
+}
+
 hgemm_status_t finish_plan(hgemm_plan_s* p)
 {
     const int64_t M = p->M, N = p->N, K = p->K;
@@ -905,6 +965,7 @@ hgemm_status_t finish_plan(hgemm_plan_s* p)
     p->tn_kernel = false;
     memset(&p->args, 0, sizeof p->args);
     p->skinny = nullptr;
+    p->skinny_lds = 0;
     if (s.fam == FAM_GENERIC) return HGEMM_OK;
     if (s.fam == FAM_SKINNY) {
         // strips of columns x K slabs of whole steps; partial planes as for split-K
@@ -918,13 +979,23 @@ hgemm_status_t finish_plan(hgemm_plan_s* p)
         if (sk > 65535) return HGEMM_ERR_UNSUPPORTED;
         s.sk = (int)sk;
         if (sk == 1) s.fr = 0;
-        if (!tn && s.nr != 16) return HGEMM_ERR_UNSUPPORTED;
+        if (!tn && s.nr != 0 && s.nr != 16) return HGEMM_ERR_UNSUPPORTED;
+        if (!tn || s.ra) s.nr = 0;
         if (p->any_b && s.wv != 4) return HGEMM_ERR_UNSUPPORTED;
         if (s.ra && (!tn || M > 32)) return HGEMM_ERR_UNSUPPORTED;
         // with A resident, one workgroup per compute unit (a multiple of the 8 XCDs) walks the strips
-        const int64_t strips = s.ra ? std::max<int64_t>(8, cu_count() / 8 * 8) : (N + skinny_cols(s, tn) - 1) / skinny_cols(s, tn);
+        const int64_t strips = s.ra ? std::max<int64_t>(8, cu_count() / 8 * 8) : (N + skinny_cols(s, tn, N) - 1) / skinny_cols(s, tn, N);
         if (s.fr && strips * (int64_t)sizeof(int) > (int64_t)kCounterBytes) return HGEMM_ERR_UNSUPPORTED;
-        p->skinny = s.ra ? skinny_strips(mb, K) : p->any_b ? skinny_any_b_kernel(mb, s.fr != 0) : skinny_kernel(mb, s.fr != 0, s.wv, tn ? s.nr : 0);
+        if (tn && !s.ra) {
+            const int rows = strip_rows(s, N);
+            const SkinnyTnKernel k = skinny_tn_kernel(mb, s.fr != 0, s.wv, rows);
+            const int instance = (((mb / 2) * 3 + s.wv / 8) * 4 + rows / 16 - 1) * 2 + s.fr;
+            if (!k.kernel || !admit_skinny_lds(p->device, instance, k)) return HGEMM_ERR_UNSUPPORTED;
+            p->skinny = k.kernel;
+            p->skinny_lds = k.lds;
+        } else {
+            p->skinny = s.ra ? skinny_strips(mb, K) : p->any_b ? skinny_any_b_kernel(mb, s.fr != 0) : skinny_kernel(mb, s.fr != 0, s.wv);
+        }
         if (!p->skinny) return HGEMM_ERR_UNSUPPORTED;
         GemmArgs& a = p->args;
         a.M = (int)M; a.N = (int)N; a.K = (int)K;
@@ -1221,6 +1292,11 @@ Choices choose_spec(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, i
     } else if (c.spec[0].ph && c.spec[0].sk > 1) {
         c.spec[c.n] = c.spec[0];                  // where there is no room for the planes: the same tile without a split
         c.spec[c.n++].sk = 1;
+    }
+    Spec strips;
+    if (tn && !padded && strcmp(c.source, "table") && c.n < 3 && strips_choice(M, N, K, c.spec[0], &strips)) {
+        for (int i = c.n++; i > 0; --i) c.spec[i] = c.spec[i - 1];
+        c.spec[0] = strips;
     }
     for (int i = 0; i < c.n; ++i)
         if (tn || padded) c.spec[i].tb = 0;       // B already has K contiguous / is copied once already
@@ -1704,7 +1780,7 @@ static hgemm_status_t run_plan(const hgemm_plan_s* plan, const void* A, const vo
     a.b_rows = (int)b_rows;
     a.c_wide = N % 8 == 0 && plan->lay.ldc % 8 == 0 && ((uintptr_t)C & 15) == 0;
     if (plan->skinny) {
-        hipLaunchKernelGGL(plan->skinny, dim3((unsigned)a.tiles_n, (unsigned)a.splits), dim3(64u * (unsigned)plan->spec.wv), 0, stream, a);
+        hipLaunchKernelGGL(plan->skinny, dim3((unsigned)a.tiles_n, (unsigned)a.splits), dim3(64u * (unsigned)plan->spec.wv), (unsigned)plan->skinny_lds, stream, a);
         if (a.splits > 1 && !plan->spec.fr) {
             if (hipGetLastError() != hipSuccess) return HGEMM_ERR_LAUNCH;
             const int64_t quads = M * ((N + 3) / 4);
@@ -1759,8 +1835,7 @@ hgemm_status_t hgemm_run(hgemm_plan_t plan, const void* A, const void* B, void* 
 static const MfmaEntry* merged_entry(const hgemm_plan_s* p, int64_t calls)
 {
     const Spec& s = p->spec;
-    if (!p->planned || p->blocked || p->padded || !p->entry || s.sk > 1 || s.sm || s.ps || s.ph || s.di || s.tb || s.ac != 32 || s.mi != 32) return nullptr;
-    if (2.0 * ((double)p->M * p->K + (double)p->K * p->N + (double)p->M * p->N) > 8.0 * 1048576.0) return nullptr;
+    if (!p->planned || p->blocked || p->padded || !p->entry || !joins_launches(s, p->M, p->N, p->K)) return nullptr;
     static const MfmaEntry* const large = batch_entry(128);
     static const MfmaEntry* const small = batch_entry(64);
     const int64_t tiles128 = ((p->M + 127) / 128) * ((p->N + 127) / 128);
@@ -1913,7 +1988,7 @@ hgemm_status_t hgemm_plan_launch_info(hgemm_plan_t plan, int64_t* workgroups, in
     int64_t wg, lds, th;
     if (plan->skinny) {
         wg = (int64_t)plan->args.tiles_n * plan->args.splits;
-        lds = plan->tn_kernel ? (plan->spec.ra ? 2 : 1) * plan->spec.wv * (plan->M <= 16 ? 1 : plan->M <= 32 ? 2 : 4) * (plan->spec.nr / 16) * 1024 : 4 * 16 * (kSkinnyCols + 4) * 4;
+        lds = plan->spec.ra ? 2 * kStripWaves * (plan->M <= 16 ? 1 : 2) * 1024 : plan->tn_kernel ? plan->skinny_lds : 4 * 16 * (kSkinnyCols + 4) * 4;
         th = 64 * plan->spec.wv;
     } else if (plan->entry) {
         wg = plan->spec.sm ? (int64_t)plan->args.dp_tiles + plan->args.sk_workers
@@ -1945,9 +2020,9 @@ const char* hgemm_spec_help(void)
             "    step, transposes its 4 x 8 blocks in registers for 16x16x16 matrix-core instructions (M on a 16-wide\n"
             "    side; no LDS and no barrier in the main loop), the waves' sums meet once at the end; slabs are summed in\n"
             "    slab order by the split-K reduction launch or, with fr = 1, by the workgroup that arrives last.\n"
-            "    Column-major B (K contiguous): a workgroup takes nr = 16 (default), 32 or 64 rows of B (columns of C), its waves split its K\n"
-            "    range into contiguous parts of whole 32-k steps, 16-byte loads are the operands of 16x16x32 instructions\n"
-            "    as they come; sk splits K further across workgroups.  ra = 1 (with sk = 1, wv = 8; M <= 32, K <= 8192, above 16 rows 4096): A stays\n"
+            "    Column-major B (K contiguous): a workgroup takes nr = 16, 32, 48 or 64 rows of B (columns of C; default: one strip for\n"
+            "    every compute unit up to 12288 columns), its waves take chunks\n"
+            "    of 64 k of them in turn, copied to LDS of their own; sk splits K further across workgroups.  ra = 1 (with sk = 1, wv = 8; M <= 32, K <= 8192, above 16 rows 4096): A stays\n"
             "    in registers, one workgroup per compute unit walks strips of 16 rows of B\n"
             "mfma,bm=BM,bn=BN,bk=BK,wm=WM,wn=WN,st=STAGES[,pf=PREFETCH][,sk=SPLITS][,gm=GROUP][,tb=1][,sm=1][,fr=1][,ps=1][,ac=16][,mi=16][,ph=1][,di=1]\n"
             "    pipelined 32x32x16 MFMA kernel; BMxBN tile per workgroup, WMxWN wavefronts, STAGES LDS buffers,\n"
@@ -2048,7 +2123,7 @@ hgemm_status_t hgemm_candidates(int64_t M, int64_t N, int64_t K, const hgemm_lay
         }
         if (l.b == HGEMM_COL_MAJOR && M <= kSkinnyMaxM) {       // the streaming family for K-contiguous B: N / 16 workgroups before any split
             const int mblocks = M <= 16 ? 1 : M <= 32 ? 2 : 4;
-            for (int nr : {16, 32, 64})
+            for (int nr : {16, 32, 48, 64})      // 16 as the default where that is what it is
                 for (int wv : {4, 8, 16}) {
                     const int blocks = mblocks * (nr / 16);
                     if (wv * blocks > 64 || (wv == 16 && blocks > 4)) continue;       // kernels that do not exist
@@ -2057,6 +2132,7 @@ hgemm_status_t hgemm_candidates(int64_t M, int64_t N, int64_t K, const hgemm_lay
                     for (int sk : {1, 2, 4, 8, 16}) {
                         Spec s;
                         s.fam = FAM_SKINNY; s.wv = wv; s.nr = nr;
+                        if (nr == 16 && (sk > 1 || strip_rows(Spec(), N) == 16)) s.nr = 0;
                         const int64_t eff = effective_splits((K + skinny_step(s, true) - 1) / skinny_step(s, true), sk);
                         if (eff == last || ((N + nr - 1) / nr) * eff > 64 * CUS) continue;
                         last = eff;

@@ -29,35 +29,38 @@ void (*kernel_for(int mb, bool fused))(GemmArgs)
     return nullptr;
 }
 
-// Column-major B.  Steps of loads in flight per lane: 16 registers' worth of 16-byte loads shared between the NR / 16
-// blocks of B and the MB blocks of A of a step, at least 2, at most 8.  Combinations whose sums would not fit 64 KiB
-// of LDS, or whose accumulators and loads would not fit the 128 registers a 16-wave workgroup leaves a lane, do not exist.
+// Column-major B.  Chunks in flight per wave: three where the workgroup then takes at most 48 KiB of LDS (three to a compute unit: M <= 16 in
+// strips of 16 rows), else two (16 x 5888 x 1920 in strips of 32 rows, 48 KiB: 7.2 us, with three chunks 7.3; 16 x 14336 x 4096 22.9, 23.6), and one
+// where two do not fit the LDS.  Combinations of more than 64 KiB of sums do not exist.
 template <int WAVES, int MB, int NR>
-void (*tn_kernel(bool fused))(GemmArgs)
+SkinnyTnKernel tn_kernel(bool fused)
 {
-    constexpr int NB = NR / 16;
-    constexpr int DEPTH = 16 / (NB + MB) < 2 ? 2 : 16 / (NB + MB) > 8 ? 8 : 16 / (NB + MB);
+    constexpr int NB = NR / 16, TWO = 2 * WAVES * 2 * (MB + NB);      // KiB of two chunks a wave
+    constexpr int DEPTH = TWO <= 32 ? 3 : TWO <= 160 ? 2 : 1;
     if constexpr (WAVES * MB * NB <= 64 && (WAVES < 16 || MB * NB <= 4))
-        return fused ? skinny_tn_gemm_kernel<MB, true, DEPTH, WAVES, NR> : skinny_tn_gemm_kernel<MB, false, DEPTH, WAVES, NR>;
+        return {fused ? skinny_tn_gemm_kernel<MB, true, DEPTH, WAVES, NR> : skinny_tn_gemm_kernel<MB, false, DEPTH, WAVES, NR>, SkinnyTnLds<MB, DEPTH, WAVES, NB>::TOTAL};
     else
-        return nullptr;
+        return {nullptr, 0};
 }
 
 template <int WAVES>
-void (*tn_kernel_for(int mb, bool fused, int nr))(GemmArgs)
+SkinnyTnKernel tn_kernel_for(int mb, bool fused, int nr)
 {
     switch (mb * 100 + nr) {
         case 116: return tn_kernel<WAVES, 1, 16>(fused);
         case 132: return tn_kernel<WAVES, 1, 32>(fused);
+        case 148: return tn_kernel<WAVES, 1, 48>(fused);
         case 164: return tn_kernel<WAVES, 1, 64>(fused);
         case 216: return tn_kernel<WAVES, 2, 16>(fused);
         case 232: return tn_kernel<WAVES, 2, 32>(fused);
+        case 248: return tn_kernel<WAVES, 2, 48>(fused);
         case 264: return tn_kernel<WAVES, 2, 64>(fused);
         case 416: return tn_kernel<WAVES, 4, 16>(fused);
         case 432: return tn_kernel<WAVES, 4, 32>(fused);
+        case 448: return tn_kernel<WAVES, 4, 48>(fused);
         case 464: return tn_kernel<WAVES, 4, 64>(fused);
     }
-    return nullptr;
+    return {nullptr, 0};
 }
 }  // namespace
 
@@ -67,17 +70,17 @@ void (*skinny_any_b_kernel(int mb, bool fused))(GemmArgs)
     return mb == 1 ? any_b_kernel<1>(fused) : mb == 2 ? any_b_kernel<2>(fused) : mb == 4 ? any_b_kernel<4>(fused) : nullptr;
 }
 
-// Kernel for M <= 16 * mb (mb in {1, 2, 4}) and workgroups of 4, 8 or 16 waves, with or without the fused
-// reduction, for row-major B (tn_rows = 0) or column-major B with tn_rows = 16, 32 or 64 rows of B per workgroup;
-// null for other values.
-void (*skinny_kernel(int mb, bool fused, int waves, int tn_rows))(GemmArgs)
+// Kernels for M <= 16 * mb (mb in {1, 2, 4}) and workgroups of 4, 8 or 16 waves, with or without the fused reduction; null for other
+// values.  Row-major B:
+void (*skinny_kernel(int mb, bool fused, int waves))(GemmArgs)
 {
-    switch (waves) {
-        case 4: return tn_rows ? tn_kernel_for<4>(mb, fused, tn_rows) : kernel_for<4>(mb, fused);
-        case 8: return tn_rows ? tn_kernel_for<8>(mb, fused, tn_rows) : kernel_for<8>(mb, fused);
-        case 16: return tn_rows ? tn_kernel_for<16>(mb, fused, tn_rows) : kernel_for<16>(mb, fused);
-    }
-    return nullptr;
+    return waves == 4 ? kernel_for<4>(mb, fused) : waves == 8 ? kernel_for<8>(mb, fused) : waves == 16 ? kernel_for<16>(mb, fused) : nullptr;
+}
+
+// Column-major B, with nr = 16, 32, 48 or 64 rows of it per workgroup.
+SkinnyTnKernel skinny_tn_kernel(int mb, bool fused, int waves, int nr)
+{
+    return waves == 4 ? tn_kernel_for<4>(mb, fused, nr) : waves == 8 ? tn_kernel_for<8>(mb, fused, nr) : waves == 16 ? tn_kernel_for<16>(mb, fused, nr) : SkinnyTnKernel{nullptr, 0};
 }
 
 // Column-major B, A resident: the instance with the fewest registers whose eight waves hold all of K, for M <= 16 * mb (mb 1 or 2); null where

@@ -235,98 +235,135 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_gemm_kernel(GemmArgs g)
 }
 
 // The same family for column-major B (stored N x K, K contiguous: the layout in which frameworks keep the
-// weights of a linear layer).  Here nothing needs transposing: v_mfma_f32_16x16x32_f16 takes 8 consecutive k
-// per lane, and a 16-byte load of row n of B is exactly that.  A workgroup owns NR = 16, 32 or 64 rows of B (as
-// many columns of C), so N / NR workgroups exist before K is split at all; its WAVES waves split the
-// workgroup's K range into contiguous parts (every row is read in runs of kilobytes), each wave keeps DEPTH
-// steps of loads in flight (NR / 16 KiB of B each), holds 4 accumulator registers per 16 x 16 block of C, and
-// the waves' sums meet in LDS at the end and are added in wave order.  Every workgroup reads the rows of A it
-// multiplies once per NR rows of B: at NR = 16 and M = 16 that is as many bytes through the L1s again as B
-// itself, which is what the wider workgroups are for.  grid.y splits K further (planes, reduction launch or
-// FUSED) for short, wide-K problems.
+// weights of a linear layer).  A workgroup owns NR = 16, 32, 48 or 64 rows of B (as many columns of C), so N / NR workgroups
+// exist before K is split at all, and most problems need no split and no second launch.  Its waves take chunks of 64 k in
+// turn: for each a wave copies 128 bytes of every row of B and of A into LDS of its own (8 rows a copy, chunks swizzled as in the
+// large tiles), DEPTH chunks ahead, reads its fragments from there and multiplies (v_mfma_f32_16x16x32_f16), with no barrier: nobody
+// else touches that LDS.  The waves' sums meet in LDS at the end and are added in wave order.  grid.y splits K further
+// (planes, reduction launch or FUSED).
+// Why LDS, where a 16-byte load of a row is an operand already: an operand has its 16 rows in consecutive lanes, and a load whose
+// neighbouring lanes lie in different rows comes from the L2 at 38 GB/s per compute unit, one line a cycle for a quarter of it; with 8
+// lanes to a row's 128 bytes it is 130 GB/s (1 MiB read by 256 workgroups, either way in registers or in LDS).  A and B together
+// passed at 9.7 TB/s that way, and up to 16 rows A is as many bytes as B at NR = 16.
+// What bounds it: the stream of B.  From HBM, the best kernel of any family before -> this: 1 x 4096 x 4096 9.8 (this family,
+// loads that were operands) -> 7.7 us, 16 x 4096 x 4096 10.0 -> 8.4, 1 x 7296 x 7296 23.6 -> 20.8; in strips of 32 rows 16 x 5888 x 1920 9.0 -> 7.2, 16 x 14336 x
+// 4096 24.8 -> 23.1; of 48 16 x 11008 x 4096 20.2 -> 19.1; from the cache 1 x 4096 x 4096 7.7 -> 4.6, 16 x 14336 x 4096 21.4 -> 18.3.  Not where K is long
+// and A of 16 rows: 16 x 4096 x 11008 21.9 from HBM, split 32-row tiles 21.1 (17.9 from the cache, this 15.7).
+// Four waves with three chunks each (48 KiB at NR = 16, three workgroups to a compute unit) are the best of 4, 8 and 16 waves and 2 to 8
+// chunks: 1 x 4096 x 4096 7.8, eight waves 8.1, sixteen 8.2.  Strips are dealt so that an XCD's workgroups hold adjacent ones (see below).
 constexpr int kSkinnyTnRows = 16;      // rows of B (columns of C) per workgroup unless a spec asks for more
+
+template <int MB, int DEPTH, int WAVES, int NB>
+struct SkinnyTnLds {                   // bytes
+    static constexpr int COPIES = 2 * (MB + NB), CHUNK = COPIES * 1024, RING = DEPTH * CHUNK;      // of a wave
+    static constexpr int SUMS = WAVES * MB * NB * 1024;
+    static constexpr int TOTAL = WAVES * RING > SUMS ? WAVES * RING : SUMS;
+    static_assert(TOTAL <= 160 * 1024 && COPIES * DEPTH <= 63, "LDS, vmcnt is 6 bits");
+};
+
+struct SkinnyTnKernel {                // an instance and its dynamic LDS
+    void (*kernel)(GemmArgs);
+    int lds;
+};
 
 template <int MB, bool FUSED, int DEPTH, int WAVES, int NR>
 __global__ __launch_bounds__(64 * WAVES) void skinny_tn_gemm_kernel(GemmArgs g)
 {
-    typedef unsigned int uint4v __attribute__((ext_vector_type(4)));
     constexpr int NB = NR / 16;                                // 16-row blocks of B per workgroup
-    static_assert(NR % 16 == 0 && WAVES * MB * NB <= 64, "the waves' sums meet in at most 64 KiB of LDS");
-    __shared__ __attribute__((aligned(16))) float red[WAVES * MB * NB * 64 * 4];
+    typedef SkinnyTnLds<MB, DEPTH, WAVES, NB> L;
+    static_assert(NR % 16 == 0, "rows of B");
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
 
     const int t = threadIdx.x;
     const int lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int n0 = blockIdx.x * NR;
+    const int strips = gridDim.x, xcd = blockIdx.x & 7;
+    const int strip = xcd * (strips >> 3) + min(xcd, strips & 7) + (blockIdx.x >> 3);
+    const int n0 = strip * NR;
     const int split = blockIdx.y;
     const int k_lo = split * g.k_per_split;
     const int k_hi = min(g.K, k_lo + g.k_per_split);
-    const int per_wave = g.k_per_split / WAVES;                // a multiple of 32
-    const int kw = k_lo + wave * per_wave;                     // this wave's part of the slab
-    const int kw_hi = min(k_hi, kw + per_wave);
-    const int steps = kw < kw_hi ? (kw_hi - kw + 31) / 32 : 0;
+    const int steps = (k_hi - k_lo + 64 * WAVES - 1) / (64 * WAVES);
 
     const unsigned OOB = 0x80000000u;
-    const __amdgpu_buffer_rsrc_t rsrcA =
-        __builtin_amdgcn_make_buffer_rsrc((void*)g.A, 0, (int)min((long long)g.M * g.lda * 2, 0x7fffffffLL), 0x00020000);
-    const __amdgpu_buffer_rsrc_t rsrcB =
-        __builtin_amdgcn_make_buffer_rsrc((void*)g.B, 0, (int)min((long long)g.N * g.ldb * 2, 0x7fffffffLL), 0x00020000);
+    const int4v rsrcA = make_rsrc(g.A, (unsigned)min((long long)g.M * g.lda * 2, 0x7fffffffLL));
+    const int4v rsrcB = make_rsrc(g.B, (unsigned)min((long long)g.N * g.ldb * 2, 0x7fffffffLL));
 
-    // lane (grp, c16): B rows n0 + 16 nb + c16 and A rows 16 mb + c16, k = kw + 32 step + 8 grp .. + 7 (K is a
-    // multiple of 8: the eight k of a lane are in range together or not at all)
-    const int c16 = lane & 15, grp = lane >> 4;
-    const int k0 = kw + 8 * grp;
-    unsigned b_off[NB], a_off[MB];
+    // A copy covers 8 rows of 128 bytes: lane i fills physical chunk i % 8 of row i / 8 with logical chunk p ^ (row / 2) % 8, in the second
+    // copy of a block with the chunk four further.  Rows past the end and k past the slab (K is a multiple of 8) read as zeros.
+    const int row8 = lane >> 3;
+    const int chunk[2] = {(lane & 7) ^ (lane >> 4), (lane & 7) ^ (lane >> 4) ^ 4};
+    int k = k_lo + wave * 64;                                  // of the chunk copied next
+    unsigned at = 0;                                           // and its distance from the first, in bytes
+    unsigned a_off[MB][2], b_off[NB][2];
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        const int n = n0 + 16 * nb + c16;
-        b_off[nb] = n < g.N ? (unsigned)((n * g.ldb + k0) * 2) : OOB;
-    }
+    for (int h = 0; h < 2; ++h) {
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-        const int m = 16 * mb + c16;
-        a_off[mb] = m < g.M ? (unsigned)((m * g.lda + k0) * 2) : OOB;
+        for (int nb = 0; nb < NB; ++nb) {
+            const int n = n0 + 16 * nb + 8 * h + row8;
+            b_off[nb][h] = n < g.N ? (unsigned)((n * g.ldb + k + chunk[h] * 8) * 2) : OOB;
+        }
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            const int m = 16 * mb + 8 * h + row8;
+            a_off[mb][h] = m < g.M ? (unsigned)((m * g.lda + k + chunk[h] * 8) * 2) : OOB;
+        }
     }
-    auto load_step = [&](int step, uint4v (&b)[NB], uint4v (&a)[MB]) {
-        const bool ok = k0 + 32 * step < kw_hi;
+    const unsigned ring = __builtin_amdgcn_readfirstlane((int)lds_addr_of(lds)) + wave * L::RING;
+    auto copy_chunk = [&](unsigned slot) {
+        const bool ok[2] = {k + chunk[0] * 8 < k_hi, k + chunk[1] * 8 < k_hi};
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
-            b[nb] = __builtin_amdgcn_raw_buffer_load_b128(rsrcB, ok && b_off[nb] != OOB ? b_off[nb] + (unsigned)(step * 64) : OOB, 0, 0);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) dma16(rsrcB, ring + slot + (2 * nb + h) * 1024, ok[h] ? b_off[nb][h] + at : OOB);
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
-            a[mb] = __builtin_amdgcn_raw_buffer_load_b128(rsrcA, ok && a_off[mb] != OOB ? a_off[mb] + (unsigned)(step * 64) : OOB, 0, 0);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) dma16(rsrcA, ring + slot + (2 * (NB + mb) + h) * 1024, ok[h] ? a_off[mb][h] + at : OOB);
+        k += 64 * WAVES;
+        at += 128 * WAVES;
     };
 
+    // fragments: lane (grp, c16) has row c16 of a block, k = 32 ks + 8 grp .. + 7 of the chunk
+    const int c16 = lane & 15, grp = lane >> 4;
+    const char* const frag = lds + wave * L::RING + c16 * 128;
+    const int at_ks[2] = {(grp ^ ((c16 >> 1) & 7)) * 16, ((4 + grp) ^ ((c16 >> 1) & 7)) * 16};
     float4v acc[MB][NB];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = float4v{0.f, 0.f, 0.f, 0.f};
 
-    uint4v bq[DEPTH][NB];
-    uint4v fa[DEPTH][MB];
+    static_for<DEPTH>([&](auto d) { copy_chunk(decltype(d)::value * L::CHUNK); });
+    unsigned slot = 0;
+    for (int step = 0; step < steps; ++step) {
+        wait_vmcnt<(DEPTH - 1) * L::COPIES>();                 // this chunk has landed: the copies of the later ones may be in flight
+        asm volatile("" ::: "memory");
+        half8 fb[NB][2], fa[MB][2];
 #pragma unroll
-    for (int u = 0; u < DEPTH; ++u) load_step(u, bq[u], fa[u]);
-    for (int base = 0; base < steps; base += DEPTH) {
+        for (int ks = 0; ks < 2; ++ks) {
 #pragma unroll
-        for (int u = 0; u < DEPTH; ++u) {
-            const int step = base + u;
-            if (step >= steps) break;
-            union { uint4v i; half8 h; } bv[NB], av[MB];
+            for (int nb = 0; nb < NB; ++nb) fb[nb][ks] = *(const half8*)(frag + slot + 2 * nb * 1024 + at_ks[ks]);
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) bv[nb].i = bq[u][nb];
+            for (int mb = 0; mb < MB; ++mb) fa[mb][ks] = *(const half8*)(frag + slot + 2 * (NB + mb) * 1024 + at_ks[ks]);
+        }
+        __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));      // lgkmcnt(0): it is in registers, its place is free
+        asm volatile("" ::: "memory");
+        copy_chunk(slot);
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) av[mb].i = fa[u][mb];
-            load_step(step + DEPTH, bq[u], fa[u]);           // refill this set
+        for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb)
-                    acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bv[nb].h, av[mb].h, acc[mb][nb], 0, 0, 0);
-        }
+                    acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fb[nb][ks], fa[mb][ks], acc[mb][nb], 0, 0, 0);
+        slot = slot == (DEPTH - 1) * L::CHUNK ? 0 : slot + L::CHUNK;
     }
+    wait_vmcnt<0>();                                           // the copies past the end write zeros into the rings
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
     // ---- the waves' sums meet in LDS.  acc[mb][nb][r] belongs to C[16 mb + c16][n0 + 16 nb + 4 grp + r]
+    float* const red = (float*)lds;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -365,7 +402,7 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_tn_gemm_kernel(GemmArgs g)
     if (!FUSED || direct) return;
 
     // fused reduction over the K slabs of these columns, as in skinny_gemm_kernel
-    if (!last_to_arrive(g.counters + blockIdx.x, g.splits, (int*)red, t == 0)) return;
+    if (!last_to_arrive(g.counters + strip, g.splits, (int*)red, t == 0)) return;
     sum_split_planes<64 * WAVES, NR / 4>(g, 0, n0, g.M, t);
 }
 

@@ -6,6 +6,7 @@ the fastest, and csrc/few_rows.inc holds for each the kernels that are close to 
 looks up the nearest.
 
     python -m paper_2512_02551_amd.few_rows gather --seed 1 --seconds 500 --out FILE [--against LIB]   # on the GPU
+    python -m paper_2512_02551_amd.few_rows recheck --out FILE [--against LIB] [FILE]       # on the GPU; after a kernel or a rule changed
     python -m paper_2512_02551_amd.few_rows build [FILE ...]          # CPU; rewrites csrc/few_rows.inc
     python -m paper_2512_02551_amd.few_rows evaluate [--against LIB] [FILE ...]     # CPU; the built library's choices
 
@@ -20,7 +21,8 @@ one's, on K from 1200 on only: on a shorter K it wins less than 5 % from HBM and
 csrc/few_rows_check.jsonl.gz holds 4885 other problems as `gather` writes them, which the choices are checked on: half products of
 layers, a quarter output heads, a quarter any multiples of 8; {"shape", "tn", "cands": [[kernel, us from HBM, us from the cache], ...]} with
 the kernels whose first timing was within a fifth of the fastest, the library's choice and that of the builds it is compared with
-(--against: another build of the library, of an earlier commit, say).
+(--against: another build of the library, of an earlier commit, say).  The 1300 that now run on strips of a column-major B through LDS
+were timed again (`recheck`); csrc/few_rows_timings.jsonl.gz has that family's kernels as they were before, when lanes loaded operands.
 """
 from __future__ import annotations
 
@@ -161,6 +163,52 @@ def gather(seed: int, seconds: float, path: str, against):
                 print(f"{done} problems, {time.time() - t0:.0f} s", flush=True)
 
 
+def recheck(src: str, path: str, against):
+    """Problems of `src` that the library now runs on a kernel `src` has no time of: timed again, with the kernels that stand there."""
+    import torch
+
+    import paper_2512_02551_amd as hg
+
+    rows = load([src])
+    pool = torch.randn(1 << 26, device="cuda").mul_(0.02).half().repeat(12)
+    c = torch.empty(32 * 160000, dtype=torch.float16, device="cuda")
+    sh = torch.cuda.current_stream().cuda_stream
+
+    def timed(p, sets, reps):
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record()
+        p.run_many(reps, sets, sh)
+        e1.record()
+        e1.synchronize()
+        return e0.elapsed_time(e1) / reps * 1e3
+
+    done = 0
+    for r in rows:
+        M, N, K = r["shape"]
+        specs = list(dict.fromkeys([choice(lib, M, N, K, r["tn"]) for lib in [None] + against] + [x[0] for x in r["cands"]]))
+        if specs[0] in {x[0] for x in r["cands"]} and number(specs[0], "nr") == 0 and specs[0] != "skinny,sk=1":
+            continue
+        elems = (M * K + 127) // 128 * 128 + N * K
+        n = max(1, min(64, pool.numel() // elems, int(6e8 // (2 * elems)) + 1))
+        assert n * elems <= pool.numel() and M * N <= c.numel(), (M, N, K)
+        sets = [(pool.data_ptr() + 2 * i * elems, pool.data_ptr() + 2 * (i * elems + elems - N * K), c.data_ptr()) for i in range(n)]
+        plans = [hg.Plan(M, N, K, hg.Layouts.make(b_col_major=r["tn"]), s) for s in specs]
+        reps = max(4, min(60, int(300 / timed(plans[0], sets, 4))))
+        times = [[[], []] for _ in plans]
+        for w, some in ((0, sets), (1, sets[:1])):
+            for _ in range(5):
+                for p, t in zip(plans, times):
+                    t[w].append(timed(p, some, reps))
+        r["cands"] = [[s] + [round(float(np.median(v[1:])), 2) for v in t] for s, t in zip(specs, times)]
+        for p in plans:
+            p.destroy()
+        done += 1
+        if done % 100 == 0:
+            print(f"{done} problems", flush=True)
+    with gzip.open(path, "wt", compresslevel=9) as f:
+        f.writelines(json.dumps(r) + "\n" for r in rows)
+
+
 def load(paths):
     rows = []
     for p in paths:
@@ -292,8 +340,14 @@ if __name__ == "__main__":
     e_ = sub.add_parser("evaluate")
     e_.add_argument("--against", default=None, metavar="LIB")
     e_.add_argument("files", nargs="*", default=[CHECK])
+    r_ = sub.add_parser("recheck")
+    r_.add_argument("--out", required=True)
+    r_.add_argument("--against", action="append", default=[], metavar="LIB")
+    r_.add_argument("file", nargs="?", default=CHECK)
     args = ap.parse_args()
-    if args.cmd == "build":
+    if args.cmd == "recheck":
+        recheck(args.file, args.out, args.against)
+    elif args.cmd == "build":
         rows = load(args.files)
         table = build(rows)
         write(table, f"From {len(rows)} random problems, each row the mean of the {NEIGHBOURS} nearest; problems that a kept neighbour speaks for are left out.")

@@ -1,0 +1,33 @@
+"""Column-major B and few rows of A: strips of B through LDS of each wave's own (skinny_tn_gemm_kernel)."""
+import pytest
+
+import paper_2512_02551_amd as hg
+from test_gpu_direct import check
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("nr", [16, 32, 48, 64])
+@pytest.mark.parametrize("wv", [4, 8, 16])
+@pytest.mark.parametrize("m,n,k", [
+    (1, 8, 8), (16, 16, 64), (7, 24, 72), (16, 200, 1000), (9, 4112, 264),         # one block of A: less than a chunk, a part of one, rows past the end
+    (17, 40, 256), (32, 136, 520), (24, 2056, 1032),                                 # two
+    (33, 72, 512), (64, 264, 776)], ids=str)                                         # four
+def test_every_instance(m, n, k, wv, nr):
+    """K off the 64 of a chunk and off the chunks of all waves, columns off the strips and off 16, padded leading dimensions, and
+    infinities and NaN in A and B; splits in two launches and fused."""
+    blocks = (1 if m <= 16 else 2 if m <= 32 else 4) * (nr // 16)
+    spec = "skinny,sk=%d%s" + (f",wv={wv}" if wv != 4 else "") + (f",nr={nr}" if nr != 16 else "")
+    if wv * blocks > 64 or (wv == 16 and blocks > 4):
+        with pytest.raises(hg.HgemmError):
+            hg.Plan(m, n, k, hg.Layouts.make(b_col_major=True), spec % (1, ""))
+        return
+    assert check(spec % (1, ""), m, n, k, True) == spec % (1, "")
+    check(spec % (1, ""), m, n, k, True, (8, 16, 8), (8, 8, 8), special=True)
+    check(spec % (2, ""), m, n, k, True, (8, 16, 8), (8, 8, 8))
+    check(spec % (3, ",fr=1"), m, n, k, True)
+
+
+@pytest.mark.parametrize("m,n,k,nr", [(1, 4096, 4096, 16), (16, 64, 4096, 16), (16, 4112, 4096, 32), (32, 8192, 2048, 32), (5, 12288, 768, 48)], ids=str)
+def test_the_planner_takes_it(m, n, k, nr):
+    assert check(None, m, n, k, True) == "skinny,sk=1" + (f",nr={nr}" if nr > 16 else "")
