@@ -520,9 +520,10 @@ double predict_skinny_us(int64_t M, int64_t N, int64_t K, int64_t sk, bool fused
 // The cheapest compiled configuration and split factor under the model.
 // Split-K with the reduction fused into the kernel against the two-launch form, as fitted to skinny
 // shapes (M = 1 and 16): the second launch (its dispatch gap and its own round trip) goes away, the planes are stored
-// device-coherently (slower per byte) and the last workgroup's re-read is a serial tail.  Too kind to the fused form: what it chooses
-// takes, enqueued or replayed, 0.6-0.7 us longer than its two launches up to 32 rows (13 492 problems, 9-10 %) and 1.4 us beyond
-// (5138, 20 %); 2 % of it is the wait for the planes' stores in last_to_arrive().
+// device-coherently (slower per byte), waited for and counted, and the last workgroup's re-read is a serial tail.  Too kind to the fused form, which takes
+// 0.6-0.7 us longer than its two launches up to 32 rows (13 492 problems) and 1.4 us beyond (5138).  Beyond 32 rows the models pick two
+// launches: 1706 problems for which they used to pick the fused form (and 699 of them now another split, or none) take 0.81 of their time from HBM and from the
+// cache, 1 and 5 more than 1.03, and 0.66 planned, run and destroyed (no counters to clear).  Up to 32 rows, where the measured neighbours choose next, it stays: two launches 0.98 (237 of 5648 slower by more than 3 %).
 double fused_delta_us(int64_t M, int64_t N, int64_t sk)
 {
     const double planes_mib = (double)sk * (double)M * (double)N * 4.0 / 1048576.0;
@@ -746,7 +747,7 @@ bool evaluate_model(int64_t M, int64_t N, int64_t K, Spec* out, bool b_row_major
         for (int sk0 : split_candidates(t, ktiles)) {
             const int64_t sk = effective_splits(ktiles, sk0);
             double us = predict_us(M, N, K, e, sk, big);
-            const bool fuse = sk > 1 && fused_delta_us(M, N, sk) < 0.0 && (int64_t)t * (int64_t)sizeof(int) <= (int64_t)kCounterBytes;
+            const bool fuse = sk > 1 && M <= 32 && fused_delta_us(M, N, sk) < 0.0 && (int64_t)t * (int64_t)sizeof(int) <= (int64_t)kCounterBytes;
             if (fuse) us += fused_delta_us(M, N, sk);
             if (us < best) {
                 best = us;
