@@ -72,6 +72,7 @@ struct Spec {
     int di = 0;     // 1 = operands read through registers, at any element's address (MODE_DIRECT)
     int wv = 4;     // skinny family: waves per workgroup (4, 8 or 16), each taking 16 k-rows of a step
     int nr = 0;     // skinny family, column-major B: rows of B (columns of C) per workgroup (16, 32, 48 or 64; 0 = as strip_rows() has it)
+    int mr = 0;     // skinny family, column-major B: rows of A per workgroup (16, 32, 48 or 64; 0 = all of them, up to 64)
     int ra = 0;     // skinny family, column-major B: 1 = A resident in registers, one workgroup per compute unit walks strips of B
 };
 
@@ -96,6 +97,7 @@ static std::string spec_to_string(const Spec& s)
         snprintf(buf, sizeof buf, "skinny,sk=%d%s", s.sk, s.fr ? ",fr=1" : "");
         if (s.wv != 4) snprintf(buf + strlen(buf), sizeof buf - strlen(buf), ",wv=%d", s.wv);
         if (s.nr) snprintf(buf + strlen(buf), sizeof buf - strlen(buf), ",nr=%d", s.nr);
+        if (s.mr) snprintf(buf + strlen(buf), sizeof buf - strlen(buf), ",mr=%d", s.mr);
         if (s.ra) snprintf(buf + strlen(buf), sizeof buf - strlen(buf), ",ra=1");
         return buf;
     }
@@ -132,7 +134,7 @@ static bool parse_spec(const char* text, Spec* out)
     const struct { char key[4]; int* value; } keys[] = {
         {"bm", &sp.bm}, {"bn", &sp.bn}, {"bk", &sp.bk}, {"wm", &sp.wm}, {"wn", &sp.wn}, {"st", &sp.st}, {"pf", &sp.pf}, {"sk", &sp.sk},
         {"gm", &sp.gm}, {"tb", &sp.tb}, {"sm", &sp.sm}, {"fr", &sp.fr}, {"ps", &sp.ps}, {"ac", &sp.ac}, {"mi", &sp.mi}, {"ph", &sp.ph},
-        {"di", &sp.di}, {"wv", &sp.wv}, {"nr", &sp.nr}, {"ra", &sp.ra},
+        {"di", &sp.di}, {"wv", &sp.wv}, {"nr", &sp.nr}, {"mr", &sp.mr}, {"ra", &sp.ra},
         {"pad", &ignored},      // reported by hgemm_plan_describe; padding follows from the shape, not from the spec
     };
     while (*p) {
@@ -160,6 +162,7 @@ static bool parse_spec(const char* text, Spec* out)
     if ((sp.wv != 4 && sp.wv != 8 && sp.wv != 16) || (sp.wv != 4 && sp.fam != FAM_SKINNY)) return false;
     if (sp.nr != -1 && (sp.nr < 16 || sp.nr > 64 || sp.nr % 16 || (sp.nr != 16 && sp.fam != FAM_SKINNY))) return false;
     if (sp.nr == -1 || sp.fam != FAM_SKINNY) sp.nr = 0;
+    if (sp.mr && (sp.mr < 16 || sp.mr > 64 || sp.mr % 16 || sp.fam != FAM_SKINNY || sp.sk > 1 || sp.ra)) return false;      // K is not split across workgroups too
     if (sp.ra > 1 || (sp.ra && (sp.fam != FAM_SKINNY || sp.wv != kStripWaves || (sp.nr != 0 && sp.nr != 16) || sp.sk > 1))) return false;
     *out = sp;
     return true;
@@ -696,6 +699,38 @@ bool joins_launches(const Spec& s, int64_t M, int64_t N, int64_t K)
            2.0 * ((double)M * K + (double)K * N + (double)M * N) <= 8.0 * 1048576.0;
 }
 
+// More than 16 rows of A: strips of B times blocks of rows of A, by the same kernel, where one workgroup for every compute unit covers the problem.  The
+// tile is the one with the fewest rows of A and B together, which is what a compute unit has to fetch of every k.  Tiles of the large
+// family read each byte for more products, but want more of them than such problems have: their K is split, with planes and a second launch.
+// Timed against the choices made without it on 37 488 random problems of 17 to 320 rows: 0.75 of their time from HBM (725 slower by more than 3 %, 245 by
+// 10 %), 0.68 from the cache (312, 51), 0.37 planned, run once and freed.  From HBM / from the cache, by rows of A and B in a tile, and where it ends:
+//  * 32: 0.59 / 0.57 at K 1024-2048, 0.66 / 0.60 to 3072, 0.74 / 0.65 to 4096, 0.85 / 0.70 to 6144, 1.0 / 0.75 to 8192, 1.25 / 0.9 beyond (a split leaves less
+//    of K to each);
+//  * 48: 0.70 / 0.65, 0.77 / 0.69, 0.83 / 0.75, then 0.98 / 0.77 to 4608, 1.05 / 0.75 to 5120; 64: 0.76 / 0.70, 0.82 / 0.69, 0.90 / 0.75, then 1.0 / 0.76;
+//  * 80: 0.89 / 0.83, 0.87 / 0.78, to 3584 0.91 / 0.79, then 0.97 / 0.85; 96: 0.97 / 0.94, left out;
+//  * fewer than twice as many columns as rows of A, where A's bytes are what HBM gives: 0.97 / 0.74 at 32 rows and K 4608-6144, 1.0 / 0.88 at 48 and K 3072-4608;
+//  * K below 1024: such picks share launches, and a strip ends before its copies flow (80 rows, K below 1280: 1.1);
+//  * 17 to 32 rows of A: tiles of 16 x 16 only (0.85 / 0.95 of strips of all rows); wider ones are level with those.
+bool strip_tiles_choice(int64_t M, int64_t N, int64_t K, const Spec& pick, Spec* out)
+{
+    if (M > 320 || N % 8 || N < 64 || K < 1024 || K > 6144 || joins_launches(pick, M, N, K)) return false;
+    const int64_t cus = cu_count();
+    int best = 81, mr = 0, nr = 0;
+    for (int a = 16; a <= 64 && a < M + 16; a += 16)
+        for (int b = 16; b <= 64; b += 16) {
+            if (((M + a - 1) / a) * ((N + b - 1) / b) > cus || a + b > best) continue;
+            if (a + b == best && std::abs(a - b) >= std::abs(mr - nr)) continue;
+            best = a + b; mr = a; nr = b;
+        }
+    if (!mr || (M <= 32 && (best > 32 || N % 16))) return false;
+    const int64_t longest = 2 * M > N ? (best <= 32 ? 4608 : 3072) : best <= 32 ? 6144 : best <= 64 ? 4096 : 3584;
+    if (K > longest || (best > 64 && K < 1280)) return false;
+    *out = Spec();
+    out->fam = FAM_SKINNY; out->mr = mr; out->nr = nr;
+    return true;
+}
+
+
 // Column-major B, up to 32 rows of A and 12288 columns: one strip of 16, 32 or 48 rows of B for every compute unit, K split among its
 // waves only, so that there are no planes and no second launch (skinny_tn_gemm_kernel).  Timed against the choices made without it,
 // table rows among them, on 10 424 problems of 1 to 32 rows (widths of layers, and any multiples of 16 and 8): on the 5955 that this takes 0.83 of their
@@ -710,6 +745,7 @@ bool joins_launches(const Spec& s, int64_t M, int64_t N, int64_t K)
 //  * columns that are no whole strip of 16 keep the measured neighbours' kernels.
 bool strips_choice(int64_t M, int64_t N, int64_t K, const Spec& pick, Spec* out)
 {
+    if (M > 16 && strip_tiles_choice(M, N, K, pick, out)) return true;
     if (M > 32 || N % 16 || N < 64 || N > 12288 || joins_launches(pick, M, N, K)) return false;
     const int64_t blocks = (N + 4095) / 4096;
     if (K < 256 * blocks) return false;
@@ -944,7 +980,7 @@ bool select_kernel(hgemm_plan_s* p)
 bool admit_skinny_lds(int dev, int instance, const SkinnyTnKernel& k)
 {
     if (k.lds <= 64 * 1024) return true;
-    static std::atomic<bool> allowed[kMaxDevices][3 * 3 * 4 * 2] = {};
+    static std::atomic<bool> allowed[kMaxDevices][4 * 3 * 4 * 2] = {};
     const bool keep = dev >= 0 && dev < kMaxDevices;
     if (keep && allowed[dev][instance].load(std::memory_order_acquire)) return true;
     if (hipFuncSetAttribute((const void*)k.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, k.lds) != hipSuccess) {
@@ -970,16 +1006,18 @@ hgemm_status_t finish_plan(hgemm_plan_s* p)
     if (s.fam == FAM_GENERIC) return HGEMM_OK;
     if (s.fam == FAM_SKINNY) {
         // strips of columns x K slabs of whole steps; partial planes as for split-K
-        if (!kernels_can_run(p) || M <= 0 || N <= 0 || K <= 0 || M > kSkinnyMaxM) return HGEMM_ERR_UNSUPPORTED;
+        if (!kernels_can_run(p) || M <= 0 || N <= 0 || K <= 0 || (M > kSkinnyMaxM && !s.mr)) return HGEMM_ERR_UNSUPPORTED;
         const bool tn = p->lay.b == HGEMM_COL_MAJOR;
         p->tn_kernel = tn;
-        const int mb = M <= 16 ? 1 : M <= 32 ? 2 : 4;
+        const int mb = s.mr ? s.mr / 16 : M <= 16 ? 1 : M <= 32 ? 2 : 4;
+        const int64_t row_blocks = s.mr ? (M + s.mr - 1) / s.mr : 1;
         const int64_t step = skinny_step(s, tn);
         const int64_t ksteps = (K + step - 1) / step;
         const int64_t sk = effective_splits(ksteps, s.sk);
         if (sk > 65535) return HGEMM_ERR_UNSUPPORTED;
         s.sk = (int)sk;
         if (sk == 1) s.fr = 0;
+        if (s.mr && (!tn || row_blocks > 65535)) return HGEMM_ERR_UNSUPPORTED;
         if (!tn && s.nr != 0 && s.nr != 16) return HGEMM_ERR_UNSUPPORTED;
         if (!tn || s.ra) s.nr = 0;
         if (p->any_b && s.wv != 4) return HGEMM_ERR_UNSUPPORTED;
@@ -990,7 +1028,7 @@ hgemm_status_t finish_plan(hgemm_plan_s* p)
         if (tn && !s.ra) {
             const int rows = strip_rows(s, N);
             const SkinnyTnKernel k = skinny_tn_kernel(mb, s.fr != 0, s.wv, rows);
-            const int instance = (((mb / 2) * 3 + s.wv / 8) * 4 + rows / 16 - 1) * 2 + s.fr;
+            const int instance = (((mb - 1) * 3 + s.wv / 8) * 4 + rows / 16 - 1) * 2 + s.fr;
             if (!k.kernel || !admit_skinny_lds(p->device, instance, k)) return HGEMM_ERR_UNSUPPORTED;
             p->skinny = k.kernel;
             p->skinny_lds = k.lds;
@@ -1001,7 +1039,7 @@ hgemm_status_t finish_plan(hgemm_plan_s* p)
         GemmArgs& a = p->args;
         a.M = (int)M; a.N = (int)N; a.K = (int)K;
         a.lda = (int)p->lay.lda; a.ldb = (int)p->lay.ldb; a.ldc = (int)p->lay.ldc;
-        a.tiles_m = 1; a.tiles_n = (int)strips;
+        a.tiles_m = (int)row_blocks; a.tiles_n = (int)strips;
         a.splits = (int)sk;
         a.k_per_split = s.ra ? (int)(ksteps * 32) : (int)(((ksteps + sk - 1) / sk) * step);      // of a wave, else of a slab
         a.b_rows = (int)(p->padded && !p->copy_b ? p->uK : K);
@@ -1781,7 +1819,9 @@ static hgemm_status_t run_plan(const hgemm_plan_s* plan, const void* A, const vo
     a.b_rows = (int)b_rows;
     a.c_wide = N % 8 == 0 && plan->lay.ldc % 8 == 0 && ((uintptr_t)C & 15) == 0;
     if (plan->skinny) {
-        hipLaunchKernelGGL(plan->skinny, dim3((unsigned)a.tiles_n, (unsigned)a.splits), dim3(64u * (unsigned)plan->spec.wv), (unsigned)plan->skinny_lds, stream, a);
+        // strips of a column-major B go round the XCDs: whole rounds of eight where several blocks of rows follow one another
+        const unsigned strips = a.tiles_m > 1 ? (unsigned)(a.tiles_n + 7) / 8u * 8u : (unsigned)a.tiles_n;
+        hipLaunchKernelGGL(plan->skinny, dim3(strips, (unsigned)(a.splits * a.tiles_m)), dim3(64u * (unsigned)plan->spec.wv), (unsigned)plan->skinny_lds, stream, a);
         if (a.splits > 1 && !plan->spec.fr) {
             if (hipGetLastError() != hipSuccess) return HGEMM_ERR_LAUNCH;
             const int64_t quads = M * ((N + 3) / 4);
@@ -1988,7 +2028,7 @@ hgemm_status_t hgemm_plan_launch_info(hgemm_plan_t plan, int64_t* workgroups, in
     }
     int64_t wg, lds, th;
     if (plan->skinny) {
-        wg = (int64_t)plan->args.tiles_n * plan->args.splits;
+        wg = (int64_t)plan->args.tiles_n * plan->args.splits * plan->args.tiles_m;
         lds = plan->spec.ra ? 2 * kStripWaves * (plan->M <= 16 ? 1 : 2) * 1024 : plan->tn_kernel ? plan->skinny_lds : 4 * 16 * (kSkinnyCols + 4) * 4;
         th = 64 * plan->spec.wv;
     } else if (plan->entry) {
@@ -2015,7 +2055,7 @@ const char* hgemm_spec_help(void)
         std::string t =
             "generic\n"
             "    one thread per element, any shape, alignment and layout\n"
-            "skinny,sk=SPLITS[,fr=1][,wv=WAVES][,nr=ROWS][,ra=1]\n"
+            "skinny,sk=SPLITS[,fr=1][,wv=WAVES][,nr=ROWS][,mr=ROWS][,ra=1]\n"
             "    memory-bound kernel for M <= 64 rows of A (row-major B): workgroups of wv = 4 (default), 8 or 16 waves\n"
             "    take 128 columns and a K slab each and stream it in steps of 16 * wv rows; a wave takes 16 rows of a\n"
             "    step, transposes its 4 x 8 blocks in registers for 16x16x16 matrix-core instructions (M on a 16-wide\n"
@@ -2023,7 +2063,8 @@ const char* hgemm_spec_help(void)
             "    slab order by the split-K reduction launch or, with fr = 1, by the workgroup that arrives last.\n"
             "    Column-major B (K contiguous): a workgroup takes nr = 16, 32, 48 or 64 rows of B (columns of C; default: one strip for\n"
             "    every compute unit up to 12288 columns), its waves take chunks\n"
-            "    of 64 k of them in turn, copied to LDS of their own; sk splits K further across workgroups.  ra = 1 (with sk = 1, wv = 8; M <= 32, K <= 8192, above 16 rows 4096): A stays\n"
+            "    of 64 k of them in turn, copied to LDS of their own; sk splits K further across workgroups.  mr = 16, 32, 48 or 64 (with\n"
+            "    sk = 1, any M; above 32 four or eight waves): a workgroup takes mr rows of A only.  ra = 1 (with sk = 1, wv = 8; M <= 32, K <= 8192, above 16 rows 4096): A stays\n"
             "    in registers, one workgroup per compute unit walks strips of 16 rows of B\n"
             "mfma,bm=BM,bn=BN,bk=BK,wm=WM,wn=WN,st=STAGES[,pf=PREFETCH][,sk=SPLITS][,gm=GROUP][,tb=1][,sm=1][,fr=1][,ps=1][,ac=16][,mi=16][,ph=1][,di=1]\n"
             "    pipelined 32x32x16 MFMA kernel; BMxBN tile per workgroup, WMxWN wavefronts, STAGES LDS buffers,\n"
@@ -2145,6 +2186,16 @@ hgemm_status_t hgemm_candidates(int64_t M, int64_t N, int64_t K, const hgemm_lay
                     }
                 }
         }
+        if (l.b == HGEMM_COL_MAJOR && M > 16 && M <= 512)       // blocks of rows of A: one workgroup for most compute units
+            for (int mr : {16, 32, 48, 64})
+                for (int nr : {16, 32, 48, 64}) {
+                    const int64_t wgs = ((M + mr - 1) / mr) * ((N + nr - 1) / nr);
+                    if (mr >= M + 16 || wgs > CUS || wgs < CUS / 2) continue;
+                    Spec s;
+                    s.fam = FAM_SKINNY; s.mr = mr; s.nr = nr;
+                    out += spec_to_string(s);
+                    out += "\n";
+                }
         if (l.b == HGEMM_COL_MAJOR && M <= 32 && N >= 16 * CUS && skinny_strips(M <= 16 ? 1 : 2, K)) out += "skinny,sk=1,wv=8,ra=1\n";
         for (const MfmaEntry& e : registry()) {
             if (!tile_fits_problem(e, M, N)) continue;

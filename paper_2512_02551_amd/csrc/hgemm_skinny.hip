@@ -37,7 +37,11 @@ SkinnyTnKernel tn_kernel(bool fused)
 {
     constexpr int NB = NR / 16, TWO = 2 * WAVES * 2 * (MB + NB);      // KiB of two chunks a wave
     constexpr int DEPTH = TWO <= 32 ? 3 : TWO <= 160 ? 2 : 1;
-    if constexpr (WAVES * MB * NB <= 64 && (WAVES < 16 || MB * NB <= 4))
+    if constexpr (MB == 3) {
+        if constexpr (WAVES * MB * NB <= 64 && WAVES < 16)
+            if (!fused) return {skinny_tn_gemm_kernel<MB, false, DEPTH, WAVES, NR>, SkinnyTnLds<MB, DEPTH, WAVES, NB>::TOTAL};
+        return {nullptr, 0};
+    } else if constexpr (WAVES * MB * NB <= 64 && (WAVES < 16 || MB * NB <= 4))
         return {fused ? skinny_tn_gemm_kernel<MB, true, DEPTH, WAVES, NR> : skinny_tn_gemm_kernel<MB, false, DEPTH, WAVES, NR>, SkinnyTnLds<MB, DEPTH, WAVES, NB>::TOTAL};
     else
         return {nullptr, 0};
@@ -55,6 +59,10 @@ SkinnyTnKernel tn_kernel_for(int mb, bool fused, int nr)
         case 232: return tn_kernel<WAVES, 2, 32>(fused);
         case 248: return tn_kernel<WAVES, 2, 48>(fused);
         case 264: return tn_kernel<WAVES, 2, 64>(fused);
+        case 316: return tn_kernel<WAVES, 3, 16>(fused);
+        case 332: return tn_kernel<WAVES, 3, 32>(fused);
+        case 348: return tn_kernel<WAVES, 3, 48>(fused);
+        case 364: return tn_kernel<WAVES, 3, 64>(fused);
         case 416: return tn_kernel<WAVES, 4, 16>(fused);
         case 432: return tn_kernel<WAVES, 4, 32>(fused);
         case 448: return tn_kernel<WAVES, 4, 48>(fused);

@@ -249,6 +249,10 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_gemm_kernel(GemmArgs g)
 // loads that were operands) -> 7.7 us, 16 x 4096 x 4096 10.0 -> 8.4, 1 x 7296 x 7296 23.6 -> 20.8; in strips of 32 rows 16 x 5888 x 1920 9.0 -> 7.2, 16 x 14336 x
 // 4096 24.8 -> 23.1; of 48 16 x 11008 x 4096 20.2 -> 19.1; from the cache 1 x 4096 x 4096 7.7 -> 4.6, 16 x 14336 x 4096 21.4 -> 18.3.  Not where K is long
 // and A of 16 rows: 16 x 4096 x 11008 21.9 from HBM, split 32-row tiles 21.1 (17.9 from the cache, this 15.7).
+// With more rows of A, a workgroup takes 16 MB of them (grid.y then counts blocks of rows, which an XCD's strips share): what bounds it is the
+// (16 MB + NR) * 2 bytes of each k that a compute unit fetches, at 57 GB/s from HBM, 110 from the cache.  From HBM / from the cache, the best
+// kernel of any family before -> this: 24 x 2048 x 2048 5.7 / 5.1 -> 4.8 / 3.8 us, 64 x 2048 x 2048 7.7 / 6.7 -> 6.1 / 4.5, 96 x 3072 x 3072 14.6 / 11.6 -> 10.7 / 7.1,
+// 48 x 8192 x 4096 18.6 / 15.0 -> 16.6 / 12.8.
 // Four waves with three chunks each (48 KiB at NR = 16, three workgroups to a compute unit) are the best of 4, 8 and 16 waves and 2 to 8
 // chunks: 1 x 4096 x 4096 7.8, eight waves 8.1, sixteen 8.2.  Strips are dealt so that an XCD's workgroups hold adjacent ones (see below).
 constexpr int kSkinnyTnRows = 16;      // rows of B (columns of C) per workgroup unless a spec asks for more
@@ -277,10 +281,12 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_tn_gemm_kernel(GemmArgs g)
     const int t = threadIdx.x;
     const int lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int strips = gridDim.x, xcd = blockIdx.x & 7;
+    const int strips = g.tiles_n, xcd = blockIdx.x & 7;
+    if ((int)(blockIdx.x >> 3) >= (strips >> 3) + (xcd < (strips & 7))) return;      // the grid is rounded up to whole XCDs
     const int strip = xcd * (strips >> 3) + min(xcd, strips & 7) + (blockIdx.x >> 3);
     const int n0 = strip * NR;
-    const int split = blockIdx.y;
+    const int m0 = g.tiles_m > 1 ? (int)blockIdx.y * 16 * MB : 0;                    // grid.y: blocks of rows of A, or slabs of K
+    const int split = g.tiles_m > 1 ? 0 : (int)blockIdx.y;
     const int k_lo = split * g.k_per_split;
     const int k_hi = min(g.K, k_lo + g.k_per_split);
     const int steps = (k_hi - k_lo + 64 * WAVES - 1) / (64 * WAVES);
@@ -305,7 +311,7 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_tn_gemm_kernel(GemmArgs g)
         }
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
-            const int m = 16 * mb + 8 * h + row8;
+            const int m = m0 + 16 * mb + 8 * h + row8;
             a_off[mb][h] = m < g.M ? (unsigned)((m * g.lda + k + chunk[h] * 8) * 2) : OOB;
         }
     }
@@ -387,7 +393,7 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_tn_gemm_kernel(GemmArgs g)
             float4v s = float4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int w = 0; w < WAVES; ++w) s += *(const float4v*)(red + (((w * MB + mb) * NB + nb) * 64 + lane) * 4);
-            const int m = 16 * mb + c16, n = n0 + 16 * nb + 4 * grp;
+            const int m = m0 + 16 * mb + c16, n = n0 + 16 * nb + 4 * grp;
             if (m >= g.M || n >= g.N) continue;
             if (direct) {
                 half4 o;

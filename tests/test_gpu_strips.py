@@ -31,3 +31,23 @@ def test_every_instance(m, n, k, wv, nr):
 @pytest.mark.parametrize("m,n,k,nr", [(1, 4096, 4096, 16), (16, 64, 4096, 16), (16, 4112, 4096, 32), (32, 8192, 2048, 32), (5, 12288, 768, 48)], ids=str)
 def test_the_planner_takes_it(m, n, k, nr):
     assert check(None, m, n, k, True) == "skinny,sk=1" + (f",nr={nr}" if nr > 16 else "")
+
+
+@pytest.mark.parametrize("nr", [16, 32, 48, 64])
+@pytest.mark.parametrize("mr", [16, 32, 48, 64])
+@pytest.mark.parametrize("m,n,k", [(17, 40, 8), (65, 136, 264), (96, 200, 1000), (130, 1032, 72)], ids=str)
+def test_blocks_of_rows(m, n, k, mr, nr):
+    """A last block of one row, of a part and of all of its rows; strips that are no whole number of XCDs."""
+    for wv in ("", ",wv=8"):
+        spec = f"skinny,sk=1{wv},nr={nr},mr={mr}"
+        if wv and mr * nr > 2048:
+            with pytest.raises(hg.HgemmError):
+                hg.Plan(m, n, k, hg.Layouts.make(b_col_major=True), spec)
+            continue
+        assert check(spec, m, n, k, True) == spec
+        check(spec, m, n, k, True, (8, 16, 8), (8, 8, 8), special=True)
+
+
+@pytest.mark.parametrize("m,n,k,tile", [(17, 2048, 2056, (16, 16)), (33, 4096, 4096, (32, 32)), (96, 3000, 3072, (48, 32)), (320, 640, 3072, (32, 32))], ids=str)
+def test_the_planner_takes_blocks_of_rows(m, n, k, tile):
+    assert check(None, m, n, k, True) == "skinny,sk=1,nr=%d,mr=%d" % tile

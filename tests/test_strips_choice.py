@@ -26,3 +26,25 @@ def test_outside(m, n, k):
 
 def test_row_major_b_is_not_touched():
     assert "nr=" not in hg.plan_choice(16, 11008, 4096) and hg.plan_choice(16, 4096, 4096).startswith("table: mfma,")
+
+
+@pytest.mark.parametrize("m,n,k,tile", [
+    (17, 2048, 6144, (16, 16)), (32, 64, 4608, (16, 16)), (33, 4096, 4096, (32, 32)), (64, 2048, 4096, None), (40, 2048, 4096, (32, 16)), (48, 8192, 3584, (32, 48)),
+    (64, 4000, 4096, (32, 32)), (96, 3072, 3584, (48, 32)), (320, 640, 3072, (32, 32)), (129, 1160, 2048, (32, 32))], ids=str)
+def test_blocks_of_rows_inside(m, n, k, tile):
+    """The fewest rows of A and B together that one workgroup for every compute unit covers; a table's row stays."""
+    assert ("mr=" not in picked(m, n, k)) if tile is None else picked(m, n, k, lda=k + 64, ldb=k + 8, ldc=n + 8) == "skinny,sk=1,nr=%d,mr=%d" % tile
+
+
+@pytest.mark.parametrize("m,n,k", [
+    (16, 2048, 4096), (17, 2064, 4096), (17, 2056, 4096), (17, 2048, 6152), (32, 32, 4616), (33, 4096, 4104), (48, 8192, 3592), (64, 8192, 2048), (64, 4001, 4096),
+    (64, 4000, 4095), (64, 4000, 1016), (72, 5000, 1272), (321, 640, 3072), (320, 632, 3080)], ids=str)
+def test_blocks_of_rows_outside(m, n, k):
+    """Fewer rows, more tiles than compute units, a longer K, a shorter one, sizes off 8, more rows than twice the columns."""
+    assert "mr=" not in picked(m, n, k)
+
+
+def test_blocks_of_rows_need_no_split():
+    for spec in ("skinny,sk=2,mr=16", "skinny,sk=1,mr=8", "skinny,sk=1,mr=24", "skinny,sk=1,mr=80", "mfma,mr=16", "skinny,sk=1,wv=8,ra=1,mr=16"):
+        with pytest.raises(hg.HgemmError):
+            hg.Plan(64, 4096, 4096, hg.Layouts.make(b_col_major=True), spec)
