@@ -49,6 +49,7 @@ static const std::vector<MfmaEntry>& registry()
 
 void (*skinny_kernel(int mb, bool fused, int waves))(GemmArgs);                   // hgemm_skinny.hip
 SkinnyTnKernel skinny_tn_kernel(int mb, bool fused, int waves, int nr);
+SkinnyTnKernel skinny_tiles_kernel(int mb);
 void (*skinny_any_b_kernel(int mb, bool fused))(GemmArgs);
 void (*skinny_strips(int mb, int64_t K))(GemmArgs);
 
@@ -758,6 +759,22 @@ bool strips_choice(int64_t M, int64_t N, int64_t K, const Spec& pick, Spec* out)
     return true;
 }
 
+// The same for a row-major B, in strips of 32 columns: half a cache line of each of its rows, which HBM gives more slowly, so the range is shorter.  On 23 596
+// random problems of 17 to 320 rows 0.80 of the time from HBM of the choices without it (84 slower by more than 3 %, 39 by 10 %), 0.65 from the cache
+// (39, 13), 0.38 planned, run once and freed.  Where it ends, from HBM / from the cache: tiles of 16 x 32 0.78 / 0.61 at K 1024-1536, 0.85 / 0.66 to 2048, 1.05 / 0.74 to
+// 3072, 1.25 / 0.82 to 4096; of 32 x 32 0.9 / 0.75 to 2048, 1.0 / 0.78 to 3072, and level with strips of all rows up to 32; fewer than twice as many columns as
+// rows 0.93 / 0.65 at K 1536-2048, a quarter of them slower; wider tiles 1.05 / 0.9.
+bool row_strip_tiles_choice(int64_t M, int64_t N, int64_t K, int64_t ldb, const Spec& pick, Spec* out)
+{
+    if (M <= 16 || M > 320 || N < 64 || K < 768 || K > 2048 || (K + 256) * ldb * 2 >= ((int64_t)1 << 31) || joins_launches(pick, M, N, K)) return false;
+    const int64_t cus = cu_count(), strips = (N + 31) / 32;
+    const int mr = (M + 15) / 16 * strips <= cus ? 16 : M > 32 && (M + 31) / 32 * strips <= cus ? 32 : 0;
+    if (!mr || (2 * M > N && K > 1280)) return false;
+    *out = Spec();
+    out->fam = FAM_SKINNY; out->mr = mr; out->nr = 32;
+    return true;
+}
+
 bool evaluate_model(int64_t M, int64_t N, int64_t K, Spec* out, bool b_row_major, bool measured)
 {
     double best = 1e300;
@@ -976,11 +993,12 @@ bool select_kernel(hgemm_plan_s* p)
     return true;
 }
 
+constexpr int kTnInstances = 4 * 3 * 4 * 2;
 // More than 64 KiB of dynamic LDS: asked for once per kernel and device.
 bool admit_skinny_lds(int dev, int instance, const SkinnyTnKernel& k)
 {
     if (k.lds <= 64 * 1024) return true;
-    static std::atomic<bool> allowed[kMaxDevices][4 * 3 * 4 * 2] = {};
+    static std::atomic<bool> allowed[kMaxDevices][kTnInstances + 2] = {};
     const bool keep = dev >= 0 && dev < kMaxDevices;
     if (keep && allowed[dev][instance].load(std::memory_order_acquire)) return true;
     if (hipFuncSetAttribute((const void*)k.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, k.lds) != hipSuccess) {
@@ -1017,18 +1035,21 @@ hgemm_status_t finish_plan(hgemm_plan_s* p)
         if (sk > 65535) return HGEMM_ERR_UNSUPPORTED;
         s.sk = (int)sk;
         if (sk == 1) s.fr = 0;
-        if (s.mr && (!tn || row_blocks > 65535)) return HGEMM_ERR_UNSUPPORTED;
-        if (!tn && s.nr != 0 && s.nr != 16) return HGEMM_ERR_UNSUPPORTED;
-        if (!tn || s.ra) s.nr = 0;
+        if (row_blocks > 65535) return HGEMM_ERR_UNSUPPORTED;
+        const bool nn_tiles = !tn && s.mr;
+        // offsets of the last copies, whose rows may lie past B
+        if (nn_tiles && (p->any_b || s.wv != 4 || s.nr != 32 || s.mr > 32 || (K + 64 * s.wv) * p->lay.ldb * 2 >= ((int64_t)1 << 31))) return HGEMM_ERR_UNSUPPORTED;
+        if (!tn && !nn_tiles && s.nr != 0 && s.nr != 16) return HGEMM_ERR_UNSUPPORTED;
+        if ((!tn && !nn_tiles) || s.ra) s.nr = 0;
         if (p->any_b && s.wv != 4) return HGEMM_ERR_UNSUPPORTED;
         if (s.ra && (!tn || M > 32)) return HGEMM_ERR_UNSUPPORTED;
         // with A resident, one workgroup per compute unit (a multiple of the 8 XCDs) walks the strips
-        const int64_t strips = s.ra ? std::max<int64_t>(8, cu_count() / 8 * 8) : (N + skinny_cols(s, tn, N) - 1) / skinny_cols(s, tn, N);
+        const int64_t strips = s.ra ? std::max<int64_t>(8, cu_count() / 8 * 8) : (N + skinny_cols(s, tn || nn_tiles, N) - 1) / skinny_cols(s, tn || nn_tiles, N);
         if (s.fr && strips * (int64_t)sizeof(int) > (int64_t)kCounterBytes) return HGEMM_ERR_UNSUPPORTED;
-        if (tn && !s.ra) {
+        if ((tn && !s.ra) || nn_tiles) {
             const int rows = strip_rows(s, N);
-            const SkinnyTnKernel k = skinny_tn_kernel(mb, s.fr != 0, s.wv, rows);
-            const int instance = (((mb - 1) * 3 + s.wv / 8) * 4 + rows / 16 - 1) * 2 + s.fr;
+            const SkinnyTnKernel k = nn_tiles ? skinny_tiles_kernel(mb) : skinny_tn_kernel(mb, s.fr != 0, s.wv, rows);
+            const int instance = nn_tiles ? kTnInstances + mb - 1 : (((mb - 1) * 3 + s.wv / 8) * 4 + rows / 16 - 1) * 2 + s.fr;
             if (!k.kernel || !admit_skinny_lds(p->device, instance, k)) return HGEMM_ERR_UNSUPPORTED;
             p->skinny = k.kernel;
             p->skinny_lds = k.lds;
@@ -1333,6 +1354,10 @@ Choices choose_spec(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, i
         c.spec[c.n++].sk = 1;
     }
     Spec strips;
+    if (!tn && !padded && strcmp(c.source, "table") && c.n < 3 && row_strip_tiles_choice(M, N, K, l.ldb, c.spec[0], &strips)) {
+        for (int i = c.n++; i > 0; --i) c.spec[i] = c.spec[i - 1];
+        c.spec[0] = strips;
+    }
     if (tn && !padded && strcmp(c.source, "table") && c.n < 3 && strips_choice(M, N, K, c.spec[0], &strips)) {
         for (int i = c.n++; i > 0; --i) c.spec[i] = c.spec[i - 1];
         c.spec[0] = strips;
@@ -2029,7 +2054,7 @@ hgemm_status_t hgemm_plan_launch_info(hgemm_plan_t plan, int64_t* workgroups, in
     int64_t wg, lds, th;
     if (plan->skinny) {
         wg = (int64_t)plan->args.tiles_n * plan->args.splits * plan->args.tiles_m;
-        lds = plan->spec.ra ? 2 * kStripWaves * (plan->M <= 16 ? 1 : 2) * 1024 : plan->tn_kernel ? plan->skinny_lds : 4 * 16 * (kSkinnyCols + 4) * 4;
+        lds = plan->spec.ra ? 2 * kStripWaves * (plan->M <= 16 ? 1 : 2) * 1024 : plan->skinny_lds ? plan->skinny_lds : 4 * 16 * (kSkinnyCols + 4) * 4;
         th = 64 * plan->spec.wv;
     } else if (plan->entry) {
         wg = plan->spec.sm ? (int64_t)plan->args.dp_tiles + plan->args.sk_workers

@@ -91,6 +91,14 @@ SkinnyTnKernel skinny_tn_kernel(int mb, bool fused, int waves, int nr)
     return waves == 4 ? tn_kernel_for<4>(mb, fused, nr) : waves == 8 ? tn_kernel_for<8>(mb, fused, nr) : waves == 16 ? tn_kernel_for<16>(mb, fused, nr) : SkinnyTnKernel{nullptr, 0};
 }
 
+// Row-major B in strips of 32 columns, blocks of 16 * mb rows of A (mb 1 or 2), four waves.
+SkinnyTnKernel skinny_tiles_kernel(int mb)
+{
+    if (mb == 1) return {skinny_tile_kernel<1, 2, 4, 32>, SkinnyTnLds<1, 2, 4, 2>::TOTAL};
+    if (mb == 2) return {skinny_tile_kernel<2, 2, 4, 32>, SkinnyTnLds<2, 2, 4, 2>::TOTAL};
+    return {nullptr, 0};
+}
+
 // Column-major B, A resident: the instance with the fewest registers whose eight waves hold all of K, for M <= 16 * mb (mb 1 or 2); null where
 // none does.  Wider instances are slower on a K that a narrower one holds (32001 x 2048: 23.3 us, for 3072 24.5), two parts of
 // K slower than one.

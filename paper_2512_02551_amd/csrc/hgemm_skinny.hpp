@@ -270,12 +270,12 @@ struct SkinnyTnKernel {                // an instance and its dynamic LDS
     int lds;
 };
 
-template <int MB, bool FUSED, int DEPTH, int WAVES, int NR>
-__global__ __launch_bounds__(64 * WAVES) void skinny_tn_gemm_kernel(GemmArgs g)
+template <int MB, bool FUSED, int DEPTH, int WAVES, int NR, bool TN>
+__device__ __forceinline__ void skinny_strip(const GemmArgs& g)
 {
     constexpr int NB = NR / 16;                                // 16-row blocks of B per workgroup
     typedef SkinnyTnLds<MB, DEPTH, WAVES, NB> L;
-    static_assert(NR % 16 == 0, "rows of B");
+    static_assert(TN ? NR % 16 == 0 : NR == 32 && !FUSED, "rows of B");
     extern __shared__ __attribute__((aligned(1024))) char lds[];
 
     const int t = threadIdx.x;
@@ -293,21 +293,28 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_tn_gemm_kernel(GemmArgs g)
 
     const unsigned OOB = 0x80000000u;
     const int4v rsrcA = make_rsrc(g.A, (unsigned)min((long long)g.M * g.lda * 2, 0x7fffffffLL));
-    const int4v rsrcB = make_rsrc(g.B, (unsigned)min((long long)g.N * g.ldb * 2, 0x7fffffffLL));
+    const int4v rsrcB = make_rsrc(g.B, (unsigned)min((long long)(TN ? g.N : min(k_hi, g.b_rows)) * g.ldb * 2, 0x7fffffffLL));
 
     // A copy covers 8 rows of 128 bytes: lane i fills physical chunk i % 8 of row i / 8 with logical chunk p ^ (row / 2) % 8, in the second
     // copy of a block with the chunk four further.  Rows past the end and k past the slab (K is a multiple of 8) read as zeros.
     const int row8 = lane >> 3;
     const int chunk[2] = {(lane & 7) ^ (lane >> 4), (lane & 7) ^ (lane >> 4) ^ 4};
     int k = k_lo + wave * 64;                                  // of the chunk copied next
-    unsigned at = 0;                                           // and its distance from the first, in bytes
-    unsigned a_off[MB][2], b_off[NB][2];
+    unsigned at = 0, b_at = 0;                                 // and its distance from the first, in bytes
+    unsigned a_off[MB][2], b_off[TN ? NB : 1][2];
+    // Row-major B: a copy covers 16 rows of 32 columns, chunks swizzled for the transposing reads; rows past K lie past the end of B.
+    const unsigned b_load = (unsigned)(16 * g.ldb * 2), b_step = (unsigned)(64 * WAVES * g.ldb * 2);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
+        if constexpr (TN) {
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            const int n = n0 + 16 * nb + 8 * h + row8;
-            b_off[nb][h] = n < g.N ? (unsigned)((n * g.ldb + k + chunk[h] * 8) * 2) : OOB;
+            for (int nb = 0; nb < NB; ++nb) {
+                const int n = n0 + 16 * nb + 8 * h + row8;
+                b_off[nb][h] = n < g.N ? (unsigned)((n * g.ldb + k + chunk[h] * 8) * 2) : OOB;
+            }
+        } else {
+            const int row = lane >> 2, n = n0 + 8 * ((lane & 3) ^ (((row >> 3) & 1) << 1));
+            b_off[0][h] = n < g.N ? (unsigned)(((k + row) * g.ldb + n) * 2) : OOB;
         }
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
@@ -318,10 +325,15 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_tn_gemm_kernel(GemmArgs g)
     const unsigned ring = __builtin_amdgcn_readfirstlane((int)lds_addr_of(lds)) + wave * L::RING;
     auto copy_chunk = [&](unsigned slot) {
         const bool ok[2] = {k + chunk[0] * 8 < k_hi, k + chunk[1] * 8 < k_hi};
+        if constexpr (TN) {
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
+            for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-            for (int h = 0; h < 2; ++h) dma16(rsrcB, ring + slot + (2 * nb + h) * 1024, ok[h] ? b_off[nb][h] + at : OOB);
+                for (int h = 0; h < 2; ++h) dma16(rsrcB, ring + slot + (2 * nb + h) * 1024, ok[h] ? b_off[nb][h] + at : OOB);
+        } else {
+            static_for<2 * NB>([&](auto j) { dma16(rsrcB, ring + slot + decltype(j)::value * 1024, b_off[0][0] + b_at + decltype(j)::value * b_load); });
+            b_at += b_step;
+        }
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -334,6 +346,16 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_tn_gemm_kernel(GemmArgs g)
     const int c16 = lane & 15, grp = lane >> 4;
     const char* const frag = lds + wave * L::RING + c16 * 128;
     const int at_ks[2] = {(grp ^ ((c16 >> 1) & 7)) * 16, ((4 + grp) ^ ((c16 >> 1) & 7)) * 16};
+    // row-major B: a lane supplies four columns of rows 8 grp + c16 / 4 and + 4 of a k-step
+    int tr_at[TN ? 1 : NB];
+    if constexpr (!TN) {
+        const int row = 8 * grp + (c16 >> 2);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            const int n = 16 * nb + 4 * (lane & 3), c = n >> 3;
+            tr_at[nb] = wave * L::RING + row * (2 * NR) + (c ^ (((row >> 3) & 1) << 1)) * 16 + (n & 7) * 2;
+        }
+    }
     float4v acc[MB][NB];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
@@ -351,7 +373,17 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_tn_gemm_kernel(GemmArgs g)
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) fb[nb][ks] = *(const half8*)(frag + slot + 2 * nb * 1024 + at_ks[ks]);
+            for (int nb = 0; nb < NB; ++nb) {
+                if constexpr (TN) {
+                    fb[nb][ks] = *(const half8*)(frag + slot + 2 * nb * 1024 + at_ks[ks]);
+                } else {
+                    const char* q = lds + tr_at[nb] + slot + ks * 32 * (2 * NR);
+                    union { struct { short4v lo, hi; } s; half8 h8; } v;
+                    v.s.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)HGEMM_LDS(q));
+                    v.s.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)HGEMM_LDS(q + 4 * (2 * NR)));
+                    fb[nb][ks] = v.h8;
+                }
+            }
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) fa[mb][ks] = *(const half8*)(frag + slot + 2 * (NB + mb) * 1024 + at_ks[ks]);
         }
@@ -418,6 +450,22 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_tn_gemm_kernel(GemmArgs g)
     // fused reduction over the K slabs of these columns, as in skinny_gemm_kernel
     if (!last_to_arrive(g.counters + strip, g.splits, (int*)red, t == 0)) return;
     sum_split_planes<64 * WAVES, NR / 4>(g, 0, n0, g.M, t);
+}
+
+template <int MB, bool FUSED, int DEPTH, int WAVES, int NR>
+__global__ __launch_bounds__(64 * WAVES) void skinny_tn_gemm_kernel(GemmArgs g)
+{
+    skinny_strip<MB, FUSED, DEPTH, WAVES, NR, true>(g);
+}
+
+// Row-major B: strips of 32 columns times blocks of 16 MB rows of A.  What bounds it are the same bytes, but half a cache line of each row of B, 16 rows a
+// copy, comes slower than eight whole lines of a column-major one; strips of 64 columns are level with these where they fill the chip, and few problems
+// have enough of them.  From HBM / from the cache, split tiles of the large family -> this: 25 x 1920 x 1920
+// 6.4 / 6.1 -> 5.5 / 4.2 us, 38 x 1280 x 1280 5.9 / 5.5 -> 4.6 / 3.5, 69 x 1920 x 1920 8.2 / 7.5 -> 6.2 / 5.2, 92 x 2480 x 1664 7.2 / 6.9 -> 6.3 / 5.6.
+template <int MB, int DEPTH, int WAVES, int NR>
+__global__ __launch_bounds__(64 * WAVES) void skinny_tile_kernel(GemmArgs g)
+{
+    skinny_strip<MB, false, DEPTH, WAVES, NR, false>(g);
 }
 
 // The same for a long column-major B (an output head, a wide projection) and up to 32 rows of A: A stays in registers.  One workgroup

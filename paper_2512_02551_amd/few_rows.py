@@ -21,7 +21,7 @@ one's, on K from 1200 on only: on a shorter K it wins less than 5 % from HBM and
 csrc/few_rows_check.jsonl.gz holds 4885 other problems as `gather` writes them, which the choices are checked on: half products of
 layers, a quarter output heads, a quarter any multiples of 8; {"shape", "tn", "cands": [[kernel, us from HBM, us from the cache], ...]} with
 the kernels whose first timing was within a fifth of the fastest, the library's choice and that of the builds it is compared with
-(--against: another build of the library, of an earlier commit, say).  The 1300 that now run on strips of a column-major B through LDS
+(--against: another build of the library, of an earlier commit, say).  The 1373 that now run on strips of B through LDS
 were timed again (`recheck`); csrc/few_rows_timings.jsonl.gz has that family's kernels as they were before, when lanes loaded operands.
 """
 from __future__ import annotations

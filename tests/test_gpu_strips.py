@@ -51,3 +51,17 @@ def test_blocks_of_rows(m, n, k, mr, nr):
 @pytest.mark.parametrize("m,n,k,tile", [(17, 2048, 2056, (16, 16)), (33, 4096, 4096, (32, 32)), (96, 3000, 3072, (48, 32)), (320, 640, 3072, (32, 32))], ids=str)
 def test_the_planner_takes_blocks_of_rows(m, n, k, tile):
     assert check(None, m, n, k, True) == "skinny,sk=1,nr=%d,mr=%d" % tile
+
+
+@pytest.mark.parametrize("mr", [16, 32])
+@pytest.mark.parametrize("m,n,k", [(16, 8, 8), (17, 40, 72), (65, 136, 264), (96, 200, 1000), (130, 1032, 520)], ids=str)
+def test_row_major_b(m, n, k, mr):
+    """Columns off the strip, K off a chunk and off the chunks of all waves, a last block of one row, of a part and of all of its rows."""
+    spec = f"skinny,sk=1,nr=32,mr={mr}"
+    assert check(spec, m, n, k, False) == spec
+    check(spec, m, n, k, False, (8, 16, 8), (8, 8, 8), special=True)
+
+
+@pytest.mark.parametrize("m,n,k,mr", [(17, 2048, 1536, 16), (64, 1920, 2048, 16), (96, 2504, 1776, 32), (128, 640, 2048, 16)], ids=str)
+def test_the_planner_takes_it_for_row_major_b(m, n, k, mr):
+    assert check(None, m, n, k, False) == f"skinny,sk=1,nr=32,mr={mr}"

@@ -48,3 +48,19 @@ def test_blocks_of_rows_need_no_split():
     for spec in ("skinny,sk=2,mr=16", "skinny,sk=1,mr=8", "skinny,sk=1,mr=24", "skinny,sk=1,mr=80", "mfma,mr=16", "skinny,sk=1,wv=8,ra=1,mr=16"):
         with pytest.raises(hg.HgemmError):
             hg.Plan(64, 4096, 4096, hg.Layouts.make(b_col_major=True), spec)
+
+
+@pytest.mark.parametrize("m,n,k,mr", [(17, 4096, 2048, 16), (32, 4032, 1536, 16), (64, 1920, 2048, 16), (65, 2504, 1776, 32), (96, 2560, 2048, 32)], ids=str)
+def test_row_major_b_inside(m, n, k, mr):
+    got = hg.plan_choice(m, n, k, hg.Layouts.make(lda=k + 64, ldb=n + 8, ldc=n + 8))
+    assert got.split(": ", 1)[1] == f"skinny,sk=1,nr=32,mr={mr}"
+
+
+@pytest.mark.parametrize("m,n,k,pad", [(16, 4096, 2048, 8), (17, 4104, 2048, 8), (17, 4096, 2056, 8), (17, 4096, 760, 8), (97, 2560, 2048, 8), (321, 256, 1024, 8), (320, 632, 1536, 8),
+                                       (17, 4095, 2048, 8), (17, 4096, 2048, 1), (17, 4096, 2048, 1 << 20)], ids=str)
+def test_row_major_b_outside(m, n, k, pad):
+    """Fewer rows, more tiles than compute units, a longer K, a shorter one, more rows, sizes off 8, a B whose offsets leave 31 bits."""
+    assert "mr=" not in hg.plan_choice(m, n, k, hg.Layouts.make(lda=k + 64, ldb=n + pad, ldc=n + 8))
+    for spec in ("skinny,sk=1,mr=16", "skinny,sk=1,nr=64,mr=16", "skinny,sk=1,nr=32,mr=48", "skinny,sk=1,wv=8,nr=32,mr=16"):
+        with pytest.raises(hg.HgemmError):
+            hg.Plan(m, n, k, hg.Layouts.make(lda=k + 64, ldb=n + pad, ldc=n + 8), spec)
