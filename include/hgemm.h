@@ -223,8 +223,9 @@ hgemm_status_t hgemm_candidates(int64_t M, int64_t N, int64_t K,
  *   "neighbour: SPEC"  a large problem the table does not hold: the kernel
  *                      tuned for the nearest shape it does hold
  *   "model: SPEC"      the fitted cost model's pick, or with few rows of A
- *                      that of the nearest measured problem;  "rules: SPEC"
- *                      its last resort
+ *                      that of the nearest measured problem, or strips of
+ *                      B for every compute unit;  "rules: SPEC"  its last
+ *                      resort
  *   "blocks,rows=R,cols=C[,bt=1]"   operands of 2 GiB and more
  *   "generic"          unaligned and too small to pad;  "empty"  M, N or K = 0
  * with ",pad=1" appended when N, K or a leading dimension is not a multiple
