@@ -80,15 +80,20 @@ struct Spec {
 // k-rows a workgroup of the skinny family takes per step (K slabs are whole numbers of steps) and the columns of C
 // it owns: row-major B 16 rows per wave and 128 columns, column-major B 32 k per wave and 16 columns
 static int64_t skinny_step(const Spec& s, bool tn = false) { return (tn ? 32 : 16) * s.wv; }
+// 16-row blocks of A that a kernel of the skinny family holds for up to 64 rows
+static int row_blocks_of_a(int64_t M) { return M <= 16 ? 1 : M <= 32 ? 2 : 4; }
 // Rows of a column-major B per workgroup where a spec does not say: one strip for every compute unit as far as that goes.  Few rows of A from HBM, all
 // four widths timed on some 80 problems of each range: 16 rows up to 4096 columns (the others leave compute units idle); 4097-8192 32 rows 0.92 of
 // the time of 16; 8193-12288 48 rows 0.89; 12289-16384 32 rows 0.95 (48 1.12, 64 level with 32); beyond, in several rounds, 32 rows 1.02.
-static int strip_rows(const Spec& s, int64_t N)
+// Narrower where these waves and blocks of A have no kernel of that width; strips of 16 always have one.
+static int strip_rows(const Spec& s, int64_t M, int64_t N)
 {
     if (s.nr || s.sk > 1) return s.nr ? s.nr : 16;
-    return N <= 4096 ? 16 : N <= 8192 ? 32 : N <= 12288 ? 48 : N <= 16384 ? 32 : 16;
+    int nr = N <= 4096 ? 16 : N <= 8192 ? 32 : N <= 12288 ? 48 : N <= 16384 ? 32 : 16;
+    while (nr > 16 && !skinny_tn_exists(s.wv, s.mr ? s.mr / 16 : row_blocks_of_a(M), nr / 16, false)) nr -= 16;
+    return nr;
 }
-static int64_t skinny_cols(const Spec& s, bool tn, int64_t N) { return tn ? strip_rows(s, N) : kSkinnyCols; }
+static int64_t skinny_cols(const Spec& s, bool tn, int64_t M, int64_t N) { return tn ? strip_rows(s, M, N) : kSkinnyCols; }
 
 static std::string spec_to_string(const Spec& s)
 {
@@ -1027,7 +1032,7 @@ hgemm_status_t finish_plan(hgemm_plan_s* p)
         if (!kernels_can_run(p) || M <= 0 || N <= 0 || K <= 0 || (M > kSkinnyMaxM && !s.mr)) return HGEMM_ERR_UNSUPPORTED;
         const bool tn = p->lay.b == HGEMM_COL_MAJOR;
         p->tn_kernel = tn;
-        const int mb = s.mr ? s.mr / 16 : M <= 16 ? 1 : M <= 32 ? 2 : 4;
+        const int mb = s.mr ? s.mr / 16 : row_blocks_of_a(M);
         const int64_t row_blocks = s.mr ? (M + s.mr - 1) / s.mr : 1;
         const int64_t step = skinny_step(s, tn);
         const int64_t ksteps = (K + step - 1) / step;
@@ -1044,10 +1049,10 @@ hgemm_status_t finish_plan(hgemm_plan_s* p)
         if (p->any_b && s.wv != 4) return HGEMM_ERR_UNSUPPORTED;
         if (s.ra && (!tn || M > 32)) return HGEMM_ERR_UNSUPPORTED;
         // with A resident, one workgroup per compute unit (a multiple of the 8 XCDs) walks the strips
-        const int64_t strips = s.ra ? std::max<int64_t>(8, cu_count() / 8 * 8) : (N + skinny_cols(s, tn || nn_tiles, N) - 1) / skinny_cols(s, tn || nn_tiles, N);
+        const int64_t strips = s.ra ? std::max<int64_t>(8, cu_count() / 8 * 8) : (N + skinny_cols(s, tn || nn_tiles, M, N) - 1) / skinny_cols(s, tn || nn_tiles, M, N);
         if (s.fr && strips * (int64_t)sizeof(int) > (int64_t)kCounterBytes) return HGEMM_ERR_UNSUPPORTED;
         if ((tn && !s.ra) || nn_tiles) {
-            const int rows = strip_rows(s, N);
+            const int rows = strip_rows(s, M, N);
             const SkinnyTnKernel k = nn_tiles ? skinny_tiles_kernel(mb) : skinny_tn_kernel(mb, s.fr != 0, s.wv, rows);
             const int instance = nn_tiles ? kTnInstances + mb - 1 : (((mb - 1) * 3 + s.wv / 8) * 4 + rows / 16 - 1) * 2 + s.fr;
             if (!k.kernel || !admit_skinny_lds(p->device, instance, k)) return HGEMM_ERR_UNSUPPORTED;
@@ -2189,17 +2194,15 @@ hgemm_status_t hgemm_candidates(int64_t M, int64_t N, int64_t K, const hgemm_lay
             }
         }
         if (l.b == HGEMM_COL_MAJOR && M <= kSkinnyMaxM) {       // the streaming family for K-contiguous B: N / 16 workgroups before any split
-            const int mblocks = M <= 16 ? 1 : M <= 32 ? 2 : 4;
             for (int nr : {16, 32, 48, 64})      // 16 as the default where that is what it is
                 for (int wv : {4, 8, 16}) {
-                    const int blocks = mblocks * (nr / 16);
-                    if (wv * blocks > 64 || (wv == 16 && blocks > 4)) continue;       // kernels that do not exist
+                    if (!skinny_tn_exists(wv, row_blocks_of_a(M), nr / 16, false)) continue;
                     if (nr > 16 && (N + nr - 1) / nr < CUS / 2) continue;             // too few workgroups to be worth timing
                     int64_t last = 0;
                     for (int sk : {1, 2, 4, 8, 16}) {
                         Spec s;
                         s.fam = FAM_SKINNY; s.wv = wv; s.nr = nr;
-                        if (nr == 16 && (sk > 1 || strip_rows(Spec(), N) == 16)) s.nr = 0;
+                        if (nr == 16) { s.nr = 0; if (sk == 1 && strip_rows(s, M, N) != 16) s.nr = 16; }
                         const int64_t eff = effective_splits((K + skinny_step(s, true) - 1) / skinny_step(s, true), sk);
                         if (eff == last || ((N + nr - 1) / nr) * eff > 64 * CUS) continue;
                         last = eff;

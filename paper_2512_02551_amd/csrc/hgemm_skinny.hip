@@ -31,18 +31,16 @@ void (*kernel_for(int mb, bool fused))(GemmArgs)
 
 // Column-major B.  Chunks in flight per wave: three where the workgroup then takes at most 48 KiB of LDS (three to a compute unit: M <= 16 in
 // strips of 16 rows), else two (16 x 5888 x 1920 in strips of 32 rows, 48 KiB: 7.2 us, with three chunks 7.3; 16 x 14336 x 4096 22.9, 23.6), and one
-// where two do not fit the LDS.  Combinations of more than 64 KiB of sums do not exist.
+// where two do not fit the LDS.
 template <int WAVES, int MB, int NR>
 SkinnyTnKernel tn_kernel(bool fused)
 {
     constexpr int NB = NR / 16, TWO = 2 * WAVES * 2 * (MB + NB);      // KiB of two chunks a wave
     constexpr int DEPTH = TWO <= 32 ? 3 : TWO <= 160 ? 2 : 1;
-    if constexpr (MB == 3) {
-        if constexpr (WAVES * MB * NB <= 64 && WAVES < 16)
-            if (!fused) return {skinny_tn_gemm_kernel<MB, false, DEPTH, WAVES, NR>, SkinnyTnLds<MB, DEPTH, WAVES, NB>::TOTAL};
-        return {nullptr, 0};
-    } else if constexpr (WAVES * MB * NB <= 64 && (WAVES < 16 || MB * NB <= 4))
+    if constexpr (skinny_tn_exists(WAVES, MB, NB, true))
         return {fused ? skinny_tn_gemm_kernel<MB, true, DEPTH, WAVES, NR> : skinny_tn_gemm_kernel<MB, false, DEPTH, WAVES, NR>, SkinnyTnLds<MB, DEPTH, WAVES, NB>::TOTAL};
+    else if constexpr (skinny_tn_exists(WAVES, MB, NB, false))
+        return fused ? SkinnyTnKernel{nullptr, 0} : SkinnyTnKernel{skinny_tn_gemm_kernel<MB, false, DEPTH, WAVES, NR>, SkinnyTnLds<MB, DEPTH, WAVES, NB>::TOTAL};
     else
         return {nullptr, 0};
 }

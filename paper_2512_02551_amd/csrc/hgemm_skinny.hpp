@@ -255,7 +255,12 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_gemm_kernel(GemmArgs g)
 // 48 x 8192 x 4096 18.6 / 15.0 -> 16.6 / 12.8.
 // Four waves with three chunks each (48 KiB at NR = 16, three workgroups to a compute unit) are the best of 4, 8 and 16 waves and 2 to 8
 // chunks: 1 x 4096 x 4096 7.8, eight waves 8.1, sixteen 8.2.  Strips are dealt so that an XCD's workgroups hold adjacent ones (see below).
-constexpr int kSkinnyTnRows = 16;      // rows of B (columns of C) per workgroup unless a spec asks for more
+// Instances for MB blocks of A and NB of B, of 16 rows each: at most 64 KiB of sums, and no more than four blocks a wave where 16 waves leave a lane 128
+// registers; MB = 3 is a block of rows of A, which is never split.
+constexpr bool skinny_tn_exists(int waves, int mb, int nb, bool fused)
+{
+    return waves * mb * nb <= 64 && (mb == 3 ? waves < 16 && !fused : waves < 16 || mb * nb <= 4);
+}
 
 template <int MB, int DEPTH, int WAVES, int NB>
 struct SkinnyTnLds {                   // bytes

@@ -2,6 +2,7 @@
 import pytest
 
 import paper_2512_02551_amd as hg
+from fake_hip import ask
 
 
 def picked(m, n, k, **layout):
@@ -64,3 +65,20 @@ def test_row_major_b_outside(m, n, k, pad):
     for spec in ("skinny,sk=1,mr=16", "skinny,sk=1,nr=64,mr=16", "skinny,sk=1,nr=32,mr=48", "skinny,sk=1,wv=8,nr=32,mr=16"):
         with pytest.raises(hg.HgemmError):
             hg.Plan(m, n, k, hg.Layouts.make(lda=k + 64, ldb=n + pad, ldc=n + 8), spec)
+
+
+def test_a_default_width_never_refuses_what_strips_of_16_rows_take():
+    """A spec without nr: the strips that fill the compute units as far as waves and blocks of A have such a kernel, narrower ones where not."""
+    qs = [{"M": m, "N": n, "K": k, "tn": True, "spec": f"skinny,sk={sk}" + (",fr=1" if fr else "") + (f",wv={wv}" if wv != 4 else "")}
+          for m in (1, 16, 17, 32, 33, 64) for n in (4096, 4104, 8192, 8200, 12288, 12296, 16384, 16392) for wv in (4, 8, 16)
+          for k, sk, fr in ((1024, 1, 0), (2048, 2, 0), (2048, 2, 1), (64, 2, 0), (64, 3, 1))]
+    wide = 0
+    for q, r, sixteen in zip(qs, ask(qs), ask([{**q, "spec": q["spec"] + ",nr=16"} for q in qs])):
+        assert sixteen["plan"] == 0 and r["plan"] == 0 and r["run"] == 0, (q, r)
+        wide += r["run_log"] != sixteen["run_log"]
+    assert wide > 100
+    # the widest strips that 8 waves times four blocks of A, and 16 waves times two, have kernels for
+    for m, wv, width in ((64, 8, 32), (32, 16, 32), (64, 16, 16), (64, 4, 48), (32, 8, 48)):
+        spec = f"skinny,sk=1,wv={wv}" if wv != 4 else "skinny,sk=1"
+        plain, wide = ask([{"M": m, "N": 12288, "K": 1024, "tn": True, "spec": spec + x} for x in ("", f",nr={width}")])
+        assert plain["plan"] == 0 and plain["run_log"] == wide["run_log"], (m, wv, plain)
