@@ -1326,13 +1326,16 @@ bool device_is_gfx950(int dev)
 // Returns the specialisations to try in order (a later one if the device or the workspace refuses an earlier one) and
 // says where the first comes from.
 // b_ld: the leading dimension of B as the kernels see it (l describes the packed problem of a padded one); copied: an operand is
-// copied first.
+// copied first, copy_b: B is.  A streaming row of the table is no pick for a column-major B that is copied first: it is worth reading B once, and
+// direct_choice knows what to do with a pick of the large tiles.  96 such problems next to those rows: 1.9 times slower with the copies from HBM and 2.4
+// from the cache than read in place (16 x 14336 x 4095 57 us, 31; 16 x 4096 x 4095 22, 14).  Copies of A only, or a C of odd rows, leave
+// the rows the faster choice (0.93 of the large tiles' time from HBM, 0.85 from the cache).
 struct Choices {
     const char* source;
     int n;
     Spec spec[3];
 };
-Choices choose_spec(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, int64_t b_ld, bool padded, bool copied, bool any_b)
+Choices choose_spec(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, int64_t b_ld, bool padded, bool copied, bool copy_b, bool any_b)
 {
     Choices c{"table", 1, {}};
     const bool tn = l.b == HGEMM_COL_MAJOR;
@@ -1342,7 +1345,7 @@ Choices choose_spec(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l, i
     }
     const bool packed = l.lda == K && l.ldc == N && l.ldb == (tn ? K : N);
     Spec model, near, phased;
-    if (!packed || !table_lookup(M, N, K, tn, &c.spec[0])) {
+    if (!packed || !table_lookup(M, N, K, tn, &c.spec[0]) || (tn && copy_b && c.spec[0].fam == FAM_SKINNY)) {
         c.source = "model";
         if (!model_choice(M, N, K, &model, !tn, !copied)) {
             model = heuristic(M, N, K);
@@ -1536,7 +1539,7 @@ hgemm_status_t init_plan(hgemm_plan_s* p, int64_t M, int64_t N, int64_t K, const
             p->spec = Spec();
             st = finish_plan(p);
         } else {
-            const Choices c = choose_spec(M, N, K, l, r.ldb, p->padded, r.copy_a || r.copy_b, p->any_b);
+            const Choices c = choose_spec(M, N, K, l, r.ldb, p->padded, r.copy_a || r.copy_b, r.copy_b, p->any_b);
             Spec direct;
             if (direct_choice(M, p->uN, p->uK, p->ulay, r, c.spec[0], &direct) && (!static_ws || copies_fit_static_scratch(M, r, c))) {
                 const hgemm_plan_s padded = *p;
@@ -1742,7 +1745,7 @@ hgemm_status_t hgemm_plan_choice(int64_t M, int64_t N, int64_t K, const hgemm_la
     } else if (!fast) {
         out = "generic";
     } else {
-        const Choices c = choose_spec(M, N, K, l, r.ldb, r.padded, r.copy_a || r.copy_b, r.any_b);
+        const Choices c = choose_spec(M, N, K, l, r.ldb, r.padded, r.copy_a || r.copy_b, r.copy_b, r.any_b);
         Spec direct;
         if (direct_choice(M, uN, uK, ul, r, c.spec[0], &direct)) out = "model: " + spec_to_string(direct) + ",pad=1";
         else out = std::string(c.source) + ": " + spec_to_string(c.spec[0]) + (r.padded ? ",pad=1" : "");

@@ -255,3 +255,16 @@ def test_few_rows_of_a_fit_the_static_scratch_and_keep_in_place_kernels_off_the_
     off = [{"M": m, "N": n, "K": k, "tn": True} for n, k in [(1729, 1545), (6747, 2667), (3137, 957), (35783, 3107)]]
     for q, r in zip(off, ask(off)):
         assert ",di=1" in r["describe"], (q, r["describe"])
+
+
+def test_streaming_rows_of_the_table_do_not_keep_a_b_off_the_grid_from_being_read_where_it_lies():
+    """Next to a row of the column-major table that names the streaming family: no copy of B.  Where B can be read as it is (only A, or C, is off the
+    grid), the row stands."""
+    shapes = [s for s, spec in table_rows(True) if spec.startswith("skinny")]
+    assert len(shapes) > 10
+    off = [{"M": m, "N": n - dn, "K": k - dk, "tn": True, **({"ldb": k + db} if db else {})} for m, n, k in shapes for dn, dk, db in ((0, 1, 0), (0, 4, 0), (3, 5, 0), (0, 0, 1), (0, 0, 4))]
+    for q, r in zip(off, ask(off)):
+        assert ",di=1" in r["describe"] and "pad_copy" not in str(r["run_log"]), (q, r["describe"])
+    read = [{"M": m, "N": n - dn, "K": k, "tn": True, **more} for m, n, k in shapes for dn, more in ((1, {}), (4, {}), (0, {"lda": k + 1}), (0, {"ldc": n + 1}))]
+    for q, r in zip(read, ask(read)):
+        assert r["describe"].startswith("skinny,") and len([k for k in kernels(r["run_log"]) if k[0] != "pad_copy_kernel"]) == 1, (q, r["describe"])
