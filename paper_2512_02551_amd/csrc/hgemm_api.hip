@@ -764,17 +764,20 @@ bool strips_choice(int64_t M, int64_t N, int64_t K, const Spec& pick, Spec* out)
     return true;
 }
 
-// The same for a row-major B, in strips of 32 columns: half a cache line of each of its rows, which HBM gives more slowly, so the range is shorter.  On 23 596
-// random problems of 17 to 320 rows 0.80 of the time from HBM of the choices without it (84 slower by more than 3 %, 39 by 10 %), 0.65 from the cache
-// (39, 13), 0.38 planned, run once and freed.  Where it ends, from HBM / from the cache: tiles of 16 x 32 0.78 / 0.61 at K 1024-1536, 0.85 / 0.66 to 2048, 1.05 / 0.74 to
+// The same for a row-major B, in strips of 32 columns: half a cache line of each of its rows, which HBM gives more slowly, so the range is shorter.  On 2572
+// problems of 17 to 320 rows, most of them of the round sizes that layers have, 0.81 of the time from HBM of the choices without it (35 slower by more than
+// 3 %, 5 by 10 %) and 0.64 from the cache.  Where it ends, from HBM / from the cache: tiles of 16 x 32 0.78 / 0.61 at K 1024-1536, 0.85 / 0.66 to 2048, 1.05 / 0.74 to
 // 3072, 1.25 / 0.82 to 4096; of 32 x 32 0.9 / 0.75 to 2048, 1.0 / 0.78 to 3072, and level with strips of all rows up to 32; fewer than twice as many columns as
-// rows 0.93 / 0.65 at K 1536-2048, a quarter of them slower; wider tiles 1.05 / 0.9.
+// rows 0.93 / 0.65 at K 1536-2048, a quarter of them slower; wider tiles 1.05 / 0.9.  Sooner where few blocks of rows share what is fetched of B, and sooner
+// again where its rows lie a multiple of 512 bytes apart, so that the half lines of all of them come from fewer channels: 16 x 32 on more than 1024 columns and up to 64
+// rows of A beyond K 1664 / 1408 1.01 / 0.70, 197 of 446 slower (20 x 2048 x 2048 7.8 / 6.4 -> 9.3 / 4.1 us); 32 x 32 on such rows beyond K 1792 18 of 72 (64 x 2560 x 1920 1.15).
 bool row_strip_tiles_choice(int64_t M, int64_t N, int64_t K, int64_t ldb, const Spec& pick, Spec* out)
 {
     if (M <= 16 || M > 320 || N < 64 || K < 768 || K > 2048 || (K + 256) * ldb * 2 >= ((int64_t)1 << 31) || joins_launches(pick, M, N, K)) return false;
     const int64_t cus = cu_count(), strips = (N + 31) / 32;
     const int mr = (M + 15) / 16 * strips <= cus ? 16 : M > 32 && (M + 31) / 32 * strips <= cus ? 32 : 0;
     if (!mr || (2 * M > N && K > 1280)) return false;
+    if (mr == 16 ? N > 1024 && M <= 64 && K > (ldb % 256 ? 1664 : 1408) : ldb % 256 == 0 && K > 1792) return false;
     *out = Spec();
     out->fam = FAM_SKINNY; out->mr = mr; out->nr = 32;
     return true;
