@@ -746,7 +746,9 @@ bool strip_tiles_choice(int64_t M, int64_t N, int64_t K, const Spec& pick, Spec*
 //  * K below 16 nr: a strip ends before its copies flow (nr = 32: K 256 1.0 / 0.95, 512 0.91 / 0.8; nr = 48: 512 0.98 / 0.9, 768 0.96 / 0.83);
 //  * a long K on strips for few compute units, which a split spreads over more of them, sooner with more rows of A, whose bytes every
 //    strip reads: up to 1024 columns K 8192 0.9 / 0.85 at M = 2, 1.3 / 0.9 at 16; 4097-5120 columns K 4096 0.92 / 0.83 at M = 4, 6144 1.16 /
-//    0.85 at 16; 3073-4096 columns K 8192-16384 0.85-0.98 / 0.84 up to 16 rows, 1.13 / 0.87 at 24.
+//    0.85 at 16; 3073-4096 columns K 8192-16384 0.85-0.98 / 0.84 up to 16 rows, 1.13 / 0.87 at 24.  Of another 5045 problems, half of them with K above 4096, 159 were slower
+//    by more than 3 % and 29 by 10 %; the limits of now leave 83 and 11 of 4812 (0.81 / 0.74), and the 233 they let go are level from HBM (76 slower; 0.81 from the cache):
+//    up to 640 columns and up to 3 rows K above 8448 1.10, 1025-2048 columns and K (M + 8) of 100 000 to 125 000 0.99, 4097-5120 columns 1.03, 5121-6144 and 150 000 to 190 000 0.99.
 //  * picks whose calls share launches stay: 16 calls in one take what two take here;
 //  * columns that are no whole strip of 16 keep the measured neighbours' kernels.
 bool strips_choice(int64_t M, int64_t N, int64_t K, const Spec& pick, Spec* out)
@@ -757,7 +759,8 @@ bool strips_choice(int64_t M, int64_t N, int64_t K, const Spec& pick, Spec* out)
     if (K < 256 * blocks) return false;
     const double filled = (double)N / (4096.0 * (double)blocks);
     const double work = (double)K * (double)(M + 8);
-    if (filled <= 0.75 ? work > (filled <= 0.25 ? 100e3 : filled <= 0.625 ? 125e3 : 190e3) : M > 16 && blocks < 3 && work > 200e3) return false;
+    const double most = filled <= 0.5 || (blocks == 2 && filled <= 0.625) ? 100e3 : filled <= 0.625 ? 125e3 : blocks == 2 ? 150e3 : 190e3;
+    if (filled <= 0.75 ? work > most || (filled <= 0.25 && K > 8448) : M > 16 && blocks < 3 && work > 200e3) return false;
     *out = Spec();
     out->fam = FAM_SKINNY;
     if (blocks > 1) out->nr = (int)(16 * blocks);

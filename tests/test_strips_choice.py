@@ -11,7 +11,7 @@ def picked(m, n, k, **layout):
 
 @pytest.mark.parametrize("m,n,k,spec", [
     (1, 4096, 4096, "skinny,sk=1"), (16, 4096, 16384, "skinny,sk=1"), (32, 4096, 4992, "skinny,sk=1"), (16, 11008, 4088, "skinny,sk=1,nr=48"),
-    (16, 4112, 5200, "skinny,sk=1,nr=32"), (4, 8192, 28672, "skinny,sk=1,nr=32"), (2, 12288, 768, "skinny,sk=1,nr=48"), (8, 512, 6240, "skinny,sk=1")], ids=str)
+    (16, 4112, 4160, "skinny,sk=1,nr=32"), (4, 8192, 28672, "skinny,sk=1,nr=32"), (2, 12288, 768, "skinny,sk=1,nr=48"), (8, 512, 6240, "skinny,sk=1")], ids=str)
 def test_inside(m, n, k, spec):
     assert picked(m, n, k) == spec
     assert picked(m, n, k, lda=k + 64, ldb=k + 8, ldc=n + 8) == spec
@@ -19,7 +19,7 @@ def test_inside(m, n, k, spec):
 
 @pytest.mark.parametrize("m,n,k", [
     (33, 4096, 4096), (16, 12304, 4096), (16, 4104, 4096), (16, 4095, 4096), (16, 4096, 4095), (32, 4096, 5008), (16, 4112, 5216), (8, 512, 6256), (4, 12288, 760),
-    (16, 512, 512)], ids=str)
+    (16, 512, 512), (1, 256, 9216), (2, 512, 8456), (1, 1152, 12096), (16, 1616, 4360), (14, 4736, 5112), (1, 4352, 11904), (2, 5504, 15616), (16, 4112, 4176)], ids=str)
 def test_outside(m, n, k):
     """More rows, more columns or columns off 16, a longer K, a shorter one, a pick whose calls share launches."""
     assert picked(m, n, k) != "skinny,sk=1" + {1: "", 2: ",nr=32", 3: ",nr=48", 4: ",nr=64"}[-(-n // 4096)]
