@@ -48,3 +48,27 @@ def test_every_fused_reduction_waits_for_its_stores_before_it_counts_itself_in(f
         barrier = max(i for i in range(counts[0]) if code[i].startswith("s_barrier"))
         store = max(i for i in range(barrier) if code[i].startswith(("global_store", "buffer_store")))
         assert any("vmcnt(0)" in line for line in code[store:barrier]), (name, code[store:barrier + 1])
+
+
+def test_the_loops_over_k_tiles_start_on_32_bytes(tmp_path):
+    """A loop that starts in the last bytes of a line waits for the next one on every pass.  The loop over K-tiles is the shortest way back over both
+    matrix instructions and copies (blocks that are laid out behind their place also jump back, once)."""
+    os.symlink(hg.lib_path(), tmp_path / "lib.so")
+    subprocess.run([LLVM + "llvm-objdump", "--offloading", "lib.so"], cwd=tmp_path, check=True, stdout=subprocess.DEVNULL)
+    kernels = 0
+    for obj in sorted(tmp_path.glob("lib.so.*gfx950")):
+        names = subprocess.run([LLVM + "llvm-objdump", "-t", str(obj)], check=True, stdout=subprocess.PIPE, text=True).stdout.split()
+        names = [n for n in names if re.search(r"mfma_gemm_kernelINS_7MfmaCfg\w+ELi0ELb[01]ENS_8GemmArgsE", n) and "." not in n]
+        if not names:
+            continue
+        text = subprocess.run([LLVM + "llvm-objdump", "-d", "--disassemble-symbols=" + ",".join(names), str(obj)], check=True, stdout=subprocess.PIPE, text=True).stdout
+        for name, body in re.findall(r"^[0-9a-f]+ <(_ZN5hgemm16mfma_gemm_kernel[^>]*)>:\n(.*?)(?=^[0-9a-f]+ <_ZN5hgemm|\Z)", text, re.M | re.S):
+            code = [(int(m[2], 16), m[1]) for m in re.finditer(r"^\s+(\S.*?)\s*// ([0-9A-F]+):", body, re.M)]
+            mfma = [at for at, line in code if line.startswith("v_mfma")]
+            copies = [at for at, line in code if line.startswith("buffer_load") and line.endswith("lds")]
+            back = [(at, at + 4 + 4 * (int(m[1]) - (1 << 16))) for at, line in code for m in [re.match(r"s_c?branch\S*\s+(\d+)", line)] if m and int(m[1]) >= 1 << 15]
+            loops = sorted((at - head, head) for at, head in back if any(head <= x <= at for x in mfma) and any(head <= x <= at for x in copies))
+            assert loops, name
+            assert loops[0][1] % 32 == 0, (name, hex(loops[0][1]))
+            kernels += 1
+    assert kernels > 100
