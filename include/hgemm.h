@@ -237,7 +237,7 @@ hgemm_status_t hgemm_plan_choice(int64_t M, int64_t N, int64_t K,
                                  const hgemm_layouts_t* layouts, char* buf, size_t n);
 
 /* The planner's cost model: predicted microseconds of one call of `spec` (an "mfma" spec without
- * tb/sm) on an M x N x K problem.  hgemm_plan() picks the compiled configuration and split factor
+ * tb/sm, or a "skinny" one without mr/ra) on an M x N x K problem.  hgemm_plan() picks the compiled configuration and split factor
  * with the smallest prediction when its measured table has no row for the shape (Section 6 reads
  * such trends -- tile size against M and N, stages against K -- off the paper's winners; here they
  * are a fitted model of one launch).  The model does not know the phased schedule: a spec with ph=1

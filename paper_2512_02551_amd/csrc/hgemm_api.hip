@@ -1276,7 +1276,7 @@ double predict_direct_us(const DirectTile& c, int64_t M, int64_t N, int64_t K, i
 bool predict_spec_us(int64_t M, int64_t N, int64_t K, const Spec& s, double* us)
 {
     if (s.fam == FAM_SKINNY) {
-        if (M > kSkinnyMaxM || s.ra) return false;         // fitted to kernels that stream slabs of K
+        if (M > kSkinnyMaxM || s.ra || s.mr) return false;         // fitted to kernels that stream slabs of K
         const int64_t eff = effective_splits((K + skinny_step(s) - 1) / skinny_step(s), s.sk);
         *us = predict_skinny_us(M, N, K, eff, s.fr != 0 && eff > 1);
         return true;

@@ -4,6 +4,8 @@ import pytest
 import paper_2512_02551_amd as hg
 from fake_hip import ask
 
+ERR_INVALID_ARG, ERR_UNSUPPORTED = 1, 2
+
 
 def picked(m, n, k, **layout):
     return hg.plan_choice(m, n, k, hg.Layouts.make(b_col_major=True, **layout)).split(": ", 1)[-1]
@@ -91,3 +93,11 @@ def test_row_major_b_whose_half_lines_come_slowly(m, n, k, ldb, mr):
     """Few blocks of rows on a wide B, sooner where its rows are a multiple of 512 bytes apart: what was up to 1.2 times slower from HBM."""
     got = hg.plan_choice(m, n, k, hg.Layouts.make(ldb=ldb, ldc=n + 8))
     assert got.split(": ", 1)[1] == f"skinny,sk=1,nr=32,mr={mr}" if mr else "mr=" not in got, got
+
+
+@pytest.mark.parametrize("spec", ["skinny,sk=1,nr=32,mr=16", "skinny,sk=1,mr=64", "skinny,sk=1,wv=8,nr=16,mr=32", "skinny,sk=1,wv=8,ra=1"])
+def test_no_model_describes_blocks_of_rows_or_resident_a(spec):
+    with pytest.raises(hg.HgemmError) as e:
+        hg.predict_us(64, 2048, 2048, spec)
+    assert e.value.status == ERR_UNSUPPORTED
+    assert hg.predict_us(64, 2048, 2048, "skinny,sk=1") > 1.0
