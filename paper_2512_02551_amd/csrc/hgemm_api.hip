@@ -1761,6 +1761,12 @@ hgemm_status_t hgemm_plan_choice(int64_t M, int64_t N, int64_t K, const hgemm_la
     return HGEMM_OK;
 }
 
+// Strips go round the XCDs: whole rounds of eight where several blocks of rows follow one another.
+static dim3 skinny_grid(const GemmArgs& a)
+{
+    return dim3(a.tiles_m > 1 ? (unsigned)(a.tiles_n + 7) / 8u * 8u : (unsigned)a.tiles_n, (unsigned)(a.splits * a.tiles_m));
+}
+
 static hgemm_status_t run_plan(const hgemm_plan_s* plan, const void* A, const void* B, void* C, void* hip_stream)
 {
     const int64_t M = plan->M, N = plan->N, K = plan->K;
@@ -1858,9 +1864,7 @@ static hgemm_status_t run_plan(const hgemm_plan_s* plan, const void* A, const vo
     a.b_rows = (int)b_rows;
     a.c_wide = N % 8 == 0 && plan->lay.ldc % 8 == 0 && ((uintptr_t)C & 15) == 0;
     if (plan->skinny) {
-        // strips of a column-major B go round the XCDs: whole rounds of eight where several blocks of rows follow one another
-        const unsigned strips = a.tiles_m > 1 ? (unsigned)(a.tiles_n + 7) / 8u * 8u : (unsigned)a.tiles_n;
-        hipLaunchKernelGGL(plan->skinny, dim3(strips, (unsigned)(a.splits * a.tiles_m)), dim3(64u * (unsigned)plan->spec.wv), (unsigned)plan->skinny_lds, stream, a);
+        hipLaunchKernelGGL(plan->skinny, skinny_grid(a), dim3(64u * (unsigned)plan->spec.wv), (unsigned)plan->skinny_lds, stream, a);
         if (a.splits > 1 && !plan->spec.fr) {
             if (hipGetLastError() != hipSuccess) return HGEMM_ERR_LAUNCH;
             const int64_t quads = M * ((N + 3) / 4);
@@ -2067,7 +2071,8 @@ hgemm_status_t hgemm_plan_launch_info(hgemm_plan_t plan, int64_t* workgroups, in
     }
     int64_t wg, lds, th;
     if (plan->skinny) {
-        wg = (int64_t)plan->args.tiles_n * plan->args.splits * plan->args.tiles_m;
+        const dim3 grid = skinny_grid(plan->args);
+        wg = (int64_t)grid.x * grid.y;
         lds = plan->spec.ra ? 2 * kStripWaves * (plan->M <= 16 ? 1 : 2) * 1024 : plan->skinny_lds ? plan->skinny_lds : 4 * 16 * (kSkinnyCols + 4) * 4;
         th = 64 * plan->spec.wv;
     } else if (plan->entry) {

@@ -1,7 +1,7 @@
 """The library's host code under a HIP runtime that computes nothing (fake_hip.cpp), in a process of its own: what
 hgemm_plan and hgemm_run_static decide, allocate and launch, on a machine without a GPU.
 
-    ask([{"M": 8, "N": 8, "K": 8, ...}, ...]) -> one dict per question: status, description, workspace bytes and log of
+    ask([{"M": 8, "N": 8, "K": 8, ...}, ...]) -> one dict per question: status, description, workspace bytes, reported workgroups and log of
     hgemm_plan (hgemm_plan_override, where a spec is given) + hgemm_run (and of hgemm_run_many, where operand sets are given), and status and log of hgemm_run_static, on
     operands at the addresses asked for."""
 import ctypes
@@ -45,6 +45,9 @@ def _answer(fake, lib, q):
         text = ctypes.create_string_buffer(512)
         assert lib.hgemm_plan_describe(plan, text, ctypes.c_size_t(512)) == 0
         r["describe"], r["workspace"] = text.value.decode(), lib.hgemm_plan_workspace_bytes(plan)
+        groups = i64()
+        assert lib.hgemm_plan_launch_info(plan, ctypes.byref(groups), None, None) == 0
+        r["workgroups"] = groups.value
         r["run"], r["run_log"] = lib.hgemm_run(plan, *at, None), log()
         if "many" in q:         # (A, B, C) per operand set
             arrays = [(vp * len(q["many"]))(*column) for column in zip(*q["many"])]

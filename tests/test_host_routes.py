@@ -268,3 +268,12 @@ def test_streaming_rows_of_the_table_do_not_keep_a_b_off_the_grid_from_being_rea
     read = [{"M": m, "N": n - dn, "K": k, "tn": True, **more} for m, n, k in shapes for dn, more in ((1, {}), (4, {}), (0, {"lda": k + 1}), (0, {"ldc": n + 1}))]
     for q, r in zip(read, ask(read)):
         assert r["describe"].startswith("skinny,") and len([k for k in kernels(r["run_log"]) if k[0] != "pad_copy_kernel"]) == 1, (q, r["describe"])
+
+
+def test_the_reported_workgroups_are_those_of_the_launch():
+    """Strips with several blocks of rows are launched in whole rounds of the XCDs."""
+    qs = [{"M": m, "N": n, "K": 2048, "tn": tn} for m, n, tn in ((17, 2040, True), (96, 3000, True), (320, 640, True), (65, 2504, False), (17, 1000, False), (16, 4096, True), (8, 5000, True),
+                                                                 (512, 512, False), (3, 30000, True))]
+    for q, r in zip(qs, ask(qs)):
+        name, x, y, *_ = kernels(r["run_log"])[0]
+        assert r["workgroups"] == x * y, (q, r)
