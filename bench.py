@@ -87,6 +87,7 @@ def parse_args():
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--spec", default=None, help="force one specialisation for every shape (tuning aid)")
     ap.add_argument("--table", action="store_true", help="print the per-shape table to stderr")
+    ap.add_argument("--per-shape", metavar="FILE", help="the metric run: write its rows of shapes there, as JSON")
     ap.add_argument("--server", action="store_true",
                     help="server mode (Section 2.4.2): calls separated by random idle gaps of 0-2 ms, each call "
                          "bracketed by its own events; the gaps are not part of any reported time")
@@ -454,12 +455,20 @@ def metric_run(args):
         "workloads": workloads,
         "roofline": roofline,
         "roofline_hbm": roofline_hbm,
-        "per_shape": per_shape,
     }
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline()
     for s in sets:
         s["plan"].destroy()
+    report(out, per_shape, args.per_shape)
+
+
+def report(out, per_shape, path):
+    """The line of the metric run.  Its 226 rows of shapes, 84 kB, go to a file of their own where one is asked for: a reader that keeps the last kilobytes of
+    the output still has the whole line."""
+    if path:
+        with open(path, "w") as f:
+            json.dump(per_shape, f)
     print(json.dumps(out))
 
 

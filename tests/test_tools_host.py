@@ -99,3 +99,16 @@ def test_bench_defaults_and_profiled_traffic_cover_the_roofline_shapes(monkeypat
     for (M, N, K) in need:
         assert (M, N, K) in bench.PROFILED_TRAFFIC_BYTES, (M, N, K)
         assert bench.PROFILED_TRAFFIC_BYTES[(M, N, K)] >= 2.0 * (M * K + K * N + M * N) * 0.98
+
+
+def test_bench_line_of_the_metric_run_is_short(tmp_path, capsys, monkeypatch):
+    """One line without the rows of its shapes, which go to a file where one is named."""
+    import bench
+    monkeypatch.setattr(sys, "argv", ["bench.py"])
+    assert bench.parse_args().per_shape is None
+    rows = [{"shape": [m, 64, 64], "spec": "mfma", "mean_us": 3.0} for m in range(226)]
+    bench.report({"metric": "m", "value": 1.0}, rows, None)
+    bench.report({"metric": "m", "value": 1.0}, rows, str(tmp_path / "rows.json"))
+    lines = capsys.readouterr().out.splitlines()
+    assert [json.loads(x) for x in lines] == [{"metric": "m", "value": 1.0}] * 2
+    assert json.load(open(tmp_path / "rows.json")) == rows
