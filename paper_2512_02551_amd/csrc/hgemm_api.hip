@@ -72,13 +72,14 @@ struct Spec {
     int ph = 0;     // 1 = the phased schedule of this tile (hgemm_phased.hpp)
     int di = 0;     // 1 = operands read through registers, at any element's address (MODE_DIRECT)
     int wv = 4;     // skinny family: waves per workgroup (4, 8 or 16), each taking 16 k-rows of a step
-    int nr = 0;     // skinny family, column-major B: rows of B (columns of C) per workgroup (16, 32, 48 or 64; 0 = as strip_rows() has it)
-    int mr = 0;     // skinny family, column-major B: rows of A per workgroup (16, 32, 48 or 64; 0 = all of them, up to 64)
+    int nr = 0;     // skinny family, column-major B: rows of B (columns of C) per workgroup (16, 32, 48 or 64; 0 = as strip_rows() has it); row-major B with mr: 32
+    int mr = 0;     // skinny family: rows of A per workgroup (16, 32, 48 or 64, with a row-major B 16 or 32; 0 = all of them, up to 64)
     int ra = 0;     // skinny family, column-major B: 1 = A resident in registers, one workgroup per compute unit walks strips of B
 };
 
-// k-rows a workgroup of the skinny family takes per step (K slabs are whole numbers of steps) and the columns of C
-// it owns: row-major B 16 rows per wave and 128 columns, column-major B 32 k per wave and 16 columns
+// K slabs of the skinny family are whole numbers of these: row-major B the 16 rows that each wave takes at a time, column-major B 32 k a wave, half of
+// what it takes (all of it with A resident), so that a slab may end with half of the waves idle.  Slabs of 64 k a wave were 0.5 % faster from HBM and 1.5 % from
+// the cache on 900 split problems (35 and 7 slower by more than 3 %, 81 and 136 faster); other splits than the measured rows name.
 static int64_t skinny_step(const Spec& s, bool tn = false) { return (tn ? 32 : 16) * s.wv; }
 // 16-row blocks of A that a kernel of the skinny family holds for up to 64 rows
 static int row_blocks_of_a(int64_t M) { return M <= 16 ? 1 : M <= 32 ? 2 : 4; }
@@ -776,7 +777,7 @@ bool strips_choice(int64_t M, int64_t N, int64_t K, const Spec& pick, Spec* out)
 // rows of A beyond K 1664 / 1408 1.01 / 0.70, 197 of 446 slower (20 x 2048 x 2048 7.8 / 6.4 -> 9.3 / 4.1 us); 32 x 32 on such rows beyond K 1792 18 of 72 (64 x 2560 x 1920 1.15).
 bool row_strip_tiles_choice(int64_t M, int64_t N, int64_t K, int64_t ldb, const Spec& pick, Spec* out)
 {
-    if (M <= 16 || M > 320 || N < 64 || K < 768 || K > 2048 || (K + 256) * ldb * 2 >= ((int64_t)1 << 31) || joins_launches(pick, M, N, K)) return false;
+    if (M <= 16 || M > 320 || N < 64 || K < 768 || K > 2048 || joins_launches(pick, M, N, K)) return false;
     const int64_t cus = cu_count(), strips = (N + 31) / 32;
     const int mr = (M + 15) / 16 * strips <= cus ? 16 : M > 32 && (M + 31) / 32 * strips <= cus ? 32 : 0;
     if (!mr || (2 * M > N && K > 1280)) return false;
@@ -1048,8 +1049,8 @@ hgemm_status_t finish_plan(hgemm_plan_s* p)
         if (sk == 1) s.fr = 0;
         if (row_blocks > 65535) return HGEMM_ERR_UNSUPPORTED;
         const bool nn_tiles = !tn && s.mr;
-        // offsets of the last copies, whose rows may lie past B
-        if (nn_tiles && (p->any_b || s.wv != 4 || s.nr != 32 || s.mr > 32 || (K + 64 * s.wv) * p->lay.ldb * 2 >= ((int64_t)1 << 31))) return HGEMM_ERR_UNSUPPORTED;
+        // (the last copies reach up to 256 rows past B, of the 512 that fast_path_ok() keeps below 2 GiB)
+        if (nn_tiles && (p->any_b || s.wv != 4 || s.nr != 32 || s.mr > 32)) return HGEMM_ERR_UNSUPPORTED;
         if (!tn && !nn_tiles && s.nr != 0 && s.nr != 16) return HGEMM_ERR_UNSUPPORTED;
         if ((!tn && !nn_tiles) || s.ra) s.nr = 0;
         if (p->any_b && s.wv != 4) return HGEMM_ERR_UNSUPPORTED;
@@ -2106,9 +2107,10 @@ const char* hgemm_spec_help(void)
             "    side; no LDS and no barrier in the main loop), the waves' sums meet once at the end; slabs are summed in\n"
             "    slab order by the split-K reduction launch or, with fr = 1, by the workgroup that arrives last.\n"
             "    Column-major B (K contiguous): a workgroup takes nr = 16, 32, 48 or 64 rows of B (columns of C; default: one strip for\n"
-            "    every compute unit up to 12288 columns), its waves take chunks\n"
+            "    every compute unit up to 12288 columns, narrower where these waves and rows of A have no such kernel), its waves take chunks\n"
             "    of 64 k of them in turn, copied to LDS of their own; sk splits K further across workgroups.  mr = 16, 32, 48 or 64 (with\n"
-            "    sk = 1, any M; above 32 four or eight waves): a workgroup takes mr rows of A only.  ra = 1 (with sk = 1, wv = 8; M <= 32, K <= 8192, above 16 rows 4096): A stays\n"
+            "    sk = 1, any M; above 32 four or eight waves): a workgroup takes mr rows of A only.  A row-major B has such strips of\n"
+            "    32 columns too: nr=32 with mr = 16 or 32, four waves.  ra = 1 (with sk = 1, wv = 8; M <= 32, K <= 8192, above 16 rows 4096): A stays\n"
             "    in registers, one workgroup per compute unit walks strips of 16 rows of B\n"
             "mfma,bm=BM,bn=BN,bk=BK,wm=WM,wn=WN,st=STAGES[,pf=PREFETCH][,sk=SPLITS][,gm=GROUP][,tb=1][,sm=1][,fr=1][,ps=1][,ac=16][,mi=16][,ph=1][,di=1]\n"
             "    pipelined 32x32x16 MFMA kernel; BMxBN tile per workgroup, WMxWN wavefronts, STAGES LDS buffers,\n"

@@ -21,8 +21,9 @@ one's, on K from 1200 on only: on a shorter K it wins less than 5 % from HBM and
 csrc/few_rows_check.jsonl.gz holds 4885 other problems as `gather` writes them, which the choices are checked on: half products of
 layers, a quarter output heads, a quarter any multiples of 8; {"shape", "tn", "cands": [[kernel, us from HBM, us from the cache], ...]} with
 the kernels whose first timing was within a fifth of the fastest, the library's choice and that of the builds it is compared with
-(--against: another build of the library, of an earlier commit, say).  The 1373 that now run on strips of B through LDS
-were timed again (`recheck`); csrc/few_rows_timings.jsonl.gz has that family's kernels as they were before, when lanes loaded operands.
+(--against: another build of the library, of an earlier commit, say); all were timed again (`recheck`) since a column-major B goes through LDS in strips and
+the large tiles drain their last K-tiles one by one.  csrc/few_rows_timings.jsonl.gz has the kernels as they were before that: of a
+column-major B the streaming ones are faster now, with the same spec in strips of up to 48 rows of B (of 16 then).
 """
 from __future__ import annotations
 
@@ -164,7 +165,7 @@ def gather(seed: int, seconds: float, path: str, against):
 
 
 def recheck(src: str, path: str, against):
-    """Problems of `src` that the library now runs on a kernel `src` has no time of: timed again, with the kernels that stand there."""
+    """Every problem of `src` again: the kernels that stand there and the library's choice."""
     import torch
 
     import paper_2512_02551_amd as hg
@@ -186,8 +187,6 @@ def recheck(src: str, path: str, against):
     for r in rows:
         M, N, K = r["shape"]
         specs = list(dict.fromkeys([choice(lib, M, N, K, r["tn"]) for lib in [None] + against] + [x[0] for x in r["cands"]]))
-        if specs[0] in {x[0] for x in r["cands"]} and number(specs[0], "nr") == 0 and specs[0] != "skinny,sk=1":
-            continue
         elems = (M * K + 127) // 128 * 128 + N * K
         n = max(1, min(64, pool.numel() // elems, int(6e8 // (2 * elems)) + 1))
         assert n * elems <= pool.numel() and M * N <= c.numel(), (M, N, K)

@@ -12,12 +12,13 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("m,n,k", [
     (1, 8, 8), (16, 16, 64), (7, 24, 72), (16, 200, 1000), (9, 4112, 264),         # one block of A: less than a chunk, a part of one, rows past the end
     (17, 40, 256), (32, 136, 520), (24, 2056, 1032),                                 # two
-    (33, 72, 512), (64, 264, 776)], ids=str)                                         # four
+    (33, 72, 512), (64, 264, 776),                                                   # four
+    (5, 40, 4104), (20, 24, 3080), (50, 40, 3144)], ids=str)                         # chunks that come round in the ring, of sixteen waves too
 def test_every_instance(m, n, k, wv, nr):
     """K off the 64 of a chunk and off the chunks of all waves, columns off the strips and off 16, padded leading dimensions, and
     infinities and NaN in A and B; splits in two launches and fused."""
     blocks = (1 if m <= 16 else 2 if m <= 32 else 4) * (nr // 16)
-    spec = "skinny,sk=%d%s" + (f",wv={wv}" if wv != 4 else "") + (f",nr={nr}" if nr != 16 else "")
+    spec = "skinny,sk=%d%s" + (f",wv={wv}" if wv != 4 else "") + f",nr={nr}"
     if wv * blocks > 64 or (wv == 16 and blocks > 4):
         with pytest.raises(hg.HgemmError):
             hg.Plan(m, n, k, hg.Layouts.make(b_col_major=True), spec % (1, ""))
@@ -28,6 +29,13 @@ def test_every_instance(m, n, k, wv, nr):
     check(spec % (3, ",fr=1"), m, n, k, True)
 
 
+@pytest.mark.parametrize("m,n,wv", [(9, 4096, 4), (9, 4112, 4), (64, 8200, 8), (32, 8200, 16), (64, 4104, 16), (40, 12288, 4), (20, 12296, 8)], ids=str)
+def test_default_widths(m, n, wv):
+    """Strips whose width follows from the columns, waves and rows of A."""
+    spec = "skinny,sk=1" + (f",wv={wv}" if wv != 4 else "")
+    assert check(spec, m, n, 264, True, (8, 8, 8), (0, 8, 8)) == spec
+
+
 @pytest.mark.parametrize("m,n,k,nr", [(1, 4096, 4096, 16), (16, 64, 4096, 16), (16, 4112, 4096, 32), (32, 8192, 2048, 32), (5, 12288, 768, 48)], ids=str)
 def test_the_planner_takes_it(m, n, k, nr):
     assert check(None, m, n, k, True) == "skinny,sk=1" + (f",nr={nr}" if nr > 16 else "")
@@ -35,7 +43,7 @@ def test_the_planner_takes_it(m, n, k, nr):
 
 @pytest.mark.parametrize("nr", [16, 32, 48, 64])
 @pytest.mark.parametrize("mr", [16, 32, 48, 64])
-@pytest.mark.parametrize("m,n,k", [(17, 40, 8), (65, 136, 264), (96, 200, 1000), (130, 1032, 72)], ids=str)
+@pytest.mark.parametrize("m,n,k", [(17, 40, 8), (65, 136, 264), (96, 200, 1000), (130, 1032, 72), (70, 40, 2056)], ids=str)
 def test_blocks_of_rows(m, n, k, mr, nr):
     """A last block of one row, of a part and of all of its rows; strips that are no whole number of XCDs."""
     for wv in ("", ",wv=8"):
@@ -65,3 +73,10 @@ def test_row_major_b(m, n, k, mr):
 @pytest.mark.parametrize("m,n,k,mr", [(17, 2048, 1408, 16), (64, 1920, 1656, 16), (96, 2504, 1776, 32), (128, 640, 2048, 16)], ids=str)
 def test_the_planner_takes_it_for_row_major_b(m, n, k, mr):
     assert check(None, m, n, k, False) == f"skinny,sk=1,nr=32,mr={mr}"
+
+
+def test_off_the_grid():
+    """Rows, columns and K that nobody rounded, and C at any element's address: copies of A and B, C stored as it is."""
+    for m, n, k, tn, spec in ((33, 201, 301, True, "skinny,sk=1,nr=32,mr=16"), (70, 95, 1003, True, "skinny,sk=1,nr=48,mr=64"), (33, 201, 301, False, "skinny,sk=1,nr=32,mr=32"),
+                              (9, 4099, 512, True, "skinny,sk=1"), (64, 8201, 136, True, "skinny,sk=1,wv=8")):
+        assert check(spec, m, n, k, tn, (3, 1, 5), (1, 3, 5)) == spec + ",pad=1"

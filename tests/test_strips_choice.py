@@ -47,10 +47,37 @@ def test_blocks_of_rows_outside(m, n, k):
     assert "mr=" not in picked(m, n, k)
 
 
-def test_blocks_of_rows_need_no_split():
-    for spec in ("skinny,sk=2,mr=16", "skinny,sk=1,mr=8", "skinny,sk=1,mr=24", "skinny,sk=1,mr=80", "mfma,mr=16", "skinny,sk=1,wv=8,ra=1,mr=16"):
-        with pytest.raises(hg.HgemmError):
-            hg.Plan(64, 4096, 4096, hg.Layouts.make(b_col_major=True), spec)
+def statuses(specs, **q):
+    return [r["plan"] for r in ask([{**q, "spec": s} for s in specs])]
+
+
+def test_which_blocks_of_rows_there_are():
+    """Of a column-major B 16 to 64 rows in steps of 16, without a split; other values are no specs, and some waves have no kernel."""
+    taken = ["skinny,sk=1,mr=16", "skinny,sk=1,mr=64", "skinny,sk=1,nr=16,mr=48", "skinny,sk=1,nr=64,mr=64", "skinny,sk=1,wv=16,nr=32,mr=32", "skinny,sk=1,fr=1,mr=16"]
+    assert statuses(taken, M=64, N=4096, K=4096, tn=True) == [0] * len(taken)
+    invalid = ["skinny,sk=2,mr=16", "skinny,sk=1,mr=8", "skinny,sk=1,mr=24", "skinny,sk=1,mr=80", "skinny,sk=1,wv=8,ra=1,mr=16", "mfma,bm=32,bn=64,bk=64,wm=1,wn=2,st=4,pf=3,sk=1,gm=8,mr=16"]
+    assert statuses(invalid, M=64, N=4096, K=4096, tn=True) == [ERR_INVALID_ARG] * len(invalid)
+    assert statuses([invalid[-1][:-6]], M=64, N=4096, K=4096, tn=True) == statuses(["skinny,sk=1,wv=8,ra=1"], M=32, N=4096, K=4096, tn=True) == [0]
+    missing = ["skinny,sk=1,wv=16,nr=16,mr=48", "skinny,sk=1,wv=16,nr=64,mr=32", "skinny,sk=1,wv=8,nr=48,mr=64"]
+    assert statuses(missing, M=64, N=4096, K=4096, tn=True) == [ERR_UNSUPPORTED] * len(missing)
+
+
+def test_which_blocks_of_rows_there_are_for_a_row_major_b():
+    taken = ["skinny,sk=1,nr=32,mr=16", "skinny,sk=1,nr=32,mr=32"]
+    assert statuses(taken, M=17, N=4096, K=2048) == [0, 0]
+    missing = ["skinny,sk=1,mr=16", "skinny,sk=1,nr=16,mr=16", "skinny,sk=1,nr=64,mr=16", "skinny,sk=1,nr=32,mr=48", "skinny,sk=1,nr=32,mr=64", "skinny,sk=1,wv=8,nr=32,mr=16"]
+    assert statuses(missing, M=17, N=4096, K=2048) == [ERR_UNSUPPORTED] * len(missing)
+
+
+def test_row_major_strips_up_to_31_bits_of_offset():
+    """Copies of the last chunk reach up to 256 rows past K; problems that come with such a pitch have 512 rows past it below 2 GiB."""
+    for k in (2048, 1536):
+        ldb = ((1 << 30) // (k + 512) - 1) // 8 * 8
+        assert (k + 512) * ldb * 2 < 1 << 31 <= (k + 512) * (ldb + 8) * 2
+        inside, outside = ask([{"M": 17, "N": 1024, "K": k, "ldb": x, "spec": "skinny,sk=1,nr=32,mr=16"} for x in (ldb, ldb + 8)])
+        assert (inside["plan"], outside["plan"]) == (0, ERR_UNSUPPORTED)
+        inside, outside = ask([{"M": 17, "N": 1024, "K": k, "ldb": x} for x in (ldb, ldb + 8)])
+        assert "mr=16" in inside["describe"] and "mr=" not in outside["describe"] and outside["plan"] == 0
 
 
 @pytest.mark.parametrize("m,n,k,mr", [(17, 4096, 1664, 16), (17, 1024, 2048, 16), (32, 4032, 1536, 16), (80, 1600, 2048, 16), (65, 2504, 1776, 32), (96, 2560, 2048, 32)], ids=str)
@@ -64,9 +91,6 @@ def test_row_major_b_inside(m, n, k, mr):
 def test_row_major_b_outside(m, n, k, pad):
     """Fewer rows, more tiles than compute units, a longer K, a shorter one, more rows, sizes off 8, a B whose offsets leave 31 bits."""
     assert "mr=" not in hg.plan_choice(m, n, k, hg.Layouts.make(lda=k + 64, ldb=n + pad, ldc=n + 8))
-    for spec in ("skinny,sk=1,mr=16", "skinny,sk=1,nr=64,mr=16", "skinny,sk=1,nr=32,mr=48", "skinny,sk=1,wv=8,nr=32,mr=16"):
-        with pytest.raises(hg.HgemmError):
-            hg.Plan(m, n, k, hg.Layouts.make(lda=k + 64, ldb=n + pad, ldc=n + 8), spec)
 
 
 def test_a_default_width_never_refuses_what_strips_of_16_rows_take():
