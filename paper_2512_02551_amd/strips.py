@@ -3,8 +3,8 @@
     python -m paper_2512_02551_amd.strips gather --seed 1 --count 4000 --against LIB --out FILE    # on the GPU; FILE: lines to add to a check file
     python -m paper_2512_02551_amd.strips evaluate [FILE ...]                       # CPU; the built library's choices, by range
 
-csrc/strips_check.jsonl.gz holds problems of 1 to 320 rows of A on both sides of the limits, half of round sizes as layers have them, a fifth with
-padded rows of B: {"shape": [M, N, K], "tn", "ldb", "before": kernel, "strips": kernel, "us": [[before, strips] from HBM, from the cache]}.
+csrc/strips_check.jsonl.gz holds 12000 problems (seed 1) of 1 to 320 rows of A on both sides of the limits, half of round sizes as layers have them, a
+fifth with padded rows of B: {"shape": [M, N, K], "tn", "ldb", "before": kernel, "strips": kernel, "us": [[before, strips] from HBM, from the cache]}.
 "before" is the choice of a build without strips (--against: one of commit 8df821b), "strips" what the tile rule gives with its limits left out.
 Both are timed in turn by their specs in the built library; shapes of the dispatch tables, calls that share a launch and problems that "before"
 ran on strips of 16 rows of B already are left out.
@@ -137,14 +137,14 @@ def takes(r):
 
 
 def figures(rows):
-    """(problems, strips over before from HBM and from the cache, slower by 3 and by 10 % from HBM, from the cache)"""
+    """(problems, strips over before from HBM and from the cache, slower by 3 % from HBM and from the cache, by 10 %)"""
     ratio = [[r["us"][w][1] / r["us"][w][0] for r in rows] for w in (0, 1)]
     return (len(rows), *(round(math.exp(sum(map(math.log, x)) / len(x)), 3) for x in ratio), *(sum(v > 1.03 for v in x) for x in ratio), *(sum(v > 1.1 for v in x) for x in ratio)) if rows else (0,)
 
 
 def evaluate(rows):
     kinds = {"row-major B": lambda r: not r["tn"], "column-major B, blocks of rows": lambda r: r["tn"] and "mr=" in r["strips"], "column-major B, all rows": lambda r: r["tn"] and "mr=" not in r["strips"]}
-    print("problems, strips / before from HBM, from the cache, slower by more than 3 % from HBM, from the cache, by 10 %")
+    print("problems, strips / before from HBM, from the cache, slower by more than 3 % from HBM, from the cache, by 10 % from HBM, from the cache")
     for name, kind in kinds.items():
         some = [r for r in rows if kind(r)]
         taken = {id(r): takes(r) for r in some}

@@ -3,7 +3,9 @@ import pytest
 
 import paper_2512_02551_amd as hg
 from fake_hip import ask
+from paper_2512_02551_amd import strips
 
+MEASURED = strips.load([strips.CHECK])
 ERR_INVALID_ARG, ERR_UNSUPPORTED = 1, 2
 
 
@@ -125,3 +127,14 @@ def test_no_model_describes_blocks_of_rows_or_resident_a(spec):
         hg.predict_us(64, 2048, 2048, spec)
     assert e.value.status == ERR_UNSUPPORTED
     assert hg.predict_us(64, 2048, 2048, "skinny,sk=1") > 1.0
+
+
+@pytest.mark.parametrize("kind,count,most_slower", [("row-major B", 900, 0.02), ("blocks of rows", 2700, 0.045), ("all rows", 3500, 0.04)])
+def test_limits_on_measured_problems(kind, count, most_slower):
+    """Strips where they are faster than the kernels chosen without them, from HBM and from the cache; what they are not taken for is not, on average, from HBM."""
+    rows = [r for r in MEASURED if kind == ("row-major B" if not r["tn"] else "blocks of rows" if "mr=" in r["strips"] else "all rows")]
+    taken = [r for r in rows if strips.takes(r)]
+    left = [r for r in rows if not strips.takes(r)]
+    n, hbm, cache, slower, slower_cache, *_ = strips.figures(taken)
+    assert n >= count and hbm < 0.83 and cache < 0.75 and slower < most_slower * n and slower_cache < 0.015 * n, strips.figures(taken)
+    assert strips.figures(left)[1] > 0.98, strips.figures(left)
