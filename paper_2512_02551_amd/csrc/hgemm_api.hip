@@ -604,7 +604,8 @@ bool streams_any_b(int64_t M, int64_t N, int64_t K, const hgemm_layouts_t& l)
 // run and destroyed 20.7 us, with counters 24.5.
 // 4848 problems that the rows do not come from, a quarter of them of any sizes, in both states: 2498 choices differ from the models', 1.15 times
 // faster from HBM and 1.13 from the cache; 131 and 185 of them are slower by more than 3 %, 40 and 54 by 10 %.  (Timed when a column-major B was
-// loaded as operands; 983 of them go to strips_choice since.)
+// loaded as operands; 983 of them go to strips_choice since.  The rows' streaming kernels of a column-major B have become faster since they were timed: where rows name
+// one, 0.85 of the time of before on 84 problems, none slower; where they name a tile, one of them is the fastest for 211 of 1384.)
 // Not for operands that would be copied: the choice between copies and direct_choice compares with the models' pick.
 constexpr double kCheapAlloc = 2097152.0 - 65536.0;      // bytes of planes beside the counters below hipMalloc's 2 MiB step
 struct FewRow { unsigned short m; unsigned n, k; signed char spec[5]; };
@@ -699,7 +700,8 @@ bool resident_a_range(int64_t M, int64_t N, int64_t K)
 }
 constexpr char kResidentA[] = "skinny,sk=1,wv=8,ra=1";
 
-// Does hgemm_run_many put calls of this pick into one launch?
+// Does hgemm_run_many put calls of this pick into one launch?  Strips leave such picks alone, and a plan that is only ever run call by call pays for it: strips
+// would take 0.99 of its time at K 256-512, 0.92 to 768, 0.81 to 1024 and 0.7-0.85 beyond (1500 problems of up to 320 rows; from HBM and from the cache alike).
 bool joins_launches(const Spec& s, int64_t M, int64_t N, int64_t K)
 {
     return s.fam == FAM_MFMA && s.sk == 1 && !s.sm && !s.ps && !s.ph && !s.di && !s.tb && s.ac == 32 && s.mi == 32 &&
@@ -710,7 +712,9 @@ bool joins_launches(const Spec& s, int64_t M, int64_t N, int64_t K)
 // tile is the one with the fewest rows of A and B together, which is what a compute unit has to fetch of every k.  Tiles of the large
 // family read each byte for more products, but want more of them than such problems have: their K is split, with planes and a second launch.
 // Timed against the choices made without it on 37 488 random problems of 17 to 320 rows: 0.75 of their time from HBM (725 slower by more than 3 %, 245 by
-// 10 %), 0.68 from the cache (312, 51), 0.37 planned, run once and freed.  From HBM / from the cache, by rows of A and B in a tile, and where it ends:
+// 10 %), 0.68 from the cache (312, 51), 0.37 planned, run once and freed.  On 4415 others on both sides of the limits, half of round sizes (`strips.py evaluate`):
+// the 2803 that are taken 0.76 / 0.66 (108 and 26 slower from HBM, 10 and 4 from the cache: mostly where a split of before happened to give nearly every
+// compute unit one workgroup), the 1612 left 0.99 / 0.84.  From HBM / from the cache, by rows of A and B in a tile, and where it ends:
 //  * 32: 0.59 / 0.57 at K 1024-2048, 0.66 / 0.60 to 3072, 0.74 / 0.65 to 4096, 0.85 / 0.70 to 6144, 1.0 / 0.75 to 8192, 1.25 / 0.9 beyond (a split leaves less
 //    of K to each);
 //  * 48: 0.70 / 0.65, 0.77 / 0.69, 0.83 / 0.75, then 0.98 / 0.77 to 4608, 1.05 / 0.75 to 5120; 64: 0.76 / 0.70, 0.82 / 0.69, 0.90 / 0.75, then 1.0 / 0.76;
@@ -750,6 +754,7 @@ bool strip_tiles_choice(int64_t M, int64_t N, int64_t K, const Spec& pick, Spec*
 //    0.85 at 16; 3073-4096 columns K 8192-16384 0.85-0.98 / 0.84 up to 16 rows, 1.13 / 0.87 at 24.  Of another 5045 problems, half of them with K above 4096, 159 were slower
 //    by more than 3 % and 29 by 10 %; the limits of now leave 83 and 11 of 4812 (0.81 / 0.74), and the 233 they let go are level from HBM (76 slower; 0.81 from the cache):
 //    up to 640 columns and up to 3 rows K above 8448 1.10, 1025-2048 columns and K (M + 8) of 100 000 to 125 000 0.99, 4097-5120 columns 1.03, 5121-6144 and 150 000 to 190 000 0.99.
+//    `strips.py evaluate`, 5389 problems on both sides: the 3635 that are taken 0.82 / 0.74 (120 slower by more than 3 % and 26 by 10 % from HBM; 46 and 5), the 1754 left 1.20 / 0.95.
 //  * picks whose calls share launches stay: 16 calls in one take what two take here;
 //  * columns that are no whole strip of 16 keep the measured neighbours' kernels.
 bool strips_choice(int64_t M, int64_t N, int64_t K, const Spec& pick, Spec* out)
@@ -770,7 +775,8 @@ bool strips_choice(int64_t M, int64_t N, int64_t K, const Spec& pick, Spec* out)
 
 // The same for a row-major B, in strips of 32 columns: half a cache line of each of its rows, which HBM gives more slowly, so the range is shorter.  On 2572
 // problems of 17 to 320 rows, most of them of the round sizes that layers have, 0.81 of the time from HBM of the choices without it (35 slower by more than
-// 3 %, 5 by 10 %) and 0.64 from the cache.  Where it ends, from HBM / from the cache: tiles of 16 x 32 0.78 / 0.61 at K 1024-1536, 0.85 / 0.66 to 2048, 1.05 / 0.74 to
+// 3 %, 5 by 10 %) and 0.64 from the cache; of 2196 others (`strips.py evaluate`) the 911 that are taken 0.81 / 0.63 (12 and 3 slower from HBM, 2 and 1 from the
+// cache), the 1285 left 0.99 / 0.73.  Where it ends, from HBM / from the cache: tiles of 16 x 32 0.78 / 0.61 at K 1024-1536, 0.85 / 0.66 to 2048, 1.05 / 0.74 to
 // 3072, 1.25 / 0.82 to 4096; of 32 x 32 0.9 / 0.75 to 2048, 1.0 / 0.78 to 3072, and level with strips of all rows up to 32; fewer than twice as many columns as
 // rows 0.93 / 0.65 at K 1536-2048, a quarter of them slower; wider tiles 1.05 / 0.9.  Sooner where few blocks of rows share what is fetched of B, and sooner
 // again where its rows lie a multiple of 512 bytes apart, so that the half lines of all of them come from fewer channels: 16 x 32 on more than 1024 columns and up to 64

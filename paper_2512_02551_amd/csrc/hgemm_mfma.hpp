@@ -954,7 +954,9 @@ __global__ __launch_bounds__(C::THREADS) void mfma_gemm_kernel(ARGS g)
             }
             // drain: no more copies to issue.  A pass for each K-tile that may be left, with a wait of its own: for the next K-tile, not for all
             // that are in flight: 320 x 3072 x 768 5.12 -> 4.85 us, 1024 x 1024 x 1024 5.82 -> 5.64, 1536 x 1536 x 1536 12.66 -> 12.37; from HBM 640 x 2048 x 640 6.1 ->
-            // 5.8.  (One pass with its wait chosen by a branch is up to 2 % slower than waiting for all, from the cache.)
+            // 5.8.  (One pass with its wait chosen by a branch is up to 2 % slower than waiting for all, from the cache.)  By K-tiles of a workgroup, 2856 problems
+            // from HBM / from the cache: 3-4 0.987 / 0.998, 5-8 0.966 / 0.993, 9-16 0.970 / 0.989, more 0.990 / 0.991; two level; one 1.009, for the code
+            // that is jumped over (349 problems; a way around all of it for one K-tile costs the others 0.5-1 %).
             static_for<C::STAGES - 1>([&](auto d) {
                 constexpr int left = C::STAGES - 2 - decltype(d)::value;         // K-tiles behind the next one
                 if (kt + 2 + left != KT) return;
