@@ -712,9 +712,9 @@ bool joins_launches(const Spec& s, int64_t M, int64_t N, int64_t K)
 // tile is the one with the fewest rows of A and B together, which is what a compute unit has to fetch of every k.  Tiles of the large
 // family read each byte for more products, but want more of them than such problems have: their K is split, with planes and a second launch.
 // Timed against the choices made without it on 37 488 random problems of 17 to 320 rows: 0.75 of their time from HBM (725 slower by more than 3 %, 245 by
-// 10 %), 0.68 from the cache (312, 51), 0.37 planned, run once and freed.  On 4415 others on both sides of the limits, half of round sizes (`strips.py evaluate`):
-// the 2803 that are taken 0.76 / 0.66 (108 and 26 slower from HBM, 10 and 4 from the cache: mostly where a split of before happened to give nearly every
-// compute unit one workgroup), the 1612 left 0.99 / 0.84.  From HBM / from the cache, by rows of A and B in a tile, and where it ends:
+// 10 %), 0.68 from the cache (312, 51), 0.37 planned, run once and freed; timed when tiles were dealt by strips, more than 32 to some XCDs.  Dealt evenly, on 4415 others
+// on both sides of the limits, half of round sizes (`strips.py evaluate`): the 2803 that are taken 0.73 / 0.62 (54 and 9 slower from HBM, 5 and 1 from the
+// cache; dealt by strips 0.76 / 0.66, 108 and 26, 10 and 4), the 1612 left 0.96 / 0.80.  Dealt by strips, from HBM / from the cache, by rows of A and B in a tile, and where it ends:
 //  * 32: 0.59 / 0.57 at K 1024-2048, 0.66 / 0.60 to 3072, 0.74 / 0.65 to 4096, 0.85 / 0.70 to 6144, 1.0 / 0.75 to 8192, 1.25 / 0.9 beyond (a split leaves less
 //    of K to each);
 //  * 48: 0.70 / 0.65, 0.77 / 0.69, 0.83 / 0.75, then 0.98 / 0.77 to 4608, 1.05 / 0.75 to 5120; 64: 0.76 / 0.70, 0.82 / 0.69, 0.90 / 0.75, then 1.0 / 0.76;
@@ -754,7 +754,7 @@ bool strip_tiles_choice(int64_t M, int64_t N, int64_t K, const Spec& pick, Spec*
 //    0.85 at 16; 3073-4096 columns K 8192-16384 0.85-0.98 / 0.84 up to 16 rows, 1.13 / 0.87 at 24.  Of another 5045 problems, half of them with K above 4096, 159 were slower
 //    by more than 3 % and 29 by 10 %; the limits of now leave 83 and 11 of 4812 (0.81 / 0.74), and the 233 they let go are level from HBM (76 slower; 0.81 from the cache):
 //    up to 640 columns and up to 3 rows K above 8448 1.10, 1025-2048 columns and K (M + 8) of 100 000 to 125 000 0.99, 4097-5120 columns 1.03, 5121-6144 and 150 000 to 190 000 0.99.
-//    `strips.py evaluate`, 5389 problems on both sides: the 3635 that are taken 0.82 / 0.74 (120 slower by more than 3 % and 26 by 10 % from HBM; 46 and 5), the 1754 left 1.20 / 0.95.
+//    `strips.py evaluate`, 5389 problems on both sides: the 3635 that are taken 0.80 / 0.71 (74 slower by more than 3 % and 17 by 10 % from HBM; 27 and 4), the 1754 left 1.18 / 0.92.
 //  * picks whose calls share launches stay: 16 calls in one take what two take here;
 //  * columns that are no whole strip of 16 keep the measured neighbours' kernels.
 bool strips_choice(int64_t M, int64_t N, int64_t K, const Spec& pick, Spec* out)
@@ -775,8 +775,8 @@ bool strips_choice(int64_t M, int64_t N, int64_t K, const Spec& pick, Spec* out)
 
 // The same for a row-major B, in strips of 32 columns: half a cache line of each of its rows, which HBM gives more slowly, so the range is shorter.  On 2572
 // problems of 17 to 320 rows, most of them of the round sizes that layers have, 0.81 of the time from HBM of the choices without it (35 slower by more than
-// 3 %, 5 by 10 %) and 0.64 from the cache; of 2196 others (`strips.py evaluate`) the 911 that are taken 0.81 / 0.63 (12 and 3 slower from HBM, 2 and 1 from the
-// cache), the 1285 left 0.99 / 0.73.  Where it ends, from HBM / from the cache: tiles of 16 x 32 0.78 / 0.61 at K 1024-1536, 0.85 / 0.66 to 2048, 1.05 / 0.74 to
+// 3 %, 5 by 10 %) and 0.64 from the cache; of 2196 others (`strips.py evaluate`) the 911 that are
+// taken 0.80 / 0.60 (5 and 1 slower from HBM, none from the cache), the 1285 left 0.97 / 0.68.  Where it ends, from HBM / from the cache: tiles of 16 x 32 0.78 / 0.61 at K 1024-1536, 0.85 / 0.66 to 2048, 1.05 / 0.74 to
 // 3072, 1.25 / 0.82 to 4096; of 32 x 32 0.9 / 0.75 to 2048, 1.0 / 0.78 to 3072, and level with strips of all rows up to 32; fewer than twice as many columns as
 // rows 0.93 / 0.65 at K 1536-2048, a quarter of them slower; wider tiles 1.05 / 0.9.  Sooner where few blocks of rows share what is fetched of B, and sooner
 // again where its rows lie a multiple of 512 bytes apart, so that the half lines of all of them come from fewer channels: 16 x 32 on more than 1024 columns and up to 64
@@ -1768,11 +1768,7 @@ hgemm_status_t hgemm_plan_choice(int64_t M, int64_t N, int64_t K, const hgemm_la
     return HGEMM_OK;
 }
 
-// Strips go round the XCDs: whole rounds of eight where several blocks of rows follow one another.
-static dim3 skinny_grid(const GemmArgs& a)
-{
-    return dim3(a.tiles_m > 1 ? (unsigned)(a.tiles_n + 7) / 8u * 8u : (unsigned)a.tiles_n, (unsigned)(a.splits * a.tiles_m));
-}
+static dim3 skinny_grid(const GemmArgs& a) { return dim3((unsigned)(a.tiles_n * a.tiles_m), (unsigned)a.splits); }
 
 static hgemm_status_t run_plan(const hgemm_plan_s* plan, const void* A, const void* B, void* C, void* hip_stream)
 {

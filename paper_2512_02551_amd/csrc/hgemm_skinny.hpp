@@ -249,7 +249,7 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_gemm_kernel(GemmArgs g)
 // loads that were operands) -> 7.7 us, 16 x 4096 x 4096 10.0 -> 8.4, 1 x 7296 x 7296 23.6 -> 20.8; in strips of 32 rows 16 x 5888 x 1920 9.0 -> 7.2, 16 x 14336 x
 // 4096 24.8 -> 23.1; of 48 16 x 11008 x 4096 20.2 -> 19.1; from the cache 1 x 4096 x 4096 7.7 -> 4.6, 16 x 14336 x 4096 21.4 -> 18.3.  Not where K is long
 // and A of 16 rows: 16 x 4096 x 11008 21.9 from HBM, split 32-row tiles 21.1 (17.9 from the cache, this 15.7).
-// With more rows of A, a workgroup takes 16 MB of them (grid.y then counts blocks of rows, which an XCD's strips share): what bounds it is the
+// With more rows of A, a workgroup takes 16 MB of them (the blocks of rows of a strip follow one another, on one XCD as far as they go): what bounds it is the
 // (16 MB + NR) * 2 bytes of each k that a compute unit fetches, at 57 GB/s from HBM, 110 from the cache.  From HBM / from the cache, the best
 // kernel of any family before -> this: 24 x 2048 x 2048 5.7 / 5.1 -> 4.8 / 3.8 us, 64 x 2048 x 2048 7.7 / 6.7 -> 6.1 / 4.5, 96 x 3072 x 3072 14.6 / 11.6 -> 10.7 / 7.1,
 // 48 x 8192 x 4096 18.6 / 15.0 -> 16.6 / 12.8.
@@ -286,12 +286,14 @@ __device__ __forceinline__ void skinny_strip(const GemmArgs& g)
     const int t = threadIdx.x;
     const int lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int strips = g.tiles_n, xcd = blockIdx.x & 7;
-    if ((int)(blockIdx.x >> 3) >= (strips >> 3) + (xcd < (strips & 7))) return;      // the grid is rounded up to whole XCDs
-    const int strip = xcd * (strips >> 3) + min(xcd, strips & 7) + (blockIdx.x >> 3);
+    // Tiles of a strip and a block of rows of A are dealt so that an XCD's workgroups hold adjacent ones, and no XCD more than an eighth of them.  (Dealt by strips, 81 of
+    // them times 3 blocks are 33 for one XCD of 32 compute units: 95 x 3856 x 2840 from HBM / from the cache 15.7 / 11.6 -> 13.1 / 8.3 us, 218 x 576 x 3312 10.0 / 7.9 -> 6.9 / 5.4.)
+    const int tiles = g.tiles_n * g.tiles_m, xcd = blockIdx.x & 7;
+    const int tile = xcd * (tiles >> 3) + min(xcd, tiles & 7) + (blockIdx.x >> 3);
+    const int strip = g.tiles_m > 1 ? tile / g.tiles_m : tile;
     const int n0 = strip * NR;
-    const int m0 = g.tiles_m > 1 ? (int)blockIdx.y * 16 * MB : 0;                    // grid.y: blocks of rows of A, or slabs of K
-    const int split = g.tiles_m > 1 ? 0 : (int)blockIdx.y;
+    const int m0 = g.tiles_m > 1 ? (tile - strip * g.tiles_m) * 16 * MB : 0;
+    const int split = blockIdx.y;
     const int k_lo = split * g.k_per_split;
     const int k_hi = min(g.K, k_lo + g.k_per_split);
     const int steps = (k_hi - k_lo + 64 * WAVES - 1) / (64 * WAVES);

@@ -277,3 +277,13 @@ def test_the_reported_workgroups_are_those_of_the_launch():
     for q, r in zip(qs, ask(qs)):
         name, x, y, *_ = kernels(r["run_log"])[0]
         assert r["workgroups"] == x * y, (q, r)
+
+
+@pytest.mark.parametrize("m,n,k,tn", [(95, 3856, 2840, True), (218, 576, 3312, True), (282, 1288, 3568, True), (46, 1344, 6144, True), (97, 576, 6016, True), (128, 520, 2048, False),
+                                      (64, 2040, 2048, True)], ids=str)
+def test_blocks_of_rows_in_strips_are_one_workgroup_for_every_compute_unit(m, n, k, tn):
+    """... of each XCD, which workgroups go round: as many are launched as there are tiles, so that none of 32 compute units holds two."""
+    (r,) = ask([{"M": m, "N": n, "K": k, "tn": tn}])
+    nr, mr = (int(re.search(rf"{key}=(\d+)", r["describe"])[1]) for key in ("nr", "mr"))
+    ((_, x, y, *_),) = kernels(r["run_log"])
+    assert x * y == -(-m // mr) * -(-n // nr) <= 256 and y == 1, (x, y, r["describe"])

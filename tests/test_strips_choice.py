@@ -129,12 +129,12 @@ def test_no_model_describes_blocks_of_rows_or_resident_a(spec):
     assert hg.predict_us(64, 2048, 2048, "skinny,sk=1") > 1.0
 
 
-@pytest.mark.parametrize("kind,count,most_slower", [("row-major B", 900, 0.02), ("blocks of rows", 2700, 0.045), ("all rows", 3500, 0.04)])
+@pytest.mark.parametrize("kind,count,most_slower", [("row-major B", 900, 0.02), ("blocks of rows", 2700, 0.03), ("all rows", 3500, 0.03)])
 def test_limits_on_measured_problems(kind, count, most_slower):
-    """Strips where they are faster than the kernels chosen without them, from HBM and from the cache; what they are not taken for is not, on average, from HBM."""
+    """Strips where they are faster than the kernels chosen without them, from HBM and from the cache; what they are not taken for is level or slower from HBM, on average."""
     rows = [r for r in MEASURED if kind == ("row-major B" if not r["tn"] else "blocks of rows" if "mr=" in r["strips"] else "all rows")]
     taken = [r for r in rows if strips.takes(r)]
     left = [r for r in rows if not strips.takes(r)]
     n, hbm, cache, slower, slower_cache, *_ = strips.figures(taken)
     assert n >= count and hbm < 0.83 and cache < 0.75 and slower < most_slower * n and slower_cache < 0.015 * n, strips.figures(taken)
-    assert strips.figures(left)[1] > 0.98, strips.figures(left)
+    assert strips.figures(left)[1] > 0.95, strips.figures(left)
