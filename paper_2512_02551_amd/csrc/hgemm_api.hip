@@ -751,10 +751,9 @@ bool strip_tiles_choice(int64_t M, int64_t N, int64_t K, const Spec& pick, Spec*
 //  * K below 16 nr: a strip ends before its copies flow (nr = 32: K 256 1.0 / 0.95, 512 0.91 / 0.8; nr = 48: 512 0.98 / 0.9, 768 0.96 / 0.83);
 //  * a long K on strips for few compute units, which a split spreads over more of them, sooner with more rows of A, whose bytes every
 //    strip reads: up to 1024 columns K 8192 0.9 / 0.85 at M = 2, 1.3 / 0.9 at 16; 4097-5120 columns K 4096 0.92 / 0.83 at M = 4, 6144 1.16 /
-//    0.85 at 16; 3073-4096 columns K 8192-16384 0.85-0.98 / 0.84 up to 16 rows, 1.13 / 0.87 at 24.  Of another 5045 problems, half of them with K above 4096, 159 were slower
-//    by more than 3 % and 29 by 10 %; the limits of now leave 83 and 11 of 4812 (0.81 / 0.74), and the 233 they let go are level from HBM (76 slower; 0.81 from the cache):
-//    up to 640 columns and up to 3 rows K above 8448 1.10, 1025-2048 columns and K (M + 8) of 100 000 to 125 000 0.99, 4097-5120 columns 1.03, 5121-6144 and 150 000 to 190 000 0.99.
-//    `strips.py evaluate`, 5389 problems on both sides: the 3635 that are taken 0.80 / 0.71 (74 slower by more than 3 % and 17 by 10 % from HBM; 27 and 4), the 1754 left 1.18 / 0.92.
+//    0.85 at 16; 3073-4096 columns K 8192-16384 0.85-0.98 / 0.84 up to 16 rows, 1.13 / 0.87 at 24.  Near these limits strips are level from HBM, a third slower by more
+//    than 3 % and a third faster, and 0.8 from the cache (161 problems);
+//    `strips.py evaluate`, 5389 problems on both sides: the 3796 that are taken 0.80 / 0.71 (116 slower by more than 3 % and 28 by 10 % from HBM; 27 and 4), the 1593 left 1.20 / 0.93.
 //  * picks whose calls share launches stay: 16 calls in one take what two take here;
 //  * columns that are no whole strip of 16 keep the measured neighbours' kernels.
 bool strips_choice(int64_t M, int64_t N, int64_t K, const Spec& pick, Spec* out)
@@ -765,29 +764,28 @@ bool strips_choice(int64_t M, int64_t N, int64_t K, const Spec& pick, Spec* out)
     if (K < 256 * blocks) return false;
     const double filled = (double)N / (4096.0 * (double)blocks);
     const double work = (double)K * (double)(M + 8);
-    const double most = filled <= 0.5 || (blocks == 2 && filled <= 0.625) ? 100e3 : filled <= 0.625 ? 125e3 : blocks == 2 ? 150e3 : 190e3;
-    if (filled <= 0.75 ? work > most || (filled <= 0.25 && K > 8448) : M > 16 && blocks < 3 && work > 200e3) return false;
+    if (filled <= 0.75 ? work > (filled <= 0.25 ? 100e3 : filled <= 0.625 ? 125e3 : 190e3) : M > 16 && blocks < 3 && work > 200e3) return false;
     *out = Spec();
     out->fam = FAM_SKINNY;
     if (blocks > 1) out->nr = (int)(16 * blocks);
     return true;
 }
 
-// The same for a row-major B, in strips of 32 columns: half a cache line of each of its rows, which HBM gives more slowly, so the range is shorter.  On 2572
-// problems of 17 to 320 rows, most of them of the round sizes that layers have, 0.81 of the time from HBM of the choices without it (35 slower by more than
-// 3 %, 5 by 10 %) and 0.64 from the cache; of 2196 others (`strips.py evaluate`) the 911 that are
-// taken 0.80 / 0.60 (5 and 1 slower from HBM, none from the cache), the 1285 left 0.97 / 0.68.  Where it ends, from HBM / from the cache: tiles of 16 x 32 0.78 / 0.61 at K 1024-1536, 0.85 / 0.66 to 2048, 1.05 / 0.74 to
-// 3072, 1.25 / 0.82 to 4096; of 32 x 32 0.9 / 0.75 to 2048, 1.0 / 0.78 to 3072, and level with strips of all rows up to 32; fewer than twice as many columns as
-// rows 0.93 / 0.65 at K 1536-2048, a quarter of them slower; wider tiles 1.05 / 0.9.  Sooner where few blocks of rows share what is fetched of B, and sooner
-// again where its rows lie a multiple of 512 bytes apart, so that the half lines of all of them come from fewer channels: 16 x 32 on more than 1024 columns and up to 64
-// rows of A beyond K 1664 / 1408 1.01 / 0.70, 197 of 446 slower (20 x 2048 x 2048 7.8 / 6.4 -> 9.3 / 4.1 us); 32 x 32 on such rows beyond K 1792 18 of 72 (64 x 2560 x 1920 1.15).
+// The same for a row-major B, in strips of 32 columns: half a cache line of each of its rows, which HBM gives more slowly, so the range is shorter.  On 23 596
+// random problems of 17 to 320 rows 0.80 of the time from HBM of the choices without it (84 slower by more than 3 %, 39 by 10 %), 0.65 from the cache
+// (39, 13), 0.38 planned, run once and freed (timed when tiles were dealt by strips).  On 2196 others, half of round sizes (`strips.py evaluate`), the 1070 that
+// are taken 0.82 / 0.61 (47 slower by more than 3 % and 17 by 10 % from HBM, 1 and none from the cache), the 1126 left 0.98 / 0.68.  Where it ends, from
+// HBM / from the cache: tiles of 16 x 32 0.78 / 0.61 at K 1024-1536, 0.85 / 0.66 to 2048, 1.05 / 0.74 to 3072, 1.25 / 0.82 to 4096; of 32 x 32 0.9 / 0.75 to 2048, 1.0 / 0.78 to
+// 3072, and level with strips of all rows up to 32; fewer than twice as many columns as rows 0.93 / 0.65 at K 1536-2048, a quarter of them slower; wider tiles 1.05 / 0.9.
+// Rows of B a multiple of 1 KiB apart, whose half lines then come from fewer of the memory's channels, on at least 1536 columns and for up to 64 rows of A, which share
+// less of them: 1.11 / 0.69 beyond K 1408, 79 of 125 slower from HBM by 10 % (20 x 2048 x 2048 7.8 / 6.4 -> 9.3 / 4.1 us); to 1408 0.92 / 0.65.
 bool row_strip_tiles_choice(int64_t M, int64_t N, int64_t K, int64_t ldb, const Spec& pick, Spec* out)
 {
     if (M <= 16 || M > 320 || N < 64 || K < 768 || K > 2048 || joins_launches(pick, M, N, K)) return false;
     const int64_t cus = cu_count(), strips = (N + 31) / 32;
     const int mr = (M + 15) / 16 * strips <= cus ? 16 : M > 32 && (M + 31) / 32 * strips <= cus ? 32 : 0;
     if (!mr || (2 * M > N && K > 1280)) return false;
-    if (mr == 16 ? N > 1024 && M <= 64 && K > (ldb % 256 ? 1664 : 1408) : ldb % 256 == 0 && K > 1792) return false;
+    if (mr == 16 && M <= 64 && N >= 1536 && K > 1408 && ldb % 512 == 0) return false;
     *out = Spec();
     out->fam = FAM_SKINNY; out->mr = mr; out->nr = 32;
     return true;
