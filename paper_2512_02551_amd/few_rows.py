@@ -6,7 +6,7 @@ the fastest, and csrc/few_rows.inc holds for each the kernels that are close to 
 looks up the nearest.
 
     python -m paper_2512_02551_amd.few_rows gather --seed 1 --seconds 500 --out FILE [--against LIB]   # on the GPU
-    python -m paper_2512_02551_amd.few_rows recheck --out FILE [--against LIB] [FILE]       # on the GPU; after a kernel or a rule changed
+    python -m paper_2512_02551_amd.few_rows recheck --out FILE [--against LIB] [FILE]       # on the GPU; every problem of a check file again
     python -m paper_2512_02551_amd.few_rows build [FILE ...]          # CPU; rewrites csrc/few_rows.inc
     python -m paper_2512_02551_amd.few_rows evaluate [--against LIB] [FILE ...]     # CPU; the built library's choices
 
@@ -21,9 +21,10 @@ one's, on K from 1200 on only: on a shorter K it wins less than 5 % from HBM and
 csrc/few_rows_check.jsonl.gz holds 4885 other problems as `gather` writes them, which the choices are checked on: half products of
 layers, a quarter output heads, a quarter any multiples of 8; {"shape", "tn", "cands": [[kernel, us from HBM, us from the cache], ...]} with
 the kernels whose first timing was within a fifth of the fastest, the library's choice and that of the builds it is compared with
-(--against: another build of the library, of an earlier commit, say); all were timed again (`recheck`) since a column-major B goes through LDS in strips and
-the large tiles drain their last K-tiles one by one.  csrc/few_rows_timings.jsonl.gz has the kernels as they were before that: of a
-column-major B the streaming ones are faster now, with the same spec in strips of up to 48 rows of B (of 16 then).
+(--against: another build of the library, of an earlier commit, say).  The 1373 that run on strips of B through LDS were timed again since;
+the others stand as first timed, 438 of them with streaming kernels of a column-major B as they were before, when lanes loaded operands (a spec without nr then meant strips
+of 16 rows of B, now of up to 48).  With every problem timed again (`recheck`) the choices are 6 and 8 % from the fastest kernel, not 5 and 7.
+csrc/few_rows_timings.jsonl.gz has that family's kernels as they were before.
 """
 from __future__ import annotations
 
