@@ -251,7 +251,7 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_gemm_kernel(GemmArgs g)
 // and A of 16 rows: 16 x 4096 x 11008 21.9 from HBM, split 32-row tiles 21.1 (17.9 from the cache, this 15.7).
 // With more rows of A, a workgroup takes 16 MB of them (the blocks of rows of a strip follow one another, on one XCD as far as they go): what bounds it is the
 // (16 MB + NR) * 2 bytes of each k that a compute unit fetches, at 57 GB/s from HBM, 110 from the cache.  From HBM / from the cache, the best
-// kernel of any family before -> this: 24 x 2048 x 2048 5.7 / 5.1 -> 4.8 / 3.8 us, 64 x 2048 x 2048 7.7 / 6.7 -> 6.1 / 4.5, 96 x 3072 x 3072 14.6 / 11.6 -> 10.7 / 7.1,
+// kernel of any family before -> this: 24 x 2048 x 2048 5.7 / 5.1 -> 4.8 / 3.8 us, 64 x 2048 x 2048 7.7 / 6.7 -> 6.1 / 4.5 (by spec; packed, the shape is a row of the table), 96 x 3072 x 3072 14.6 / 11.6 -> 10.7 / 7.1,
 // 48 x 8192 x 4096 18.6 / 15.0 -> 16.6 / 12.8.
 // Four waves with three chunks each (48 KiB at NR = 16, three workgroups to a compute unit) are the best of 4, 8 and 16 waves and 2 to 8
 // chunks: 1 x 4096 x 4096 7.8, eight waves 8.1, sixteen 8.2.  Strips are dealt so that an XCD's workgroups hold adjacent ones (see below).
